@@ -53,12 +53,13 @@ __device__ inline void accept_greedy_walk(int b, int r0, int nn, const int32_t* 
     n_out[b] = a + 1;
 }
 
+__device__ inline double shfl_xor_f64(double v, int o) {
+    return __hiloint2double(__shfl_xor(__double2hiint(v), o), __shfl_xor(__double2loint(v), o));
+}
+
 __device__ inline double block_sum_f64(double v, double* red) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        int lo = __shfl_xor(__double2loint(v), o), hi = __shfl_xor(__double2hiint(v), o);
-        v += __hiloint2double(hi, lo);
-    }
+    for (int o = 32; o > 0; o >>= 1) v += shfl_xor_f64(v, o);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -74,108 +75,337 @@ __device__ inline float block_max_f32(float v, float* red) {
     return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// Rejection sampling of one sequence by its workgroup (nn > 0).  Probabilities are evaluated in fp64 from the fp32
-// logits.
+// ---- rejection sampling.  Probabilities are evaluated in fp64 from the fp32 logits.
+//
+// A decision at a node needs the node's largest logit and the sum of exp((logit - largest) / T) over the vocabulary:
+// some 20 operations, most of them fp64, for each of up to 152064 tokens, which is what bounds this path.  The walk from
+// node to node is a chain, but the sums do not depend on it: a first launch computes them for all rows side by side, cut
+// into slices of SLICE tokens (a workgroup keeps a slice in registers, so every logit is read once), and the walk that
+// follows only combines the slices of the rows it visits.  64 trees of 17 rows over 152064 tokens: 0.16 to 0.2 ms for the sums
+// (3 to 4 TB/s of logits) and 0.03 ms for the walk; with everything in one workgroup per sequence, two passes over the
+// vocabulary per visited node and one lane that walked 594 tokens at the end, it was 2.6 to 3.4 ms.  Slices of 8192
+// tokens took 5 % longer (twice the registers, half the wavefronts).
+// With very many rows most of them are never visited: beyond STATS_ALL_ROWS only the roots and their children are
+// computed ahead (2048 rows of 152064 tokens take 0.4 ms, about what the walk needs for five rows by itself), and the
+// walk computes the rest of what it visits.
+constexpr int SLICE = HS_REJECT_SLICE, PER = SLICE / 256;   // tokens of a slice; of a slice, per thread
+constexpr int STATS_ALL_ROWS = 2048;
+
+__device__ inline bool stats_ahead(int m, int pos, int root_pos) { return m <= STATS_ALL_ROWS || pos - root_pos <= 1; }
+
+// exp((l - ref) / T) in fp64 for l <= ref, with c = 16 / (T ln 2): (l - ref) c = n + f, |f| <= 1/2, and the result is
+// 2^(n >> 4) tab[n & 15] exp(f ln2/16), tab[j] = 2^(j/16), the last factor by its Taylor series to the seventh power
+// (remainder 1.3e-18).  15 fp64 operations against about 30 of the library's exp, and the sums are bound by them; the
+// error is that of rounding c and the result, 2^-53 |x| + 2 ulp.  The sixteen table entries cover the 32 LDS banks once:
+// no lookup conflicts with another.  Differences below -746 T, -inf among them, are taken as -746 T, where the result is
+// 0 or the smallest number; a NaN comes out as such a value, too, so callers look for NaNs themselves.
+struct exp_scale { float low; double c; };
+__device__ inline exp_scale make_scale(double inv_temp) {
+    return {(float)fmax(-746.0 / inv_temp, -3.0e38), inv_temp * 23.083120654223414};
+}
+__device__ inline double exp_diff(float l, float ref, const exp_scale& k, const double* tab) {
+    const double d = (double)fmaxf(l, ref + k.low) - (double)ref;
+    const double t = __builtin_fma(d, k.c, 6755399441055744.0);      // + 1.5 2^52: n in the low bits
+    const int n = __double2loint(t);
+    const double f = __builtin_fma(d, k.c, -(t - 6755399441055744.0));
+    double p = 5.682086126528621e-14;
+    p = __builtin_fma(p, f, 9.181219573844438e-12);
+    p = __builtin_fma(p, f, 1.2715871950558131e-09);
+    p = __builtin_fma(p, f, 1.467610032291943e-07);
+    p = __builtin_fma(p, f, 1.3550807779497457e-05);
+    p = __builtin_fma(p, f, 0.0009383847928089872);
+    p = __builtin_fma(p, f, 0.04332169878499658);
+    p = __builtin_fma(p, f, 1.0);
+    return __builtin_amdgcn_ldexp(p * tab[n & 15], n >> 4);
+}
+__device__ inline void fill_exp_table(double* tab) {
+    if (threadIdx.x < 16) tab[threadIdx.x] = exp2((double)threadIdx.x * 0.0625);
+    __syncthreads();
+}
+
+// A thread's share of a slice, -inf beyond the vocabulary: 16-byte pieces 4 KB apart where rows are 16-byte aligned.
+__device__ inline int slice_token(int slice, int j, bool vec) {
+    return slice * SLICE + (vec ? 4 * ((int)threadIdx.x + 256 * (j >> 2)) + (j & 3) : (int)threadIdx.x + 256 * j);
+}
+__device__ inline void load_slice(const float* __restrict__ lg, int vocab, int slice, bool vec, float (&v)[PER]) {
+    if (vec) {
+#pragma unroll
+        for (int j = 0; j < PER / 4; j++) {
+            const int i = slice_token(slice, 4 * j, true);
+            float4 f = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            if (i < vocab) f = *reinterpret_cast<const float4*>(lg + i);
+            v[4 * j] = f.x; v[4 * j + 1] = f.y; v[4 * j + 2] = f.z; v[4 * j + 3] = f.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER; j++) {
+            const int i = slice_token(slice, j, false);
+            v[j] = i < vocab ? lg[i] : -INFINITY;
+        }
+    }
+}
+
+// Sum of exp((logit - ref) / T) over a thread's logits; excluded ones (-inf) add nothing, a NaN makes it NaN.
+__device__ inline double sum_weights(const float (&v)[PER], float ref, double inv_temp, const double* tab) {
+    const exp_scale k = make_scale(inv_temp);
+    double s = 0.0;
+    unsigned worst = 0u;
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+        s += exp_diff(v[j], ref, k, tab);
+        worst = max(worst, __float_as_uint(v[j]) << 1);
+    }
+    return ref == -INFINITY && worst <= 0xFF000000u ? 0.0 : worst > 0xFF000000u || ref == INFINITY ? NAN : s;
+}
+
+// Largest logit and sum of one slice, relative to that largest logit, by a workgroup of 256 threads.  A slice in which
+// every token is excluded (-inf) has the sum 0; a NaN anywhere makes the sum NaN.
+__device__ inline void slice_stats(const float (&v)[PER], double inv_temp, const double* tab,
+                                   hs_reject_stat* __restrict__ dst) {
+    __shared__ float redf[4];
+    __shared__ double redd[4];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < PER; j++) mx = fmaxf(mx, v[j]);
+    mx = block_max_f32(mx, redf);
+    const double s = block_sum_f64(sum_weights(v, mx, inv_temp, tab), redd);
+    if (threadIdx.x == 0) { dst->m = mx; dst->s = s; }
+}
+
+// grid (slices, sequences, row split): a workgroup takes rows blockIdx.z, blockIdx.z + gridDim.z, ... of its sequence,
+// the next row's logits on their way while it sums the current one's.
+__global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __restrict__ row_off,
+                                                            const int32_t* __restrict__ pos,
+                                                            const float* __restrict__ logits, int vocab, int batch,
+                                                            double inv_temp, hs_reject_stat* __restrict__ stats) {
+    __shared__ double tab[16];
+    fill_exp_table(tab);
+    const int b = blockIdx.y, n_slices = gridDim.x, slice = blockIdx.x, m = row_off[batch];
+    const int r0 = row_off[b], r1 = row_off[b + 1];
+    const bool vec = (vocab & 3) == 0 && ((unsigned long long)logits & 15ull) == 0;
+    auto next_row = [&](int r) {      // the first row from r on that is computed ahead
+        while (r < r1 && !stats_ahead(m, pos[r], pos[r0])) r += gridDim.z;
+        return r;
+    };
+    int r = next_row(r0 + blockIdx.z);
+    if (r >= r1) return;
+    float v[PER], w[PER];
+    load_slice(logits + (size_t)r * vocab, vocab, slice, vec, v);
+    while (r < r1) {
+        const int rn = next_row(r + gridDim.z);
+        if (rn < r1) load_slice(logits + (size_t)rn * vocab, vocab, slice, vec, w);
+        slice_stats(v, inv_temp, tab, stats + (size_t)r * n_slices + slice);
+#pragma unroll
+        for (int j = 0; j < PER; j++) v[j] = w[j];
+        r = rn;
+    }
+}
+
+// Sum over the lanes up to and including this one, in lane order by a fixed tree.
+__device__ inline double wave_prefix_f64(double v, int lane) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double t = __hiloint2double(__shfl_up(__double2hiint(v), o), __shfl_up(__double2loint(v), o));
+        if (lane >= o) v += t;
+    }
+    return v;
+}
+
+// Rejection sampling of one sequence by its workgroup (nn > 0).  The four wavefronts take every decision redundantly:
+// same values, same order, no exchange.
 __device__ inline void accept_rejection_seq(
-    int b, int r0, int nn, int vocab, const int32_t* __restrict__ tok,
+    int b, int r0, int nn, int m_rows, int vocab, const int32_t* __restrict__ tok,
     const int32_t* __restrict__ parent, const int32_t* __restrict__ pos, const float* __restrict__ logits,
+    hs_reject_stat* __restrict__ stats, int n_slices,
     const uint64_t* __restrict__ seq_id, double inv_temp, uint64_t seed, int k_stride,
     int32_t* __restrict__ accept_len, int32_t* __restrict__ n_out, int32_t* __restrict__ out_tok,
     int32_t* __restrict__ path_row) {
-    __shared__ float redf[4];
+    __shared__ double wave_tot[4];
     __shared__ double redd[4];
-    __shared__ double chunk_sum[256];
-    __shared__ int s_next, s_nrej, s_rej[8], s_chunk, s_pick;
-    __shared__ double s_before, s_target;
-    const int tid = threadIdx.x;
+    __shared__ int s_first, s_last, s_pick;
+    __shared__ double tab[16];
+    __shared__ float node_max[64];
+    __shared__ double node_sum[64];
+    fill_exp_table(tab);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t sid = seq_id[b];
+    const bool vec = (vocab & 3) == 0 && ((unsigned long long)logits & 15ull) == 0;
+    const int root_pos = pos[r0];
+    // a row's largest logit and sum, put together from its slices by half a wavefront
+    auto row_total = [&](const hs_reject_stat* st, float& mx, double& z) {
+        mx = -INFINITY;
+        for (int s = lane & 31; s < n_slices; s += 32) mx = fmaxf(mx, st[s].m);
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        z = 0.0;
+        for (int s = lane & 31; s < n_slices; s += 32) z += st[s].s * exp(((double)st[s].m - (double)mx) * inv_temp);
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) z += shfl_xor_f64(z, o);
+    };
+    // Everything that the walk may ask of the first 64 nodes (there are no more in a draft tree), fetched side by side
+    // instead of node after node: lane i holds node i's parent, position, token and that token's logit at the parent.
+    for (int i = tid >> 5; i < min(nn, 64); i += 8)
+        if (stats_ahead(m_rows, pos[r0 + i], root_pos)) {
+            float mx;
+            double z;
+            row_total(stats + (size_t)(r0 + i) * n_slices, mx, z);
+            if ((lane & 31) == 0) { node_max[i] = mx; node_sum[i] = z; }
+        }
+    int pre_par = -2, pre_tok = 0, pre_pos = root_pos;
+    float pre_lg = 0.f;
+    if (lane < nn) {
+        pre_par = parent[r0 + lane];
+        pre_tok = tok[r0 + lane];
+        pre_pos = pos[r0 + lane];
+        if (lane > 0 && pre_par >= 0 && pre_par < nn) pre_lg = logits[(size_t)(r0 + pre_par) * vocab + pre_tok];
+    }
+    __syncthreads();
     int cur = 0, a = 0;
     if (tid == 0) path_row[(size_t)b * k_stride] = 0;
     for (;;) {
         const float* lg = logits + (size_t)(r0 + cur) * vocab;
-        float mx = -INFINITY;
-        for (int i = tid; i < vocab; i += 256) mx = fmaxf(mx, lg[i]);
-        mx = block_max_f32(mx, redf);
-        double z = 0.0;
-        for (int i = tid; i < vocab; i += 256) z += exp(((double)lg[i] - (double)mx) * inv_temp);
-        z = block_sum_f64(z, redd);
-        const uint32_t position = (uint32_t)(pos[r0 + cur] + 1);
-        if (tid == 0) {
-            int next = -1, tried = 0, nrej = 0;
-            double zr = z;
-            for (int i = 1; i < nn && next < 0; i++) {
-                if (parent[r0 + i] != cur) continue;
-                int t = tok[r0 + i];
-                double w = exp(((double)lg[t] - (double)mx) * inv_temp);
-                for (int r = 0; r < nrej; r++) if (s_rej[r] == t) w = 0.0;
-                double u = uniform01(seed, sid, position, (uint32_t)tried);
-                if (u < w / zr) next = i;
-                else if (nrej < 8) { s_rej[nrej++] = t; zr -= w; }
+        hs_reject_stat* st = stats + (size_t)(r0 + cur) * n_slices;
+        const int cur_pos = cur < 64 ? __shfl(pre_pos, cur) : pos[r0 + cur];
+        const bool ahead = stats_ahead(m_rows, cur_pos, root_pos);
+        if (!ahead) {
+            for (int s = 0; s < n_slices; s++) {
+                float v[PER];
+                load_slice(lg, vocab, s, vec, v);
+                slice_stats(v, inv_temp, tab, st + s);
+            }
+            __syncthreads();
+        }
+        float mx;
+        double z;
+        if (ahead && cur < 64) { mx = node_max[cur]; z = node_sum[cur]; }
+        else row_total(st, mx, z);
+        const uint32_t position = (uint32_t)(cur_pos + 1);
+        auto weight = [&](float l) { return exp(((double)l - (double)mx) * inv_temp); };
+        // children in node order, 64 nodes at a time
+        int next = -1, next_tok = 0, tried = 0, nrej = 0, rej = -1;   // lane q < nrej: the q-th rejected token
+        double zr = z;
+        for (int i0 = 0; i0 < nn && next < 0; i0 += 64) {
+            const int i = i0 + lane;
+            const bool child = i > 0 && i < nn && (i0 == 0 ? pre_par : parent[r0 + i]) == cur;
+            const int my_tok = !child ? 0 : i0 == 0 ? pre_tok : tok[r0 + i];
+            const double my_w = child ? weight(i0 == 0 ? pre_lg : lg[my_tok]) : 0.0;
+            for (unsigned long long todo = __ballot(child); todo && next < 0; todo &= todo - 1) {
+                const int q = __ffsll(todo) - 1;
+                const int t = __shfl(my_tok, q);
+                double w = __hiloint2double(__shfl(__double2hiint(my_w), q), __shfl(__double2loint(my_w), q));
+                if (__any(lane < nrej && rej == t)) w = 0.0;
+                const double u = uniform01(seed, sid, position, (uint32_t)tried);
+                if (u < w / zr) {
+                    next = i0 + q;
+                    next_tok = t;
+                } else if (nrej < 8) {
+                    if (lane == nrej) rej = t;
+                    nrej++;
+                    zr -= w;
+                }
                 tried++;
             }
-            s_next = next;
-            s_nrej = nrej;
         }
-        __syncthreads();
-        const int next = s_next;
         if (next >= 0 && a + 1 < k_stride) {
             if (tid == 0) {
-                out_tok[(size_t)b * k_stride + a] = tok[r0 + next];
+                out_tok[(size_t)b * k_stride + a] = next_tok;
                 path_row[(size_t)b * k_stride + a + 1] = next;
             }
             cur = next;
             a++;
-            __syncthreads();
             continue;
         }
-        // final sample from the remaining distribution: contiguous chunk per thread, chunk sums, then the
-        // owning thread walks its chunk in token-id order
-        const int nrej = s_nrej;
-        const int per = (vocab + 255) / 256;
-        const int lo = tid * per, hi = min(vocab, lo + per);
-        double cs = 0.0;
-        for (int i = lo; i < hi; i++) {
-            double w = exp(((double)lg[i] - (double)mx) * inv_temp);
-            for (int r = 0; r < nrej; r++) if (s_rej[r] == i) w = 0.0;
-            cs += w;
-        }
-        chunk_sum[tid] = cs;
-        __syncthreads();
-        if (tid == 0) {
-            double zt = 0.0;
-            for (int c = 0; c < 256; c++) zt += chunk_sum[c];
-            double u = uniform01(seed, sid, position, 7u);
-            double target = u * zt, cum = 0.0;
-            int chunk = -1;
-            for (int c = 0; c < 256; c++) {
-                if (chunk_sum[c] > 0.0 && cum + chunk_sum[c] >= target) { chunk = c; break; }
-                cum += chunk_sum[c];
+        // Final sample from the remaining distribution, in token-id order.  A slice that holds rejected tokens is summed
+        // again without them (subtracting would leave rounding where a rejected token had nearly all the weight).
+        for (int q = 0; q < nrej; q++) {
+            const int s = __shfl(rej, q) / SLICE;
+            float v[PER];
+            load_slice(lg, vocab, s, vec, v);
+            for (int q2 = 0; q2 < nrej; q2++) {
+                const int t = __shfl(rej, q2);
+#pragma unroll
+                for (int j = 0; j < PER; j++)
+                    if (slice_token(s, j, vec) == t) v[j] = -INFINITY;
             }
-            s_chunk = chunk; s_before = cum; s_target = target; s_pick = -1;
+            const double sum = block_sum_f64(sum_weights(v, mx, inv_temp, tab), redd);
+            if (tid == 0) { st[s].m = mx; st[s].s = sum; }
+            __syncthreads();
         }
-        __syncthreads();
-        if (s_chunk >= 0 && tid == s_chunk) {
-            double cum = s_before;
-            int pick = -1, last_nz = -1;
-            for (int i = lo; i < hi; i++) {
-                double w = exp(((double)lg[i] - (double)mx) * inv_temp);
-                for (int r = 0; r < nrej; r++) if (s_rej[r] == i) w = 0.0;
-                if (w > 0.0) last_nz = i;
-                cum += w;
-                if (w > 0.0 && cum >= s_target) { pick = i; break; }
-            }
-            s_pick = pick >= 0 ? pick : last_nz;
+        auto slice_weight = [&](int s) { return s < n_slices ? st[s].s * exp(((double)st[s].m - (double)mx) * inv_temp) : 0.0; };
+        double zt = 0.0;
+        for (int s0 = 0; s0 < n_slices; s0 += 64) {
+            double t = slice_weight(s0 + lane);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) t += shfl_xor_f64(t, o);
+            zt += t;
         }
+        const double target = uniform01(seed, sid, position, 7u) * zt;
+        int slice = -1;
+        double before = 0.0;   // weight in front of the chosen slice
+        for (int s0 = 0; s0 < n_slices && slice < 0; s0 += 64) {
+            const double w = slice_weight(s0 + lane), incl = wave_prefix_f64(w, lane);
+            const unsigned long long hit = __ballot(w > 0.0 && before + incl >= target);
+            const int q = hit ? __ffsll(hit) - 1 : 63;
+            const double upto = hit ? incl - w : incl;
+            before += __hiloint2double(__shfl(__double2hiint(upto), q), __shfl(__double2loint(upto), q));
+            if (hit) slice = s0 + q;
+        }
+        if (tid == 0) { s_first = 256; s_last = -1; s_pick = -1; }
         __syncthreads();
-        if (tid == 0) {
-            int pick = s_pick;
-            if (pick < 0) {  // rounding left the target beyond every chunk: last token with weight
-                for (int i = vocab - 1; i >= 0; i--) {
-                    bool rej = false;
-                    for (int r = 0; r < nrej; r++) if (s_rej[r] == i) rej = true;
-                    if (!rej) { pick = i; break; }
+        if (slice >= 0) {
+            // PER consecutive tokens per thread: the first thread whose running sum reaches the target holds the token
+            const int lo = slice * SLICE + tid * PER;
+            float v[PER];
+            if (vec) {
+#pragma unroll
+                for (int j = 0; j < PER; j += 4) {
+                    float4 f = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+                    if (lo + j < vocab) f = *reinterpret_cast<const float4*>(lg + lo + j);
+                    v[j] = f.x; v[j + 1] = f.y; v[j + 2] = f.z; v[j + 3] = f.w;
                 }
+            } else {
+#pragma unroll
+                for (int j = 0; j < PER; j++) v[j] = lo + j < vocab ? lg[lo + j] : -INFINITY;
             }
+            for (int q = 0; q < nrej; q++) {
+                const int t = __shfl(rej, q);
+#pragma unroll
+                for (int j = 0; j < PER; j++)
+                    if (lo + j == t) v[j] = -INFINITY;
+            }
+            const double sum = sum_weights(v, mx, inv_temp, tab);
+            const double incl = wave_prefix_f64(sum, lane);
+            if (lane == 63) wave_tot[wave] = incl;
+            __syncthreads();
+            double base = before + (incl - sum);
+            for (int q = 0; q < wave; q++) base += wave_tot[q];
+            if (sum > 0.0) {
+                atomicMax(&s_last, tid);
+                if (base + sum >= target) atomicMin(&s_first, tid);
+            }
+            __syncthreads();
+            // (rounding can leave the target just beyond the slice: its last token with weight then)
+            const int owner = s_first < 256 ? s_first : s_last;
+            if (owner >= 0 && wave == owner >> 6) {
+                const int at = slice * SLICE + owner * PER, i = at + lane;
+                bool in = lane < PER && i < vocab;
+                for (int q = 0; q < nrej; q++) in = in && __shfl(rej, q) != i;
+                const float l = in ? lg[i] : -INFINITY;
+                const double w = exp_diff(l, mx, make_scale(inv_temp), tab);
+                const double cum = __hiloint2double(__shfl(__double2hiint(base), owner & 63), __shfl(__double2loint(base), owner & 63)) +
+                                   wave_prefix_f64(w, lane);
+                const unsigned long long nz = __ballot(w > 0.0), hit = __ballot(w > 0.0 && cum >= target);
+                if (lane == 0) s_pick = hit ? at + __ffsll(hit) - 1 : nz ? at + 63 - __clzll(nz) : -1;
+            }
+            __syncthreads();
+        }
+        int pick = s_pick;
+        if (pick < 0) {  // no slice reaches the target (NaN among the logits): the last token that was not rejected
+            for (pick = vocab - 1; pick >= 0; pick--) {
+                if (!__any(lane < nrej && rej == pick)) break;
+            }
+        }
+        if (tid == 0) {
             out_tok[(size_t)b * k_stride + a] = pick;
             accept_len[b] = a;
             n_out[b] = a + 1;
@@ -269,6 +499,8 @@ struct accept_commit_args {
     const float* logits;
     const unsigned long long* keys;
     int n_keys;
+    hs_reject_stat* stats;
+    int n_slices;
     int32_t* argmax;
     const uint64_t* seq_id;
     double inv_temp;
@@ -315,8 +547,8 @@ __global__ __launch_bounds__(256) void accept_commit_kernel(accept_commit_args p
                     accept_greedy_walk(b, r0, nn, p.tok, p.parent, p.argmax, p.k_stride, p.accept_len, p.n_out,
                                        p.out_tok, p.path_row);
             } else {
-                accept_rejection_seq(b, r0, nn, p.vocab, p.tok, p.parent, p.pos, p.logits, p.seq_id, p.inv_temp,
-                                     p.seed, p.k_stride, p.accept_len, p.n_out, p.out_tok, p.path_row);
+                accept_rejection_seq(b, r0, nn, p.row_off[p.batch], p.vocab, p.tok, p.parent, p.pos, p.logits,
+                                     p.stats, p.n_slices, p.seq_id, p.inv_temp, p.seed, p.k_stride, p.accept_len, p.n_out, p.out_tok, p.path_row);
             }
         }
         __syncthreads();           // the commit reads what thread 0 wrote
@@ -370,6 +602,16 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
         p.mode = args->mode;
         p.inv_temp = args->mode == HS_ACCEPT_REJECTION ? 1.0 / (double)args->temperature : 1.0;
         p.seed = args->seed;
+    }
+    if (args && args->mode == HS_ACCEPT_REJECTION) {
+        p.stats = reinterpret_cast<hs_reject_stat*>(ctx->ws + ctx->lay.reject_stats);
+        p.n_slices = hs_reject_slices(d.vocab);
+        // enough workgroups to fill the chip: small batches split a sequence's rows, too
+        const int nodes = 1 + ctx->lim.c_max * ctx->lim.k_max;
+        int split = 2048 / (p.n_slices * p.batch);
+        split = split < 1 ? 1 : (split > nodes ? nodes : split);
+        hipLaunchKernelGGL(reject_stats_kernel, dim3(p.n_slices, p.batch, split), dim3(256), 0, st, p.row_off, p.pos,
+                           logits, p.vocab, p.batch, p.inv_temp, p.stats);
     }
     p.accept_len = step->accept_len; p.n_out = step->n_out; p.out_tok = step->out_tok; p.path_row = step->path_row;
     if (policy) {

@@ -17,8 +17,14 @@ constexpr int HS_ATT_PART_DEFAULT = 512;
 constexpr int HS_DRAFT_SEG = 4096;
 constexpr int HS_MAX_NODES = 64;  // ancestor masks are 64-bit
 
+// Rejection sampling: the vocabulary is summed in slices of this many tokens; per row and slice the largest logit and the
+// sum of exp((logit - largest) / temperature) are kept.
+constexpr int HS_REJECT_SLICE = 4096;
+struct hs_reject_stat { float m; double s; };
+static inline int hs_reject_slices(int vocab) { return (vocab + HS_REJECT_SLICE - 1) / HS_REJECT_SLICE; }
+
 struct hs_workspace_layout {
-    size_t x, xn, qkv, q, attn, act, part_o, part_ml, logits, logits_bytes, rowmax, draft_best, gemm_part, gemm_part_bytes, err, pf_len, att_work, att_list, total;
+    size_t x, xn, qkv, q, attn, act, part_o, part_ml, logits, logits_bytes, rowmax, draft_best, gemm_part, gemm_part_bytes, err, pf_len, att_work, att_list, reject_stats, total;
 };
 
 struct hs_ctx {

@@ -222,3 +222,54 @@ def test_philox_words_equal_the_oracles_on_a_million_counters():
         got = d_out.cpu().numpy().view(np.uint32)
         want = oracle.philox_batch(ctr, [seed & 0xFFFFFFFF, seed >> 32])
         assert (got == want).all(), seed
+
+
+@pytest.mark.parametrize("V,B,k,rows_big", [(1, 2, 1, False), (4095, 3, 4, False), (4097, 3, 4, False),
+                                            (12290, 5, 8, False), (8192, 70, 31, True)])
+def test_rejection_over_several_vocabulary_slices(toy, V, B, k, rows_big):
+    """The sampler sums the vocabulary in slices of 4096 tokens: widths at a slice's edge, one that is not a multiple of 4
+    (rows then are not 16-byte aligned), rejected tokens in the first, a middle and the last slice, whole slices masked
+    with -inf; and with more than 2048 rows the launch that computes sums ahead, which then covers the roots and their
+    children only.  Same logits, seed and ids as the oracle: the same decisions, unless the oracle's margin is below 1e-9."""
+    from paper_2508_18588_amd import HS_ACCEPT_REJECTION
+    from paper_2508_18588_amd.runtime import Engine
+    from hs_inputs import ModelShape
+    shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
+    rng = np.random.default_rng(V + B)
+    eng = Engine(shape, make_weights(shape, 3), rope_table(64, 64), max_batch=B, k_max=k, c_max=1 if rows_big else 2, max_len=80)
+    ids = rng.integers(0, 2 ** 62, B)
+    eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B, seq_ids=ids.astype(np.int64))
+    accepted = 0
+    for trial in range(3):
+        trees = []
+        for b in range(B):
+            c0 = rng.choice([0, V // 2, V - 1, int(rng.integers(0, V))], k)
+            chains = [c0] if rows_big else [c0, rng.integers(0, V, k)]
+            trees.append(oracle.build_tree(chains, 0, int(rng.integers(0, 3000))))
+        m = eng.set_rows([dict(tok=t["tok"], parent=t["parent"], pos=t["pos"]) for t in trees])
+        assert (m > 2048) == rows_big
+        lg = rng.normal(0.0, 2.0, size=(m, V)).astype(np.float32)
+        if V > 9000:
+            lg[:, 4096:8192] = -np.inf
+        r = 0
+        for t in trees:
+            for i in range(1, len(t["tok"])):
+                lg[r + t["parent"][i], t["tok"][i]] = rng.choice([-np.inf, 9.0, 12.0, 30.0], p=[0.1, 0.2, 0.3, 0.4]) if V > 1 else 1.0
+            r += len(t["tok"])
+        eng.logits[:m].copy_(torch.from_numpy(lg))
+        seed = int(rng.integers(0, 2 ** 63))
+        eng.accept(HS_ACCEPT_REJECTION, 1.0, seed)
+        torch.cuda.synchronize()
+        st = {n: np_of(v) for n, v in eng.st.items()}
+        r = 0
+        for b, t in enumerate(trees):
+            n = len(t["tok"])
+            a, out, path, margin = oracle.accept_stochastic(t["tok"], t["parent"], t["pos"], lg[r:r + n].astype(np.float64),
+                                                            1.0, seed, int(ids[b]))
+            g = st["n_out"][b]
+            got = (int(st["accept_len"][b]), st["out_tok"][b, :g].tolist(), st["path_row"][b, :g].tolist())
+            assert got == (a, out.tolist(), path.tolist()) or margin < 1e-9, (trial, b, got, a, out, path, margin)
+            accepted += a
+            r += n
+    eng.close()
+    assert accepted > 0

@@ -319,17 +319,14 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
     int whole_slot = ctx->ev_used;
     if (ctx->profile) ctx->ev_used += 2;  // the whole-call pair is closed at the end
 
-    pr.begin(3);
-    hs_launch_embed(ctx, step, seq->batch, x, st);
-    hs_launch_attention_worklist(ctx, seq, step, st);
-    pr.end();
     // A projection run in the split execution leaves its chunk partials for the next kernel in line (RMSNorm for
     // the residual projections, rotary/KV write for QKV), which adds them up in chunk order: one launch fewer per
     // projection.  `pend` carries the number of chunks from the projection to that kernel.
     int pend = 0;
     for (int l = 0; l < d.n_layers; l++) {
         pr.begin(3);
-        hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, st);
+        if (l == 0) hs_launch_embed_norm(ctx, seq, step, seq->batch, x, ctx->norm1[0], xn, st);
+        else hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, st);
         pr.end();
         if (ctx->capture && l + 1 == d.n_layers) {
             (void)hipMemcpyAsync(ctx->capture, xn, cap_xn, hipMemcpyDeviceToDevice, st);
@@ -424,10 +421,10 @@ hs_status hs_prefill(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* 
 
     (void)hipGetLastError();
     hs_launch_prefill_rows(ctx, seq, args->kv_done, args->chunk, step, len_plus1, st);
-    hs_launch_embed(ctx, step, seq->batch, x, st);
     int pend = 0;
     for (int l = 0; l < d.n_layers; l++) {
-        hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, st);
+        if (l == 0) hs_launch_embed_norm(ctx, nullptr, step, seq->batch, x, ctx->norm1[0], xn, st);
+        else hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, st);
         hs_launch_gemm(ctx, HS_EPI_STORE_F32, xn, ctx->wqkv[l], nullptr, qkv, m_dev, m_max, nqkv, d.d_model, hint, st,
                        &pend);
         hs_launch_rope_kv(ctx, l, cache, &pf, step, qkv, q, pend, st);

@@ -31,7 +31,7 @@
 // partitions merge in index order, so a row's result is bit-identical whether it is verified next to other draft
 // rows or decoded alone.
 //
-// Launch.  The units of a step are listed on the device once per verify call (attn_worklist_kernel) and a
+// Launch.  The units of a step are listed on the device once per verify call (hs_worklist.h) and a
 // persistent grid -- exactly the workgroups that are resident at once -- works the lists off: wavefront units by a
 // static deal, workgroup units through a counter (see attn_verify_mfma).  K and V are read with non-temporal loads.
 // A second entry, attn_prefill_mfma, runs the same sub-tile routine causally over a chunk of consecutive tokens.
@@ -481,78 +481,6 @@ __device__ inline void attn_unit_wg(const AttnArgs& a, const AttnUnit& un, bf16_
     else attn_unit_wg_n<HD, RTW, 4>(a, un, sK, sV, tid);   // also a single live tile: everyone stages a quarter
 }
 
-// The units of one step, built once per hs_verify call (the same for every layer): a unit = one partition of one
-// (sequence, KV head), in (sequence, partition, head) order.  List A: units of sequences with more than 32 query rows
-// per KV head (taken by whole workgroups), list B: the others (taken by single wavefronts).  An entry is two int4:
-// (sequence, head, partition, first row) (rows, cached length, first row tile, 0).  work[0] = |A|, work[1] = |B|, work[2 + l] = the
-// counter through which layer l's launch hands out list A (zeroed here).
-__global__ __launch_bounds__(256) void attn_worklist_kernel(const int32_t* __restrict__ seq_len,
-                                                             const int32_t* __restrict__ row_off, int batch,
-                                                             int part_keys, int G, int hkv, int max_parts, int n_layers,
-                                                             int32_t* __restrict__ work, int4* __restrict__ list_a,
-                                                             int4* __restrict__ list_b) {
-    __shared__ int s_nu[256], s_off[256], s_r0[256], s_nn[256], s_len[256], s_grp[256];
-    __shared__ int sw_a[4], sw_b[4];
-    __shared__ int carry_a, carry_b;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < n_layers; i += 256) work[2 + i] = 0;
-    if (tid == 0) { carry_a = 0; carry_b = 0; }
-    __syncthreads();
-    for (int b0 = 0; b0 < batch; b0 += 256) {
-        const int b = b0 + tid;
-        int nu = 0, r0 = 0, nn = 0, L = 0, ngrp = 1;
-        bool is_a = false;
-        if (b < batch) {
-            r0 = row_off[b];
-            nn = row_off[b + 1] - r0;
-            L = seq_len[b] - 1;
-            if (nn > 0 && L >= 0) {
-                const int nparts = min(max_parts, (L + nn + part_keys - 1) / part_keys);
-                is_a = nn * G > 32;
-                // a workgroup covers four 32-row tiles: a sequence with more query rows per KV head than that gets
-                // one unit per group of four tiles (each walks the partition's keys on its own)
-                if (is_a) ngrp = (nn * G + 127) / 128;
-                nu = nparts * hkv * ngrp;
-            }
-        }
-        int ia = is_a ? nu : 0, ib = is_a ? 0 : nu;
-        const int va = ia, vb = ib;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            int ta = __shfl_up(ia, o), tb = __shfl_up(ib, o);
-            if (lane >= o) { ia += ta; ib += tb; }
-        }
-        if (lane == 63) { sw_a[wave] = ia; sw_b[wave] = ib; }
-        __syncthreads();
-        int ba = carry_a, bb = carry_b;
-        for (int w2 = 0; w2 < wave; w2++) { ba += sw_a[w2]; bb += sw_b[w2]; }
-        // the sign of s_nu tells the list: positive = B, negative = A
-        s_nu[tid] = is_a ? -nu : nu;
-        s_off[tid] = is_a ? ba + ia - va : bb + ib - vb;
-        s_r0[tid] = r0;
-        s_nn[tid] = nn;
-        s_len[tid] = L;
-        s_grp[tid] = ngrp;
-        __syncthreads();
-        if (tid == 255) { carry_a = ba + ia; carry_b = bb + ib; }
-        const int nb = min(256, batch - b0);
-        for (int i = wave; i < nb; i += 4) {     // a wavefront per sequence: a sequence has a few dozen units
-            const int n = s_nu[i];
-            int4* dst = (n < 0 ? list_a : list_b) + 2 * (size_t)s_off[i];
-            const int cnt = n < 0 ? -n : n, grp = s_grp[i];
-            for (int u = lane; u < cnt; u += 64) {
-                // v = (partition, head); the tile groups of one (partition, head) are neighbours (grp is 1 or 2: at
-                // most 256 query rows per KV head)
-                const int v = grp == 1 ? u : (grp == 2 ? (u >> 1) : u / grp);
-                dst[2 * u] = make_int4(b0 + i, v % hkv, v / hkv, s_r0[i]);
-                dst[2 * u + 1] = make_int4(s_nn[i], s_len[i], 4 * (u - v * grp), 0);
-            }
-        }
-        __syncthreads();
-    }
-    if (tid == 0) { work[0] = carry_a; work[1] = carry_b; }
-}
-
 // Persistent launch: exactly as many workgroups as the chip holds at once.  First every wavefront streams its share
 // of the wavefront units (wavefront w of workgroup g: units 4 g + w, 4 g + w + 4 gridDim.x, ... -- dealt out
 // statically, so that nothing but K/V tiles is ever waited for); then the workgroups take the workgroup units one by
@@ -894,7 +822,7 @@ void hs_launch_attention(const hs_ctx* ctx, int layer, const hs_kv_cache* cache,
     }
     const bf16_t* q = (const bf16_t*)q_any;
     // one row tile per wavefront, two workgroups per compute unit, whatever the longest draft: a sequence with more
-    // than 128 query rows per KV head comes as several units (see attn_worklist_kernel)
+    // than 128 query rows per KV head comes as several units (see hs_worklist.h)
     if (d.head_dim == 128) launch_mfma<128, 1>(ctx, layer, layer_off, cache, seq, step, q, st);
     else launch_mfma<64, 1>(ctx, layer, layer_off, cache, seq, step, q, st);
 }
@@ -905,15 +833,18 @@ size_t hs_attention_max_units(const hs_ctx* ctx) {
     return (size_t)ctx->lim.max_batch * ctx->max_parts * ctx->desc.n_kv_heads * ((r_max + 127) / 128);
 }
 
-void hs_launch_attention_worklist(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, hipStream_t st) {
-    if (hs_plain_kernels(ctx)) return;
+hs_attn_lists hs_attention_lists(const hs_ctx* ctx) {
     const hs_model_desc& d = ctx->desc;
-    int32_t* work = reinterpret_cast<int32_t*>(ctx->ws + ctx->lay.att_work);
-    int4* list_a = reinterpret_cast<int4*>(ctx->ws + ctx->lay.att_list);
-    int4* list_b = list_a + 2 * hs_attention_max_units(ctx);
-    hipLaunchKernelGGL(attn_worklist_kernel, dim3(1), dim3(256), 0, st, seq->seq_len, step->row_off, seq->batch,
-                       ctx->att_part, d.n_q_heads / d.n_kv_heads, d.n_kv_heads, ctx->max_parts, d.n_layers, work, list_a,
-                       list_b);
+    hs_attn_lists l;
+    l.work = reinterpret_cast<int32_t*>(ctx->ws + ctx->lay.att_work);
+    l.list_a = reinterpret_cast<int4*>(ctx->ws + ctx->lay.att_list);
+    l.list_b = l.list_a + 2 * hs_attention_max_units(ctx);
+    l.part_keys = ctx->att_part;
+    l.G = d.n_q_heads / d.n_kv_heads;
+    l.hkv = d.n_kv_heads;
+    l.max_parts = ctx->max_parts;
+    l.n_layers = d.n_layers;
+    return l;
 }
 
 void hs_launch_attention_prefill(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,

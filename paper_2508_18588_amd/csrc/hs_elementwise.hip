@@ -6,6 +6,7 @@
 // workgroups, most of which only find that their row does not exist, costs several rounds of workgroup launches
 // (a few microseconds) in each of the ~150 row-kernel launches of a step.
 #include "hs_internal.h"
+#include "hs_worklist.h"
 
 namespace {
 
@@ -26,18 +27,6 @@ __device__ inline float block_sum(float v, float* red) {
     return s;
 }
 
-__global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ embed, const int32_t* __restrict__ tok,
-                                                     const int32_t* __restrict__ m_dev, float* __restrict__ x, int d,
-                                                     int vocab) {
-    const int m = *m_dev;
-    for (int row = blockIdx.x; row < m; row += gridDim.x) {
-        int t = tok[row];
-        if (t < 0 || t >= vocab) t = 0;
-        const bf16_t* e = embed + (size_t)t * d;
-        for (int i = threadIdx.x; i < d; i += 256) x[(size_t)row * d + i] = bf16_to_f32(e[i]);
-    }
-}
-
 // One workgroup per row.  With chunks > 0 the row of the residual stream first receives the pending partial sums of
 // the preceding projection: t = p0 + p1 + ... in chunk order, x += t -- the arithmetic of the stand-alone ordered
 // reduce, so that the split execution gives the same bits whichever kernel finishes it.
@@ -52,7 +41,72 @@ __device__ __forceinline__ void put4(bf16_t* p, float4 v) {
     o.y = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
     *reinterpret_cast<uint2*>(p) = o;
 }
-__device__ __forceinline__ void put4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
+__device__ __forceinline__ void put4(float* p, float4 v) { p[0] = v.x; p[1] = v.y; p[2] = v.z; p[3] = v.w; }   // (any alignment)
+
+template <typename OutT>
+__device__ inline void norm_row(const float4 (&v)[NORM_ITEMS], const float4 (&g)[NORM_ITEMS], bool store_x, float* xr,
+                                OutT* out, int d, float eps, float* red) {
+    // the sum of squares: same element-to-thread assignment and order wherever the row came from -- the norm must not
+    // depend on which execution the preceding projection used
+    float ss = 0.f;
+#pragma unroll
+    for (int it = 0; it < NORM_ITEMS; it++) {
+        const int i = (threadIdx.x + it * NORM_THREADS) * 4;
+        if (i >= d) continue;
+        if (store_x) *reinterpret_cast<float4*>(xr + i) = v[it];
+        ss += v[it].x * v[it].x;
+        ss += v[it].y * v[it].y;
+        ss += v[it].z * v[it].z;
+        ss += v[it].w * v[it].w;
+    }
+    ss = block_sum(ss, red);
+    const float r = rsqrtf(ss / (float)d + eps);
+#pragma unroll
+    for (int it = 0; it < NORM_ITEMS; it++) {
+        const int i = (threadIdx.x + it * NORM_THREADS) * 4;
+        if (i >= d) continue;
+        float4 o;
+        o.x = v[it].x * r * g[it].x; o.y = v[it].y * r * g[it].y;
+        o.z = v[it].z * r * g[it].z; o.w = v[it].w * r * g[it].w;
+        put4(out + i, o);
+    }
+}
+
+// The first norm of a forward pass: the residual stream starts as the token's embedding.  The first list_groups
+// workgroups write the attention's unit lists instead (nothing here depends on them), the others take rows.
+// (As three launches -- 2-byte gathers, the lists by one workgroup, the norm reading the gathers back -- 28 us at 220 rows
+// of 3584 and 128 sequences, now 6.5; 1067 rows of 5120: 45, now 19.)
+template <typename OutT>
+__global__ __launch_bounds__(NORM_THREADS) void embed_norm_kernel(
+    const bf16_t* __restrict__ embed, const int32_t* __restrict__ tok, int vocab, float* __restrict__ x,
+    const float* __restrict__ w, OutT* __restrict__ out, const int32_t* __restrict__ row_off, int batch, int d, float eps,
+    int list_groups, hs_attn_lists lists, const int32_t* __restrict__ seq_len) {
+    __shared__ float red[NORM_THREADS / 64];
+    if ((int)blockIdx.x < list_groups) {
+        hs_write_worklist(lists, seq_len, row_off, batch, blockIdx.x);
+        return;
+    }
+    const int m = row_off[batch];
+    // (the embedding rows may start at any bf16: 8-byte loads where their base allows)
+    const bool vec = ((unsigned long long)embed & 7ull) == 0;
+    for (int row = (int)blockIdx.x - list_groups; row < m; row += (int)gridDim.x - list_groups) {
+        int t = tok[row];
+        if (t < 0 || t >= vocab) t = 0;
+        const bf16_t* e = embed + (size_t)t * d;
+        float4 v[NORM_ITEMS], g[NORM_ITEMS];
+#pragma unroll
+        for (int it = 0; it < NORM_ITEMS; it++) {
+            const int i = (threadIdx.x + it * NORM_THREADS) * 4;
+            if (i >= d) continue;
+            g[it] = *reinterpret_cast<const float4*>(w + i);
+            ushort4 b;
+            if (vec) b = *reinterpret_cast<const ushort4*>(e + i);
+            else b = make_ushort4(e[i], e[i + 1], e[i + 2], e[i + 3]);
+            v[it] = make_float4(bf16_to_f32(b.x), bf16_to_f32(b.y), bf16_to_f32(b.z), bf16_to_f32(b.w));
+        }
+        norm_row<OutT>(v, g, true, x + (size_t)row * d, out + (size_t)row * d, d, eps, red);
+    }
+}
 
 template <typename OutT>
 __global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
@@ -83,38 +137,21 @@ __global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(float* __restrict
                 v[it].x += t.x; v[it].y += t.y; v[it].z += t.z; v[it].w += t.w;
             }
         }
-        // the sum of squares: same element-to-thread assignment and order with and without pending partials -- the
-        // norm must not depend on which execution the preceding projection used
-        float ss = 0.f;
-#pragma unroll
-        for (int it = 0; it < NORM_ITEMS; it++) {
-            const int i = (threadIdx.x + it * NORM_THREADS) * 4;
-            if (i >= d) continue;
-            if (chunks > 0) *reinterpret_cast<float4*>(xr + i) = v[it];
-            ss += v[it].x * v[it].x;
-            ss += v[it].y * v[it].y;
-            ss += v[it].z * v[it].z;
-            ss += v[it].w * v[it].w;
-        }
-        ss = block_sum(ss, red);
-        const float r = rsqrtf(ss / (float)d + eps);
-#pragma unroll
-        for (int it = 0; it < NORM_ITEMS; it++) {
-            const int i = (threadIdx.x + it * NORM_THREADS) * 4;
-            if (i >= d) continue;
-            float4 o;
-            o.x = v[it].x * r * g[it].x; o.y = v[it].y * r * g[it].y;
-            o.z = v[it].z * r * g[it].z; o.w = v[it].w * r * g[it].w;
-            put4(out + (size_t)row * d + i, o);
-        }
+        norm_row<OutT>(v, g, chunks > 0, xr, out + (size_t)row * d, d, eps, red);
     }
 }
 
-// One workgroup per row.  Rotates q and k heads at the row's position (pairs i, i + h/2), writes q as bf16,
-// K into its page row-major and V into its page with the token index fastest.
-// T = bf16_t, or float in the fp32-activation mode (queries and cache entries then keep every bit).
+// Rotates q and k heads at the row's position (pairs i, i + h/2), writes q as bf16, K into its page row-major and V into
+// its page with the token index fastest.  T = bf16_t, or float in the fp32-activation mode (queries and cache entries
+// then keep every bit).
+// One workgroup per row, an item per thread: four neighbouring pairs of a q or k head, or four elements of a v head.  A
+// thread adds up its own elements' pending partials (chunk order) and rotates them; nothing passes through LDS, no
+// barrier, and the loads depend on nothing but the row, so they are on their way while the chain row -> sequence ->
+// slot -> page is followed.  Bound by the partial sums it reads.  With the row gathered in LDS by 1024 threads first:
+// 74 us for 4096 rows of 4608 in three chunks, 28 us for 1067 rows of 7168 in two, 28 us
+// for 2048 rows of 2048 in six; now 70, 25 and 21 (2.7 to 5 TB/s of partial sums).
 template <typename T>
-__global__ __launch_bounds__(NORM_THREADS) void rope_kv_kernel(const float* __restrict__ qkv, const float* __restrict__ rope_cs,
+__global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__ qkv, const float* __restrict__ rope_cs,
                                                        const int32_t* __restrict__ pos, const int32_t* __restrict__ row2seq,
                                                        const int32_t* __restrict__ row_off,
                                                        const int32_t* __restrict__ seq_len,
@@ -124,65 +161,65 @@ __global__ __launch_bounds__(NORM_THREADS) void rope_kv_kernel(const float* __re
                                                        int h, int max_pos, int n_blocks,
                                                        const float* __restrict__ part, int chunks,
                                                        size_t chunk_stride) {
-    extern __shared__ float row_buf[];
     const int m = row_off[batch];
+    const int half = h >> 1, per_head = half >> 2;         // items of a q or k head
+    const int n_rot = (hq + hkv) * per_head, n_items = n_rot + hkv * (h >> 2);
+    const int nqkv = (hq + 2 * hkv) * h;
+    const bool cs_vec = ((unsigned long long)rope_cs & 15ull) == 0;
     // (the conditions that skip a row are the same for all threads of the workgroup)
     for (int row = blockIdx.x; row < m; row += gridDim.x) {
-        // The row's QKV vector: the projection's output, or the chunk-ordered sum of its pending partials, which is
-        // first gathered into LDS with 16-byte loads (several partials of an element in flight at once).  The
-        // gather comes first: it depends on nothing but the row, so its loads are on their way while the chain
-        // row -> sequence -> slot -> page below is followed.
-        const int nqkv = (hq + 2 * hkv) * h;
-        if (chunks > 0) {
-            if (row != (int)blockIdx.x) __syncthreads();  // row_buf of the previous row has been read
-            const float* pr = part + (size_t)row * nqkv;
-            for (int i = threadIdx.x * 4; i < nqkv; i += 4 * NORM_THREADS) {
-                float4 t = *reinterpret_cast<const float4*>(pr + i);
+        const float* src = (chunks > 0 ? part : qkv) + (size_t)row * nqkv;
+        const int n_src = chunks > 0 ? chunks : 1;
+        int b = -1, p = 0, slot = 0, page = -1;
+        for (int i = threadIdx.x; i < n_items; i += blockDim.x) {
+            const bool rot = i < n_rot;
+            const int head = rot ? i / per_head : hq + hkv + (i - n_rot) / (h >> 2);      // head of the QKV vector
+            const int j = rot ? 4 * (i % per_head) : 4 * ((i - n_rot) % (h >> 2));        // first element in it
+            const float* s0 = src + head * h + j;
+            float4 x = *reinterpret_cast<const float4*>(s0), y = x;
+            if (rot) y = *reinterpret_cast<const float4*>(s0 + half);
 #pragma unroll 8
-                for (int c = 1; c < chunks; c++) {
-                    const float4 q4 = *reinterpret_cast<const float4*>(pr + c * chunk_stride + i);
-                    t.x += q4.x; t.y += q4.y; t.z += q4.z; t.w += q4.w;
+            for (int c = 1; c < n_src; c++) {
+                const float4 t = *reinterpret_cast<const float4*>(s0 + c * chunk_stride);
+                x.x += t.x; x.y += t.y; x.z += t.z; x.w += t.w;
+                if (rot) {
+                    const float4 u = *reinterpret_cast<const float4*>(s0 + c * chunk_stride + half);
+                    y.x += u.x; y.y += u.y; y.z += u.z; y.w += u.w;
                 }
-                *reinterpret_cast<float4*>(row_buf + i) = t;
             }
-        }
-        int b = row2seq[row];
-        int node = row - row_off[b];
-        int p = pos[row];
-        int slot = seq_len[b] - 1 + node;
-        int page = (slot >= 0 && (slot >> 4) < max_blocks) ? block_table[(size_t)b * max_blocks + (slot >> 4)] : -1;
-        if (chunks > 0) __syncthreads();
-        // (a position flagged by the draft step, a slot beyond the block table, a missing page: nothing is written)
-        if (p < 0 || p >= max_pos || page < 0 || page >= n_blocks) continue;
-        int in_page = slot & 15;
-        int half = h >> 1;
-        const float* cs = rope_cs + (size_t)p * half * 2;
-        const float* src = qkv + (size_t)row * nqkv;
-        auto val = [&](int e) -> float { return chunks > 0 ? row_buf[e] : src[e]; };
-        // q heads
-        for (int i = threadIdx.x; i < hq * half; i += NORM_THREADS) {
-            int head = i / half, j = i % half;
-            float c = cs[2 * j], s = cs[2 * j + 1];
-            float a = val(head * h + j), bb = val(head * h + j + half);
-            T* dst = q_out + (size_t)row * hq * h + head * h;
-            put(dst + j, a * c - bb * s);
-            put(dst + j + half, bb * c + a * s);
-        }
-        // k heads -> cache [page][kv head][16][h]
-        const int koff = hq * h;
-        for (int i = threadIdx.x; i < hkv * half; i += NORM_THREADS) {
-            int head = i / half, j = i % half;
-            float c = cs[2 * j], s = cs[2 * j + 1];
-            float a = val(koff + head * h + j), bb = val(koff + head * h + j + half);
-            T* dst = kc + layer_off + (((size_t)page * hkv + head) * 16 + in_page) * h;
-            put(dst + j, a * c - bb * s);
-            put(dst + j + half, bb * c + a * s);
-        }
-        // v heads -> cache [page][kv head][h][16]
-        const int voff = koff + hkv * h;
-        for (int i = threadIdx.x; i < hkv * h; i += NORM_THREADS) {
-            int head = i / h, j = i % h;
-            put(vc + layer_off + (((size_t)page * hkv + head) * h + j) * 16 + in_page, val(voff + head * h + j));
+            if (b < 0) {
+                b = row2seq[row];
+                p = pos[row];
+                slot = seq_len[b] - 1 + (row - row_off[b]);
+                page = (slot >= 0 && (slot >> 4) < max_blocks) ? block_table[(size_t)b * max_blocks + (slot >> 4)] : -1;
+            }
+            // (a position flagged by the draft step, a slot beyond the block table, a missing page: nothing is written)
+            if (p < 0 || p >= max_pos || page < 0 || page >= n_blocks) break;
+            const int in_page = slot & 15;
+            if (!rot) {   // v head -> cache [page][kv head][h][16]
+                T* dst = vc + layer_off + (((size_t)page * hkv + (head - hq - hkv)) * h + j) * 16 + in_page;
+                put(dst, x.x); put(dst + 16, x.y); put(dst + 32, x.z); put(dst + 48, x.w);
+                continue;
+            }
+            const float* cs = rope_cs + ((size_t)p * half + j) * 2;
+            float4 c0, c1;   // (cos, sin) of pairs j, j + 1 and j + 2, j + 3
+            if (cs_vec) {
+                c0 = *reinterpret_cast<const float4*>(cs);
+                c1 = *reinterpret_cast<const float4*>(cs + 4);
+            } else {
+                c0 = make_float4(cs[0], cs[1], cs[2], cs[3]);
+                c1 = make_float4(cs[4], cs[5], cs[6], cs[7]);
+            }
+            float4 lo, hi;
+            lo.x = x.x * c0.x - y.x * c0.y; hi.x = y.x * c0.x + x.x * c0.y;
+            lo.y = x.y * c0.z - y.y * c0.w; hi.y = y.y * c0.z + x.y * c0.w;
+            lo.z = x.z * c1.x - y.z * c1.y; hi.z = y.z * c1.x + x.z * c1.y;
+            lo.w = x.w * c1.z - y.w * c1.w; hi.w = y.w * c1.z + x.w * c1.w;
+            // k heads -> cache [page][kv head][16][h]
+            T* dst = head < hq ? q_out + ((size_t)row * hq + head) * h + j
+                               : kc + layer_off + (((size_t)page * hkv + (head - hq)) * 16 + in_page) * h + j;
+            put4(dst, lo);
+            put4(dst + half, hi);
         }
     }
 }
@@ -228,18 +265,19 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
 // from its token log), sequences served in index order until max_rows rows are laid out.  One workgroup.
 // len_plus1[b] = kv_done[b] + 1 before the call (the later kernels' "sequence length": cached positions + 1);
 // kv_done advances by n_b.
-__global__ __launch_bounds__(256) void prefill_rows_kernel(
+__global__ __launch_bounds__(1024) void prefill_rows_kernel(
     const int32_t* __restrict__ seq_len, int32_t* __restrict__ kv_done, const int32_t* __restrict__ tokens,
     int tokens_stride, int batch, int chunk, int max_rows, int max_pos, const int32_t* __restrict__ block_table,
     int max_blocks, int32_t* __restrict__ row_off,
     int32_t* __restrict__ tok, int32_t* __restrict__ pos, int32_t* __restrict__ parent, int32_t* __restrict__ row2seq,
     int32_t* __restrict__ len_plus1, uint32_t* __restrict__ err) {
-    __shared__ int sw[4];
+    __shared__ int sw[16];
+    __shared__ int s_first[1024], s_n[1024], s_done[1024];
     __shared__ int carry_s;
     if (threadIdx.x == 0) carry_s = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int b0 = 0; b0 < batch; b0 += 256) {
+    for (int b0 = 0; b0 < batch; b0 += 1024) {
         const int b = b0 + threadIdx.x;
         int want = 0, done = 0;
         if (b < batch) {
@@ -272,38 +310,53 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(
             row_off[b] = s0;
             len_plus1[b] = done + 1;
             kv_done[b] = done + n;
+            s_first[threadIdx.x] = s0;
+            s_n[threadIdx.x] = n;
+            s_done[threadIdx.x] = done;
         }
         __syncthreads();
-        if (threadIdx.x == 255) carry_s = before + incl;
+        // a wavefront per sequence writes its rows
+        for (int q = wave; q < min(1024, batch - b0); q += 16) {
+            const int s0 = s_first[q], dn = s_done[q];
+            for (int i = lane; i < s_n[q]; i += 64) {
+                tok[s0 + i] = tokens[(size_t)(b0 + q) * tokens_stride + dn + i];
+                pos[s0 + i] = dn + i;
+                parent[s0 + i] = i - 1;
+                row2seq[s0 + i] = b0 + q;
+            }
+        }
+        if (threadIdx.x == 1023) carry_s = before + incl;
         __syncthreads();
     }
     if (threadIdx.x == 0) row_off[batch] = min(carry_s, max_rows);
-    __syncthreads();   // this workgroup's row_off / len_plus1 writes are visible to all its threads
-    for (int b = 0; b < batch; b++) {
-        const int s0 = row_off[b], n = row_off[b + 1] - s0, done = len_plus1[b] - 1;
-        for (int i = threadIdx.x; i < n; i += 256) {
-            tok[s0 + i] = tokens[(size_t)b * tokens_stride + done + i];
-            pos[s0 + i] = done + i;
-            parent[s0 + i] = i - 1;
-            row2seq[s0 + i] = b;
-        }
-    }
 }
 
 }  // namespace
 
 void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_seq_state* seq, int32_t* kv_done, int chunk, hs_step* step,
                             int32_t* len_plus1, hipStream_t st) {
-    hipLaunchKernelGGL(prefill_rows_kernel, dim3(1), dim3(256), 0, st, seq->seq_len, kv_done, seq->tokens,
+    hipLaunchKernelGGL(prefill_rows_kernel, dim3(1), dim3(1024), 0, st, seq->seq_len, kv_done, seq->tokens,
                        seq->tokens_stride, seq->batch, chunk, ctx->lim.max_rows, ctx->lim.max_pos, seq->block_table,
                        ctx->lim.max_blocks_per_seq, step->row_off,
                        step->tok, step->pos, step->parent, step->row2seq, len_plus1,
                        reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.err));
 }
 
-void hs_launch_embed(const hs_ctx* ctx, const hs_step* step, int batch, float* x, hipStream_t st) {
-    hipLaunchKernelGGL(embed_kernel, dim3(hs_row_grid(ctx, 256)), dim3(256), 0, st, ctx->embed, step->tok,
-                       step->row_off + batch, x, ctx->desc.d_model, ctx->desc.vocab);
+void hs_launch_embed_norm(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, int batch, float* x,
+                          const float* w, void* out, hipStream_t st) {
+    const hs_model_desc& d = ctx->desc;
+    static_assert(HS_LIST_THREADS == NORM_THREADS, "the list writers are workgroups of this launch");
+    const bool lists = seq && !hs_plain_kernels(ctx);
+    const int groups = lists ? HS_LIST_GROUPS : 0;
+    const hs_attn_lists l = lists ? hs_attention_lists(ctx) : hs_attn_lists{};
+    const dim3 grid(hs_row_grid(ctx, NORM_THREADS) + groups), block(NORM_THREADS);
+    if (hs_fp32_activations(ctx))
+        hipLaunchKernelGGL(embed_norm_kernel<float>, grid, block, 0, st, ctx->embed, step->tok, d.vocab, x, w, (float*)out,
+                           step->row_off, batch, d.d_model, d.rms_eps, groups, l, seq ? seq->seq_len : nullptr);
+    else
+        hipLaunchKernelGGL(embed_norm_kernel<bf16_t>, grid, block, 0, st, ctx->embed, step->tok, d.vocab, x, w,
+                           (bf16_t*)out, step->row_off, batch, d.d_model, d.rms_eps, groups, l,
+                           seq ? seq->seq_len : nullptr);
 }
 
 void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, const int32_t* m_dev,
@@ -324,18 +377,19 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
     size_t layer_off = (size_t)layer * cache->n_blocks * d.n_kv_heads * 16 * d.head_dim;
     const float* part = reinterpret_cast<const float*>(ctx->ws + ctx->lay.gemm_part);
     const size_t nqkv = (size_t)(d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
-    const size_t lds = pending_chunks > 0 ? nqkv * 4 : 0;
+    // an item per thread if a workgroup has that many, else as many rounds of equal size as it takes
+    const int items = (d.n_q_heads + d.n_kv_heads) * (d.head_dim / 8) + d.n_kv_heads * (d.head_dim / 4);
+    const int rounds = (items + 1023) / 1024, threads = ((items + rounds - 1) / rounds + 63) / 64 * 64;
+    const dim3 grid(hs_row_grid(ctx, threads)), block(threads);
 #define HS_ROPE_ARGS(T)                                                                                          \
     qkv, ctx->rope_cs, step->pos, step->row2seq, step->row_off, seq->seq_len, seq->block_table,                  \
         ctx->lim.max_blocks_per_seq, seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off, d.n_q_heads,      \
         d.n_kv_heads, d.head_dim, ctx->lim.max_pos, cache->n_blocks, part, pending_chunks,                       \
         (size_t)ctx->lim.max_rows * nqkv
     if (hs_fp32_activations(ctx))
-        hipLaunchKernelGGL(rope_kv_kernel<float>, dim3(hs_row_grid(ctx, NORM_THREADS)), dim3(NORM_THREADS), lds, st,
-                           HS_ROPE_ARGS(float));
+        hipLaunchKernelGGL(rope_kv_kernel<float>, grid, block, 0, st, HS_ROPE_ARGS(float));
     else
-        hipLaunchKernelGGL(rope_kv_kernel<bf16_t>, dim3(hs_row_grid(ctx, NORM_THREADS)), dim3(NORM_THREADS), lds, st,
-                           HS_ROPE_ARGS(bf16_t));
+        hipLaunchKernelGGL(rope_kv_kernel<bf16_t>, grid, block, 0, st, HS_ROPE_ARGS(bf16_t));
 #undef HS_ROPE_ARGS
 }
 

@@ -379,11 +379,20 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
 #pragma unroll
                     for (int ni = 0; ni < NU; ni++) {
                         if (p.n0 + 32 * ni + lc >= p.N) continue;
+        // (adding: all of a tile's loads before its first store -- element by element each load waited for
+                        // the one before it, 17 us of a launch with 16 rows)
+                        float old[16];
+                        if (!PARTIAL && EPI == HS_EPI_ADD_F32) {
+#pragma unroll
+                            for (int e = 0; e < 16; e++)
+                                old[e] = *reinterpret_cast<float*>(tile + (size_t)(8 * (e >> 2) + (e & 3)) * p.N * 4 +
+                                                                   (lane_bytes + 128u * ni));
+                        }
 #pragma unroll
                         for (int e = 0; e < 16; e++) {
                             unsigned char* rowp = tile + (size_t)(8 * (e >> 2) + (e & 3)) * p.N * 4;
                             float* dst = reinterpret_cast<float*>(rowp + (lane_bytes + 128u * ni));
-                            if (!PARTIAL && EPI == HS_EPI_ADD_F32) *dst += acc[mi][ni][e];
+                            if (!PARTIAL && EPI == HS_EPI_ADD_F32) *dst = old[e] + acc[mi][ni][e];
                             else *dst = acc[mi][ni][e];
                         }
                     }
@@ -392,12 +401,18 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
                     for (int ni = 0; ni < NU; ni++) {
                         const int col = p.n0 + 32 * ni + lc;
                         if (col >= p.N) continue;
+                        float old[16];
+                        if (!PARTIAL && EPI == HS_EPI_ADD_F32) {
+#pragma unroll
+                            for (int e = 0; e < 16; e++)   // (rows beyond M: the last row's element, not stored)
+                                old[e] = C[(size_t)min(row0 + 8 * (e >> 2) + (e & 3), p.M - 1) * p.N + col];
+                        }
 #pragma unroll
                         for (int e = 0; e < 16; e++) {
                             const int row = row0 + 8 * (e >> 2) + (e & 3);
                             if (row < p.M) {
                                 float* dst = &C[(size_t)row * p.N + col];
-                                if (!PARTIAL && EPI == HS_EPI_ADD_F32) *dst += acc[mi][ni][e];
+                                if (!PARTIAL && EPI == HS_EPI_ADD_F32) *dst = old[e] + acc[mi][ni][e];
                                 else *dst = acc[mi][ni][e];
                             }
                         }

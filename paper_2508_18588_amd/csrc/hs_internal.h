@@ -111,7 +111,10 @@ void hs_launch_gemm(const hs_ctx* ctx, int epi, const void* a, const bf16_t* w, 
                     int* pending = nullptr);
 int hs_gemm_rowmax_groups(int n);   // column groups (= keys per row) of an HS_EPI_ROWMAX launch over n columns
 
-void hs_launch_embed(const hs_ctx* ctx, const hs_step* step, int batch, float* x, hipStream_t st);
+// Embedding gather into the residual stream and its first RMSNorm; with seq (hs_verify), the unit lists of the step's
+// attention are written by further workgroups of the same launch.
+void hs_launch_embed_norm(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, int batch, float* x,
+                          const float* w, void* out, hipStream_t st);
 // RMSNorm of the residual stream; with pending_chunks > 0 it first adds the pending chunk partials of the
 // preceding projection (in chunk order) to x.
 void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, const int32_t* m_dev,
@@ -129,8 +132,13 @@ void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_seq_state* seq, int32_t*
 void hs_launch_attention_prefill(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
                                  const int32_t* len_plus1, const hs_step* step, const bf16_t* q, bf16_t* out, int chunk,
                                  hipStream_t st);
-// Unit lists of the verify attention (one per hs_verify call, before the first layer) and their capacity.
-void hs_launch_attention_worklist(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, hipStream_t st);
+// Unit lists of the verify attention (hs_worklist.h) and their capacity.
+struct hs_attn_lists {
+    int32_t* work;
+    int4 *list_a, *list_b;
+    int part_keys, G, hkv, max_parts, n_layers;
+};
+hs_attn_lists hs_attention_lists(const hs_ctx* ctx);
 size_t hs_attention_max_units(const hs_ctx* ctx);
 void hs_launch_attention_merge(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, void* out,
                                hipStream_t st);

@@ -182,13 +182,17 @@ void launch(const hs_ctx* ctx, const void* a_any, const bf16_t* w, const bf16_t*
 
 // Number of K chunks of a projection: a function of the shape alone.  Narrow outputs get as many chunks as put
 // about one workgroup of the weight-streaming execution on every one of the 256 compute units; every chunk keeps at
-// least 4 k-tiles.  A workgroup takes 128 weight rows, or 64 when the reduction is short (hs_gemm_narrow_groups):
-// with half as many chunks the projection writes -- and the kernel after it reads -- half the partial sums, and
-// with K < 8192 the activation tile that every workgroup re-reads is small enough for that to pay.
-bool hs_gemm_narrow_groups(int k) { return k < 8192; }
+// least 4 k-tiles.  A workgroup takes 128 weight rows, or 64 (hs_gemm_narrow_groups): with half as many chunks the
+// projection writes -- and the kernel after it reads -- half the partial sums, 2 x 16384 / n chunks x n x 4 bytes = 128 KB
+// per row whatever the shape, while twice as many groups each re-read the activations from L2, n k / 64 bytes more per
+// row.  An L2 byte costs about a fifth of a byte of partial sums, so the line lies at 600 KB of re-reads, or K < 8192.  (By K < 8192
+// alone the 1.5B shape's down projection, 1536 x 8960 or 210 KB, ran in 20 chunks:
+// 102 -> 71 us at 2048 rows, and the norm that reads the sums 28 -> 25 us a launch; a step of 248 rows through four layers
+// 674 -> 642 us.)
+bool hs_gemm_narrow_groups(int n, int k) { return k < 8192 || (long long)n * k <= 600ll * 1024 * 64; }
 
 int hs_gemm_chunks(int n, int k) {
-    const int groups = hs_gemm_narrow_groups(k) ? (n + 63) / 64 : (n + 127) / 128;
+    const int groups = hs_gemm_narrow_groups(n, k) ? (n + 63) / 64 : (n + 127) / 128;
     int chunks = 256 / groups;
     const int nk = k / BK;
     if (chunks > nk / 4) chunks = nk / 4;

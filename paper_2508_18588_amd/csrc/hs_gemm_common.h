@@ -44,8 +44,8 @@ __device__ __forceinline__ void load_to_lds_16_stream(const unsigned char* base,
 
 }  // namespace hs_gemm_detail
 
-// Split-K projections with a short reduction run in groups of 64 weight rows (see hs_gemm_chunks).
-bool hs_gemm_narrow_groups(int k);
+// Split-K projections whose activations are cheap to re-read run in groups of 64 weight rows (see hs_gemm_chunks).
+bool hs_gemm_narrow_groups(int n, int k);
 
 // The MFMA kernel (defined in hs_gemm_stream.hip).  `chunks`/`tpc` are the K chunking of
 // the shape (chunks > 1: chunk sums go to `part`, laid out [chunk][m_max][n], for the ordered reduce).

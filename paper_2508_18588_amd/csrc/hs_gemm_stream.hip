@@ -573,10 +573,10 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
     // not pay a second pass over the weights.  Row tiles that do not exist cost nothing in either shape.
     const bool tall = rows_hint > 160;
 #define HS_ARGS a, w, w2, c, part, m_dev, m_max, n, k, chunks, tpc, rows_hint, st
-    // The 64-row groups of the short-reduction split-K shapes (QKV, O) pay at a few hundred rows, where they halve the
+    // The 64-row groups of the smaller split-K shapes (QKV, O) pay at a few hundred rows, where they halve the
     // partial sums; with many row passes every group re-reads the whole activation slab of its pass, and wider groups
     // (half as many re-reads) win.  The K chunking -- the reduction order -- is the shape's either way.
-    if (PARTIAL && chunks > 1 && hs_gemm_narrow_groups(k) && rows_hint < HS_WIDE_GROUP_ROWS) {
+    if (PARTIAL && chunks > 1 && hs_gemm_narrow_groups(n, k) && rows_hint < HS_WIDE_GROUP_ROWS) {
         if (tall) launch_stream<EPI, PARTIAL, 2, 3, 2, 6>(HS_ARGS);
         else launch_stream<EPI, PARTIAL, 2, 2, 2, 8>(HS_ARGS);
     } else if (nu == 5) {

@@ -519,21 +519,36 @@ __global__ __launch_bounds__(256, (RTW == 1 ? 2 : 1)) void attn_verify_mfma(Attn
 }
 
 // Prefill of a chunk of consecutive tokens per sequence (KV recomputation of a resumed rollout): token i of the chunk
-// attends to positions [0, L + i].  One workgroup per (block of 256 query rows, KV head, sequence) walks the keys
+// attends to positions [0, L + i].  One workgroup per (block of 128 query rows, KV head, sequence) walks the keys
 // from position 0 in 64-key tiles -- a row's arithmetic depends on absolute key positions only, not on how the text
 // was cut into chunks -- and writes the normalised output itself: with hundreds of rows per sequence there is
-// enough parallelism without cutting the key axis.  Row tiles of 32 rows (rows of one token's G query heads are
-// adjacent) are dealt to the four wavefronts, two each; a row tile skips the key tiles that lie wholly behind it.
+// enough parallelism without cutting the key axis.  A wavefront has one row tile of 32 rows (rows of one token's G query
+// heads are adjacent); a row tile skips the key tiles that lie wholly behind it.
+// Bound by the softmax's vector arithmetic and, a little less, the matrix cores; a wavefront alternates between the two,
+// so it takes two wavefronts per SIMD to keep either busy: two workgroups per compute unit, each with its own barriers.
+// One workgroup per compute unit with two row tiles per wavefront, which ran them one after the other: 467 us for 4096
+// rows of 28 heads against 512 to 4096 keys, 115 us for 2048 rows of 12 heads; now 225 and 49 (530 TFLOP/s).
 template <int HD>
-__global__ __launch_bounds__(256, 1) void attn_prefill_mfma(
+__global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, size_t layer_off,
     const int32_t* __restrict__ len_plus1, const int32_t* __restrict__ block_table, int max_blocks, int n_blocks,
-    const int32_t* __restrict__ row_off, bf16_t* __restrict__ out, int hq, int hkv, float scale_log2) {
-    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32, RTW = 2, TILE = 64, NCK = HD / 32;
+    const int32_t* __restrict__ row_off, bf16_t* __restrict__ out, int hq, int hkv, float scale_log2, int batch, int nx) {
+    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32, RTW = 1, TILE = 64, NCK = HD / 32;
     __shared__ __attribute__((aligned(16))) bf16_t sK[TILE * KS];
     __shared__ __attribute__((aligned(16))) bf16_t sV[4 * HD * VS];
 
-    const int j = blockIdx.y, b = blockIdx.z;
+    // Workgroup id -> (sequence, KV head) pair and block of rows, the blocks that see the most keys first.  Ids are dealt
+    // round-robin to the eight XCDs: with a multiple of eight pairs, all blocks of a pair go to one XCD and find its K
+    // and V in that L2 (other numbers of pairs would leave some XCDs with more pairs than others).
+    const int pairs = hkv * batch;
+    int pair = blockIdx.x / nx, bx = blockIdx.x % nx;
+    if ((pairs & 7) == 0) {
+        const int local = blockIdx.x >> 3;
+        pair = (local / nx) * 8 + (blockIdx.x & 7);
+        bx = local % nx;
+    }
+    bx = nx - 1 - bx;
+    const int j = pair % hkv, b = pair / hkv;
     const int r0 = row_off[b];
     const int nn = row_off[b + 1] - r0;
     if (nn <= 0) return;
@@ -541,7 +556,7 @@ __global__ __launch_bounds__(256, 1) void attn_prefill_mfma(
     const int total = L + nn;
     const int G = hq / hkv;
     const int R = nn * G;
-    const int row_base = blockIdx.x * (128 * RTW);
+    const int row_base = bx * (128 * RTW);
     if (row_base >= R) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, l32 = lane & 31;
@@ -560,7 +575,7 @@ __global__ __launch_bounds__(256, 1) void attn_prefill_mfma(
     bool rt_on[RTW];
 #pragma unroll
     for (int t = 0; t < RTW; t++) {
-        const int rt = blockIdx.x * (4 * RTW) + wave + 4 * t;
+        const int rt = bx * (4 * RTW) + wave + 4 * t;
         rt_on[t] = rt * 32 < R;
         uint64_t unused;
         load_query_tile<HD>(q, nullptr, r0, rt_on[t] ? rt : 0, rt_on[t] ? R : 0, G, hq, j, half, l32, qf[t], unused);
@@ -618,7 +633,7 @@ __global__ __launch_bounds__(256, 1) void attn_prefill_mfma(
 #undef HS_P_FETCH
 #pragma unroll
     for (int t = 0; t < RTW; t++) {
-        const int rho = (blockIdx.x * (4 * RTW) + wave + 4 * t) * 32 + l32;
+        const int rho = (bx * (4 * RTW) + wave + 4 * t) * 32 + l32;
         if (!rt_on[t] || rho >= R) continue;
         const int node = rho / G, g = rho - node * G;
         const float inv = 1.f / l_run[t];     // a row always sees its own key: the sum is positive
@@ -854,17 +869,18 @@ void hs_launch_attention_prefill(const hs_ctx* ctx, int layer, const hs_kv_cache
     const size_t layer_off = (size_t)layer * cache->n_blocks * d.n_kv_heads * 16 * d.head_dim;
     const int G = d.n_q_heads / d.n_kv_heads;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)d.head_dim);
-    dim3 grid((chunk * G + 255) / 256, d.n_kv_heads, seq->batch);
+    const int nx = (chunk * G + 127) / 128;
+    const dim3 grid(nx * d.n_kv_heads * seq->batch);
     if (d.head_dim == 128)
         hipLaunchKernelGGL((attn_prefill_mfma<128>), grid, dim3(256), 0, st, q, (const bf16_t*)cache->k,
                            (const bf16_t*)cache->v, layer_off, len_plus1, seq->block_table,
                            ctx->lim.max_blocks_per_seq, cache->n_blocks, step->row_off, out, d.n_q_heads, d.n_kv_heads,
-                           scale_log2);
+                           scale_log2, seq->batch, nx);
     else
         hipLaunchKernelGGL((attn_prefill_mfma<64>), grid, dim3(256), 0, st, q, (const bf16_t*)cache->k,
                            (const bf16_t*)cache->v, layer_off, len_plus1, seq->block_table,
                            ctx->lim.max_blocks_per_seq, cache->n_blocks, step->row_off, out, d.n_q_heads, d.n_kv_heads,
-                           scale_log2);
+                           scale_log2, seq->batch, nx);
 }
 
 void hs_launch_attention_merge(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, void* out_any,

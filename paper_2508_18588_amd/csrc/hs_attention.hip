@@ -34,7 +34,7 @@
 // Launch.  The units of a step are listed on the device once per verify call (hs_worklist.h) and a
 // persistent grid -- exactly the workgroups that are resident at once -- works the lists off: wavefront units by a
 // static deal, workgroup units through a counter (see attn_verify_mfma).  K and V are read with non-temporal loads.
-// A second entry, attn_prefill_mfma, runs the same sub-tile routine causally over a chunk of consecutive tokens.
+// A second entry, attn_prefill_mfma, does the same causally over a chunk of consecutive tokens.
 #include "hs_internal.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -49,9 +49,7 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // One 32-key sub-tile for one 32-row query tile: S^T = K.Q^T, online softmax per lane, O^T += V^T.P^T.
 // sK points at the sub-tile's 32 key rows, sV at its two 16-token pages.  Every query row's arithmetic is
 // independent of which other rows are in flight.
-// CHAIN (prefill): the rows are consecutive tokens; L is then a position below which every row of the tile sees every
-// key and `total` the lane's own bound (keys < total are visible), no ancestor mask.
-template <int HD, bool CHAIN = false>
+template <int HD>
 __device__ inline void attn_subtile(const bf16_t* sK, const bf16_t* sV, const bf16x8 (&qf)[HD / 16],
                                     f32x16 (&o)[HD / 32], float& m_run, float& l_run, uint64_t anc, int kbase, int L,
                                     int total, float scale_log2, int half, int l32) {
@@ -70,7 +68,7 @@ __device__ inline void attn_subtile(const bf16_t* sK, const bf16_t* sV, const bf
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             int kp = kbase + 8 * (e >> 2) + 4 * half + (e & 3);
-            bool vis = kp < L || (kp < total && (CHAIN || ((anc >> (kp - L)) & 1ull)));
+            bool vis = kp < L || (kp < total && ((anc >> (kp - L)) & 1ull));
             s[e] = vis ? s[e] : -INFINITY;
         }
     }
@@ -121,17 +119,86 @@ __device__ inline void attn_subtile(const bf16_t* sK, const bf16_t* sV, const bf
         }
 }
 
-// Page holding position p0, as a wavefront-uniform value.  Positions at or beyond `total` (nothing written yet) and
-// malformed table entries resolve to the sequence's first page: its keys are masked and its finite values are
-// multiplied by exact zeros, so every load can be unconditional.
-__device__ inline int safe_page(const int32_t* bt, int p0, int total, int max_blocks, int n_blocks) {
-    int pidx = p0 >> 4;
-    int page = (p0 < total && pidx < max_blocks) ? bt[pidx] : bt[0];
-    page = (page >= 0 && page < n_blocks) ? page : 0;
-    return __builtin_amdgcn_readfirstlane(page);
+// A 64-key tile (four pages) of the prefill: the same steps with one maximum and one rescale per 64 keys and the two
+// halves' products independent of each other.  The rows are consecutive tokens: every row of the tile sees every key below
+// `all`, and the lane's own row the keys below `mine`.
+template <int HD>
+__device__ inline void attn_tile64(const bf16_t* sK, const bf16_t* sV, const bf16x8 (&qf)[HD / 16], f32x16 (&o)[HD / 32],
+                                   float& m_run, float& l_run, int kbase, int all, int mine, float scale_log2, int half,
+                                   int l32) {
+    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32;
+    f32x16 s[2];
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) s[u][e] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ks++)
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const bf16x8 ka = *reinterpret_cast<const bf16x8*>(&sK[(32 * u + l32) * KS + ks * 16 + half * 8]);
+            s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[ks], s[u], 0, 0, 0);
+        }
+    if (kbase + 64 > all) {
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const int kp = kbase + 32 * u + 8 * (e >> 2) + 4 * half + (e & 3);
+                s[u][e] = kp < all || kp < mine ? s[u][e] : -INFINITY;
+            }
+    }
+    float tmax = s[0][0];
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) tmax = fmaxf(tmax, s[u][e]);
+    {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
+        tmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2;
+    }
+    const float m_new = fmaxf(m_run, tmax);
+    const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+    const float alpha = fast_exp2(m_run - m_safe);
+    float psum[2] = {0.f, 0.f};
+    bf16x8 pb[4];
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const float p = fast_exp2(__builtin_fmaf(s[u][e], scale_log2, -m_safe));
+            psum[u] += p;
+            pb[2 * u + (e >> 3)][e & 7] = (__bf16)p;
+        }
+    float sum = psum[0] + psum[1];
+    {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+        sum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    }
+    l_run = l_run * alpha + sum;
+    m_run = m_new;
+    if (__any(alpha != 1.f)) {
+#pragma unroll
+        for (int dt = 0; dt < NDT; dt++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) o[dt][e] *= alpha;
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4; kk++)
+#pragma unroll
+        for (int dt = 0; dt < NDT; dt++) {
+            const bf16_t* vrow = &sV[(kk * HD + dt * 32 + l32) * VS];
+            const u32x2 lo = *reinterpret_cast<const u32x2*>(vrow + 4 * half);
+            const u32x2 hi = *reinterpret_cast<const u32x2*>(vrow + 8 + 4 * half);
+            union { u32x4 u; bf16x8 v; } va;
+            va.u = u32x4{lo.x, lo.y, hi.x, hi.y};
+            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.v, pb[kk], o[dt], 0, 0, 0);
+        }
 }
 
-// Per-lane variant: the page of position p0 (which differs from lane to lane), same fall-backs.
+// Page holding position p0 (which differs from lane to lane).  Positions at or beyond `total` (nothing written yet) and
+// malformed table entries resolve to the sequence's first page: its keys are masked and its finite values are
+// multiplied by exact zeros, so every load can be unconditional.
 __device__ inline int safe_page_lane(const int32_t* bt, int p0, int total, int max_blocks, int n_blocks) {
     int pidx = p0 >> 4;
     int page = (p0 < total && pidx < max_blocks) ? bt[pidx] : bt[0];
@@ -527,15 +594,18 @@ __global__ __launch_bounds__(256, (RTW == 1 ? 2 : 1)) void attn_verify_mfma(Attn
 // Bound by the softmax's vector arithmetic and, a little less, the matrix cores; a wavefront alternates between the two,
 // so it takes two wavefronts per SIMD to keep either busy: two workgroups per compute unit, each with its own barriers.
 // One workgroup per compute unit with two row tiles per wavefront, which ran them one after the other: 467 us for 4096
-// rows of 28 heads against 512 to 4096 keys, 115 us for 2048 rows of 12 heads; now 225 and 49 (530 TFLOP/s).
+// rows of 28 heads against 512 to 4096 keys, 115 us for 2048 rows of 12 heads.  Two workgroups: 225 and 49 us.  With two
+// tiles of keys in LDS (one barrier per tile instead of two, the next tile written while this one is multiplied), page
+// numbers held in a register and one softmax step per 64 keys: 190 and 38 us (630 TFLOP/s).
 template <int HD>
 __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, size_t layer_off,
     const int32_t* __restrict__ len_plus1, const int32_t* __restrict__ block_table, int max_blocks, int n_blocks,
     const int32_t* __restrict__ row_off, bf16_t* __restrict__ out, int hq, int hkv, float scale_log2, int batch, int nx) {
-    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32, RTW = 1, TILE = 64, NCK = HD / 32;
-    __shared__ __attribute__((aligned(16))) bf16_t sK[TILE * KS];
-    __shared__ __attribute__((aligned(16))) bf16_t sV[4 * HD * VS];
+    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32, TILE = 64, NCK = HD / 32;
+    constexpr int K_BUF = TILE * KS, V_BUF = 4 * HD * VS;
+    __shared__ __attribute__((aligned(16))) bf16_t sK[2 * K_BUF];
+    __shared__ __attribute__((aligned(16))) bf16_t sV[2 * V_BUF];
 
     // Workgroup id -> (sequence, KV head) pair and block of rows, the blocks that see the most keys first.  Ids are dealt
     // round-robin to the eight XCDs: with a multiple of eight pairs, all blocks of a pair go to one XCD and find its K
@@ -556,7 +626,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
     const int total = L + nn;
     const int G = hq / hkv;
     const int R = nn * G;
-    const int row_base = bx * (128 * RTW);
+    const int row_base = bx * 128;
     if (row_base >= R) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, l32 = lane & 31;
@@ -565,89 +635,78 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
     const bf16_t* vbase_ptr = vc + layer_off + (size_t)j * HD * 16;
     const size_t page_stride = (size_t)hkv * 16 * HD;
     // keys this block needs: up to the position of its last row's token
-    const int last_node = min(nn - 1, (min(R, row_base + 128 * RTW) - 1) / G);
+    const int last_node = min(nn - 1, (min(R, row_base + 128) - 1) / G);
     const int k_end = L + last_node + 1;
 
-    bf16x8 qf[RTW][NKS];
-    f32x16 o[RTW][NDT];
-    float m_run[RTW], l_run[RTW];
-    int lim_lane[RTW], lim_min[RTW], lim_max[RTW];
-    bool rt_on[RTW];
-#pragma unroll
-    for (int t = 0; t < RTW; t++) {
-        const int rt = bx * (4 * RTW) + wave + 4 * t;
-        rt_on[t] = rt * 32 < R;
+    const int rt = bx * 4 + wave;              // the wavefront's row tile
+    const bool rt_on = rt * 32 < R;
+    bf16x8 qf[NKS];
+    f32x16 o[NDT];
+    float m_run = -INFINITY, l_run = 0.f;
+    {
         uint64_t unused;
-        load_query_tile<HD>(q, nullptr, r0, rt_on[t] ? rt : 0, rt_on[t] ? R : 0, G, hq, j, half, l32, qf[t], unused);
-        const int rho = rt * 32 + l32;
-        lim_lane[t] = (rt_on[t] && rho < R) ? L + rho / G + 1 : 0;
-        lim_min[t] = L + (rt * 32) / G + 1;
-        lim_max[t] = L + min(nn - 1, (rt * 32 + 31) / G) + 1;
-#pragma unroll
-        for (int dt = 0; dt < NDT; dt++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) o[t][dt][e] = 0.f;
-        m_run[t] = -INFINITY;
-        l_run[t] = 0.f;
+        load_query_tile<HD>(q, nullptr, r0, rt_on ? rt : 0, rt_on ? R : 0, G, hq, j, half, l32, qf, unused);
     }
+    const int rho = rt * 32 + l32;
+    const int lim_lane = rho < R ? L + rho / G + 1 : 0;
+    const int lim_min = L + (rt * 32) / G + 1;
+    const int lim_max = L + min(nn - 1, (rt * 32 + 31) / G) + 1;
+#pragma unroll
+    for (int dt = 0; dt < NDT; dt++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) o[dt][e] = 0.f;
 
+    // Two tiles in LDS, a third on its way in registers: tile t + 1 is written while tile t is multiplied, one barrier per
+    // tile.  Lane p holds the page of keys 1024 n + 16 p .. + 15, handed out by readlane (a table look-up per tile and
+    // page would put a trip to memory between two tiles).  Every wavefront fetches one page of a tile.
+    static_assert(TILE == 64, "a wavefront per page");
     u32x4 rk[NCK], rv[NCK];
-    const int wave_c0 = tid & ~63;
-#define HS_P_FETCH(KB)                                                                                            \
-    {                                                                                                             \
-        _Pragma("unroll") for (int i = 0; i < NCK; i++) {                                                         \
-            const int kk = (wave_c0 + 256 * i) / (2 * HD);                                                        \
-            const int within = (tid + 256 * i) % (2 * HD);                                                        \
-            const size_t pofs = (size_t)safe_page(bt, (KB) + 16 * kk, total, max_blocks, n_blocks) * page_stride; \
-            rk[i] = *reinterpret_cast<const u32x4*>(kbase_ptr + pofs + within * 8);                               \
-            rv[i] = *reinterpret_cast<const u32x4*>(vbase_ptr + pofs + within * 8);                               \
-        }                                                                                                         \
-    }
-    HS_P_FETCH(0)
-    for (int kbase = 0; kbase < k_end; kbase += TILE) {
-        __syncthreads();  // previous tile fully consumed
+    int my_page = safe_page_lane(bt, 16 * lane, total, max_blocks, n_blocks);
+    auto fetch = [&](int kb) {
+        if ((kb & 1023) == 0 && kb > 0) my_page = safe_page_lane(bt, kb + 16 * lane, total, max_blocks, n_blocks);
+        const size_t pofs = (size_t)__builtin_amdgcn_readlane(my_page, ((kb >> 4) & 63) + wave) * page_stride;
 #pragma unroll
         for (int i = 0; i < NCK; i++) {
-            const int kk = (wave_c0 + 256 * i) / (2 * HD);
-            const int within = (tid + 256 * i) % (2 * HD);
-            int key = kk * 16 + within / (HD / 8), c16 = within % (HD / 8);
-            *reinterpret_cast<u32x4*>(&sK[key * KS + c16 * 8]) = rk[i];
-            int dim = within >> 1, hf = within & 1;
-            u32x2* dst = reinterpret_cast<u32x2*>(&sV[(kk * HD + dim) * VS + hf * 8]);
+            rk[i] = *reinterpret_cast<const u32x4*>(kbase_ptr + pofs + (lane + 64 * i) * 8);
+            rv[i] = *reinterpret_cast<const u32x4*>(vbase_ptr + pofs + (lane + 64 * i) * 8);
+        }
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < NCK; i++) {
+            const int c = lane + 64 * i;
+            *reinterpret_cast<u32x4*>(&sK[buf * K_BUF + (wave * 16 + c / (HD / 8)) * KS + (c % (HD / 8)) * 8]) = rk[i];
+            u32x2* dst = reinterpret_cast<u32x2*>(&sV[buf * V_BUF + (wave * HD + (c >> 1)) * VS + (c & 1) * 8]);
             dst[0] = u32x2{rv[i].x, rv[i].y};
             dst[1] = u32x2{rv[i].z, rv[i].w};
         }
+    };
+    fetch(0);
+    stage(0);
+    if (TILE < k_end) fetch(TILE);
+    __syncthreads();
+    int buf = 0;
+    for (int kbase = 0; kbase < k_end; kbase += TILE, buf ^= 1) {
+        if (kbase + TILE < k_end) stage(buf ^ 1);
+        if (kbase + 2 * TILE < k_end) fetch(kbase + 2 * TILE);
+        if (rt_on && kbase < lim_max)          // wavefront-uniform: something of this tile is visible
+            attn_tile64<HD>(sK + buf * K_BUF, sV + buf * V_BUF, qf, o, m_run, l_run, kbase, lim_min, lim_lane, scale_log2,
+                            half, l32);
         __syncthreads();
-        if (kbase + TILE < k_end) HS_P_FETCH(kbase + TILE)
+    }
+    if (!rt_on || rho >= R) return;
+    const int node = rho / G, g = rho - node * G;
+    const float inv = 1.f / l_run;     // a row always sees its own key: the sum is positive
+    bf16_t* po = out + ((size_t)(r0 + node) * hq + j * G + g) * HD;
 #pragma unroll
-        for (int sub = 0; sub < 2; sub++) {
-            const int kb = kbase + 32 * sub;
+    for (int dt = 0; dt < NDT; dt++)
 #pragma unroll
-            for (int t = 0; t < RTW; t++) {
-                if (!rt_on[t] || kb >= lim_max[t]) continue;   // wavefront-uniform: nothing of this sub-tile is visible
-                attn_subtile<HD, true>(sK + sub * 32 * KS, sV + sub * 2 * HD * VS, qf[t], o[t], m_run[t], l_run[t], 0ull,
-                                       kb, lim_min[t], lim_lane[t], scale_log2, half, l32);
-            }
+        for (int g4 = 0; g4 < 4; g4++) {
+            u32x2 w;
+            w.x = (uint32_t)f32_to_bf16(o[dt][4 * g4] * inv) | ((uint32_t)f32_to_bf16(o[dt][4 * g4 + 1] * inv) << 16);
+            w.y = (uint32_t)f32_to_bf16(o[dt][4 * g4 + 2] * inv) | ((uint32_t)f32_to_bf16(o[dt][4 * g4 + 3] * inv) << 16);
+            *reinterpret_cast<u32x2*>(po + dt * 32 + 8 * g4 + 4 * half) = w;
         }
-    }
-#undef HS_P_FETCH
-#pragma unroll
-    for (int t = 0; t < RTW; t++) {
-        const int rho = (bx * (4 * RTW) + wave + 4 * t) * 32 + l32;
-        if (!rt_on[t] || rho >= R) continue;
-        const int node = rho / G, g = rho - node * G;
-        const float inv = 1.f / l_run[t];     // a row always sees its own key: the sum is positive
-        bf16_t* po = out + ((size_t)(r0 + node) * hq + j * G + g) * HD;
-#pragma unroll
-        for (int dt = 0; dt < NDT; dt++)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; g4++) {
-                u32x2 w;
-                w.x = (uint32_t)f32_to_bf16(o[t][dt][4 * g4] * inv) | ((uint32_t)f32_to_bf16(o[t][dt][4 * g4 + 1] * inv) << 16);
-                w.y = (uint32_t)f32_to_bf16(o[t][dt][4 * g4 + 2] * inv) | ((uint32_t)f32_to_bf16(o[t][dt][4 * g4 + 3] * inv) << 16);
-                *reinterpret_cast<u32x2*>(po + dt * 32 + 8 * g4 + 4 * half) = w;
-            }
-    }
 }
 
 // Combine the partitions of one (row, query head) in partition order: one wavefront per (row, head), four per

@@ -171,15 +171,19 @@ hs_status hs_create(const hs_model_desc* desc, const hs_weights* w, const hs_lim
     // Split-KV partition length (a multiple of 32 keys, at most 64 pages): a function of the context's limits only,
     // so results are identical across calls.  The longest of 1024 / 512 / 256 keys that still cuts a full batch at
     // maximum length into a few thousand partitions per layer: longer partitions mean fewer partial results for the
-    // merge kernel to re-read, shorter ones keep a small batch spread over the whole chip.
+    // merge kernel to re-read, shorter ones keep a small batch spread over the whole chip.  Where 256 keys give fewer than
+    // 1024 partitions there is at most one for every second wavefront, and the launch lasts as long as one wavefront's
+    // chain of 32-key steps: 128 keys (7 sequences of up to 2600 tokens, four 1.5B layers: 300 -> 285 us; 4 short ones
+    // through the two toy layers: 113 -> 110 us).  With 1408 partitions 128 keys were 0.6 % slower.  (Not where a context
+    // made for large prefill calls would need more than 512 MB for the partial results.)
     {
         const long long keys = (long long)l.max_blocks_per_seq * 16;
         ctx->att_part = 256;
-        for (int part : {1024, 512}) {
-            if ((long long)l.max_batch * d.n_kv_heads * ((keys + part - 1) / part) >= 4096) {
-                ctx->att_part = part;
-                break;
-            }
+        for (int part : {1024, 512, 256, 128}) {
+            const long long parts = (keys + part - 1) / part, total = parts * l.max_batch * d.n_kv_heads;
+            if (part == 128 && (long long)l.max_rows * d.n_q_heads * parts * d.head_dim * 2 > (512ll << 20)) break;
+            ctx->att_part = part;
+            if (total >= (part == 256 ? 1024 : 4096)) break;
         }
     }
     const long long max_keys = (long long)l.max_blocks_per_seq * 16;

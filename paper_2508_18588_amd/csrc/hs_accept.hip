@@ -99,12 +99,11 @@ __device__ inline bool stats_ahead(int m, int pos, int root_pos) { return m <= S
 // error is that of rounding c and the result, 2^-53 |x| + 2 ulp.  The sixteen table entries cover the 32 LDS banks once:
 // no lookup conflicts with another.  Differences below -746 T, -inf among them, are taken as -746 T, where the result is
 // 0 or the smallest number; a NaN comes out as such a value, too, so callers look for NaNs themselves.
-struct exp_scale { float low; double c; };
-__device__ inline exp_scale make_scale(double inv_temp) {
-    return {(float)fmax(-746.0 / inv_temp, -3.0e38), inv_temp * 23.083120654223414};
-}
+// (The clamp is on the fp64 difference: at a low temperature -746 T is less than an fp32 logit resolves.)
+struct exp_scale { double low, c; };
+__device__ inline exp_scale make_scale(double inv_temp) { return {-746.0 / inv_temp, inv_temp * 23.083120654223414}; }
 __device__ inline double exp_diff(float l, float ref, const exp_scale& k, const double* tab) {
-    const double d = (double)fmaxf(l, ref + k.low) - (double)ref;
+    const double d = fmax((double)l - (double)ref, k.low);
     const double t = __builtin_fma(d, k.c, 6755399441055744.0);      // + 1.5 2^52: n in the low bits
     const int n = __double2loint(t);
     const double f = __builtin_fma(d, k.c, -(t - 6755399441055744.0));
@@ -172,7 +171,7 @@ __device__ inline void slice_stats(const float (&v)[PER], double inv_temp, const
     if (threadIdx.x == 0) { dst->m = mx; dst->s = s; }
 }
 
-// grid (slices, sequences, row split): a workgroup takes rows blockIdx.z, blockIdx.z + gridDim.z, ... of its sequence,
+// grid (sequences, slices, row split): a workgroup takes rows blockIdx.z, blockIdx.z + gridDim.z, ... of its sequence,
 // the next row's logits on their way while it sums the current one's.
 __global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __restrict__ row_off,
                                                             const int32_t* __restrict__ pos,
@@ -180,7 +179,7 @@ __global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __r
                                                             double inv_temp, hs_reject_stat* __restrict__ stats) {
     __shared__ double tab[16];
     fill_exp_table(tab);
-    const int b = blockIdx.y, n_slices = gridDim.x, slice = blockIdx.x, m = row_off[batch];
+    const int b = blockIdx.x, n_slices = gridDim.y, slice = blockIdx.y, m = row_off[batch];
     const int r0 = row_off[b], r1 = row_off[b + 1];
     const bool vec = (vocab & 3) == 0 && ((unsigned long long)logits & 15ull) == 0;
     auto next_row = [&](int r) {      // the first row from r on that is computed ahead
@@ -610,7 +609,7 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
         const int nodes = 1 + ctx->lim.c_max * ctx->lim.k_max;
         int split = 2048 / (p.n_slices * p.batch);
         split = split < 1 ? 1 : (split > nodes ? nodes : split);
-        hipLaunchKernelGGL(reject_stats_kernel, dim3(p.n_slices, p.batch, split), dim3(256), 0, st, p.row_off, p.pos,
+        hipLaunchKernelGGL(reject_stats_kernel, dim3(p.batch, p.n_slices, split), dim3(256), 0, st, p.row_off, p.pos,
                            logits, p.vocab, p.batch, p.inv_temp, p.stats);
     }
     p.accept_len = step->accept_len; p.n_out = step->n_out; p.out_tok = step->out_tok; p.path_row = step->path_row;

@@ -273,3 +273,39 @@ def test_rejection_over_several_vocabulary_slices(toy, V, B, k, rows_big):
             r += n
     eng.close()
     assert accepted > 0
+
+
+@pytest.mark.parametrize("temperature", [1e-12, 1e-6, 1e-3, 50.0, 1e30])
+def test_rejection_at_extreme_temperatures(toy, temperature):
+    """Far below the spacing of fp32 logits (only the largest ones count, ties among them included) and far above their
+    range (every token counts alike): same decisions as the oracle, unless its margin is below 1e-9."""
+    from paper_2508_18588_amd import HS_ACCEPT_REJECTION
+    from paper_2508_18588_amd.runtime import Engine
+    shape, w, rope = toy
+    V, B, T = shape.vocab, 6, float(np.float32(temperature))
+    rng = np.random.default_rng(17)
+    eng = Engine(shape, w, rope, max_batch=B, k_max=4, c_max=2, max_len=80)
+    eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B)
+    trees = [oracle.build_tree([rng.integers(0, V, 4), rng.integers(0, V, 4)], 0, 50) for _ in range(B)]
+    m = eng.set_rows([dict(tok=t["tok"], parent=t["parent"], pos=t["pos"]) for t in trees])
+    lg = rng.normal(10.0, 2.0, size=(m, V)).astype(np.float32)
+    r = 0
+    for t in trees:
+        top = lg[r:r + len(t["tok"])].max()
+        for i in range(1, len(t["tok"])):              # drafted tokens tie with, or lie one spacing off, the largest logit
+            lg[r + t["parent"][i], t["tok"][i]] = rng.choice([top, np.nextafter(top, np.float32(0)), 3.0])
+        lg[r:r + len(t["tok"]), 7] = top
+        r += len(t["tok"])
+    eng.logits[:m].copy_(torch.from_numpy(lg))
+    eng.accept(HS_ACCEPT_REJECTION, T, 99)
+    torch.cuda.synchronize()
+    st = {n: np_of(v) for n, v in eng.st.items()}
+    r = 0
+    for b, t in enumerate(trees):
+        n = len(t["tok"])
+        a, out, path, margin = oracle.accept_stochastic(t["tok"], t["parent"], t["pos"], lg[r:r + n].astype(np.float64), T, 99, b)
+        g = st["n_out"][b]
+        got = (int(st["accept_len"][b]), st["out_tok"][b, :g].tolist(), st["path_row"][b, :g].tolist())
+        assert got == (a, out.tolist(), path.tolist()) or margin < 1e-9, (b, got, a, out, path, margin)
+        r += n
+    eng.close()

@@ -2,10 +2,10 @@
 // the longest suffix of its committed tokens (at most `window`, at least `m_min` tokens) inside its previous-epoch
 // response and takes the tokens that follow as its draft.
 //
-// Kernel 1 (scan): one workgroup per (history segment, candidate).  The segment plus a `window`-token halo is
-// staged in LDS with coalesced loads; every thread then tests end positions p against the pattern held in
-// registers/LDS, and the best (match length, leftmost p) is reduced with wavefront shuffles as one packed 64-bit
-// key.  Kernel 2 (build): one thread per sequence reduces the segment winners, applies the draft-length policy
+// Kernel 1 (scan): one workgroup per (history segment, candidate), or for several segments in turn.  The segment plus a
+// `window`-token halo is staged in LDS with coalesced loads; every thread then tests end positions p against the pattern,
+// and the best (match length, leftmost p) is reduced with wavefront shuffles as one packed 64-bit key.  Kernel 2 (build):
+// one thread per sequence reduces the segment winners, applies the draft-length policy
 // and finds the candidates' shared prefix, a workgroup-wide prefix sum over node counts yields the ragged row offsets,
 // and the rows of the token trees are written a node per lane.
 #include <mutex>
@@ -26,6 +26,12 @@ __device__ inline unsigned long long shfl_xor_u64(unsigned long long v, int o) {
 __device__ inline int draft_key_len(unsigned long long k) { return (int)((k >> 32) & 0xFFu); }
 __device__ inline int draft_key_count(unsigned long long k) { return (int)(k >> 40); }
 
+// Bound by reading the histories, and by what a workgroup waits for before it can: offsets and lengths (asked for
+// together), then the tokens (all in flight at once, in registers), then LDS.  A workgroup takes the segments blockIdx.x,
+// blockIdx.x + gridDim.x, ... of its history, the next one's tokens on their way while it compares the current one.
+// 2048 histories of 2k to 16k tokens (75 MB, 12 us at the rate of a plain read): 25 -> 20 us; 128 sequences with up to
+// 16k tokens, a workgroup per segment: 5.8 -> 5.3 us.  A cap at 64 registers for eight workgroups per compute unit
+// instead of five: 22 us.
 template <bool COUNT>
 __global__ __launch_bounds__(256) void draft_scan_kernel(const int32_t* __restrict__ hist,
                                                           const int32_t* __restrict__ hist_off, int n_cand,
@@ -38,69 +44,106 @@ __global__ __launch_bounds__(256) void draft_scan_kernel(const int32_t* __restri
     __shared__ int32_t pat[32];
     __shared__ unsigned long long red[4];
     __shared__ int red_cnt[4];
-    const int seg = blockIdx.x, bc = blockIdx.y, b = bc / n_cand;
-    const int tid = threadIdx.x;
-    unsigned long long* dst = best + (size_t)bc * max_segs + seg;
-    const int off = hist_off[bc];
-    const int lh = hist_off[bc + 1] - off;
-    const int p_lo = seg * HS_DRAFT_SEG + 1;                   // end positions handled here: [p_lo, p_hi]
-    const int p_hi = min((seg + 1) * HS_DRAFT_SEG, lh - 1);
-    int n_pat = min(min(tail_len[b], window), w_max);
-    if (budget_left[b] <= 0 || p_lo > p_hi || n_pat < m_min || n_pat <= 0) {
-        if (tid == 0) *dst = 0ull;
-        return;
-    }
-    // pattern, newest token first: pat[i] = i-th token from the end
-    if (tid < n_pat) pat[tid] = tail[(size_t)b * w_max + (w_max - 1 - tid)];
-    // tokens hist[base .. p_hi) are needed: base = p_lo - window (clamped).  They are staged with 16-byte loads
-    // from the 16-byte boundary at or below the first token: LDS entry `shift` + i holds hist[off + base + i].
-    // (Tokens in front of that boundary belong to this or the previous history: in bounds, never compared.  A
-    // vector that would reach past this history's end is loaded token by token.)
-    const int base = max(0, p_lo - window);
-    const int count = p_hi - base;
-    const int g0 = off + base, a0 = g0 & ~3, shift = g0 - a0, g_end = off + lh;
-    const int4* src4 = reinterpret_cast<const int4*>(hist + a0);
-    for (int v = tid; 4 * v < shift + count; v += 256) {
-        if (a0 + 4 * v + 4 <= g_end) {
-            *reinterpret_cast<int4*>(&sh[4 * v]) = src4[v];
-        } else {
-            for (int e = 0; e < 4; e++)
-                if (a0 + 4 * v + e < g_end) sh[4 * v + e] = hist[a0 + 4 * v + e];
-        }
-    }
-    __syncthreads();
-    unsigned long long k = 0ull;
-    int cnt = 0;   // places that reach the length in k
-    const int32_t* shb = sh + shift - base;          // shb[i] = hist[off + i]
-    for (int p = p_lo + tid; p <= p_hi; p += 256) {
-        int lim = min(n_pat, p);
-        int m = 0;
-        while (m < lim && shb[p - 1 - m] == pat[m]) m++;
-        if (m >= m_min) {
-            unsigned long long cand = ((unsigned long long)m << 32) | (0xFFFFFFFFu - (unsigned)p);
-            if (COUNT) cnt = (cand >> 32) > (k >> 32) ? 1 : cnt + ((cand >> 32) == (k >> 32));
-            if (cand > k) k = cand;
-        }
-    }
+    const int bc = blockIdx.y, b = bc / n_cand;
+    const int tid = threadIdx.x, lane = tid & 63;
+    unsigned long long* dst = best + (size_t)bc * max_segs;
+    const int32_t* newest = tail + (size_t)b * w_max + (w_max - 1);
+    // all asked for before any is used
+    const int off = hist_off[bc], g_end = hist_off[bc + 1], n_tail = tail_len[b], left = budget_left[b];
+    const int pat0 = newest[0];
+    const int lh = g_end - off;
+    const int n_pat = min(min(n_tail, window), w_max);
+    // segments with a place to test (end positions p run from 1 to lh - 1); none if nothing is looked for
+    const bool looks = left > 0 && n_pat >= m_min && n_pat > 0;
+    const int n_seg = looks ? min(max_segs, (lh - 1 + HS_DRAFT_SEG - 1) / HS_DRAFT_SEG) : 0;
+    for (int seg = max(n_seg, 0) + tid; seg < max_segs; seg += 256)
+        if (seg % (int)gridDim.x == (int)blockIdx.x) dst[seg] = 0ull;
+    if ((int)blockIdx.x >= n_seg) return;
+    // tokens hist[base .. p_hi) of a segment are needed: base = p_lo - window (clamped).  They are fetched with 16-byte
+    // loads from the 16-byte boundary at or below the first token: LDS entry `shift` + i holds hist[off + base + i].
+    // (Tokens in front of that boundary belong to this or the previous history: in bounds, never compared.  Up to three
+    // tokens of a vector that would reach past this history's end are loaded one by one.)
+    constexpr int NV = (HS_DRAFT_SEG + 32 + 3 + 4 * 256 - 1) / (4 * 256);
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+    i32x4 r[NV] = {};
+    int32_t r_end = 0;
+    auto fetch = [&](int seg) {
+        const int p_lo = seg * HS_DRAFT_SEG + 1, p_hi = min((seg + 1) * HS_DRAFT_SEG, lh - 1);
+        const int base = max(0, p_lo - window), a0 = (off + base) & ~3, n = off + p_hi - a0;
+        const int n_vec = min((n + 3) & ~3, (g_end - a0) & ~3);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        unsigned long long other = shfl_xor_u64(k, o);
-        if (COUNT) {
-            const int oc = __shfl_xor(cnt, o);
-            cnt = (other >> 32) > (k >> 32) ? oc : (other >> 32) == (k >> 32) ? cnt + oc : cnt;
+        for (int j = 0; j < NV; j++)
+            if (4 * (tid + 256 * j) < n_vec) r[j] = *reinterpret_cast<const i32x4*>(hist + a0 + 4 * (tid + 256 * j));
+        if (n_vec + tid < n && tid < 4) r_end = hist[a0 + n_vec + tid];
+    };
+    fetch(blockIdx.x);
+    // pattern, newest token first: pat[i] = i-th token from the end
+    if (tid < n_pat) pat[tid] = newest[-tid];
+    for (int seg = blockIdx.x; seg < n_seg; seg += gridDim.x) {
+        const int p_lo = seg * HS_DRAFT_SEG + 1;                   // end positions handled here: [p_lo, p_hi]
+        const int p_hi = min((seg + 1) * HS_DRAFT_SEG, lh - 1);
+        const int base = max(0, p_lo - window), a0 = (off + base) & ~3, n = off + p_hi - a0;
+        const int n_vec = min((n + 3) & ~3, (g_end - a0) & ~3);
+        if (seg != (int)blockIdx.x) __syncthreads();               // the previous segment has been compared
+#pragma unroll
+        for (int j = 0; j < NV; j++)
+            if (4 * (tid + 256 * j) < n_vec) *reinterpret_cast<i32x4*>(&sh[4 * (tid + 256 * j)]) = r[j];
+        if (n_vec + tid < n && tid < 4) sh[n_vec + tid] = r_end;
+        __syncthreads();
+        if (seg + (int)gridDim.x < n_seg) fetch(seg + gridDim.x);
+        const int32_t* shb = sh + off - a0;              // shb[i] = hist[off + i]
+        // a match ends with the pattern's newest token: sixteen places per thread are tested for it at once
+        // (places past p_hi read LDS entries that nothing was staged to; they are masked)
+        int32_t t[HS_DRAFT_SEG / 256];
+#pragma unroll
+        for (int i = 0; i < HS_DRAFT_SEG / 256; i++) t[i] = shb[p_lo - 1 + tid + 256 * i];
+        unsigned hits = 0u;
+#pragma unroll
+        for (int i = 0; i < HS_DRAFT_SEG / 256; i++)
+            hits |= ((p_lo + tid + 256 * i <= p_hi) & (t[i] == pat0)) ? 1u << i : 0u;
+        unsigned long long k = 0ull;
+        int cnt = 0;   // places that reach the length in k
+        for (; hits; hits &= hits - 1) {
+            const int p = p_lo + tid + 256 * (__ffs(hits) - 1);
+            const int lim = min(n_pat, p);
+            int m = 1;
+            while (m < lim && shb[p - 1 - m] == pat[m]) m++;
+            if (m >= m_min) {
+                unsigned long long cand = ((unsigned long long)m << 32) | (0xFFFFFFFFu - (unsigned)p);
+                if (COUNT) cnt = (cand >> 32) > (k >> 32) ? 1 : cnt + ((cand >> 32) == (k >> 32));
+                if (cand > k) k = cand;
+            }
         }
-        if (other > k) k = other;
-    }
-    if ((tid & 63) == 0) { red[tid >> 6] = k; red_cnt[tid >> 6] = cnt; }
-    __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < 4; w++) {
-            if (COUNT)
-                cnt = (red[w] >> 32) > (k >> 32) ? red_cnt[w] : (red[w] >> 32) == (k >> 32) ? cnt + red_cnt[w] : cnt;
-            if (red[w] > k) k = red[w];
+        if (__any(k != 0ull)) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                unsigned long long other = shfl_xor_u64(k, o);
+                if (COUNT) {
+                    const int oc = __shfl_xor(cnt, o);
+                    cnt = (other >> 32) > (k >> 32) ? oc : (other >> 32) == (k >> 32) ? cnt + oc : cnt;
+                }
+                if (other > k) k = other;
+            }
         }
-        *dst = COUNT && k ? k | ((unsigned long long)cnt << 40) : k;
+        if (lane == 0) { red[tid >> 6] = k; red_cnt[tid >> 6] = cnt; }
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < 4; w++) {
+                if (COUNT)
+                    cnt = (red[w] >> 32) > (k >> 32) ? red_cnt[w] : (red[w] >> 32) == (k >> 32) ? cnt + red_cnt[w] : cnt;
+                if (red[w] > k) k = red[w];
+            }
+            dst[seg] = COUNT && k ? k | ((unsigned long long)cnt << 40) : k;
+        }
     }
+}
+
+// Workgroups per history: all of its segments side by side, unless there are more histories than that fills the chip with
+// (eight workgroups per compute unit; 2048 histories of up to 5 segments take 19.6 us with one each, 21.5 with five); no
+// more than eight segments in turn, so that one long history does not keep the others waiting.
+int hs_scan_groups(const hs_ctx* ctx, int histories) {
+    const int fill = (8 * ctx->n_cu + histories - 1) / histories, most = (ctx->max_segs + 7) / 8;
+    return min(ctx->max_segs, max(fill, most));
 }
 
 // Exclusive prefix sum over a workgroup of NT threads: wavefront scans by shuffles, then the wavefront totals.
@@ -416,7 +459,7 @@ __global__ __launch_bounds__(256) void draft_group_walk_kernel(
     kk = max(0, min(min(kk, pol.k_max), budget_left[b] - 1));
     // Few occurrences (the usual case): their next tokens are fetched at once and one wavefront walks alone, an occurrence
     // per lane -- no memory and no barrier between two draft tokens.  128 prompts with 16 responses: the whole kernel
-    // 88 -> 13 us, the call 127 -> 43 us.
+    // 88 -> 13 us.
     if (n_occ <= 64) {
         for (int i = tid; i < n_occ * kk; i += 256) {
             const int q = i / kk, j = i - q * kk;
@@ -528,7 +571,7 @@ namespace {
 void launch_draft(const hs_ctx* ctx, const hs_draft_args* args, const hs_seq_state* seq, hs_step* step,
                   unsigned long long* best, uint32_t* err, hipStream_t st) {
     const hs_policy& p = args->policy;
-    dim3 grid(ctx->max_segs, seq->batch * args->n_cand);
+    dim3 grid(hs_scan_groups(ctx, seq->batch * args->n_cand), seq->batch * args->n_cand);
     hipLaunchKernelGGL(draft_scan_kernel<false>, grid, dim3(256), 0, st, args->hist, args->hist_off, args->n_cand,
                        seq->tail, seq->tail_len, seq->budget_left, ctx->lim.w_max, p.window, p.m_min,
                        ctx->max_segs, best);
@@ -597,7 +640,7 @@ void hs_launch_draft_group(const hs_ctx* ctx, const hs_group_draft_args* args, c
     unsigned long long* best = reinterpret_cast<unsigned long long*>(ctx->ws + ctx->lay.draft_best);
     uint32_t* err = reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.err);
     const hs_policy& p = args->policy;
-    dim3 grid(ctx->max_segs, seq->batch * args->n_resp);
+    dim3 grid(hs_scan_groups(ctx, seq->batch * args->n_resp), seq->batch * args->n_resp);
     hipLaunchKernelGGL(draft_scan_kernel<true>, grid, dim3(256), 0, st, args->hist, args->hist_off, args->n_resp,
                        seq->tail, seq->tail_len, seq->budget_left, ctx->lim.w_max, p.window, p.m_min,
                        ctx->max_segs, best);

@@ -166,3 +166,36 @@ def test_group_draft_end_to_end_equals_autoregressive_greedy(toy):
     eng.close()
     print("group draft end to end: steps", steps, "accepted", accepted)
     assert accepted > 40
+
+
+@pytest.mark.parametrize("B,G", [(128, 16), (64, 16), (3, 16)])
+def test_group_draft_with_segments_in_turn(toy, B, G):
+    """A workgroup of the scan takes one, two or all of a history's segments of 4096 tokens, by the number of histories:
+    lengths around the segments' edges, at every alignment of a history's first and last token, a planted match of every
+    length up to the window on either side of an edge."""
+    from paper_2508_18588_amd import HS_K_FIXED
+    from paper_2508_18588_amd.runtime import Engine, Policy
+    shape, w, _ = toy
+    rng = np.random.default_rng(1000 * B + G)
+    eng = Engine(shape, w, rope_table(16384, shape.head_dim), max_batch=B, k_max=16, c_max=1, max_len=10000, g_max=16)
+    pol = Policy(window=16, m_min=2, k_mode=HS_K_FIXED, k_fixed=8, k_max=16)
+    xs, groups = [], []
+    for b in range(B):
+        xs.append(rng.integers(0, 300, 20).astype(np.int32))
+        responses = []
+        for g in range(G):
+            edge = 4096 * int(rng.integers(0, 3))
+            n = max(0, edge + int(rng.integers(-5, 24)))
+            h = rng.integers(0, 300, n).astype(np.int32)
+            m = int(rng.integers(1, 17))
+            at = min(n, max(0, 4096 * int(rng.integers(0, 3)) + int(rng.integers(-18, 3)))) - m
+            if at >= 0:
+                h[at:at + m] = xs[b][-m:]
+            responses.append(h)
+        groups.append(responses)
+    rewards = [rng.integers(0, 4, G).astype(np.int32) for _ in range(B)]
+    st = run_group_draft(eng, xs, groups, rewards, pol)
+    check_against_oracle(st, xs, groups, rewards, pol, [8] * B)
+    assert (st["draft_len"][:B] > 0).any()
+    assert B < 64 or len(set(st["draft_start"][:B] // 4096)) == 3        # chosen in each of the segments
+    eng.close()

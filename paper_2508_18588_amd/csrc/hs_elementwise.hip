@@ -10,10 +10,17 @@
 
 namespace {
 
-constexpr int NORM_THREADS = 1024;  // one workgroup of 16 wavefronts per row: few rows, many loads in flight each
+// A row's norm is a workgroup of norm_threads(d) threads, each with 4 elements in up to NORM_ITEMS rounds
+// (d_model <= 16384, checked by hs_create).
+constexpr int NORM_ITEMS = 4, NORM_THREADS_MAX = 1024;
 
 __device__ __forceinline__ void put(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 __device__ __forceinline__ void put(float* p, float v) { *p = v; }
+
+// once, before the first block_sum (whose first barrier publishes it)
+__device__ inline void clear_sums(float* red) {
+    if (threadIdx.x < NORM_THREADS_MAX / 64) red[threadIdx.x] = 0.f;
+}
 
 __device__ inline float block_sum(float v, float* red) {
     // fixed tree: xor-shuffle inside each wavefront, then the wavefront sums left to right
@@ -23,7 +30,8 @@ __device__ inline float block_sum(float v, float* red) {
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     float s = red[0];
-    for (int w = 1; w < NORM_THREADS / 64; w++) s += red[w];
+#pragma unroll
+    for (int w = 1; w < NORM_THREADS_MAX / 64; w++) s += red[w];     // (0 beyond the last wavefront: clear_sums)
     return s;
 }
 
@@ -32,9 +40,8 @@ __device__ inline float block_sum(float v, float* red) {
 // reduce, so that the split execution gives the same bits whichever kernel finishes it.
 // OutT = bf16_t (rounded activations) or float (fp32-activation mode).
 // The kernel is a chain of memory round trips, not a stream: a thread keeps its (up to NORM_ITEMS x 4) elements in
-// registers from the first load to the normalised store, and the norm weights are fetched with them.
-constexpr int NORM_ITEMS = 4;  // d_model <= 4 * NORM_THREADS * NORM_ITEMS = 16384 (checked by hs_create)
-
+// registers from the first load to the normalised store, and the norm weights are fetched with them.  What hides the
+// chain when there are many rows is other rows: HS_NORM_NOW
 __device__ __forceinline__ void put4(bf16_t* p, float4 v) {
     uint2 o;
     o.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
@@ -43,15 +50,23 @@ __device__ __forceinline__ void put4(bf16_t* p, float4 v) {
 }
 __device__ __forceinline__ void put4(float* p, float4 v) { p[0] = v.x; p[1] = v.y; p[2] = v.z; p[3] = v.w; }   // (any alignment)
 
-template <typename OutT>
-__device__ inline void norm_row(const float4 (&v)[NORM_ITEMS], const float4 (&g)[NORM_ITEMS], bool store_x, float* xr,
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// four floats `bytes` from a pointer that all threads share (a 32-bit offset leaves the address in scalar registers)
+template <typename T>
+__device__ __forceinline__ T load4(const float* base, unsigned bytes) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
+}
+
+template <typename OutT, int ITEMS>
+__device__ inline void norm_row(const float4 (&v)[ITEMS], const float4 (&g)[ITEMS], bool store_x, float* xr,
                                 OutT* out, int d, float eps, float* red) {
     // the sum of squares: same element-to-thread assignment and order wherever the row came from -- the norm must not
     // depend on which execution the preceding projection used
     float ss = 0.f;
 #pragma unroll
-    for (int it = 0; it < NORM_ITEMS; it++) {
-        const int i = (threadIdx.x + it * NORM_THREADS) * 4;
+    for (int it = 0; it < ITEMS; it++) {
+        const int i = (threadIdx.x + it * blockDim.x) * 4;
         if (i >= d) continue;
         if (store_x) *reinterpret_cast<float4*>(xr + i) = v[it];
         ss += v[it].x * v[it].x;
@@ -62,8 +77,8 @@ __device__ inline void norm_row(const float4 (&v)[NORM_ITEMS], const float4 (&g)
     ss = block_sum(ss, red);
     const float r = rsqrtf(ss / (float)d + eps);
 #pragma unroll
-    for (int it = 0; it < NORM_ITEMS; it++) {
-        const int i = (threadIdx.x + it * NORM_THREADS) * 4;
+    for (int it = 0; it < ITEMS; it++) {
+        const int i = (threadIdx.x + it * blockDim.x) * 4;
         if (i >= d) continue;
         float4 o;
         o.x = v[it].x * r * g[it].x; o.y = v[it].y * r * g[it].y;
@@ -76,16 +91,17 @@ __device__ inline void norm_row(const float4 (&v)[NORM_ITEMS], const float4 (&g)
 // workgroups write the attention's unit lists instead (nothing here depends on them), the others take rows.
 // (As three launches -- 2-byte gathers, the lists by one workgroup, the norm reading the gathers back -- 28 us at 220 rows
 // of 3584 and 128 sequences, now 6.5; 1067 rows of 5120: 45, now 19.)
-template <typename OutT>
-__global__ __launch_bounds__(NORM_THREADS) void embed_norm_kernel(
+template <typename OutT, int ITEMS>
+__global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void embed_norm_kernel(
     const bf16_t* __restrict__ embed, const int32_t* __restrict__ tok, int vocab, float* __restrict__ x,
     const float* __restrict__ w, OutT* __restrict__ out, const int32_t* __restrict__ row_off, int batch, int d, float eps,
     int list_groups, hs_attn_lists lists, const int32_t* __restrict__ seq_len) {
-    __shared__ float red[NORM_THREADS / 64];
+    __shared__ float red[NORM_THREADS_MAX / 64];
     if ((int)blockIdx.x < list_groups) {
-        hs_write_worklist(lists, seq_len, row_off, batch, blockIdx.x);
+        hs_write_worklist(lists, seq_len, row_off, batch, blockIdx.x, list_groups);
         return;
     }
+    clear_sums(red);
     const int m = row_off[batch];
     // (the embedding rows may start at any bf16: 8-byte loads where their base allows)
     const bool vec = ((unsigned long long)embed & 7ull) == 0;
@@ -93,10 +109,10 @@ __global__ __launch_bounds__(NORM_THREADS) void embed_norm_kernel(
         int t = tok[row];
         if (t < 0 || t >= vocab) t = 0;
         const bf16_t* e = embed + (size_t)t * d;
-        float4 v[NORM_ITEMS], g[NORM_ITEMS];
+        float4 v[ITEMS], g[ITEMS];
 #pragma unroll
-        for (int it = 0; it < NORM_ITEMS; it++) {
-            const int i = (threadIdx.x + it * NORM_THREADS) * 4;
+        for (int it = 0; it < ITEMS; it++) {
+            const int i = (threadIdx.x + it * blockDim.x) * 4;
             if (i >= d) continue;
             g[it] = *reinterpret_cast<const float4*>(w + i);
             ushort4 b;
@@ -104,40 +120,62 @@ __global__ __launch_bounds__(NORM_THREADS) void embed_norm_kernel(
             else b = make_ushort4(e[i], e[i + 1], e[i + 2], e[i + 3]);
             v[it] = make_float4(bf16_to_f32(b.x), bf16_to_f32(b.y), bf16_to_f32(b.z), bf16_to_f32(b.w));
         }
-        norm_row<OutT>(v, g, true, x + (size_t)row * d, out + (size_t)row * d, d, eps, red);
+        norm_row<OutT, ITEMS>(v, g, true, x + (size_t)row * d, out + (size_t)row * d, d, eps, red);
     }
 }
 
-template <typename OutT>
-__global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
+template <typename OutT, int ITEMS>
+__global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
                                                        OutT* __restrict__ out, const int32_t* __restrict__ m_dev,
                                                        int d, float eps,
                                                        const float* __restrict__ part, int chunks,
                                                        size_t chunk_stride) {
-    __shared__ float red[NORM_THREADS / 64];
+    __shared__ float red[NORM_THREADS_MAX / 64];
+    clear_sums(red);
     const int m = *m_dev;
     for (int row = blockIdx.x; row < m; row += gridDim.x) {
         float* xr = x + (size_t)row * d;
         const float* pr = part + (size_t)row * d;
-        float4 v[NORM_ITEMS], g[NORM_ITEMS];
+        float4 v[ITEMS], g[ITEMS];
+        unsigned at[ITEMS]; // byte offsets (beyond the row's end its last elements': no branch between the loads)
 #pragma unroll
-        for (int it = 0; it < NORM_ITEMS; it++) {
-            const int i = (threadIdx.x + it * NORM_THREADS) * 4;
-            if (i >= d) continue;
-            v[it] = *reinterpret_cast<const float4*>(xr + i);
-            g[it] = *reinterpret_cast<const float4*>(w + i);
-            if (chunks > 0) {
-                // several partials of an element in flight at once
-                float4 t = *reinterpret_cast<const float4*>(pr + i);
-#pragma unroll 8
-                for (int c = 1; c < chunks; c++) {
-                    const float4 q = *reinterpret_cast<const float4*>(pr + c * chunk_stride + i);
-                    t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
-                }
-                v[it].x += t.x; v[it].y += t.y; v[it].z += t.z; v[it].w += t.w;
+        for (int it = 0; it < ITEMS; it++) {
+            at[it] = min((int)(threadIdx.x + it * blockDim.x) * 4, d - 4) * 4u;
+            v[it] = load4<float4>(xr, at[it]);
+            g[it] = load4<float4>(w, at[it]);
+        }
+        if (chunks > 0) {
+            // PER partials of each element in flight at once (written out: left to itself the compiler waits for each)
+            constexpr int PER = ITEMS == 1 ? 5 : 2;
+            float4 t[ITEMS];
+            const float* pc = pr;
+            for (int c0 = 0; c0 < chunks; c0 += PER) {
+                f32x4 q[PER][ITEMS];
+#pragma unroll
+                for (int j = 0; j < PER; j++)
+                    if (c0 + j < chunks) {
+#pragma unroll
+                        for (int it = 0; it < ITEMS; it++)
+                            q[j][it] = load4<f32x4>(pc, at[it]);
+                        pc += chunk_stride;
+                    }
+#pragma unroll
+                for (int j = 0; j < PER; j++)
+                    if (c0 + j < chunks) {
+#pragma unroll
+                        for (int it = 0; it < ITEMS; it++) {
+                            const f32x4 u = q[j][it];
+                            if (c0 + j == 0) t[it] = make_float4(u.x, u.y, u.z, u.w);
+                            else { t[it].x += u.x; t[it].y += u.y; t[it].z += u.z; t[it].w += u.w; }
+                        }
+                    }
+            }
+#pragma unroll
+            for (int it = 0; it < ITEMS; it++) {
+                v[it].x += t[it].x; v[it].y += t[it].y; v[it].z += t[it].z; v[it].w += t[it].w;
             }
         }
-        norm_row<OutT>(v, g, chunks > 0, xr, out + (size_t)row * d, d, eps, red);
+        norm_row<OutT, ITEMS>(v, g, chunks > 0, xr, out + (size_t)row * d, d, eps, red);
     }
 }
 
@@ -175,17 +213,32 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
             const bool rot = i < n_rot;
             const int head = rot ? i / per_head : hq + hkv + (i - n_rot) / (h >> 2);      // head of the QKV vector
             const int j = rot ? 4 * (i % per_head) : 4 * ((i - n_rot) % (h >> 2));        // first element in it
-            const float* s0 = src + head * h + j;
-            float4 x = *reinterpret_cast<const float4*>(s0), y = x;
-            if (rot) y = *reinterpret_cast<const float4*>(s0 + half);
-#pragma unroll 8
-            for (int c = 1; c < n_src; c++) {
-                const float4 t = *reinterpret_cast<const float4*>(s0 + c * chunk_stride);
-                x.x += t.x; x.y += t.y; x.z += t.z; x.w += t.w;
-                if (rot) {
-                    const float4 u = *reinterpret_cast<const float4*>(s0 + c * chunk_stride + half);
-                    y.x += u.x; y.y += u.y; y.z += u.z; y.w += u.w;
-                }
+            // PER chunks in flight at once (v items load their elements twice: no branch between the loads)
+            constexpr int PER = 3;
+            const unsigned at = (unsigned)(head * h + j) * 4u, at_y = at + (rot ? (unsigned)half * 4u : 0u);
+            const float* pc = src;
+            float4 x, y;
+            for (int c0 = 0; c0 < n_src; c0 += PER) {
+                f32x4 qx[PER], qy[PER];
+#pragma unroll
+                for (int c = 0; c < PER; c++)
+                    if (c0 + c < n_src) {
+                        qx[c] = load4<f32x4>(pc, at);
+                        qy[c] = load4<f32x4>(pc, at_y);
+                        pc += chunk_stride;
+                    }
+#pragma unroll
+                for (int c = 0; c < PER; c++)
+                    if (c0 + c < n_src) {
+                        const f32x4 t = qx[c], u = qy[c];
+                        if (c0 + c == 0) {
+                            x = make_float4(t.x, t.y, t.z, t.w);
+                            y = make_float4(u.x, u.y, u.z, u.w);
+                        } else {
+                            x.x += t.x; x.y += t.y; x.z += t.z; x.w += t.w;
+                            y.x += u.x; y.y += u.y; y.z += u.z; y.w += u.w;
+                        }
+                    }
             }
             if (b < 0) {
                 b = row2seq[row];
@@ -342,34 +395,56 @@ void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_seq_state* seq, int32_t*
                        reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.err));
 }
 
+// Rounds of a row's elements over its workgroup, and the threads that this takes: about 512, so that four rows are under
+// way on a compute unit, more only for rows that four rounds would not cover; at least 256 for the list writers.
+static int norm_rounds(int d) { return std::min(NORM_ITEMS, (d / 4 + NORM_THREADS_MAX - 1) / NORM_THREADS_MAX); }
+static int norm_threads(int d) {
+    const int rounds = norm_rounds(d);
+    return std::max(256, ((d / 4 + rounds - 1) / rounds + 63) / 64 * 64);
+}
+
+#define HS_NORM_LAUNCH(KERNEL, OUT, GRID, ...)                                                                        \
+    switch (norm_rounds(d.d_model)) {                                                                                 \
+        case 1: hipLaunchKernelGGL((KERNEL<OUT, 1>), GRID, block, 0, st, __VA_ARGS__); break;                         \
+        case 2: hipLaunchKernelGGL((KERNEL<OUT, 2>), GRID, block, 0, st, __VA_ARGS__); break;                         \
+        case 3: hipLaunchKernelGGL((KERNEL<OUT, 3>), GRID, block, 0, st, __VA_ARGS__); break;                         \
+        default: hipLaunchKernelGGL((KERNEL<OUT, 4>), GRID, block, 0, st, __VA_ARGS__);                               \
+    }
+
 void hs_launch_embed_norm(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, int batch, float* x,
                           const float* w, void* out, hipStream_t st) {
     const hs_model_desc& d = ctx->desc;
-    static_assert(HS_LIST_THREADS == NORM_THREADS, "the list writers are workgroups of this launch");
+    static_assert(HS_LIST_THREADS == NORM_THREADS_MAX, "the list writers are workgroups of this launch");
     const bool lists = seq && !hs_plain_kernels(ctx);
-    const int groups = lists ? HS_LIST_GROUPS : 0;
+    const dim3 block(norm_threads(d.d_model));
+    const int groups = lists ? hs_list_groups(block.x) : 0;
     const hs_attn_lists l = lists ? hs_attention_lists(ctx) : hs_attn_lists{};
-    const dim3 grid(hs_row_grid(ctx, NORM_THREADS) + groups), block(NORM_THREADS);
-    if (hs_fp32_activations(ctx))
-        hipLaunchKernelGGL(embed_norm_kernel<float>, grid, block, 0, st, ctx->embed, step->tok, d.vocab, x, w, (float*)out,
-                           step->row_off, batch, d.d_model, d.rms_eps, groups, l, seq ? seq->seq_len : nullptr);
-    else
-        hipLaunchKernelGGL(embed_norm_kernel<bf16_t>, grid, block, 0, st, ctx->embed, step->tok, d.vocab, x, w,
-                           (bf16_t*)out, step->row_off, batch, d.d_model, d.rms_eps, groups, l,
-                           seq ? seq->seq_len : nullptr);
+    const dim3 grid(hs_row_grid(ctx, block.x) + groups);
+    const int32_t* len = seq ? seq->seq_len : nullptr;
+    if (hs_fp32_activations(ctx)) {
+        HS_NORM_LAUNCH(embed_norm_kernel, float, grid, ctx->embed, step->tok, d.vocab, x, w, (float*)out, step->row_off,
+                       batch, d.d_model, d.rms_eps, groups, l, len)
+    } else {
+        HS_NORM_LAUNCH(embed_norm_kernel, bf16_t, grid, ctx->embed, step->tok, d.vocab, x, w, (bf16_t*)out, step->row_off,
+                       batch, d.d_model, d.rms_eps, groups, l, len)
+    }
 }
 
 void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, const int32_t* m_dev,
                        int pending_chunks, hipStream_t st) {
+    const hs_model_desc& d = ctx->desc;
     const float* part = reinterpret_cast<const float*>(ctx->ws + ctx->lay.gemm_part);
-    const size_t stride = (size_t)ctx->lim.max_rows * ctx->desc.d_model;
-    if (hs_fp32_activations(ctx))
-        hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(hs_row_grid(ctx, NORM_THREADS)), dim3(NORM_THREADS), 0, st, x, w, (float*)out,
-                           m_dev, ctx->desc.d_model, ctx->desc.rms_eps, part, pending_chunks, stride);
-    else
-        hipLaunchKernelGGL(rmsnorm_kernel<bf16_t>, dim3(hs_row_grid(ctx, NORM_THREADS)), dim3(NORM_THREADS), 0, st, x, w,
-                           (bf16_t*)out, m_dev, ctx->desc.d_model, ctx->desc.rms_eps, part, pending_chunks, stride);
+    const size_t stride = (size_t)ctx->lim.max_rows * d.d_model;
+    const dim3 block(norm_threads(d.d_model)), grid(hs_row_grid(ctx, block.x));
+    if (hs_fp32_activations(ctx)) {
+        HS_NORM_LAUNCH(rmsnorm_kernel, float, grid, x, w, (float*)out, m_dev, d.d_model, d.rms_eps, part, pending_chunks,
+                       stride)
+    } else {
+        HS_NORM_LAUNCH(rmsnorm_kernel, bf16_t, grid, x, w, (bf16_t*)out, m_dev, d.d_model, d.rms_eps, part,
+                       pending_chunks, stride)
+    }
 }
+#undef HS_NORM_LAUNCH
 
 void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
                        const hs_step* step, const float* qkv, void* q, int pending_chunks, hipStream_t st) {

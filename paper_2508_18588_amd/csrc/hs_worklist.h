@@ -2,27 +2,30 @@
 #pragma once
 #include "hs_internal.h"
 
-constexpr int HS_LIST_THREADS = 1024, HS_LIST_GROUPS = 16;
+constexpr int HS_LIST_THREADS = 1024;   // most threads of a workgroup that writes
+// workgroups of `threads` that write the lists: 256 wavefronts in all
+static inline int hs_list_groups(int threads) { return 256 * 64 / threads; }
 
 // A unit = one partition of one (sequence, KV head), in (sequence, partition, head) order.  List A: units of sequences
 // with more than 32 query rows per KV head (taken by whole workgroups), list B: the others (taken by single wavefronts).
 // An entry is two int4: (sequence, head, partition, first row) (rows, cached length, first row tile, 0).  work[0] = |A|,
 // work[1] = |B|, work[2 + l] = the counter through which layer l's launch hands out list A (zeroed here).
-// Called by HS_LIST_GROUPS workgroups of HS_LIST_THREADS threads: each computes every sequence's place in the lists (a
+// Called by `groups` workgroups: each computes every sequence's place in the lists (a
 // prefix sum over the batch), a wavefront then writes the units of one sequence.  These workgroups are part of the launch
 // that gathers the embeddings, which needs nothing of the lists: one workgroup of four wavefronts in a launch of its own
 // took 8 us at 64 sequences, 14 at 128 and 26 at 256, with the rest of the chip idle.
 __device__ inline void hs_write_worklist(const hs_attn_lists& l, const int32_t* __restrict__ seq_len,
-                                         const int32_t* __restrict__ row_off, int batch, int group) {
-    constexpr int NW = HS_LIST_THREADS / 64;
+                                         const int32_t* __restrict__ row_off, int batch, int group, int groups) {
+    constexpr int NW_MAX = HS_LIST_THREADS / 64;
+    const int nt = blockDim.x, nw = nt >> 6;
     __shared__ int s_nu[HS_LIST_THREADS], s_off[HS_LIST_THREADS], s_r0[HS_LIST_THREADS], s_nn[HS_LIST_THREADS],
         s_len[HS_LIST_THREADS];
-    __shared__ int sw_a[NW], sw_b[NW];
+    __shared__ int sw_a[NW_MAX], sw_b[NW_MAX];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (group == 0)
-        for (int i = tid; i < l.n_layers; i += HS_LIST_THREADS) l.work[2 + i] = 0;
+        for (int i = tid; i < l.n_layers; i += nt) l.work[2 + i] = 0;
     int carry_a = 0, carry_b = 0;
-    for (int b0 = 0; b0 < batch; b0 += HS_LIST_THREADS) {
+    for (int b0 = 0; b0 < batch; b0 += nt) {
         const int b = b0 + tid;
         int nu = 0, r0 = 0, nn = 0, L = 0;
         bool is_a = false;
@@ -49,7 +52,7 @@ __device__ inline void hs_write_worklist(const hs_attn_lists& l, const int32_t* 
         if (lane == 63) { sw_a[wave] = ia; sw_b[wave] = ib; }
         __syncthreads();
         int ba = carry_a, bb = carry_b;
-        for (int w = 0; w < NW; w++) {
+        for (int w = 0; w < nw; w++) {
             if (w < wave) { ba += sw_a[w]; bb += sw_b[w]; }
             carry_a += sw_a[w];
             carry_b += sw_b[w];
@@ -61,8 +64,8 @@ __device__ inline void hs_write_worklist(const hs_attn_lists& l, const int32_t* 
         s_nn[tid] = nn;
         s_len[tid] = L;
         __syncthreads();
-        const int nb = min(HS_LIST_THREADS, batch - b0);
-        for (int i = group * NW + wave; i < nb; i += HS_LIST_GROUPS * NW) {
+        const int nb = min(nt, batch - b0);
+        for (int i = group * nw + wave; i < nb; i += groups * nw) {
             const int n = s_nu[i], rows = s_nn[i];
             int4* dst = (n < 0 ? l.list_a : l.list_b) + 2 * (size_t)s_off[i];
             const int cnt = n < 0 ? -n : n, grp = n < 0 ? (rows * l.G + 127) / 128 : 1;

@@ -264,10 +264,12 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
                 c1 = make_float4(cs[4], cs[5], cs[6], cs[7]);
             }
             float4 lo, hi;
-            lo.x = x.x * c0.x - y.x * c0.y; hi.x = y.x * c0.x + x.x * c0.y;
-            lo.y = x.y * c0.z - y.y * c0.w; hi.y = y.y * c0.z + x.y * c0.w;
-            lo.z = x.z * c1.x - y.z * c1.y; hi.z = y.z * c1.x + x.z * c1.y;
-            lo.w = x.w * c1.z - y.w * c1.w; hi.w = y.w * c1.z + x.w * c1.w;
+            // (fused multiply-adds written out: left to contract x s + y c by itself the compiler rounds one product of the
+            // four pairs' second halves the other way round, and results change with the shape of the code)
+            lo.x = __builtin_fmaf(x.x, c0.x, -(y.x * c0.y)); hi.x = __builtin_fmaf(x.x, c0.y, y.x * c0.x);
+            lo.y = __builtin_fmaf(x.y, c0.z, -(y.y * c0.w)); hi.y = __builtin_fmaf(x.y, c0.w, y.y * c0.z);
+            lo.z = __builtin_fmaf(x.z, c1.x, -(y.z * c1.y)); hi.z = __builtin_fmaf(x.z, c1.y, y.z * c1.x);
+            lo.w = __builtin_fmaf(x.w, c1.z, -(y.w * c1.w)); hi.w = __builtin_fmaf(x.w, c1.w, y.w * c1.z);
             // k heads -> cache [page][kv head][16][h]
             T* dst = head < hq ? q_out + ((size_t)row * hq + head) * h + j
                                : kc + layer_off + (((size_t)page * hkv + (head - hq)) * 16 + in_page) * h + j;

@@ -69,10 +69,12 @@ __device__ inline void norm_row(const float4 (&v)[ITEMS], const float4 (&g)[ITEM
         const int i = (threadIdx.x + it * blockDim.x) * 4;
         if (i >= d) continue;
         if (store_x) *reinterpret_cast<float4*>(xr + i) = v[it];
-        ss += v[it].x * v[it].x;
-        ss += v[it].y * v[it].y;
-        ss += v[it].z * v[it].z;
-        ss += v[it].w * v[it].w;
+        // (fused multiply-adds written out, the very first one onto y y: a sum left to the compiler is rounded the one way
+        // in one instance of the kernel and the other way in the next)
+        ss = __builtin_fmaf(v[it].x, v[it].x, it == 0 ? v[it].y * v[it].y : ss);
+        if (it > 0) ss = __builtin_fmaf(v[it].y, v[it].y, ss);
+        ss = __builtin_fmaf(v[it].z, v[it].z, ss);
+        ss = __builtin_fmaf(v[it].w, v[it].w, ss);
     }
     ss = block_sum(ss, red);
     const float r = rsqrtf(ss / (float)d + eps);

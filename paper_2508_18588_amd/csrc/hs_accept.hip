@@ -7,6 +7,8 @@
 // removed; the walk ends with one inverse-CDF sample in token-id order.  Uniforms come from Philox-4x32-10
 // (Salmon et al., SC'11) keyed by the seed, with counter (position, draw kind, sequence id): the stream does not
 // depend on the batch slot or on how many steps it took to reach the position.
+#include <algorithm>
+
 #include "hs_internal.h"
 
 namespace {
@@ -599,7 +601,9 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
     p.seq_id = seq->seq_id;
     if (args) {
         p.mode = args->mode;
-        p.inv_temp = args->mode == HS_ACCEPT_REJECTION ? 1.0 / (double)args->temperature : 1.0;
+        // (at an infinite temperature every finite difference still scales to nothing against 1, while an excluded logit,
+        // -inf, keeps the weight 0: -inf times a true 0 would be a NaN)
+        p.inv_temp = args->mode == HS_ACCEPT_REJECTION ? std::max(1.0 / (double)args->temperature, 1e-300) : 1.0;
         p.seed = args->seed;
     }
     if (args && args->mode == HS_ACCEPT_REJECTION) {

@@ -309,3 +309,41 @@ def test_rejection_at_extreme_temperatures(toy, temperature):
         assert got == (a, out.tolist(), path.tolist()) or margin < 1e-9, (b, got, a, out, path, margin)
         r += n
     eng.close()
+
+
+@pytest.mark.parametrize("V", [4096, 4097, 6000])
+def test_rejection_at_an_infinite_temperature_is_uniform_over_the_tokens_that_are_not_excluded(toy, V):
+    """Every finite logit weighs the same and an excluded one (-inf) nothing, whether the vocabulary fills its last slice
+    of 4096 tokens or not.  Finite logits: the oracle's decisions.  With half the vocabulary excluded: the oracle's
+    decisions at a temperature so high that every finite difference is lost, 1e30."""
+    from paper_2508_18588_amd import HS_ACCEPT_REJECTION
+    from paper_2508_18588_amd.runtime import Engine
+    from hs_inputs import ModelShape
+    shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
+    rng = np.random.default_rng(V)
+    B = 40
+    eng = Engine(shape, make_weights(shape, 3), rope_table(64, 64), max_batch=B, k_max=3, c_max=2, max_len=60)
+    eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B)
+    trees = [oracle.build_tree([rng.integers(0, V, 3), rng.integers(0, V, 3)], 0, 50) for _ in range(B)]
+    m = eng.set_rows([dict(tok=t["tok"], parent=t["parent"], pos=t["pos"]) for t in trees])
+    for excluded in (False, True):
+        lg = rng.normal(0.0, 3.0, size=(m, V)).astype(np.float32)
+        if excluded:
+            lg[:, rng.permutation(V)[:V // 2]] = -np.inf
+        eng.logits[:m].copy_(torch.from_numpy(lg))
+        eng.accept(HS_ACCEPT_REJECTION, float("inf"), 7)
+        torch.cuda.synchronize()
+        st = {n: np_of(v) for n, v in eng.st.items()}
+        r, last = 0, []
+        for b, t in enumerate(trees):
+            n = len(t["tok"])
+            a, out, path, margin = oracle.accept_stochastic(t["tok"], t["parent"], t["pos"], lg[r:r + n].astype(np.float64),
+                                                            1e30 if excluded else float("inf"), 7, b)
+            g = st["n_out"][b]
+            got = (int(st["accept_len"][b]), st["out_tok"][b, :g].tolist(), st["path_row"][b, :g].tolist())
+            assert got == (a, out.tolist(), path.tolist()) or margin < 1e-9, (b, got, a, out, path, margin)
+            assert np.isfinite(lg[r + st["path_row"][b, g - 1], got[1][-1]])
+            last.append(got[1][-1])
+            r += n
+        assert len(set(last)) > B // 2
+    eng.close()

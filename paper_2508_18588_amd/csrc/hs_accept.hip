@@ -232,6 +232,8 @@ __device__ inline void accept_rejection_seq(
     const uint64_t sid = seq_id[b];
     const bool vec = (vocab & 3) == 0 && ((unsigned long long)logits & 15ull) == 0;
     const int root_pos = pos[r0];
+    // a drafted id outside the vocabulary has no logit: it is a token of weight 0, rejected like any other
+    auto in_vocab = [&](int t) { return t >= 0 && t < vocab; };
     // a row's largest logit and sum, put together from its slices by half a wavefront
     auto row_total = [&](const hs_reject_stat* st, float& mx, double& z) {
         mx = -INFINITY;
@@ -253,12 +255,13 @@ __device__ inline void accept_rejection_seq(
             if ((lane & 31) == 0) { node_max[i] = mx; node_sum[i] = z; }
         }
     int pre_par = -2, pre_tok = 0, pre_pos = root_pos;
-    float pre_lg = 0.f;
+    float pre_lg = -INFINITY;
     if (lane < nn) {
         pre_par = parent[r0 + lane];
         pre_tok = tok[r0 + lane];
         pre_pos = pos[r0 + lane];
-        if (lane > 0 && pre_par >= 0 && pre_par < nn) pre_lg = logits[(size_t)(r0 + pre_par) * vocab + pre_tok];
+        if (lane > 0 && pre_par >= 0 && pre_par < nn && in_vocab(pre_tok))
+            pre_lg = logits[(size_t)(r0 + pre_par) * vocab + pre_tok];
     }
     __syncthreads();
     int cur = 0, a = 0;
@@ -289,7 +292,7 @@ __device__ inline void accept_rejection_seq(
             const int i = i0 + lane;
             const bool child = i > 0 && i < nn && (i0 == 0 ? pre_par : parent[r0 + i]) == cur;
             const int my_tok = !child ? 0 : i0 == 0 ? pre_tok : tok[r0 + i];
-            const double my_w = child ? weight(i0 == 0 ? pre_lg : lg[my_tok]) : 0.0;
+            const double my_w = child ? weight(i0 == 0 ? pre_lg : in_vocab(my_tok) ? lg[my_tok] : -INFINITY) : 0.0;
             for (unsigned long long todo = __ballot(child); todo && next < 0; todo &= todo - 1) {
                 const int q = __ffsll(todo) - 1;
                 const int t = __shfl(my_tok, q);
@@ -319,7 +322,8 @@ __device__ inline void accept_rejection_seq(
         // Final sample from the remaining distribution, in token-id order.  A slice that holds rejected tokens is summed
         // again without them (subtracting would leave rounding where a rejected token had nearly all the weight).
         for (int q = 0; q < nrej; q++) {
-            const int s = __shfl(rej, q) / SLICE;
+            const int t0 = __shfl(rej, q), s = t0 / SLICE;
+            if (!in_vocab(t0)) continue;   // (it has no share in any slice)
             float v[PER];
             load_slice(lg, vocab, s, vec, v);
             for (int q2 = 0; q2 < nrej; q2++) {

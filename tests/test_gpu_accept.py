@@ -347,3 +347,49 @@ def test_rejection_at_an_infinite_temperature_is_uniform_over_the_tokens_that_ar
             r += n
         assert len(set(last)) > B // 2
     eng.close()
+
+
+@pytest.mark.parametrize("V,B,k", [(4096, 5, 4), (4097, 5, 4), (12290, 3, 8), (8192, 70, 31)])
+def test_a_drafted_id_outside_the_vocabulary_is_a_token_of_weight_zero(toy, V, B, k):
+    """Histories are the caller's: an id that the model does not know (negative, the vocabulary's size, far beyond) is
+    rejected like a token whose logit is -inf, and the other rows of the batch are decided as if it were not there.  The
+    oracle gets the logits with one more column, all -inf, and that column's id for every such token.  The last shape has
+    more than 2048 rows (sums of deeper nodes computed by the walk itself)."""
+    from paper_2508_18588_amd import HS_ACCEPT_REJECTION
+    from paper_2508_18588_amd.runtime import Engine
+    from hs_inputs import ModelShape
+    shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
+    rng = np.random.default_rng(V + 1)
+    eng = Engine(shape, make_weights(shape, 3), rope_table(64, 64), max_batch=B, k_max=k, c_max=2 if k < 31 else 1, max_len=80)
+    eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B)
+    strange = [-1, -5000, V, V + 1, V + 4096, 2 ** 31 - 1, -2 ** 31]
+    accepted = 0
+    for trial in range(3):
+        trees = [oracle.build_tree([rng.integers(0, V, k) for _ in range(eng.c_max)], 0, 50) for _ in range(B)]
+        tok, lg = [], rng.normal(0.0, 2.0, size=(sum(len(t["tok"]) for t in trees), V)).astype(np.float32)
+        r = 0
+        for t in trees:
+            x = t["tok"].astype(np.int32).copy()
+            for i in range(1, len(x)):
+                lg[r + t["parent"][i], x[i]] = 30.0
+                if rng.random() < 0.3:
+                    x[i] = rng.choice(strange)
+            tok.append(x)
+            r += len(x)
+        m = eng.set_rows([dict(tok=x, parent=t["parent"], pos=t["pos"]) for x, t in zip(tok, trees)])
+        eng.logits[:m].copy_(torch.from_numpy(lg))
+        eng.accept(HS_ACCEPT_REJECTION, 1.0, 5 + trial)
+        torch.cuda.synchronize()
+        st = {n: np_of(v) for n, v in eng.st.items()}
+        wide = np.concatenate([lg.astype(np.float64), np.full((m, 1), -np.inf)], 1)
+        r = 0
+        for b, (x, t) in enumerate(zip(tok, trees)):
+            n, known = len(x), np.where((x >= 0) & (x < V), x, V).astype(np.int32)
+            a, out, path, margin = oracle.accept_stochastic(known, t["parent"], t["pos"], wide[r:r + n], 1.0, 5 + trial, b)
+            g = st["n_out"][b]
+            got = (int(st["accept_len"][b]), st["out_tok"][b, :g].tolist(), st["path_row"][b, :g].tolist())
+            assert got == (a, out.tolist(), path.tolist()) or margin < 1e-9, (trial, b, got, a, out, path, margin)
+            accepted += a
+            r += n
+    eng.close()
+    assert accepted > 0

@@ -456,7 +456,17 @@ __device__ inline void commit_seq(
         }
     }
     __syncthreads();
+    if (tid >= 64) return;
+    // pattern tail: the last w_max (at most 32) tokens of (old valid tail ++ emitted tokens), an entry per lane: all lanes
+    // have loaded before the first one stores
+    const int tl = tail_len[b], new_len = min(w_max, tl + no);
+    if (tid < new_len) {
+        int32_t* tb = tail + (size_t)b * w_max;
+        const int ci = tl + no - new_len + tid;  // index in the concatenation
+        tb[w_max - new_len + tid] = ci < tl ? tb[w_max - tl + ci] : out_tok[(size_t)b * k_stride + ci - tl];
+    }
     if (tid != 0) return;
+    tail_len[b] = new_len;
     // window rule: every drafted token on the path accepted <=> the last accepted node is a leaf
     if (pol.k_mode == HS_K_AIMD && nn > 1) {
         int last = path_row[(size_t)b * k_stride + a];
@@ -467,17 +477,6 @@ __device__ inline void commit_seq(
         else k = pol.aimd_reset;
         k_state[b] = k;
     }
-    // pattern tail: the last w_max tokens of (old valid tail ++ emitted tokens)
-    int tl = tail_len[b];
-    int32_t* tb = tail + (size_t)b * w_max;
-    int new_len = min(w_max, tl + no);
-    int32_t tmp[32];
-    for (int i = 0; i < new_len; i++) {
-        int ci = tl + no - new_len + i;  // index in the concatenation
-        tmp[i] = ci < tl ? tb[w_max - tl + ci] : out_tok[(size_t)b * k_stride + ci - tl];
-    }
-    for (int i = 0; i < new_len; i++) tb[w_max - new_len + i] = tmp[i];
-    tail_len[b] = new_len;
     if (tokens) {
         for (int i = 0; i < no; i++)
             if (n_old + i < tokens_stride) tokens[(size_t)b * tokens_stride + n_old + i] = out_tok[(size_t)b * k_stride + i];
@@ -499,7 +498,7 @@ __device__ inline void commit_seq(
 //   2. Acceptance: greedy walk (thread 0) or rejection sampling (the workgroup).
 //   3. Commit.
 struct accept_commit_args {
-    int batch, vocab, k_stride, mode, do_accept, do_commit;
+    int batch, vocab, k_stride, do_accept, do_commit;
     const int32_t *row_off, *tok, *parent, *pos;
     const float* logits;
     const unsigned long long* keys;
@@ -520,7 +519,10 @@ struct accept_commit_args {
     hs_policy pol;
 };
 
-template <typename CT>
+// REJECT: acceptance is rejection sampling; else greedy, or commit alone.  Two kernels, because the sampler takes more than a
+// hundred registers and the rest 23: in one kernel the greedy walk of more than 256 sequences ran in rounds of a workgroup
+// per compute unit (greedy acceptance of 1024 trees of 17 nodes 40 us, on its own 16).
+template <typename CT, bool REJECT>
 __global__ __launch_bounds__(256) void accept_commit_kernel(accept_commit_args p) {
     const int b = blockIdx.x, tid = threadIdx.x;
     const int r0 = p.row_off[b], nn = p.row_off[b + 1] - r0;
@@ -528,7 +530,7 @@ __global__ __launch_bounds__(256) void accept_commit_kernel(accept_commit_args p
         if (nn <= 0) {
             if (tid == 0) { p.accept_len[b] = 0; p.n_out[b] = 0; }
         } else {
-            if (p.keys) {
+            if (!REJECT && p.keys) {
                 const int lane = tid & 63, wave = tid >> 6;
                 for (int r = wave; r < nn; r += 4) {
                     const unsigned long long* kr = p.keys + (size_t)(r0 + r) * p.n_keys;
@@ -547,13 +549,12 @@ __global__ __launch_bounds__(256) void accept_commit_kernel(accept_commit_args p
                 }
                 __syncthreads();   // the walk reads argmax[] written by the other wavefronts
             }
-            if (p.mode == HS_ACCEPT_GREEDY) {
-                if (tid == 0)
-                    accept_greedy_walk(b, r0, nn, p.tok, p.parent, p.argmax, p.k_stride, p.accept_len, p.n_out,
-                                       p.out_tok, p.path_row);
-            } else {
+            if (REJECT) {
                 accept_rejection_seq(b, r0, nn, p.row_off[p.batch], p.vocab, p.tok, p.parent, p.pos, p.logits,
                                      p.stats, p.n_slices, p.seq_id, p.inv_temp, p.seed, p.k_stride, p.accept_len, p.n_out, p.out_tok, p.path_row);
+            } else if (tid == 0) {
+                accept_greedy_walk(b, r0, nn, p.tok, p.parent, p.argmax, p.k_stride, p.accept_len, p.n_out, p.out_tok,
+                                   p.path_row);
             }
         }
         __syncthreads();           // the commit reads what thread 0 wrote
@@ -604,7 +605,6 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
     p.argmax = step->argmax;
     p.seq_id = seq->seq_id;
     if (args) {
-        p.mode = args->mode;
         // (at an infinite temperature every finite difference still scales to nothing against 1, while an excluded logit,
         // -inf, keeps the weight 0: -inf times a true 0 would be a NaN)
         p.inv_temp = args->mode == HS_ACCEPT_REJECTION ? std::max(1.0 / (double)args->temperature, 1e-300) : 1.0;
@@ -632,8 +632,13 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
         p.counters = (unsigned long long*)seq->counters;
         p.pol = *policy;
     }
-    if (hs_fp32_activations(ctx))
-        hipLaunchKernelGGL(accept_commit_kernel<float>, dim3(seq->batch), dim3(256), 0, st, p);
-    else
-        hipLaunchKernelGGL(accept_commit_kernel<bf16_t>, dim3(seq->batch), dim3(256), 0, st, p);
+    const dim3 grid(seq->batch), block(256);
+    const bool fp32 = hs_fp32_activations(ctx);
+    if (args && args->mode == HS_ACCEPT_REJECTION) {
+        if (fp32) hipLaunchKernelGGL((accept_commit_kernel<float, true>), grid, block, 0, st, p);
+        else hipLaunchKernelGGL((accept_commit_kernel<bf16_t, true>), grid, block, 0, st, p);
+    } else {
+        if (fp32) hipLaunchKernelGGL((accept_commit_kernel<float, false>), grid, block, 0, st, p);
+        else hipLaunchKernelGGL((accept_commit_kernel<bf16_t, false>), grid, block, 0, st, p);
+    }
 }

@@ -61,3 +61,14 @@ def test_hot_gemm_instances_use_no_scratch():
         assert len(names) == 1, (tag, sorted(rep))
         r = rep[names[0]]
         assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (names[0], r)
+
+
+def test_greedy_acceptance_and_commit_fill_a_compute_unit():
+    """hs_accept_commit of a thousand sequences is one workgroup each: seven or eight of them per compute unit, not the one
+    that the sampler's registers would leave."""
+    rep = resource_report("hs_accept.hip")
+    kernels = {k: v for k, v in rep.items() if "accept_commit_kernel" in k and "Lb0E" in k}
+    assert len(kernels) == 2, sorted(rep)                      # bf16 and float caches
+    for name, r in kernels.items():
+        assert r["VGPRs"] <= 72 and r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
+        assert r["Occupancy [waves/SIMD]"] >= 7, (name, r)

@@ -295,7 +295,8 @@ hs_status hs_prefill(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* 
  * child j at a node with probability p(tok), p = softmax(logits/temperature) with earlier rejected tokens
  * removed; finish with one inverse-CDF sample (token-id order).  Uniforms: Philox-4x32-10, key = seed, counter
  * = (position of the token being decided, j or 7 for the final sample, seq_id lo, seq_id hi), word 0 >> 8.  Rejection
- * sampling keeps per-row sums in the workspace during the call, like every other call of the context. */
+ * sampling keeps per-row sums in the workspace during the call; calls with step arrays and logits of their own may
+ * overlap on different streams all the same (a call sums again what another one has overwritten). */
 hs_status hs_accept(hs_ctx* ctx, const hs_accept_args* args, const hs_seq_state* seq, hs_step* step, hs_stream stream);
 
 /* Moves accepted nodes' K/V to consecutive slots L_b+1.. (a no-op for a chain), then seq_len += n_out,

@@ -13,7 +13,7 @@
 
 namespace {
 
-__device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
+__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
                                      uint32_t out[4]) {
 #pragma unroll
     for (int r = 0; r < 10; r++) {
@@ -27,14 +27,14 @@ __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-__device__ inline double uniform01(uint64_t seed, uint64_t seq_id, uint32_t position, uint32_t kind) {
+__device__ __forceinline__ double uniform01(uint64_t seed, uint64_t seq_id, uint32_t position, uint32_t kind) {
     uint32_t o[4];
     philox4x32_10(position, kind, (uint32_t)seq_id, (uint32_t)(seq_id >> 32), (uint32_t)seed, (uint32_t)(seed >> 32), o);
     return (double)(o[0] >> 8) * (1.0 / 16777216.0);
 }
 
 // Greedy walk of one sequence's tree (one thread): follow the child whose token is the current node's argmax.
-__device__ inline void accept_greedy_walk(int b, int r0, int nn, const int32_t* __restrict__ tok,
+__device__ __forceinline__ void accept_greedy_walk(int b, int r0, int nn, const int32_t* __restrict__ tok,
                                           const int32_t* __restrict__ parent, const int32_t* __restrict__ argmax,
                                           int k_stride, int32_t* __restrict__ accept_len, int32_t* __restrict__ n_out,
                                           int32_t* __restrict__ out_tok, int32_t* __restrict__ path_row) {
@@ -55,25 +55,69 @@ __device__ inline void accept_greedy_walk(int b, int r0, int nn, const int32_t* 
     n_out[b] = a + 1;
 }
 
-__device__ inline double shfl_xor_f64(double v, int o) {
-    return __hiloint2double(__shfl_xor(__double2hiint(v), o), __shfl_xor(__double2loint(v), o));
+// The value of lane (own ^ O), by DPP and permlane moves: a butterfly of __shfl_xor is a chain of trips through the LDS unit,
+// which is most of what a workgroup waits for when it sums one slice after another.
+// (quad_perm 1 0 3 2 and 2 3 0 1; half-row mirror, then the quad mirrored back; a row rotated by eight; rows and halves
+// swapped: the results of a swap of a register with itself are own and partner, in an order that depends on the lane)
+template <int O>
+__device__ __forceinline__ unsigned lane_xor(unsigned v) {
+    if constexpr (O == 1) return __builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xF, 0xF, true);
+    else if constexpr (O == 2) return __builtin_amdgcn_update_dpp(0u, v, 0x4E, 0xF, 0xF, true);
+    else if constexpr (O == 4)
+        return __builtin_amdgcn_update_dpp(0u, __builtin_amdgcn_update_dpp(0u, v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else if constexpr (O == 8) return __builtin_amdgcn_update_dpp(0u, v, 0x128, 0xF, 0xF, true);
+    else {
+        static_assert(O == 16 || O == 32, "within a wavefront");
+        const auto sw = O == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return (threadIdx.x & O) ? sw[0] : sw[1];
+    }
+}
+template <int O>
+__device__ __forceinline__ double lane_xor_f64(double v) {
+    return __hiloint2double((int)lane_xor<O>((unsigned)__double2hiint(v)), (int)lane_xor<O>((unsigned)__double2loint(v)));
+}
+// Butterflies over 64 lanes (WIDTH = 32: over either half): every lane gets the result, added up in the same tree.
+template <int WIDTH = 64>
+__device__ __forceinline__ double wave_sum_f64(double v) {
+    if constexpr (WIDTH == 64) v += lane_xor_f64<32>(v);
+    v += lane_xor_f64<16>(v);
+    v += lane_xor_f64<8>(v);
+    v += lane_xor_f64<4>(v);
+    v += lane_xor_f64<2>(v);
+    return v + lane_xor_f64<1>(v);
+}
+template <int WIDTH = 64>
+__device__ __forceinline__ float wave_max_f32(float v) {
+    auto step = [&](unsigned other) { v = fmaxf(v, __uint_as_float(other)); };
+    if constexpr (WIDTH == 64) step(lane_xor<32>(__float_as_uint(v)));
+    step(lane_xor<16>(__float_as_uint(v)));
+    step(lane_xor<8>(__float_as_uint(v)));
+    step(lane_xor<4>(__float_as_uint(v)));
+    step(lane_xor<2>(__float_as_uint(v)));
+    step(lane_xor<1>(__float_as_uint(v)));
+    return v;
 }
 
-__device__ inline double block_sum_f64(double v, double* red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += shfl_xor_f64(v, o);
-    __syncthreads();
+// Workgroup barrier for values in LDS alone: unlike __syncthreads it leaves loads from memory on their way.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ double block_sum_f64(double v, double* red) {
+    v = wave_sum_f64(v);
+    lds_barrier();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
+    lds_barrier();
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-__device__ inline float block_max_f32(float v, float* red) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    __syncthreads();
+__device__ __forceinline__ float block_max_f32(float v, float* red) {
+    v = wave_max_f32(v);
+    lds_barrier();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
+    lds_barrier();
     return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
@@ -90,21 +134,26 @@ __device__ inline float block_max_f32(float v, float* red) {
 // With very many rows most of them are never visited: beyond STATS_ALL_ROWS only the roots and their children are
 // computed ahead (2048 rows of 152064 tokens take 0.4 ms, about what the walk needs for five rows by itself), and the
 // walk computes the rest of what it visits.
+// Another rejection-sampling call of the context may run at the same time on another stream, with rows of its own and the
+// same place in the workspace.  So every sum carries a word made of itself and the number of the call that wrote it; the
+// walk takes what carries its own call's number and computes anything else itself, into LDS.
 constexpr int SLICE = HS_REJECT_SLICE, PER = SLICE / 256;   // tokens of a slice; of a slice, per thread
 constexpr int STATS_ALL_ROWS = 2048;
+constexpr int STATS_AT_ONCE = 16, WALK_AT_ONCE = 16;
 
-__device__ inline bool stats_ahead(int m, int pos, int root_pos) { return m <= STATS_ALL_ROWS || pos - root_pos <= 1; }
+__device__ __forceinline__ bool stats_ahead(int m, int pos, int root_pos) { return m <= STATS_ALL_ROWS || pos - root_pos <= 1; }
 
 // exp((l - ref) / T) in fp64 for l <= ref, with c = 16 / (T ln 2): (l - ref) c = n + f, |f| <= 1/2, and the result is
-// 2^(n >> 4) tab[n & 15] exp(f ln2/16), tab[j] = 2^(j/16), the last factor by its Taylor series to the seventh power
-// (remainder 1.3e-18).  15 fp64 operations against about 30 of the library's exp, and the sums are bound by them; the
-// error is that of rounding c and the result, 2^-53 |x| + 2 ulp.  The sixteen table entries cover the 32 LDS banks once:
-// no lookup conflicts with another.  Differences below -746 T, -inf among them, are taken as -746 T, where the result is
-// 0 or the smallest number; a NaN comes out as such a value, too, so callers look for NaNs themselves.
+// 2^(n >> 4) tab[n & 15] exp(f ln2/16), tab[j] = 2^(j/16) -- the table method of P. T. P. Tang (ACM TOMS 15, 1989) -- the
+// last factor by its Taylor series to the seventh power (remainder 1.3e-18).  15 fp64 operations against about 30 of the
+// library's exp, and the sums are bound by them.  Error: c is a rounded product of a rounded constant, 2^-52 |x| of the
+// result x = (l - ref) / T, plus 2 ulp for the factors.  The sixteen table entries cover the 32 LDS banks once: no lookup
+// conflicts with another.  Differences below -746 T, -inf among them, are taken as -746 T, where the result is
+// 0; a NaN comes out as such a value, too, so callers look for NaNs themselves.
 // (The clamp is on the fp64 difference: at a low temperature -746 T is less than an fp32 logit resolves.)
 struct exp_scale { double low, c; };
-__device__ inline exp_scale make_scale(double inv_temp) { return {-746.0 / inv_temp, inv_temp * 23.083120654223414}; }
-__device__ inline double exp_diff(float l, float ref, const exp_scale& k, const double* tab) {
+__device__ __forceinline__ exp_scale make_scale(double inv_temp) { return {-746.0 / inv_temp, inv_temp * 23.083120654223414}; }
+__device__ __forceinline__ double exp_diff(float l, float ref, const exp_scale& k, const double* tab) {
     const double d = fmax((double)l - (double)ref, k.low);
     const double t = __builtin_fma(d, k.c, 6755399441055744.0);      // + 1.5 2^52: n in the low bits
     const int n = __double2loint(t);
@@ -119,16 +168,16 @@ __device__ inline double exp_diff(float l, float ref, const exp_scale& k, const 
     p = __builtin_fma(p, f, 1.0);
     return __builtin_amdgcn_ldexp(p * tab[n & 15], n >> 4);
 }
-__device__ inline void fill_exp_table(double* tab) {
+__device__ __forceinline__ void fill_exp_table(double* tab) {
     if (threadIdx.x < 16) tab[threadIdx.x] = exp2((double)threadIdx.x * 0.0625);
     __syncthreads();
 }
 
 // A thread's share of a slice, -inf beyond the vocabulary: 16-byte pieces 4 KB apart where rows are 16-byte aligned.
-__device__ inline int slice_token(int slice, int j, bool vec) {
+__device__ __forceinline__ int slice_token(int slice, int j, bool vec) {
     return slice * SLICE + (vec ? 4 * ((int)threadIdx.x + 256 * (j >> 2)) + (j & 3) : (int)threadIdx.x + 256 * j);
 }
-__device__ inline void load_slice(const float* __restrict__ lg, int vocab, int slice, bool vec, float (&v)[PER]) {
+__device__ __forceinline__ void load_slice(const float* __restrict__ lg, int vocab, int slice, bool vec, float (&v)[PER]) {
     if (vec) {
 #pragma unroll
         for (int j = 0; j < PER / 4; j++) {
@@ -146,31 +195,67 @@ __device__ inline void load_slice(const float* __restrict__ lg, int vocab, int s
     }
 }
 
-// Sum of exp((logit - ref) / T) over a thread's logits; excluded ones (-inf) add nothing, a NaN makes it NaN.
-__device__ inline double sum_weights(const float (&v)[PER], float ref, double inv_temp, const double* tab) {
+// Sum of exp((logit - ref) / T) over a thread's logits; excluded ones (-inf) add nothing, a NaN makes it NaN.  AT_ONCE of
+// them are computed side by side, then the array moves on by as many (all sixteen side by side take 100 registers and more).
+template <int AT_ONCE>
+__device__ __forceinline__ double sum_weights(const float (&v)[PER], float ref, double inv_temp, const double* tab) {
     const exp_scale k = make_scale(inv_temp);
     double s = 0.0;
     unsigned worst = 0u;
+    float u[PER];
 #pragma unroll
-    for (int j = 0; j < PER; j++) {
-        s += exp_diff(v[j], ref, k, tab);
-        worst = max(worst, __float_as_uint(v[j]) << 1);
+    for (int j = 0; j < PER; j++) u[j] = v[j];
+    static_assert(PER % AT_ONCE == 0, "whole rounds");
+#pragma unroll 1
+    for (int r = 0; r < PER / AT_ONCE; r++) {
+#pragma unroll
+        for (int j = 0; j < AT_ONCE; j++) {
+            s += exp_diff(u[j], ref, k, tab);
+            worst = max(worst, __float_as_uint(u[j]) << 1);
+        }
+#pragma unroll
+        for (int j = 0; j + AT_ONCE < PER; j++) u[j] = u[j + AT_ONCE];
     }
     return ref == -INFINITY && worst <= 0xFF000000u ? 0.0 : worst > 0xFF000000u || ref == INFINITY ? NAN : s;
 }
 
-// Largest logit and sum of one slice, relative to that largest logit, by a workgroup of 256 threads.  A slice in which
-// every token is excluded (-inf) has the sum 0; a NaN anywhere makes the sum NaN.
-__device__ inline void slice_stats(const float (&v)[PER], double inv_temp, const double* tab,
-                                   hs_reject_stat* __restrict__ dst) {
+// Largest logit and sum of one slice, relative to that largest logit, by a workgroup of 256 threads.
+// A slice in which every token is excluded (-inf) has the sum 0; a NaN anywhere makes the sum NaN.
+struct slice_stat { float m; double s; };
+template <int AT_ONCE>
+__device__ __forceinline__ slice_stat slice_stats(const float (&v)[PER], double inv_temp, const double* tab) {
     __shared__ float redf[4];
     __shared__ double redd[4];
     float mx = -INFINITY;
 #pragma unroll
     for (int j = 0; j < PER; j++) mx = fmaxf(mx, v[j]);
     mx = block_max_f32(mx, redf);
-    const double s = block_sum_f64(sum_weights(v, mx, inv_temp, tab), redd);
-    if (threadIdx.x == 0) { dst->m = mx; dst->s = s; }
+    const double s = block_sum_f64(sum_weights<AT_ONCE>(v, mx, inv_temp, tab), redd);
+    // (the same in every lane: in scalar registers from here on)
+    return {__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(mx))),
+            __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(s)), __builtin_amdgcn_readfirstlane(__double2loint(s)))};
+}
+
+// A slice's entry in the workspace, one 16-byte access.  The check word ties the value to the call: an entry of another
+// call, or put together from two, passes for one of this call's in one of 2^32 cases.
+__device__ __forceinline__ uint32_t stat_check(const slice_stat& v, uint32_t call) {
+    uint32_t h = __float_as_uint(v.m) * 0x9E3779B1u;
+    h = (h ^ (h >> 15)) + (uint32_t)__double2loint(v.s);
+    h *= 0x85EBCA6Bu;
+    h = (h ^ (h >> 13)) + (uint32_t)__double2hiint(v.s);
+    h *= 0xC2B2AE35u;
+    return h ^ (h >> 16) ^ call;
+}
+__device__ __forceinline__ void put_stat(hs_reject_stat* dst, const slice_stat& v, uint32_t call) {
+    *reinterpret_cast<uint4*>(dst) = make_uint4(__float_as_uint(v.m), stat_check(v, call), (uint32_t)__double2loint(v.s),
+                                                (uint32_t)__double2hiint(v.s));
+}
+__device__ __forceinline__ bool take_stat(const uint4& u, uint32_t call, slice_stat& v) {
+    v = {__uint_as_float(u.x), __hiloint2double((int)u.w, (int)u.z)};
+    return u.y == stat_check(v, call);
+}
+__device__ __forceinline__ bool get_stat(const hs_reject_stat* src, uint32_t call, slice_stat& v) {
+    return take_stat(*reinterpret_cast<const uint4*>(src), call, v);
 }
 
 // grid (sequences, slices, row split): a workgroup takes rows blockIdx.z, blockIdx.z + gridDim.z, ... of its sequence,
@@ -178,7 +263,8 @@ __device__ inline void slice_stats(const float (&v)[PER], double inv_temp, const
 __global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __restrict__ row_off,
                                                             const int32_t* __restrict__ pos,
                                                             const float* __restrict__ logits, int vocab, int batch,
-                                                            double inv_temp, hs_reject_stat* __restrict__ stats) {
+                                                            double inv_temp, uint32_t call,
+                                                            hs_reject_stat* __restrict__ stats) {
     __shared__ double tab[16];
     fill_exp_table(tab);
     const int b = blockIdx.x, n_slices = gridDim.y, slice = blockIdx.y, m = row_off[batch];
@@ -195,7 +281,8 @@ __global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __r
     while (r < r1) {
         const int rn = next_row(r + gridDim.z);
         if (rn < r1) load_slice(logits + (size_t)rn * vocab, vocab, slice, vec, w);
-        slice_stats(v, inv_temp, tab, stats + (size_t)r * n_slices + slice);
+        const slice_stat sum = slice_stats<STATS_AT_ONCE>(v, inv_temp, tab);
+        if (threadIdx.x == 0) put_stat(stats + (size_t)r * n_slices + slice, sum, call);
 #pragma unroll
         for (int j = 0; j < PER; j++) v[j] = w[j];
         r = rn;
@@ -203,7 +290,7 @@ __global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __r
 }
 
 // Sum over the lanes up to and including this one, in lane order by a fixed tree.
-__device__ inline double wave_prefix_f64(double v, int lane) {
+__device__ __forceinline__ double wave_prefix_f64(double v, int lane) {
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const double t = __hiloint2double(__shfl_up(__double2hiint(v), o), __shfl_up(__double2loint(v), o));
@@ -214,46 +301,55 @@ __device__ inline double wave_prefix_f64(double v, int lane) {
 
 // Rejection sampling of one sequence by its workgroup (nn > 0).  The four wavefronts take every decision redundantly:
 // same values, same order, no exchange.
-__device__ inline void accept_rejection_seq(
+__device__ __forceinline__ void accept_rejection_seq(
     int b, int r0, int nn, int m_rows, int vocab, const int32_t* __restrict__ tok,
     const int32_t* __restrict__ parent, const int32_t* __restrict__ pos, const float* __restrict__ logits,
-    hs_reject_stat* __restrict__ stats, int n_slices,
+    const hs_reject_stat* __restrict__ stats, int n_slices, uint32_t call,
     const uint64_t* __restrict__ seq_id, double inv_temp, uint64_t seed, int k_stride,
     int32_t* __restrict__ accept_len, int32_t* __restrict__ n_out, int32_t* __restrict__ out_tok,
     int32_t* __restrict__ path_row) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn_lds[];
+    slice_stat* own = reinterpret_cast<slice_stat*>(dyn_lds);   // [n_slices]: the sums of the node at hand
     __shared__ double wave_tot[4];
-    __shared__ double redd[4];
     __shared__ int s_first, s_last, s_pick;
     __shared__ double tab[16];
-    __shared__ float node_max[64];
-    __shared__ double node_sum[64];
+    __shared__ float node_max[HS_MAX_NODES];
+    __shared__ double node_sum[HS_MAX_NODES];
+    __shared__ int node_ok[HS_MAX_NODES];
     fill_exp_table(tab);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t sid = seq_id[b];
     const bool vec = (vocab & 3) == 0 && ((unsigned long long)logits & 15ull) == 0;
     const int root_pos = pos[r0];
+    nn = min(nn, HS_MAX_NODES);   // (a draft tree has no more: hs_create)
     // a drafted id outside the vocabulary has no logit: it is a token of weight 0, rejected like any other
     auto in_vocab = [&](int t) { return t >= 0 && t < vocab; };
-    // a row's largest logit and sum, put together from its slices by half a wavefront
-    auto row_total = [&](const hs_reject_stat* st, float& mx, double& z) {
+    // a row's largest logit and sum, put together by half a wavefront from its slices: slice(s, v) gets one, false if it
+    // cannot be used
+    auto row_total = [&](auto slice, float& mx, double& z) __attribute__((always_inline)) {
+        bool ok = true;
+        slice_stat v;
         mx = -INFINITY;
-        for (int s = lane & 31; s < n_slices; s += 32) mx = fmaxf(mx, st[s].m);
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        for (int s = lane & 31; s < n_slices; s += 32) { ok &= slice(s, v); mx = fmaxf(mx, v.m); }
+        mx = wave_max_f32<32>(mx);
         z = 0.0;
-        for (int s = lane & 31; s < n_slices; s += 32) z += st[s].s * exp(((double)st[s].m - (double)mx) * inv_temp);
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) z += shfl_xor_f64(z, o);
+        for (int s = lane & 31; s < n_slices; s += 32) { ok &= slice(s, v); z += v.s * exp(((double)v.m - (double)mx) * inv_temp); }
+        z = wave_sum_f64<32>(z);
+        return (__ballot(ok) >> (lane & 32) & 0xFFFFFFFFull) == 0xFFFFFFFFull;
     };
-    // Everything that the walk may ask of the first 64 nodes (there are no more in a draft tree), fetched side by side
-    // instead of node after node: lane i holds node i's parent, position, token and that token's logit at the parent.
-    for (int i = tid >> 5; i < min(nn, 64); i += 8)
-        if (stats_ahead(m_rows, pos[r0 + i], root_pos)) {
+    // Everything that the walk may ask of the nodes, fetched side by side instead of node after node: lane i holds node i's
+    // parent, position, token and that token's logit at the parent.
+    for (int i = tid >> 5; i < nn; i += 8) {
+        bool ok = stats_ahead(m_rows, pos[r0 + i], root_pos);
+        if (ok) {
+            const hs_reject_stat* st = stats + (size_t)(r0 + i) * n_slices;
             float mx;
             double z;
-            row_total(stats + (size_t)(r0 + i) * n_slices, mx, z);
+            ok = row_total([&](int s, slice_stat& v) __attribute__((always_inline)) { return get_stat(st + s, call, v); }, mx, z);
             if ((lane & 31) == 0) { node_max[i] = mx; node_sum[i] = z; }
         }
+        if ((lane & 31) == 0) node_ok[i] = ok;
+    }
     int pre_par = -2, pre_tok = 0, pre_pos = root_pos;
     float pre_lg = -INFINITY;
     if (lane < nn) {
@@ -266,41 +362,71 @@ __device__ inline void accept_rejection_seq(
     __syncthreads();
     int cur = 0, a = 0;
     if (tid == 0) path_row[(size_t)b * k_stride] = 0;
+    // Two turns at a node: decide about its children, then -- at the last node -- sample among what is left.
+    bool last = false;
+    int nrej = 0, rej = -1;     // lane q < nrej: the q-th rejected token
+    float mx = 0.f;
+    uint4 my_stat = make_uint4(0u, 0u, 0u, 0u);
     for (;;) {
         const float* lg = logits + (size_t)(r0 + cur) * vocab;
-        hs_reject_stat* st = stats + (size_t)(r0 + cur) * n_slices;
-        const int cur_pos = cur < 64 ? __shfl(pre_pos, cur) : pos[r0 + cur];
-        const bool ahead = stats_ahead(m_rows, cur_pos, root_pos);
-        if (!ahead) {
-            for (int s = 0; s < n_slices; s++) {
-                float v[PER];
-                load_slice(lg, vocab, s, vec, v);
-                slice_stats(v, inv_temp, tab, st + s);
+        const uint4* st = reinterpret_cast<const uint4*>(stats + (size_t)(r0 + cur) * n_slices);
+        bool all = !node_ok[cur] && !last;          // every slice has to be summed here ...
+        if (!last && tid < n_slices) my_stat = st[tid];   // (for the sample, if this is the last node: not waited for here)
+        if (last && node_ok[cur]) {
+            bool ok = true;
+            for (int s = tid; s < n_slices; s += 256) {
+                slice_stat v;
+                ok &= take_stat(s < 256 ? my_stat : st[s], call, v);
+                own[s] = v;
+            }
+            all = __syncthreads_or(!ok);
+        }
+        // ... or, before the sample, those that hold rejected tokens, without these (subtracting would leave rounding where a
+        // rejected token had nearly all the weight)
+        if (all || last) {
+            const int rej_slice = lane < nrej && in_vocab(rej) ? rej / SLICE : -1;
+            auto next_slice = [&](int s) __attribute__((always_inline)) {
+                while (s < n_slices && !all && !__any(rej_slice == s)) s++;
+                return s;
+            };
+            int s = next_slice(0);
+            float v[PER], w[PER];
+            if (s < n_slices) load_slice(lg, vocab, s, vec, v);
+            while (s < n_slices) {
+                const int sn = next_slice(s + 1);
+                if (sn < n_slices) load_slice(lg, vocab, sn, vec, w);   // (on its way while this one is summed)
+                for (int q = 0; q < nrej; q++) {
+                    const int t = __shfl(rej, q);
+#pragma unroll
+                    for (int j = 0; j < PER; j++)
+                        if (slice_token(s, j, vec) == t) v[j] = -INFINITY;
+                }
+                const slice_stat sum = slice_stats<WALK_AT_ONCE>(v, inv_temp, tab);
+                if (tid == 0) own[s] = sum;
+#pragma unroll
+                for (int j = 0; j < PER; j++) v[j] = w[j];
+                s = sn;
             }
             __syncthreads();
         }
-        float mx;
-        double z;
-        if (ahead && cur < 64) { mx = node_max[cur]; z = node_sum[cur]; }
-        else row_total(st, mx, z);
-        const uint32_t position = (uint32_t)(cur_pos + 1);
-        auto weight = [&](float l) { return exp(((double)l - (double)mx) * inv_temp); };
-        // children in node order, 64 nodes at a time
-        int next = -1, next_tok = 0, tried = 0, nrej = 0, rej = -1;   // lane q < nrej: the q-th rejected token
-        double zr = z;
-        for (int i0 = 0; i0 < nn && next < 0; i0 += 64) {
-            const int i = i0 + lane;
-            const bool child = i > 0 && i < nn && (i0 == 0 ? pre_par : parent[r0 + i]) == cur;
-            const int my_tok = !child ? 0 : i0 == 0 ? pre_tok : tok[r0 + i];
-            const double my_w = child ? weight(i0 == 0 ? pre_lg : in_vocab(my_tok) ? lg[my_tok] : -INFINITY) : 0.0;
+        const uint32_t position = (uint32_t)(__shfl(pre_pos, cur) + 1);
+        if (!last) {
+            double z;
+            if (all) row_total([&](int s, slice_stat& v) __attribute__((always_inline)) { v = own[s]; return true; }, mx, z);
+            else { mx = node_max[cur]; z = node_sum[cur]; }
+            // children in node order, a node per lane
+            const bool child = lane > 0 && lane < nn && pre_par == cur;
+            const double my_w = child ? exp(((double)pre_lg - (double)mx) * inv_temp) : 0.0;
+            int next = -1, next_tok = 0, tried = 0;
+            double zr = z;
             for (unsigned long long todo = __ballot(child); todo && next < 0; todo &= todo - 1) {
                 const int q = __ffsll(todo) - 1;
-                const int t = __shfl(my_tok, q);
+                const int t = __shfl(pre_tok, q);
                 double w = __hiloint2double(__shfl(__double2hiint(my_w), q), __shfl(__double2loint(my_w), q));
                 if (__any(lane < nrej && rej == t)) w = 0.0;
                 const double u = uniform01(seed, sid, position, (uint32_t)tried);
                 if (u < w / zr) {
-                    next = i0 + q;
+                    next = q;
                     next_tok = t;
                 } else if (nrej < 8) {
                     if (lane == nrej) rej = t;
@@ -309,40 +435,26 @@ __device__ inline void accept_rejection_seq(
                 }
                 tried++;
             }
-        }
-        if (next >= 0 && a + 1 < k_stride) {
-            if (tid == 0) {
-                out_tok[(size_t)b * k_stride + a] = next_tok;
-                path_row[(size_t)b * k_stride + a + 1] = next;
+            if (next >= 0 && a + 1 < k_stride) {
+                if (tid == 0) {
+                    out_tok[(size_t)b * k_stride + a] = next_tok;
+                    path_row[(size_t)b * k_stride + a + 1] = next;
+                }
+                cur = next;
+                a++;
+                nrej = 0;
+                rej = -1;
+            } else {
+                last = true;
             }
-            cur = next;
-            a++;
+            if (all) __syncthreads();   // (own[] has been read)
             continue;
         }
-        // Final sample from the remaining distribution, in token-id order.  A slice that holds rejected tokens is summed
-        // again without them (subtracting would leave rounding where a rejected token had nearly all the weight).
-        for (int q = 0; q < nrej; q++) {
-            const int t0 = __shfl(rej, q), s = t0 / SLICE;
-            if (!in_vocab(t0)) continue;   // (it has no share in any slice)
-            float v[PER];
-            load_slice(lg, vocab, s, vec, v);
-            for (int q2 = 0; q2 < nrej; q2++) {
-                const int t = __shfl(rej, q2);
-#pragma unroll
-                for (int j = 0; j < PER; j++)
-                    if (slice_token(s, j, vec) == t) v[j] = -INFINITY;
-            }
-            const double sum = block_sum_f64(sum_weights(v, mx, inv_temp, tab), redd);
-            if (tid == 0) { st[s].m = mx; st[s].s = sum; }
-            __syncthreads();
-        }
-        auto slice_weight = [&](int s) { return s < n_slices ? st[s].s * exp(((double)st[s].m - (double)mx) * inv_temp) : 0.0; };
+        // Final sample from the remaining distribution, in token-id order.
+        auto slice_weight = [&](int s) __attribute__((always_inline)) { return s < n_slices ? own[s].s * exp(((double)own[s].m - (double)mx) * inv_temp) : 0.0; };
         double zt = 0.0;
         for (int s0 = 0; s0 < n_slices; s0 += 64) {
-            double t = slice_weight(s0 + lane);
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) t += shfl_xor_f64(t, o);
-            zt += t;
+            zt += wave_sum_f64(slice_weight(s0 + lane));
         }
         const double target = uniform01(seed, sid, position, 7u) * zt;
         int slice = -1;
@@ -378,7 +490,7 @@ __device__ inline void accept_rejection_seq(
                 for (int j = 0; j < PER; j++)
                     if (lo + j == t) v[j] = -INFINITY;
             }
-            const double sum = sum_weights(v, mx, inv_temp, tab);
+            const double sum = sum_weights<WALK_AT_ONCE>(v, mx, inv_temp, tab);
             const double incl = wave_prefix_f64(sum, lane);
             if (lane == 63) wave_tot[wave] = incl;
             __syncthreads();
@@ -422,7 +534,7 @@ __device__ inline void accept_rejection_seq(
 // Commit of one sequence by its workgroup: relocate accepted tree nodes' K/V to consecutive slots, then advance the
 // state.  CT = cache element type (bf16 bits, or float in the fp32-activation mode).
 template <typename CT>
-__device__ inline void commit_seq(
+__device__ __forceinline__ void commit_seq(
     int b, int n_layers, int hkv, int hd, int n_blocks, CT* __restrict__ kc, CT* __restrict__ vc,
     const int32_t* __restrict__ block_table, int max_blocks, int32_t* __restrict__ seq_len,
     int32_t* __restrict__ tail, int32_t* __restrict__ tail_len, int w_max, int32_t* __restrict__ k_state,
@@ -503,8 +615,9 @@ struct accept_commit_args {
     const float* logits;
     const unsigned long long* keys;
     int n_keys;
-    hs_reject_stat* stats;
+    const hs_reject_stat* stats;
     int n_slices;
+    uint32_t call;
     int32_t* argmax;
     const uint64_t* seq_id;
     double inv_temp;
@@ -519,11 +632,11 @@ struct accept_commit_args {
     hs_policy pol;
 };
 
-// REJECT: acceptance is rejection sampling; else greedy, or commit alone.  Two kernels, because the sampler takes more than a
-// hundred registers and the rest 23: in one kernel the greedy walk of more than 256 sequences ran in rounds of a workgroup
+// REJECT: acceptance is rejection sampling; else greedy, or commit alone.  Two kernels, because the sampler takes
+// nearly two hundred registers and the rest 23: in one kernel the greedy walk of more than 256 sequences ran in rounds of a workgroup
 // per compute unit (greedy acceptance of 1024 trees of 17 nodes 40 us, on its own 16).
 template <typename CT, bool REJECT>
-__global__ __launch_bounds__(256) void accept_commit_kernel(accept_commit_args p) {
+__global__ __launch_bounds__(256, REJECT ? 1 : 7) void accept_commit_kernel(accept_commit_args p) {
     const int b = blockIdx.x, tid = threadIdx.x;
     const int r0 = p.row_off[b], nn = p.row_off[b + 1] - r0;
     if (p.do_accept) {
@@ -551,7 +664,8 @@ __global__ __launch_bounds__(256) void accept_commit_kernel(accept_commit_args p
             }
             if (REJECT) {
                 accept_rejection_seq(b, r0, nn, p.row_off[p.batch], p.vocab, p.tok, p.parent, p.pos, p.logits,
-                                     p.stats, p.n_slices, p.seq_id, p.inv_temp, p.seed, p.k_stride, p.accept_len, p.n_out, p.out_tok, p.path_row);
+                                     p.stats, p.n_slices, p.call, p.seq_id, p.inv_temp, p.seed, p.k_stride, p.accept_len,
+                                     p.n_out, p.out_tok, p.path_row);
             } else if (tid == 0) {
                 accept_greedy_walk(b, r0, nn, p.tok, p.parent, p.argmax, p.k_stride, p.accept_len, p.n_out, p.out_tok,
                                    p.path_row);
@@ -611,14 +725,16 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
         p.seed = args->seed;
     }
     if (args && args->mode == HS_ACCEPT_REJECTION) {
-        p.stats = reinterpret_cast<hs_reject_stat*>(ctx->ws + ctx->lay.reject_stats);
+        hs_reject_stat* stats = reinterpret_cast<hs_reject_stat*>(ctx->ws + ctx->lay.reject_stats);
+        p.stats = stats;
         p.n_slices = hs_reject_slices(d.vocab);
+        p.call = ctx->reject_calls.fetch_add(1, std::memory_order_relaxed);
         // enough workgroups to fill the chip: small batches split a sequence's rows, too
         const int nodes = 1 + ctx->lim.c_max * ctx->lim.k_max;
         int split = 2048 / (p.n_slices * p.batch);
         split = split < 1 ? 1 : (split > nodes ? nodes : split);
         hipLaunchKernelGGL(reject_stats_kernel, dim3(p.batch, p.n_slices, split), dim3(256), 0, st, p.row_off, p.pos,
-                           logits, p.vocab, p.batch, p.inv_temp, p.stats);
+                           logits, p.vocab, p.batch, p.inv_temp, p.call, stats);
     }
     p.accept_len = step->accept_len; p.n_out = step->n_out; p.out_tok = step->out_tok; p.path_row = step->path_row;
     if (policy) {
@@ -635,8 +751,11 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
     const dim3 grid(seq->batch), block(256);
     const bool fp32 = hs_fp32_activations(ctx);
     if (args && args->mode == HS_ACCEPT_REJECTION) {
-        if (fp32) hipLaunchKernelGGL((accept_commit_kernel<float, true>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((accept_commit_kernel<bf16_t, true>), grid, block, 0, st, p);
+        const size_t lds = (size_t)p.n_slices * sizeof(slice_stat);
+        const auto kernel = fp32 ? &accept_commit_kernel<float, true> : &accept_commit_kernel<bf16_t, true>;
+        if (lds > 48 * 1024)   // (vocabularies beyond 12 million)
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(kernel, grid, block, lds, st, p);
     } else {
         if (fp32) hipLaunchKernelGGL((accept_commit_kernel<float, false>), grid, block, 0, st, p);
         else hipLaunchKernelGGL((accept_commit_kernel<bf16_t, false>), grid, block, 0, st, p);

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -18,9 +19,10 @@ constexpr int HS_DRAFT_SEG = 4096;
 constexpr int HS_MAX_NODES = 64;  // ancestor masks are 64-bit
 
 // Rejection sampling: the vocabulary is summed in slices of this many tokens; per row and slice the largest logit and the
-// sum of exp((logit - largest) / temperature) are kept.
+// sum of exp((logit - largest) / temperature) are kept in the workspace, with a word that says which call wrote them
+// (calls of one context may overlap on different streams).
 constexpr int HS_REJECT_SLICE = 4096;
-struct hs_reject_stat { float m; double s; };
+struct alignas(16) hs_reject_stat { float m; uint32_t check; double s; };
 static inline int hs_reject_slices(int vocab) { return (vocab + HS_REJECT_SLICE - 1) / HS_REJECT_SLICE; }
 
 struct hs_workspace_layout {
@@ -42,6 +44,7 @@ struct hs_ctx {
     int att_part = HS_ATT_PART_DEFAULT;
     int max_parts = 0;
     int max_segs = 0;
+    mutable std::atomic<uint32_t> reject_calls{0};   // numbers the rejection-sampling calls (any host thread)
     int n_cu = 256;  // compute units of the device the context was created on
     std::string err;
     // profiling

@@ -393,3 +393,75 @@ def test_a_drafted_id_outside_the_vocabulary_is_a_token_of_weight_zero(toy, V, B
             r += n
     eng.close()
     assert accepted > 0
+
+
+def sampled(eng, step, st, mode_args, stream):
+    from paper_2508_18588_amd import hs_accept
+    hs_accept(eng.ctx, mode_args, eng.c_seq, step, stream.cuda_stream)
+    return st
+
+
+def results_of(st):
+    return [np_of(st[n]).copy() for n in ("accept_len", "n_out", "out_tok", "path_row")]
+
+
+def test_overlapping_rejection_sampling_of_one_context_on_two_streams(toy):
+    """Two calls of one context, each with its own step arrays and logits, are independent of each other also while they
+    run side by side: both sum their rows into the same place of the workspace.  And whatever else happens to that place
+    during a call (here another stream that keeps filling it with random bits) the call notices and sums for itself: the
+    results are those of the same calls one after the other."""
+    from paper_2508_18588_amd import HS_ACCEPT_REJECTION, hs_accept_args, hs_step
+    from paper_2508_18588_amd.runtime import Engine
+    from hs_inputs import ModelShape
+    V, B, k = 65540, 16, 8
+    shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
+    rng = np.random.default_rng(4)
+    eng = Engine(shape, make_weights(shape, 3), rope_table(64, 64), max_batch=B, k_max=k, c_max=2, max_len=80)
+    eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B, seq_ids=rng.integers(0, 2 ** 62, B).astype(np.int64))
+    sides = []
+    for temperature in (1.0, 0.5):
+        trees = [oracle.build_tree([rng.integers(0, V, k), rng.integers(0, V, k)], 0, 50) for _ in range(B)]
+        m = eng.set_rows([dict(tok=t["tok"], parent=t["parent"], pos=t["pos"]) for t in trees])
+        lg = torch.randn(eng.max_rows, V, generator=torch.Generator(device="cuda:0").manual_seed(9), device="cuda:0")
+        r = 0
+        for t in trees:
+            for i in range(1, len(t["tok"])):
+                lg[r + int(t["parent"][i]), int(t["tok"][i])] = temperature * (np.log(V) + 2.0)
+            r += len(t["tok"])
+        st = {n: v.clone() for n, v in eng.st.items()}
+        step = hs_step(*[st[n].data_ptr() for n in ("draft_start", "match_len", "draft_len", "row_off", "tok", "pos", "parent",
+                                                    "anc_mask", "row2seq")], lg.data_ptr(),
+                       *[st[n].data_ptr() for n in ("argmax", "accept_len", "n_out", "out_tok", "path_row")], 0,
+                       st["draft_src"].data_ptr())
+        sides.append((step, st, hs_accept_args(HS_ACCEPT_REJECTION, temperature, 77), lg))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    want = []
+    for (step, st, args, _), s in zip(sides, streams):
+        torch.cuda.synchronize()
+        sampled(eng, step, st, args, s)
+        torch.cuda.synchronize()
+        want.append(results_of(st))
+    assert want[0][0].sum() > 0 and want[1][0].sum() > 0
+    for _ in range(60):
+        for (step, st, args, _), s in zip(sides, streams):
+            sampled(eng, step, st, args, s)
+        torch.cuda.synchronize()
+        for (step, st, args, _), w_ in zip(sides, want):
+            assert all((a == b).all() for a, b in zip(results_of(st), w_))
+    # the sums are the workspace's last region: 16 bytes per row and slice of 4096 tokens
+    n = eng.max_rows * ((V + 4095) // 4096) * 16
+    end = eng._ws_ptr - eng.workspace.data_ptr() + hs_workspace_bytes_of(eng)
+    place = eng.workspace[end - (n + 255) // 256 * 256:end].view(torch.int32)
+    for _ in range(10):
+        with torch.cuda.stream(streams[1]):
+            for _ in range(40):
+                place.random_()
+        sampled(eng, *sides[0][:3], streams[0])
+        torch.cuda.synchronize()
+        assert all((a == b).all() for a, b in zip(results_of(sides[0][1]), want[0]))
+    eng.close()
+
+
+def hs_workspace_bytes_of(eng):
+    from paper_2508_18588_amd import hs_workspace_bytes
+    return hs_workspace_bytes(eng.ctx)

@@ -72,3 +72,7 @@ def test_greedy_acceptance_and_commit_fill_a_compute_unit():
     for name, r in kernels.items():
         assert r["VGPRs"] <= 72 and r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
         assert r["Occupancy [waves/SIMD]"] >= 7, (name, r)
+    sampler = {k: v for k, v in rep.items() if "reject_stats_kernel" in k or ("accept_commit_kernel" in k and "Lb1E" in k)}
+    assert len(sampler) == 3, sorted(rep)                      # the sums, and the walk for either cache
+    for name, r in sampler.items():
+        assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)

@@ -139,7 +139,6 @@ __device__ __forceinline__ float block_max_f32(float v, float* red) {
 // walk takes what carries its own call's number and computes anything else itself, into LDS.
 constexpr int SLICE = HS_REJECT_SLICE, PER = SLICE / 256;   // tokens of a slice; of a slice, per thread
 constexpr int STATS_ALL_ROWS = 2048;
-constexpr int STATS_AT_ONCE = 16, WALK_AT_ONCE = 16;
 
 __device__ __forceinline__ bool stats_ahead(int m, int pos, int root_pos) { return m <= STATS_ALL_ROWS || pos - root_pos <= 1; }
 
@@ -195,26 +194,15 @@ __device__ __forceinline__ void load_slice(const float* __restrict__ lg, int voc
     }
 }
 
-// Sum of exp((logit - ref) / T) over a thread's logits; excluded ones (-inf) add nothing, a NaN makes it NaN.  AT_ONCE of
-// them are computed side by side, then the array moves on by as many (all sixteen side by side take 100 registers and more).
-template <int AT_ONCE>
+// Sum of exp((logit - ref) / T) over a thread's logits; excluded ones (-inf) add nothing, a NaN makes it NaN.
 __device__ __forceinline__ double sum_weights(const float (&v)[PER], float ref, double inv_temp, const double* tab) {
     const exp_scale k = make_scale(inv_temp);
     double s = 0.0;
     unsigned worst = 0u;
-    float u[PER];
 #pragma unroll
-    for (int j = 0; j < PER; j++) u[j] = v[j];
-    static_assert(PER % AT_ONCE == 0, "whole rounds");
-#pragma unroll 1
-    for (int r = 0; r < PER / AT_ONCE; r++) {
-#pragma unroll
-        for (int j = 0; j < AT_ONCE; j++) {
-            s += exp_diff(u[j], ref, k, tab);
-            worst = max(worst, __float_as_uint(u[j]) << 1);
-        }
-#pragma unroll
-        for (int j = 0; j + AT_ONCE < PER; j++) u[j] = u[j + AT_ONCE];
+    for (int j = 0; j < PER; j++) {
+        s += exp_diff(v[j], ref, k, tab);
+        worst = max(worst, __float_as_uint(v[j]) << 1);
     }
     return ref == -INFINITY && worst <= 0xFF000000u ? 0.0 : worst > 0xFF000000u || ref == INFINITY ? NAN : s;
 }
@@ -222,7 +210,6 @@ __device__ __forceinline__ double sum_weights(const float (&v)[PER], float ref, 
 // Largest logit and sum of one slice, relative to that largest logit, by a workgroup of 256 threads.
 // A slice in which every token is excluded (-inf) has the sum 0; a NaN anywhere makes the sum NaN.
 struct slice_stat { float m; double s; };
-template <int AT_ONCE>
 __device__ __forceinline__ slice_stat slice_stats(const float (&v)[PER], double inv_temp, const double* tab) {
     __shared__ float redf[4];
     __shared__ double redd[4];
@@ -230,7 +217,7 @@ __device__ __forceinline__ slice_stat slice_stats(const float (&v)[PER], double 
 #pragma unroll
     for (int j = 0; j < PER; j++) mx = fmaxf(mx, v[j]);
     mx = block_max_f32(mx, redf);
-    const double s = block_sum_f64(sum_weights<AT_ONCE>(v, mx, inv_temp, tab), redd);
+    const double s = block_sum_f64(sum_weights(v, mx, inv_temp, tab), redd);
     // (the same in every lane: in scalar registers from here on)
     return {__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(mx))),
             __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(s)), __builtin_amdgcn_readfirstlane(__double2loint(s)))};
@@ -281,7 +268,7 @@ __global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __r
     while (r < r1) {
         const int rn = next_row(r + gridDim.z);
         if (rn < r1) load_slice(logits + (size_t)rn * vocab, vocab, slice, vec, w);
-        const slice_stat sum = slice_stats<STATS_AT_ONCE>(v, inv_temp, tab);
+        const slice_stat sum = slice_stats(v, inv_temp, tab);
         if (threadIdx.x == 0) put_stat(stats + (size_t)r * n_slices + slice, sum, call);
 #pragma unroll
         for (int j = 0; j < PER; j++) v[j] = w[j];
@@ -401,7 +388,7 @@ __device__ __forceinline__ void accept_rejection_seq(
                     for (int j = 0; j < PER; j++)
                         if (slice_token(s, j, vec) == t) v[j] = -INFINITY;
                 }
-                const slice_stat sum = slice_stats<WALK_AT_ONCE>(v, inv_temp, tab);
+                const slice_stat sum = slice_stats(v, inv_temp, tab);
                 if (tid == 0) own[s] = sum;
 #pragma unroll
                 for (int j = 0; j < PER; j++) v[j] = w[j];
@@ -490,7 +477,7 @@ __device__ __forceinline__ void accept_rejection_seq(
                 for (int j = 0; j < PER; j++)
                     if (lo + j == t) v[j] = -INFINITY;
             }
-            const double sum = sum_weights<WALK_AT_ONCE>(v, mx, inv_temp, tab);
+            const double sum = sum_weights(v, mx, inv_temp, tab);
             const double incl = wave_prefix_f64(sum, lane);
             if (lane == 63) wave_tot[wave] = incl;
             __syncthreads();
@@ -633,8 +620,8 @@ struct accept_commit_args {
 };
 
 // REJECT: acceptance is rejection sampling; else greedy, or commit alone.  Two kernels, because the sampler takes
-// nearly two hundred registers and the rest 23: in one kernel the greedy walk of more than 256 sequences ran in rounds of a workgroup
-// per compute unit (greedy acceptance of 1024 trees of 17 nodes 40 us, on its own 16).
+// nearly two hundred registers and the rest 23: in one kernel the greedy walk of more than 256 sequences ran in rounds of a
+// workgroup per compute unit (greedy acceptance of 1024 trees of 17 nodes 40 us, on its own 16).
 template <typename CT, bool REJECT>
 __global__ __launch_bounds__(256, REJECT ? 1 : 7) void accept_commit_kernel(accept_commit_args p) {
     const int b = blockIdx.x, tid = threadIdx.x;

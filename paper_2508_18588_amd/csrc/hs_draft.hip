@@ -472,6 +472,7 @@ __global__ __launch_bounds__(256) void draft_group_walk_kernel(
             int n = 0;
             for (; n < kk; n++) {
                 const int t = live ? ahead[n][tid] : -1;
+                live = t != -1;   // (as below, an id of -1 drops its occurrence; other negative ids have no vote)
                 // every live occurrence prices its own token: (reward sum, votes) packed, larger is better
                 unsigned long long sum = 0ull;
                 unsigned votes = 0u;
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(256) void draft_group_walk_kernel(
                 live = live && t == chosen;
             }
             const unsigned long long alive = __ballot(live);
-            if (tid == 0) { first_s = __ffsll(alive) - 1; len_s = n; }
+            if (tid == 0) { first_s = n == 0 ? 0 : __ffsll(alive) - 1; len_s = n; }   // (nothing drafted: all are live)
         }
         __syncthreads();
     } else {
@@ -554,7 +555,7 @@ __global__ __launch_bounds__(256) void draft_group_walk_kernel(
         __syncthreads();
     }
     const int first = first_s;
-    if (first < 0) { none(); return; }   // cannot happen: the chosen token came from a live occurrence
+    if (first < 0 || n_occ <= 0) { none(); return; }   // (every occurrence ran into an id of -1)
     if (tid == 0) {
         const int g = occ_resp[first];
         draft_src[b] = g;

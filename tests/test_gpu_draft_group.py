@@ -199,3 +199,63 @@ def test_group_draft_with_segments_in_turn(toy, B, G):
     assert (st["draft_len"][:B] > 0).any()
     assert B < 64 or len(set(st["draft_start"][:B] // 4096)) == 3        # chosen in each of the segments
     eng.close()
+
+
+@pytest.mark.parametrize("n_occ", [1, 3, 64, 65, 200])
+def test_negative_ids_in_a_response_end_a_walk_alike_for_few_and_many_occurrences(toy, n_occ):
+    """A response may hold ids that are no tokens.  They never vote; an occurrence whose next id is -1 drops out, one with
+    another negative id next stays live until somebody else votes -- whether the occurrences are walked by one wavefront
+    (up to 64) or by the workgroup.  The rule written out in plain Python."""
+    from paper_2508_18588_amd import HS_K_FIXED
+    from paper_2508_18588_amd.runtime import Engine, Policy
+    shape, w, _ = toy
+    B, G, k = 24, 4, 6
+    rng = np.random.default_rng(n_occ)
+    eng = Engine(shape, w, rope_table(16384, shape.head_dim), max_batch=B, k_max=8, c_max=1, max_len=64, g_max=G)
+    xs, groups, occs, rewards = [], [], [], []
+    for b in range(B):
+        x = np.array([100, 101, 102, 103], np.int32)
+        resp, occ = [[] for _ in range(G)], []
+        for g in np.sort(rng.integers(0, G, n_occ)):
+            text = rng.choice([7, 8, -1, -1, -9], 7, p=[0.4, 0.2, 0.2, 0.1, 0.1])
+            resp[g] += [50 + len(resp[g]) % 3] + x.tolist()
+            occ.append((int(g), len(resp[g])))
+            resp[g] += text.tolist()
+        xs.append(x)
+        groups.append([np.asarray(r + [60], np.int32) for r in resp])
+        occs.append(occ)
+        rewards.append(rng.integers(0, 3, G).astype(np.int32))
+    pol = Policy(window=4, m_min=3, k_mode=HS_K_FIXED, k_fixed=k, k_max=8)
+    st = run_group_draft(eng, xs, groups, rewards, pol)
+    eng.close()
+    ended = 0
+    for b in range(B):
+        live, draft = {i: True for i in range(n_occ)}, []
+        for j in range(k):
+            nxt = {}
+            for i in [i for i in live if live[i]]:
+                g, p = occs[b][i]
+                nxt[i] = int(groups[b][g][p + j]) if p + j < len(groups[b][g]) else -2
+                live[i] = nxt[i] != -1
+            votes = {}
+            for i, t in nxt.items():
+                if t >= 0:
+                    s, v = votes.get(t, (0, 0))
+                    votes[t] = (s + int(rewards[b][occs[b][i][0]]), v + 1)
+            if not votes:
+                break
+            best = min(votes, key=lambda t: (-votes[t][0], -votes[t][1], t))
+            for i, t in nxt.items():
+                live[i] = live[i] and t == best
+            draft.append(best)
+        left = [i for i in live if live[i]] if draft else [0]
+        r0, r1 = st["row_off"][b], st["row_off"][b + 1]
+        if left:
+            want = (4, len(draft), *occs[b][left[0]], draft)
+        else:
+            want = (0, 0, -1, -1, [])
+            ended += 1
+        got = (int(st["match_len"][b]), int(st["draft_len"][b]), int(st["draft_src"][b]), int(st["draft_start"][b]),
+               st["tok"][r0 + 1:r1].tolist())
+        assert got == want, (b, got, want)
+    assert ended > 0 or n_occ > 3

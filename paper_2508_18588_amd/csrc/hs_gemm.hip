@@ -191,8 +191,10 @@ void launch(const hs_ctx* ctx, const void* a_any, const bf16_t* w, const bf16_t*
 // 674 -> 642 us.)
 bool hs_gemm_narrow_groups(int n, int k) { return k < 8192 || (long long)n * k <= 600ll * 1024 * 64; }
 
-int hs_gemm_chunks(int n, int k) {
-    const int groups = hs_gemm_narrow_groups(n, k) ? (n + 63) / 64 : (n + 127) / 128;
+int hs_gemm_chunks(int n, int k) { return hs_gemm_chunks(n, k, hs_gemm_narrow_groups(n, k)); }
+
+int hs_gemm_chunks(int n, int k, bool narrow) {
+    const int groups = narrow ? (n + 63) / 64 : (n + 127) / 128;
     int chunks = 256 / groups;
     const int nk = k / BK;
     if (chunks > nk / 4) chunks = nk / 4;

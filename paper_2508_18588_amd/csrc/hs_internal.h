@@ -76,6 +76,7 @@ static inline bool hs_plain_kernels(const hs_ctx* ctx) {
     return (ctx->flags & (HS_FLAG_REFERENCE_KERNELS | HS_FLAG_FP32_ACTIVATIONS)) != 0;
 }
 int hs_gemm_chunks(int n, int k);
+int hs_gemm_chunks(int n, int k, bool narrow);   // with groups of 64 (narrow) or 128 weight rows
 // Must the logits exist as an [rows][vocab] array?  Yes if the caller asks for them (a destination in the step, or
 // HS_FLAG_WORKSPACE_LOGITS), with the plain kernels, and when the LM head splits K (a small vocabulary).  Otherwise the
 // LM head reduces every row to its argmax in its epilogue and hs_accept finishes the reduction.

@@ -186,3 +186,21 @@ def test_projections_at_the_real_layer_shapes(which):
             assert (np.abs(sub - want) <= tol).all(), (which, name, m, "host dot products")
         del ref
     eng.close()
+
+
+def test_a_square_projection_of_the_feed_forward_width_has_room_for_its_partial_sums():
+    """hs_debug_gemm takes any shape within the model's widths whose partial sums fit the scratch at all of its rows: at the
+    1.5B widths 8960 x 8960, in three chunks, does -- however few chunks the model's own down projection runs in."""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=1, d_model=1536, n_q_heads=2, n_kv_heads=1, head_dim=128, d_ffn=8960, vocab=64)
+    eng = Engine(shape, make_weights(shape, 5), rope_table(64, shape.head_dim), max_batch=2, k_max=15, c_max=1, max_len=32)
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    m, n = eng.max_rows, 8960
+    a = torch.randn(m, n, device="cuda:0", generator=g).to(torch.bfloat16)
+    w = (torch.randn(n, n, device="cuda:0", generator=g) * 0.02).to(torch.bfloat16)
+    c = torch.zeros(m, n, dtype=torch.float32, device="cuda:0")
+    eng.gemm(0, a, w, None, c, torch.full((1,), m, dtype=torch.int32, device="cuda:0"), m, m)
+    torch.cuda.synchronize()
+    want = a.double() @ w.double().T.contiguous()
+    assert float((c.double() - want).abs().max()) <= 2e-5 * (float(want.abs().max()) + 1.0)
+    eng.close()

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from hs_inputs import ModelShape, bf16_bits, make_weights, rope_table, make_prompts
-from gpu_common import derived_logit_tol, np_of
+from gpu_common import OracleBatch, check_cache, check_last_layer_projections, derived_logit_tol, np_of
 
 pytestmark = pytest.mark.gpu
 
@@ -106,3 +106,88 @@ def test_sum_of_squares_is_a_chain_of_fused_multiply_adds_in_a_fixed_order(d):
     r = xn2[at] / embed[at]                       # (a division by a power of two)
     want = x * r[:, None] * w["norm_f"].astype(np.float32)
     assert (got == want).all(), (d, int((got != want).any(1).sum()), m)
+
+
+def last_row_logits(eng, prompts, how):
+    """Logits of every prompt's last token: the text before it by hs_prefill (how = a chunk length) or through hs_verify."""
+    eng.load_sequences(list(prompts), budgets=[9] * len(prompts))
+    eng.prefill(list(prompts)) if how == "verify" else eng.prefill_chunked(how)
+    eng.set_rows([dict(tok=p[-1:], parent=[-1], pos=[len(p) - 1]) for p in prompts])
+    eng.verify()
+    torch.cuda.synchronize()
+    assert eng.poll_error() == 0
+    return np_of(eng.logits)[:len(prompts)].astype(np.float64)
+
+
+@pytest.mark.parametrize("d,hq,hkv,h", [(8256, 1, 1, 64), (12288, 1, 1, 64), (12352, 1, 1, 64), (16384, 2, 1, 64),
+                                        (256, 64, 8, 128), (192, 33, 11, 128)])
+def test_wide_rows_and_many_heads_against_the_oracle(d, hq, hkv, h):
+    """Rows of three and four rounds of a workgroup (d_model beyond 8192 and 12288; the last round full and ragged), and
+    heads with more than 1024 rotary items per row: logits and cache against the oracle, in the default and in the
+    fp32-activation mode, the prompt written by hs_prefill and by hs_verify."""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=2, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=h, d_ffn=64, vocab=64)
+    w, rope = make_weights(shape, d + hq, norm_jitter=0.1), rope_table(64, h)
+    prompts = [p[:n] for p, n in zip(make_prompts(3, 21, shape.vocab, 3), (21, 2, 18))]
+    ob = OracleBatch(oracle.Model(shape, w, rope), prompts, [9] * 3, 32)
+    want = np.stack([ob.seqs[b].tree_logits(p[-1:], np.array([-1], np.int32))[0] for b, p in enumerate(prompts)])
+    scale = np.abs(want).max(1, keepdims=True)
+    for precise, how in ((False, 16), (False, "verify"), (True, "verify")):
+        eng = Engine(shape, w, rope, max_batch=3, k_max=6, c_max=1, max_len=24, shuffle_pages_seed=2, precise=precise)
+        got = last_row_logits(eng, prompts, how)
+        if precise:
+            assert (np.abs(got - want) <= 1e-4 * scale).all()
+        else:
+            assert np.abs(got - want).max() <= derived_logit_tol(shape, shape.n_layers)
+            check_cache(eng, ob, 0, tol=2.0 ** -7 * 0.02 * np.sqrt(d) * 4)
+        eng.close()
+
+
+@pytest.mark.parametrize("d", [8256, 16384])
+def test_wide_rows_with_pending_partial_sums(d):
+    """A down projection of 8192 columns leaves two or three partial sums per element to a norm of three and four rounds.
+    The residual stream after it against fp64 products of the path's own operands, and the norms on either side of it
+    against the definition: one rounding to the 8 significant bits of bf16 (half a place is 2^-8 of a power of two) of a value
+    computed with a few fp32 roundings."""
+    from hs_inputs.device import make_weights_device
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=2, d_model=d, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=8192, vocab=64)
+    eng = Engine(shape, make_weights_device(shape, 7), rope_table(64, 64), max_batch=3, k_max=15, c_max=1, max_len=32)
+    prompts = make_prompts(3, 14, shape.vocab, 3)
+    eng.load_sequences(list(prompts), budgets=[9] * 3)
+    eng.seq_len.fill_(1)
+    m = eng.set_rows([dict(tok=p, parent=np.arange(-1, len(p) - 1), pos=np.arange(len(p))) for p in prompts])
+    cap = eng.capture_last_layer()
+    eng.verify()
+    torch.cuda.synchronize()
+    check_last_layer_projections(eng, cap, m, range(m), np.random.default_rng(1))
+    for x, xn in ((cap[3], cap[2]), (eng.debug_tensor(4), eng.debug_tensor(0))):
+        x = np_of(x.view(torch.float32)[:m * d]).reshape(m, d).astype(np.float64)
+        got = np_of(xn.view(torch.bfloat16)[:m * d].double()).reshape(m, d)
+        want = x / np.sqrt((x * x).mean(1, keepdims=True) + shape.rms_eps)
+        assert (np.abs(got - want) <= (2.0 ** -8 + 2e-6) * np.abs(want)).all()
+    eng.close()
+
+
+def test_tables_that_only_allow_narrow_loads():
+    """The header asks no alignment of the embedding and of the rotary table beyond their elements': both one element off a
+    16-byte boundary give the bits of the aligned ones."""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=2, d_model=384, n_q_heads=6, n_kv_heads=2, head_dim=64, d_ffn=128, vocab=300)
+    w, rope = make_weights(shape, 3, norm_jitter=0.1), rope_table(64, 64)
+    prompts = make_prompts(3, 21, shape.vocab, 3)
+    shifted = {}
+    for name, a in (("embed", torch.from_numpy(w["embed"].view(np.int16))), ("rope", torch.from_numpy(rope))):
+        flat = torch.empty(a.numel() + 1, dtype=a.dtype, device="cuda:0")
+        flat[1:] = a.flatten().cuda()
+        shifted[name] = flat[1:].view(a.shape)
+        assert shifted[name].data_ptr() % 16 == a.element_size()
+    for precise in (False, True):
+        logits = []
+        for table, cs in ((w["embed"], rope), (shifted["embed"], rope), (w["embed"], shifted["rope"])):
+            eng = Engine(shape, dict(w, embed=table), cs, max_batch=3, k_max=6, c_max=1, max_len=24, precise=precise)
+            assert (eng.w["embed"].data_ptr() % 8 != 0) == (table is shifted["embed"])
+            assert (eng.rope.data_ptr() % 16 != 0) == (cs is shifted["rope"])
+            logits.append(last_row_logits(eng, list(prompts), "verify"))
+            eng.close()
+        assert (logits[0] == logits[1]).all() and (logits[0] == logits[2]).all()

@@ -10,8 +10,8 @@
 
 namespace {
 
-// A row's norm is a workgroup of norm_threads(d) threads, each with 4 elements in up to NORM_ITEMS rounds
-// (d_model <= 16384, checked by hs_create).
+// A row's norm is a workgroup of norm_threads(d) threads, each with 4 elements in each of up to NORM_ITEMS rounds: thread t
+// holds elements 4 t .. 4 t + 3, the same 4096 further on, ... (d_model <= 16384, checked by hs_create).
 constexpr int NORM_ITEMS = 4, NORM_THREADS_MAX = 1024;
 
 __device__ __forceinline__ void put(bf16_t* p, float v) { *p = f32_to_bf16(v); }
@@ -35,13 +35,6 @@ __device__ inline float block_sum(float v, float* red) {
     return s;
 }
 
-// One workgroup per row.  With chunks > 0 the row of the residual stream first receives the pending partial sums of
-// the preceding projection: t = p0 + p1 + ... in chunk order, x += t -- the arithmetic of the stand-alone ordered
-// reduce, so that the split execution gives the same bits whichever kernel finishes it.
-// OutT = bf16_t (rounded activations) or float (fp32-activation mode).
-// The kernel is a chain of memory round trips, not a stream: a thread keeps its (up to NORM_ITEMS x 4) elements in
-// registers from the first load to the normalised store, and the norm weights are fetched with them.  What hides the
-// chain when there are many rows is other rows: HS_NORM_NOW
 __device__ __forceinline__ void put4(bf16_t* p, float4 v) {
     uint2 o;
     o.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
@@ -126,6 +119,14 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void embed_no
     }
 }
 
+// One workgroup per row.  With chunks > 0 the row of the residual stream first receives the pending partial sums of
+// the preceding projection: t = p0 + p1 + ... in chunk order, x += t -- the arithmetic of the stand-alone ordered
+// reduce, so that the split execution gives the same bits whichever kernel finishes it.
+// OutT = bf16_t (rounded activations) or float (fp32-activation mode).
+// The kernel is a chain of memory round trips, not a stream: a thread keeps its (up to NORM_ITEMS x 4) elements in
+// registers from the first load to the normalised store, and the norm weights are fetched with them.  With many rows the
+// other rows of a compute unit hide the chain; how many share one does not matter (rows of 3584 and of 5120 in
+// workgroups of 448 to 1024 threads: a step takes the same within 0.3 %).
 template <typename OutT, int ITEMS>
 __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
                                                        OutT* __restrict__ out, const int32_t* __restrict__ m_dev,
@@ -399,13 +400,10 @@ void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_seq_state* seq, int32_t*
                        reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.err));
 }
 
-// Rounds of a row's elements over its workgroup, and the threads that this takes: about 512, so that four rows are under
-// way on a compute unit, more only for rows that four rounds would not cover; at least 256 for the list writers.
+// Rounds of a row's elements over its workgroup, and its threads: one round where 1024 threads hold the row, no more threads
+// than it has elements for, and at least 256 (the list writers).
 static int norm_rounds(int d) { return std::min(NORM_ITEMS, (d / 4 + NORM_THREADS_MAX - 1) / NORM_THREADS_MAX); }
-static int norm_threads(int d) {
-    const int rounds = norm_rounds(d);
-    return std::max(256, ((d / 4 + rounds - 1) / rounds + 63) / 64 * 64);
-}
+static int norm_threads(int d) { return std::max(256, std::min(NORM_THREADS_MAX, (d / 4 + 63) / 64 * 64)); }
 
 #define HS_NORM_LAUNCH(KERNEL, OUT, GRID, ...)                                                                        \
     switch (norm_rounds(d.d_model)) {                                                                                 \

@@ -61,7 +61,7 @@ def final_norm_rows(shape, w, tokens):
 def test_sum_of_squares_is_a_chain_of_fused_multiply_adds_in_a_fixed_order(d):
     """The final norm of the fp32-activation mode against its own residual stream, bit for bit: a thread's sum of
     squares starts with fma(x, x, y y) and goes on with one fma per element, lanes are added by a butterfly, wavefronts
-    left to right, and the row is x r g with r = 1 / sqrt(sum / d + eps) as the hardware rounds it.  That r is read off a
+    left to right (thread t holds elements 4 t .. 4 t + 3 and the same 4096 further on), and the row is x r g with r = 1 / sqrt(sum / d + eps) as the hardware rounds it.  That r is read off a
     second model whose residual stream is its embedding (O and down projection zero), rows of powers of two that square
     and add up, without any rounding, to the sums of the first.  One and two rounds of elements per thread."""
     shape = ModelShape(n_layers=1, d_model=d, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=96)
@@ -73,7 +73,7 @@ def test_sum_of_squares_is_a_chain_of_fused_multiply_adds_in_a_fixed_order(d):
         return (a.astype(np.longdouble) * a + addend).astype(np.float32)
 
     rounds = (d // 4 + 1023) // 1024
-    threads = max(256, ((d // 4 + rounds - 1) // rounds + 63) // 64 * 64)
+    threads = max(256, min(1024, (d // 4 + 63) // 64 * 64))
     v = np.zeros((m, rounds * threads, 4), np.float32)
     v[:, :d // 4] = x.reshape(m, d // 4, 4)
     v = v.reshape(m, rounds, threads, 4)

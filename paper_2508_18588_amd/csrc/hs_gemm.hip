@@ -183,12 +183,15 @@ void launch(const hs_ctx* ctx, const void* a_any, const bf16_t* w, const bf16_t*
 // Number of K chunks of a projection: a function of the shape alone.  Narrow outputs get as many chunks as put
 // about one workgroup of the weight-streaming execution on every one of the 256 compute units; every chunk keeps at
 // least 4 k-tiles.  A workgroup takes 128 weight rows, or 64 (hs_gemm_narrow_groups): with half as many chunks the
-// projection writes -- and the kernel after it reads -- half the partial sums, 2 x 16384 / n chunks x n x 4 bytes = 128 KB
-// per row whatever the shape, while twice as many groups each re-read the activations from L2, n k / 64 bytes more per
-// row.  An L2 byte costs about a fifth of a byte of partial sums, so the line lies at 600 KB of re-reads, or K < 8192.  (By K < 8192
-// alone the 1.5B shape's down projection, 1536 x 8960 or 210 KB, ran in 20 chunks:
-// 102 -> 71 us at 2048 rows, and the norm that reads the sums 28 -> 25 us a launch; a step of 248 rows through four layers
-// 674 -> 642 us.)
+// projection writes -- and the kernel after it reads -- half the partial sums, 128 KB per row less whatever the shape,
+// while twice as many groups each re-read the activations from L2, n k / 64 bytes more per row.
+// The line lies at 600 KB of re-reads (128- against 64-row groups, us at 64, 220, 1000 and 2048 rows, ordered reduce
+// included): 1536 x 8960, 210 KB: 19, 29, 73, 144 against 16, 24, 54, 99; 3072 x 12288, 576 KB: 24, 37, 113, 231 against
+// 25, 37, 101, 185; 3584 x 14336, 784 KB: 27, 42, 139, 282 against 32, 48, 132, 240; 3584 x 18944, 1036 KB: 32, 48, 167, 340
+// against 39, 58, 167, 305 -- below it nothing is lost with few rows, above it a fifth.
+// K < 8192 overrides it: those shapes keep the chunks, and so the order of addition, that they always had.  Between
+// 600 KB and the 1 MB that such a shape can reach they pay for it with few rows and gain with many (6144 x 7168, 672 KB:
+// 24, 39, 127, 260 against 30, 46, 103, 200; 8192 x 8064, 1008 KB: 30, 48, 169, 337 against 35, 55, 170, 302).
 bool hs_gemm_narrow_groups(int n, int k) { return k < 8192 || (long long)n * k <= 600ll * 1024 * 64; }
 
 int hs_gemm_chunks(int n, int k) { return hs_gemm_chunks(n, k, hs_gemm_narrow_groups(n, k)); }

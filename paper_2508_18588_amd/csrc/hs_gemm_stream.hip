@@ -353,7 +353,7 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
 #pragma unroll
                     for (int ni = 0; ni < NUW; ni++) {
                         if (p.n0 + 32 * (U0 + ni) + lc >= p.N) continue;
-        // (adding: all of a tile's loads before its first store -- element by element each load waited for
+                        // (adding: all of a tile's loads before its first store -- element by element each load waited for
                         // the one before it, 17 us of a launch with 16 rows)
                         float old[16];
                         if (!PARTIAL && EPI == HS_EPI_ADD_F32) {
@@ -536,8 +536,10 @@ void launch_stream(const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, 
 #define HS_WIDE_GROUP_ROWS 352   // measured cross-over at the 7B shape: 33 vs 40 us at 300 rows, 49 vs 37 us at 385
 #endif
 
-// Units per workgroup: the candidate with the least (rounds of 256 workgroups) x (time of one).  A workgroup's time per
-// k-tile is that of its LDS traffic and goes like units + 6: the activation tile's share does not shrink with the units.
+// Units per workgroup: the candidate with the least (rounds of 256 workgroups) x (time of one); a round grows by less than
+// its units, because the activation tile's share does not grow with them.  (One round of a SwiGLU projection with K = 3584
+// in 3, 4 and 5 units: 38, 43, 53 us at 64 rows, 56, 67, 80 at 220, which is units + 2; for the benchmark configurations'
+// shapes at 16 to 4096 rows any constant from 2 to 6 picks the same.)
 // The reduction order does not depend on it, so the expected number of row passes counts, too.
 int choose_units(int units, int chunks, int passes) {
     int best = 4, best_cost = 1 << 30;
@@ -567,7 +569,7 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
     const int passes = std::max(1, (std::min(rows_hint, m_max) + pass_rows - 1) / pass_rows);
     const int nu = EPI == HS_EPI_ROWMAX ? rowmax_units(n) : choose_units((n + unit_cols - 1) / unit_cols, chunks, passes);
 #define HS_ARGS a, w, w2, c, part, m_dev, m_max, n, k, chunks, tpc, rows_hint, st
-    // The 64-row groups of the smaller split-K shapes (QKV, O) pay at a few hundred rows, where they halve the
+    // The 64-row groups of the smaller split-K shapes (QKV, O, the 1.5B down projection) pay at a few hundred rows, where they halve the
     // partial sums; with many row passes every group re-reads the whole activation slab of its pass, and wider groups
     // (half as many re-reads) win.  The K chunking -- the reduction order -- is the shape's either way.
     if (PARTIAL && chunks > 1 && hs_gemm_narrow_groups(n, k) && rows_hint < HS_WIDE_GROUP_ROWS) {

@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "hs_internal.h"
+#include "hs_lanes.h"
 
 namespace {
 
@@ -55,23 +56,6 @@ __device__ __forceinline__ void accept_greedy_walk(int b, int r0, int nn, const 
     n_out[b] = a + 1;
 }
 
-// The value of lane (own ^ O), by DPP and permlane moves: a butterfly of __shfl_xor is a chain of trips through the LDS unit,
-// which is most of what a workgroup waits for when it sums one slice after another.
-// (quad_perm 1 0 3 2 and 2 3 0 1; half-row mirror, then the quad mirrored back; a row rotated by eight; rows and halves
-// swapped: the results of a swap of a register with itself are own and partner, in an order that depends on the lane)
-template <int O>
-__device__ __forceinline__ unsigned lane_xor(unsigned v) {
-    if constexpr (O == 1) return __builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xF, 0xF, true);
-    else if constexpr (O == 2) return __builtin_amdgcn_update_dpp(0u, v, 0x4E, 0xF, 0xF, true);
-    else if constexpr (O == 4)
-        return __builtin_amdgcn_update_dpp(0u, __builtin_amdgcn_update_dpp(0u, v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
-    else if constexpr (O == 8) return __builtin_amdgcn_update_dpp(0u, v, 0x128, 0xF, 0xF, true);
-    else {
-        static_assert(O == 16 || O == 32, "within a wavefront");
-        const auto sw = O == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        return (threadIdx.x & O) ? sw[0] : sw[1];
-    }
-}
 template <int O>
 __device__ __forceinline__ double lane_xor_f64(double v) {
     return __hiloint2double((int)lane_xor<O>((unsigned)__double2hiint(v)), (int)lane_xor<O>((unsigned)__double2loint(v)));

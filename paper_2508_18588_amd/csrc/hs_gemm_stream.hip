@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "hs_gemm_common.h"
+#include "hs_lanes.h"
 
 using namespace hs_gemm_detail;
 
@@ -266,48 +267,47 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
     if (EPI == HS_EPI_ROWMAX) {
         // Each row's largest value among this workgroup's columns, as a key that orders by value and then by lower column:
         // first over the lane's columns, then over the 32 lanes that hold the row, then over the two wavefronts that share
-        // it -- group 1 leaves its keys in LDS (every fragment has been read), group 0 takes the larger and stores.
+        // it: every wavefront leaves its keys in LDS (every fragment has been read), a thread per row takes the larger.
+        // (152064 columns of K = 3584 at 220 and 2176 rows: one group after the other, with exchanges through the LDS unit,
+        // 310 and 2276 us; as it is 276 and 1987; four wavefronts with all units each, 295 and 2105.)
+        constexpr int ROWS = 128 * MT;
         unsigned long long* keys = reinterpret_cast<unsigned long long*>(p.Cout);
-        unsigned long long* other_half = reinterpret_cast<unsigned long long*>(smem);
+        unsigned long long* wave_keys = reinterpret_cast<unsigned long long*>(smem);   // [2][ROWS]
         const int lr = 4 * (lane_e >> 5), lc = lane_e & 31;
-        __builtin_amdgcn_s_barrier();
+        __syncthreads();
+        if (NMI > 0) {
 #pragma unroll
-        for (int turn = 0; turn < 2; turn++) {
-            if (NMI > 0 && turn == 1 - GRP) {
+            for (int mi = 0; mi < NMI; mi++) {
 #pragma unroll
-                for (int mi = 0; mi < NMI; mi++) {
-                    const int tile_row = 32 * (quad + 4 * mi) + lr;     // within the pass
+                for (int e = 0; e < 16; e++) {
+                    unsigned long long key = 0ull;
 #pragma unroll
-                    for (int e = 0; e < 16; e++) {
-                        unsigned long long key = 0ull;
-#pragma unroll
-                        for (int ni = 0; ni < NUW; ni++) {
-                            const int col = p.n0 + 32 * (U0 + ni) + lc;
-                            unsigned u = __float_as_uint(acc[mi][ni][e]);
-                            u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-                            const unsigned long long k2 = ((unsigned long long)u << 32) | (0xFFFFFFFFu - (unsigned)col);
-                            if (col < p.N && k2 > key) key = k2;
-                        }
-#pragma unroll
-                        for (int o = 16; o > 0; o >>= 1) {
-                            const unsigned lo = __shfl_xor((unsigned)key, o), hi = __shfl_xor((unsigned)(key >> 32), o);
-                            const unsigned long long other = ((unsigned long long)hi << 32) | lo;
-                            if (other > key) key = other;
-                        }
-                        __builtin_amdgcn_sched_barrier(0);   // (one row at a time: the accumulators leave few registers)
-                        const int row = tile_row + 8 * (e >> 2) + (e & 3);
-                        if (lc == 0) {
-                            if (GRP == 1) {
-                                other_half[row] = key;
-                            } else if (p.m0 + row < p.M) {
-                                const unsigned long long other = other_half[row];
-                                keys[(size_t)(p.m0 + row) * p.n_groups + p.group] = other > key ? other : key;
-                            }
-                        }
+                    for (int ni = 0; ni < NUW; ni++) {
+                        const int col = p.n0 + 32 * (U0 + ni) + lc;
+                        unsigned u = __float_as_uint(acc[mi][ni][e]);
+                        u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+                        const unsigned long long k2 = ((unsigned long long)u << 32) | (0xFFFFFFFFu - (unsigned)col);
+                        if (col < p.N && k2 > key) key = k2;
                     }
+                    auto take = [&](unsigned lo, unsigned hi) __attribute__((always_inline)) {
+                        const unsigned long long other = ((unsigned long long)hi << 32) | lo;
+                        if (other > key) key = other;
+                    };
+                    take(lane_xor<16>((unsigned)key), lane_xor<16>((unsigned)(key >> 32)));
+                    take(lane_xor<8>((unsigned)key), lane_xor<8>((unsigned)(key >> 32)));
+                    take(lane_xor<4>((unsigned)key), lane_xor<4>((unsigned)(key >> 32)));
+                    take(lane_xor<2>((unsigned)key), lane_xor<2>((unsigned)(key >> 32)));
+                    take(lane_xor<1>((unsigned)key), lane_xor<1>((unsigned)(key >> 32)));
+                    __builtin_amdgcn_sched_barrier(0);   // (one row at a time: the accumulators leave few registers)
+                    if (lc == 0) wave_keys[GRP * ROWS + 32 * (quad + 4 * mi) + lr + 8 * (e >> 2) + (e & 3)] = key;
                 }
             }
-            if (turn == 0) __syncthreads();
+        }
+        __syncthreads();
+        const int row = GRP * 256 + quad * 64 + lane_e;     // within the pass
+        if (row < ROWS && p.m0 + row < p.M) {
+            const unsigned long long k0 = wave_keys[row], k1 = wave_keys[ROWS + row];
+            keys[(size_t)(p.m0 + row) * p.n_groups + p.group] = k0 > k1 ? k0 : k1;
         }
         return;
     }

@@ -356,13 +356,19 @@ __device__ __forceinline__ void accept_rejection_seq(
         // rejected token had nearly all the weight)
         if (all || last) {
             const int rej_slice = lane < nrej && in_vocab(rej) ? rej / SLICE : -1;
-            auto next_slice = [&](int s) __attribute__((always_inline)) {
-                while (s < n_slices && !all && !__any(rej_slice == s)) s++;
-                return s;
+            auto next_slice = [&](int s) __attribute__((always_inline)) {   // the first one from s on
+                if (all) return s;
+                int next = n_slices;
+                for (int q = 0; q < nrej; q++) {
+                    const int t = __shfl(rej_slice, q);
+                    if (t >= s && t < next) next = t;
+                }
+                return next;
             };
             int s = next_slice(0);
+            const bool any = s < n_slices;
             float v[PER], w[PER];
-            if (s < n_slices) load_slice(lg, vocab, s, vec, v);
+            if (any) load_slice(lg, vocab, s, vec, v);
             while (s < n_slices) {
                 const int sn = next_slice(s + 1);
                 if (sn < n_slices) load_slice(lg, vocab, sn, vec, w);   // (on its way while this one is summed)
@@ -378,7 +384,7 @@ __device__ __forceinline__ void accept_rejection_seq(
                 for (int j = 0; j < PER; j++) v[j] = w[j];
                 s = sn;
             }
-            __syncthreads();
+            if (any) __syncthreads();
         }
         const uint32_t position = (uint32_t)(__shfl(pre_pos, cur) + 1);
         if (!last) {
@@ -574,7 +580,7 @@ __device__ __forceinline__ void commit_seq(
     }
 }
 
-// Acceptance and commit of one step in ONE launch, one workgroup per sequence (either half can be switched off: the
+// Acceptance and commit of one step in one launch (behind reject_stats_kernel's where it samples), one workgroup per sequence (either half can be switched off: the
 // two entry points that run them separately use the same kernel).
 //   1. With `keys` (the LM head ran with its row-maximum epilogue and no logits exist): every row's argmax = the
 //      largest of its n_keys per-column-group keys, one wavefront per row; written to argmax[].

@@ -304,9 +304,9 @@ hs_status hs_accept(hs_ctx* ctx, const hs_accept_args* args, const hs_seq_state*
 hs_status hs_kv_commit(hs_ctx* ctx, const hs_kv_cache* cache, hs_seq_state* seq, const hs_step* step,
                        const hs_policy* policy, hs_stream stream);
 
-/* hs_accept followed by hs_kv_commit as ONE kernel launch (one workgroup per sequence: argmax of its rows where the
- * LM head left only row maxima, acceptance walk or rejection sampling, K/V relocation, state update): same arguments,
- * same results bit for bit as the two calls in a row. */
+/* hs_accept followed by hs_kv_commit as one kernel launch, behind the one for its sums with rejection sampling (one
+ * workgroup per sequence: argmax of its rows where the LM head left only row maxima, acceptance walk or rejection
+ * sampling, K/V relocation, state update): same arguments, same results bit for bit as the two calls in a row. */
 hs_status hs_accept_commit(hs_ctx* ctx, const hs_accept_args* args, const hs_kv_cache* cache, hs_seq_state* seq,
                            hs_step* step, const hs_policy* policy, hs_stream stream);
 

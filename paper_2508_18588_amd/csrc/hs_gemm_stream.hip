@@ -23,10 +23,11 @@
 //     across tile boundaries, one by one behind single MFMAs, and the steady state carries no modulo arithmetic and as
 //     few guards as possible.  The tile hand-over (wait for the loads of the next tile, workgroup barrier, issue of new
 //     loads) sits before a tile's last k-step, after the last fragment read of the tile has been issued.
-//   * What bounds it now: at up to 128 rows the weight stream (271 MB of gate/up weights in 50 us); at 220 to 1000 rows LDS
-//     and matrix cores in balance at the clock that this load leaves the chip (1500 and 1280 clocks a tile); with more
-//     rows the matrix cores at that clock.  A third activation stage made every shape slower (71 -> 77 us), the row
-//     pitch of the operands (55 to 65 lines of 128 bytes) is worth 5 % either way.
+//   * What bounds it now: at up to 128 rows the weight stream (271 MB of gate/up weights in 50 us); at 220 rows LDS and
+//     matrix cores in balance (counters: matrix cores busy 39 % of gate/up's cycles; 184 KB through LDS a tile are 1440
+//     clocks, its MFMAs 1280), with a prologue and an epilogue that nothing overlaps; at 2176 rows LDS (65 to 70 %) and
+//     matrix cores (62 to 67 %) at the 1.6 to 1.8 GHz that this load leaves the chip.  A third activation stage made
+//     every shape slower (71 -> 77 us), the row pitch of the operands (55 to 65 lines of 128 bytes) is worth 5 % either way.
 // SwiGLU pairs the gate and up rows of 16 output columns in one 32-row weight unit, so that both pre-activations of
 // a column meet in one MFMA tile (lanes c and c+16).
 #include <algorithm>

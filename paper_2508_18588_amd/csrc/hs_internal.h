@@ -159,7 +159,7 @@ bool hs_launch_draft_static(const hs_ctx* ctx, const hs_draft_args* args, const 
 uint32_t* hs_draft_static_error_word(hipError_t* why);
 void hs_launch_draft_group(const hs_ctx* ctx, const hs_group_draft_args* args, const hs_seq_state* seq,
                            hs_step* step, hipStream_t st);
-// Acceptance and/or commit of one step in one launch.  args == nullptr: no acceptance; policy == nullptr: no commit.
+// Acceptance and/or commit of one step in one launch (rejection sampling: after one for its sums).  args == nullptr: no acceptance; policy == nullptr: no commit.
 // keys != nullptr: the rows' argmax is first reduced from the LM head's row-maximum keys (n_keys per row).
 void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, const hs_kv_cache* cache,
                              const hs_seq_state* seq, const hs_step* step, const float* logits,

@@ -116,7 +116,7 @@ __device__ __forceinline__ float block_max_f32(float v, float* red) {
 // vocabulary per visited node and one lane that walked 594 tokens at the end, it was 2.6 to 3.4 ms.  Slices of 8192
 // tokens took 5 % longer (twice the registers, half the wavefronts).
 // With very many rows most of them are never visited: beyond STATS_ALL_ROWS only the roots and their children are
-// computed ahead (2048 rows of 152064 tokens take 0.4 ms, about what the walk needs for five rows by itself), and the
+// computed ahead (2048 rows of 152064 tokens take 0.4 ms, about what the walk needs for six rows by itself), and the
 // walk computes the rest of what it visits.
 // Another rejection-sampling call of the context may run at the same time on another stream, with rows of its own and the
 // same place in the workspace.  So every sum carries a word made of itself and the number of the call that wrote it; the

@@ -20,13 +20,12 @@
 //     the other through a private LDS slice and never synchronises with the others.  With a single 32-row tile the
 //     softmax arithmetic of a partition is one instruction stream; giving every wavefront its own stream keeps all
 //     four SIMDs of a compute unit busy and the KV stream bandwidth-bound.
-//   R > 32: one WORKGROUP per unit; K/V tiles of 128 keys are staged once and shared, the (up to four) 32-row tiles
-//     are dealt to the 4 wavefronts.  A sequence with more than 128 query rows per KV head is cut into units of
-//     four row tiles, each of which walks the partition's keys on its own: holding two row tiles per wavefront
-//     instead would cost every workgroup unit of the launch half the resident workgroups (registers), which was
-//     measured to be far dearer than reading the K/V of the few very long drafts twice.  In a unit with two or three
-//     live row tiles the wavefronts without a tile only stage K/V (most of each tile); the computing ones keep one
-//     page per tile.
+//   R > 32: one WORKGROUP per unit; the (up to four) 32-row tiles are dealt to the 4 wavefronts, and the 32-key sub-tiles
+//     travel from global memory straight into a ring in LDS that all four fill and all four read (attn_wg_stream).
+//     A sequence with more than 128 query rows per KV head is cut into units of four row tiles, each of which walks the
+//     partition's keys on its own: holding two row tiles per wavefront instead would cost every workgroup unit of the
+//     launch half the resident workgroups (registers), which was measured to be far dearer than reading the K/V of the
+//     few very long drafts twice.
 // Both run the identical per-row arithmetic on the identical partitions: masked keys contribute exact zeros and
 // partitions merge in index order, so a row's result is bit-identical whether it is verified next to other draft
 // rows or decoded alone.
@@ -35,40 +34,68 @@
 // persistent grid -- exactly the workgroups that are resident at once -- works the lists off: wavefront units by a
 // static deal, workgroup units through a counter (see attn_verify_mfma).  K and V are read with non-temporal loads.
 // A second entry, attn_prefill_mfma, does the same causally over a chunk of consecutive tokens.
+#include "hs_gemm_common.h"   // fragment types, loads into LDS
 #include "hs_internal.h"
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
+constexpr int ATT_RING = 4;   // sub-tiles of 32 keys in LDS: one per wavefront, or a ring of them per workgroup
+
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// One 32-key sub-tile for one 32-row query tile: S^T = K.Q^T, online softmax per lane, O^T += V^T.P^T.
-// sK points at the sub-tile's 32 key rows, sV at its two 16-token pages.  Every query row's arithmetic is
-// independent of which other rows are in flight.
+// A 32-key sub-tile (two pages) in LDS: K as 32 rows of HD elements, then V^T as two pages of HD rows of 16 tokens, both
+// without padding, so that a page's K or V^T block is one contiguous run that a load into LDS can fill.  16-byte chunks are
+// permuted instead, within a row of K and within a pair of V^T, so that 16 consecutive rows read at the same chunk
+// cover the 64 banks once (and a write of consecutive chunks does anyway).
 template <int HD>
-__device__ inline void attn_subtile(const bf16_t* sK, const bf16_t* sV, const bf16x8 (&qf)[HD / 16],
-                                    f32x16 (&o)[HD / 32], float& m_run, float& l_run, uint64_t anc, int kbase, int L,
-                                    int total, float scale_log2, int half, int l32) {
-    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32;
+struct sub_tile {
+    static constexpr int PAGE = 32 * HD, V = 2 * PAGE, BYTES = 4 * PAGE;   // a page's K (or V^T) block, V^T's place, all
+    static __device__ __forceinline__ int k_at(int key, int chunk) {
+        return key * 2 * HD + ((chunk ^ (HD == 128 ? key & 15 : (key >> 1) & 7)) << 4);
+    }
+    // what 1 KB further on changes in the permutation
+    static constexpr int k_step(int i) { return (HD == 128 ? 4 * i & 15 : 4 * i & 7) << 4; }
+    static __device__ __forceinline__ int v_at(int dim, int chunk) { return dim * 32 + ((chunk ^ ((dim >> 3) & 1)) << 4); }
+};
+
+// One 32-key sub-tile for one 32-row query tile: S^T = K.Q^T, online softmax per lane, O^T += V^T.P^T.
+// Every query row's arithmetic is independent of which other rows are in flight.
+// Row i of the A operand is not key i but key pi(i), bits 2 and 3 exchanged: element e of a lane's scores is then key
+// 16 (e / 8) + 8 half + e % 8, so that the eight probabilities of a page that a lane feeds to the second product belong to
+// eight consecutive tokens -- one 16-byte piece of a V^T row instead of two of 8 bytes.
+template <int HD>
+__device__ __forceinline__ void load_keys(const unsigned char* tile, bf16x8 (&ka)[HD / 16], int half, int l32) {
+    const int krow = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
+    int k0 = sub_tile<HD>::k_at(krow, half);  // chunk 2 ks + half: the permutation is an exclusive or, and so is 2 ks
+    asm volatile("" : "+v"(k0));              // (eight addresses kept across the caller's loop would spill)
+#pragma unroll
+    for (int ks = 0; ks < HD / 16; ks++) ka[ks] = *reinterpret_cast<const bf16x8*>(tile + (k0 ^ (ks << 5)));
+}
+template <int HD>
+__device__ __forceinline__ f32x16 scores(const bf16x8 (&ka)[HD / 16], const bf16x8 (&qf)[HD / 16]) {
     f32x16 s;
 #pragma unroll
     for (int e = 0; e < 16; e++) s[e] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ks++) {
-        bf16x8 ka = *reinterpret_cast<const bf16x8*>(&sK[l32 * KS + ks * 16 + half * 8]);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[ks], s, 0, 0, 0);
-    }
-    // element e: key kbase + 8*(e/4) + 4*half + e%4, query row = this lane's.  Only tiles that reach past the
-    // cached prefix need the tree mask.
+    for (int ks = 0; ks < HD / 16; ks++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qf[ks], s, 0, 0, 0);
+    return s;
+}
+
+// Masks the scores (in tiles that reach past the cached prefix) and moves the running maximum.  (A maximum that only moves
+// where a score exceeds it by 2^8 spares most of the rescales, 1 % of a step with trees, but its probabilities are no longer
+// exactly 1 at the maximum: the error of a layer against 64 bits grew by 3 %.)
+template <int HD>
+__device__ __forceinline__ void take_maximum(f32x16& s, f32x16 (&o)[HD / 32], float& m_run, float& l_run, uint64_t anc,
+                                              int kbase, int L, int total, float scale_log2, int half) {
+    // query row = this lane's.  Only tiles that reach past the cached prefix need the tree mask.
     if (kbase + 32 > L) {
 #pragma unroll
         for (int e = 0; e < 16; e++) {
-            int kp = kbase + 8 * (e >> 2) + 4 * half + (e & 3);
-            bool vis = kp < L || (kp < total && ((anc >> (kp - L)) & 1ull));
+            const int kp = kbase + 16 * (e >> 3) + 8 * half + (e & 7);
+            const bool vis = (kp < L) | ((kp < total) & (bool)((anc >> ((kp - L) & 63)) & 1ull));
             s[e] = vis ? s[e] : -INFINITY;
         }
     }
@@ -82,41 +109,53 @@ __device__ inline void attn_subtile(const bf16_t* sK, const bf16_t* sV, const bf
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
         tmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2;   // scale > 0: commutes with max
     }
-    float m_new = fmaxf(m_run, tmax);
-    float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-    float alpha = fast_exp2(m_run - m_safe);
-    float psum = 0.f;
-    bf16x8 pb[2];
+    const float m_new = fmaxf(m_run, tmax);
+    // where it does not move for any of the 32 rows, multiplying by exactly 1 is skipped
+    if (__any(m_new != m_run)) {
+        const float alpha = fast_exp2(m_run - (m_new == -INFINITY ? 0.f : m_new));
+        m_run = m_new;
+        l_run *= alpha;
 #pragma unroll
-    for (int e = 0; e < 16; e++) {
-        float p = fast_exp2(__builtin_fmaf(s[e], scale_log2, -m_safe));
-        psum += p;
-        pb[e >> 3][e & 7] = (__bf16)p;
-    }
-    {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(psum), __float_as_uint(psum), false, false);
-        psum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
-    l_run = l_run * alpha + psum;
-    m_run = m_new;
-    // the running maximum rarely moves after the first tiles: multiplying by exactly 1 is skipped
-    if (__any(alpha != 1.f)) {
-#pragma unroll
-        for (int dt = 0; dt < NDT; dt++)
+        for (int dt = 0; dt < HD / 32; dt++)
 #pragma unroll
             for (int e = 0; e < 16; e++) o[dt][e] *= alpha;
     }
+}
+
+// Probabilities of a sub-tile, as the second product's operand, and their sum.
+__device__ __forceinline__ void probabilities(const f32x16& s, float m_run, float& l_run, float scale_log2, bf16x8 (&pb)[2]) {
+    const float m_safe = (m_run == -INFINITY) ? 0.f : m_run;
+    float psum = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < 2; kk++)
+    for (int e = 0; e < 16; e++) {
+        const float p = fast_exp2(__builtin_fmaf(s[e], scale_log2, -m_safe));
+        psum += p;
+        pb[e >> 3][e & 7] = (__bf16)p;
+    }
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(psum), __float_as_uint(psum), false, false);
+    l_run += __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+}
+
+template <int HD>
+__device__ __forceinline__ bf16x8 load_values(const unsigned char* tile, int i, int half, int l32) {
+    using T = sub_tile<HD>;
+    constexpr int NDT = HD / 32;
+    return *reinterpret_cast<const bf16x8*>(tile + T::V + T::v_at(l32, half) + (i / NDT) * T::PAGE + (i % NDT) * 1024);
+}
+
+template <int HD>
+__device__ inline void attn_subtile(const unsigned char* tile, const bf16x8 (&qf)[HD / 16], f32x16 (&o)[HD / 32], float& m_run,
+                                    float& l_run, uint64_t anc, int kbase, int L, int total, float scale_log2, int half,
+                                    int l32) {
+    constexpr int NDT = HD / 32;
+    bf16x8 ka[HD / 16], pb[2];
+    load_keys<HD>(tile, ka, half, l32);
+    f32x16 s = scores<HD>(ka, qf);
+    take_maximum<HD>(s, o, m_run, l_run, anc, kbase, L, total, scale_log2, half);
+    probabilities(s, m_run, l_run, scale_log2, pb);
 #pragma unroll
-        for (int dt = 0; dt < NDT; dt++) {
-            const bf16_t* vrow = &sV[(kk * HD + dt * 32 + l32) * VS];
-            u32x2 lo = *reinterpret_cast<const u32x2*>(vrow + 4 * half);
-            u32x2 hi = *reinterpret_cast<const u32x2*>(vrow + 8 + 4 * half);
-            union { u32x4 u; bf16x8 v; } va;
-            va.u = u32x4{lo.x, lo.y, hi.x, hi.y};
-            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.v, pb[kk], o[dt], 0, 0, 0);
-        }
+    for (int i = 0; i < 2 * NDT; i++)
+        o[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_values<HD>(tile, i, half, l32), pb[i / NDT], o[i % NDT], 0, 0, 0);
 }
 
 // A 64-key tile (four pages) of the prefill: the same steps with one maximum and one rescale per 64 keys and the two
@@ -295,8 +334,9 @@ __device__ inline AttnUnit attn_unit_from(const int4& p, const int4& q) {
 // atomic that returns late holds back every later load of its wavefront.
 template <int HD>
 __device__ inline void attn_wave_stream(const AttnArgs& a, const int4* __restrict__ list, int n_units, int first,
-                                        int stride, bf16_t* sKw, bf16_t* sVw, int lane) {
-    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32;
+                                        int stride, unsigned char* tile, int lane) {
+    using T = sub_tile<HD>;
+    constexpr int NKS = HD / 16, NDT = HD / 32;
     if (first >= n_units) return;
     const int half = lane >> 5, l32 = lane & 31;
     const int G = a.hq / a.hkv;
@@ -308,8 +348,8 @@ __device__ inline void attn_wave_stream(const AttnArgs& a, const int4* __restric
     int k_end = min(total, k_begin + a.part_keys);
     const bf16_t* kbase_ptr = a.kc + (size_t)cu.j * 16 * HD;   // + page * page_stride
     const bf16_t* vbase_ptr = a.vc + (size_t)cu.j * HD * 16;
-    // the unit's page numbers, fetched once: lane l holds the page of positions k_begin + 16 l .. + 15 (a partition
-    // has at most 64 pages), handed out by readlane -- no table look-up sits between two sub-tiles
+    // the unit's page numbers, 64 at a time: lane l holds the page of positions 16 l .. + 15 of 1024, handed out by
+    // readlane -- no table look-up sits between two sub-tiles
     int my_page = safe_page_lane(a.block_table + (size_t)cu.b * a.max_blocks, k_begin + 16 * lane, total, a.max_blocks,
                                  a.n_blocks);
 
@@ -350,35 +390,44 @@ __device__ inline void attn_wave_stream(const AttnArgs& a, const int4* __restric
         }                                                                                                         \
     }
     HS_W_FETCH(my_page, kbase_ptr, vbase_ptr, 0)
+    const int k_put = T::k_at(lane / (HD / 8), lane % (HD / 8)), v_put = T::V + T::v_at(lane >> 1, lane & 1);
     int kb = k_begin;
     for (;;) {
+        int k_to = k_put;
+        asm volatile("" : "+v"(k_to));   // (see attn_subtile)
 #pragma unroll
         for (int pp = 0; pp < 2; pp++)
 #pragma unroll
             for (int ii = 0; ii < NCP; ii++) {
-                int c = lane + 64 * ii;
-                int key = pp * 16 + c / (HD / 8), c16 = c % (HD / 8);
-                *reinterpret_cast<u32x4*>(&sKw[key * KS + c16 * 8]) = rk[pp * NCP + ii];
-                int dim = c >> 1, hf = c & 1;
-                u32x2* dst = reinterpret_cast<u32x2*>(&sVw[(pp * HD + dim) * VS + hf * 8]);
-                dst[0] = u32x2{rv[pp * NCP + ii].x, rv[pp * NCP + ii].y};
-                dst[1] = u32x2{rv[pp * NCP + ii].z, rv[pp * NCP + ii].w};
+                // (64 chunks further on: 512 / HD rows, whose permutation differs by an exclusive or, or 32 rows of V^T)
+                *reinterpret_cast<u32x4*>(tile + (k_to ^ T::k_step(ii)) + pp * T::PAGE + ii * 1024) = rk[pp * NCP + ii];
+                *reinterpret_cast<u32x4*>(tile + v_put + pp * T::PAGE + ii * 1024) = rv[pp * NCP + ii];
             }
         const bool last = kb + 32 >= k_end;
-        if (have_n && !n_ready && (kb > k_begin || last)) {
-            nu = attn_unit_from(en0, en1);
-            total_n = nu.L + nu.nn;
-            k_begin_n = nu.part * a.part_keys;
-            k_end_n = min(total_n, k_begin_n + a.part_keys);
-            kbase_n = a.kc + (size_t)nu.j * 16 * HD;
-            vbase_n = a.vc + (size_t)nu.j * HD * 16;
-            my_page_n = safe_page_lane(a.block_table + (size_t)nu.b * a.max_blocks, k_begin_n + 16 * lane, total_n,
-                                       a.max_blocks, a.n_blocks);
-            n_ready = true;
+        const bool last_page = last || ((kb + 32 - k_begin) & 1023) == 0;   // my_page ends with this sub-tile
+        if (!n_ready && (last_page || ((kb - k_begin) & 1023) != 0)) {
+            const int k_more = k_begin + ((kb - k_begin) & ~1023) + 1024;
+            if (k_more < k_end) {
+                my_page_n = safe_page_lane(a.block_table + (size_t)cu.b * a.max_blocks, k_more + 16 * lane, total, a.max_blocks,
+                                           a.n_blocks);
+                n_ready = true;
+            } else if (have_n) {
+                nu = attn_unit_from(en0, en1);
+                total_n = nu.L + nu.nn;
+                k_begin_n = nu.part * a.part_keys;
+                k_end_n = min(total_n, k_begin_n + a.part_keys);
+                kbase_n = a.kc + (size_t)nu.j * 16 * HD;
+                vbase_n = a.vc + (size_t)nu.j * HD * 16;
+                my_page_n = safe_page_lane(a.block_table + (size_t)nu.b * a.max_blocks, k_begin_n + 16 * lane, total_n,
+                                           a.max_blocks, a.n_blocks);
+                n_ready = true;
+            }
         }
-        if (!last) HS_W_FETCH(my_page, kbase_ptr, vbase_ptr, (kb + 32 - k_begin) >> 4)
-        else if (have_n) HS_W_FETCH(my_page_n, kbase_n, vbase_n, 0)
-        attn_subtile<HD>(sKw, sVw, qf, o, m_run, l_run, anc, kb, cu.L, total, a.scale_log2, half, l32);
+        if (!last) {
+            if (last_page) { my_page = my_page_n; n_ready = false; }
+            HS_W_FETCH(my_page, kbase_ptr, vbase_ptr, ((kb + 32 - k_begin) >> 4) & 63)
+        } else if (have_n) HS_W_FETCH(my_page_n, kbase_n, vbase_n, 0)
+        attn_subtile<HD>(tile, qf, o, m_run, l_run, anc, kb, cu.L, total, a.scale_log2, half, l32);
         kb += 32;
         if (last) {
             store_partial<HD>(o, m_run, l_run, a.part_o, a.part_ml, cu.r0, 0, cu.nn * G, G, a.hq, cu.j, a.max_parts, cu.part,
@@ -405,184 +454,207 @@ __device__ inline void attn_wave_stream(const AttnArgs& a, const int4* __restric
 #undef HS_W_FETCH
 }
 
-// One partition of one (sequence, KV head) by the WORKGROUP (R > 32): 128-key tiles shared by the four wavefronts, the
-// unit's 32-row tiles (un.rt0 .. un.rt0 + 3) dealt to them round-robin, one tile of register prefetch.  (RTW row
-// tiles per wavefront; the launcher instantiates RTW = 1.)
-template <int HD, int RTW, int NLIVE>
-__device__ inline void attn_unit_wg_n(const AttnArgs& a, const AttnUnit& un, bf16_t* sK, bf16_t* sV, int tid) {
-    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32;
-    // keys per shared tile: with one row tile per wavefront there are registers for a 128-key tile in flight (twice
-    // the bytes on their way per workgroup), with two only for 64
-    constexpr int TILE = RTW == 1 ? 128 : 64;
-    constexpr int NCK = TILE * HD / 2048;   // 16-byte K chunks per thread and tile
-    const int lane = tid & 63, wave = tid >> 6;
-    const int half = lane >> 5, l32 = lane & 31;
-    const int b = un.b, j = un.j, part = un.part, r0 = un.r0, nn = un.nn, L = un.L;
-    const int total = L + nn;
-    const int G = a.hq / a.hkv;
-    const int R = nn * G;
-    const int nrt = (R + 31) >> 5;
-    const int k_begin = part * a.part_keys;
-    if (nn <= 0 || k_begin >= total) return;     // uniform over the workgroup
-    const int k_end = min(total, k_begin + a.part_keys);
-    const int32_t* bt = a.block_table + (size_t)b * a.max_blocks;
-    const bf16_t* kbase_ptr = a.kc + (size_t)j * 16 * HD;
-    const bf16_t* vbase_ptr = a.vc + (size_t)j * HD * 16;
-    const size_t page_stride = (size_t)a.hkv * 16 * HD;
-    // row tiles start at a unit-dependent wavefront so that two-tile sequences do not all use the same SIMDs
-    const int slot = (wave - (part + j + b)) & 3;
+// A word that is the same for the whole wavefront and that no kernel in flight writes, read through the scalar cache: its
+// wait does not touch the vector memory counter, on which the loads into LDS are counted.
+__device__ __forceinline__ int scalar_word(const int32_t* p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<unsigned long long>(p));
+}
+__device__ inline AttnUnit attn_unit_scalar(const int4* list, int it) {
+    const int32_t* p = reinterpret_cast<const int32_t*>(list + 2 * (size_t)it);
+    return {scalar_word(p), scalar_word(p + 1), scalar_word(p + 2), scalar_word(p + 3), scalar_word(p + 4), scalar_word(p + 5),
+            scalar_word(p + 6)};
+}
 
-    bf16x8 qf[RTW][NKS];
-    f32x16 o[RTW][NDT];
-    float m_run[RTW], l_run[RTW];
-    uint64_t anc[RTW];
-    bool rt_on[RTW];
+// Units with more than 32 query rows, taken by the WORKGROUP one after the other: a stream of 32-key sub-tiles through a ring
+// of RING of them in LDS, across unit boundaries.  Sub-tile s is a page's K or V^T block per wavefront, fetched straight into
+// LDS while s - 3 .. s - 1 are multiplied: no staging registers, no LDS writes and no wavefronts that only stage, and up
+// to 48 KB on their way per workgroup at any time (a 128-key tile at a time through registers, two barriers per tile, left
+// the memory system idle while it was written and multiplied).  One barrier per sub-tile: it says that the sub-tile has
+// landed (every wavefront has waited for its own part) and that its predecessor has been read, whose place in the ring is
+// then refilled.  The unit's 32-row tiles (rt0 .. rt0 + 3) are dealt round-robin, from a unit-dependent wavefront on so that
+// two-tile sequences do not all use the same SIMDs.
+// The next unit is claimed (`take`, zeroed by the list writers) shortly before the fetches reach it, not earlier: with
+// about as many units as workgroups an early claim gives some of them two and others none.
+// The keys run one sub-tile ahead of the values, so that the next sub-tile's first product is issued between this one's
+// exponentials: an instruction takes a wavefront about eight clocks, and there are two of them on a SIMD.
+// Steps with a 128-key tile at a time and now (us; launches of the first 45 -> 40): 64 sequences of 2560 tokens, a third of
+// them with 9 rows, four 1.5B layers 579 -> 560; 64 trees of 17 rows over 8192 keys, one 14B layer 1413 -> 1390, with
+// partitions of 2048 keys (hs_create) 1368; 256 sequences with a long tail of lengths, a 7B layer 1338 -> 1315.  What is
+// left there: without its arithmetic the 14B launch takes 400 us of 470, without its loads 250, and the partial results
+// (see hs_create) are 70 of the 400.
+template <int HD>
+__device__ inline void attn_wg_stream(const AttnArgs& a, const int4* __restrict__ list, int n_units, int first_idle,
+                                      int32_t* __restrict__ take, unsigned char* ring, int* s_item, int tid) {
+    using T = sub_tile<HD>;
+    constexpr int NKS = HD / 16, NDT = HD / 32, CPW = T::PAGE / 1024;   // 1 KB loads per wavefront and sub-tile
+    static_assert(ATT_RING == 4, "the wait counts below");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int G = a.hq / a.hkv;
+    const size_t page_bytes = (size_t)a.hkv * T::PAGE;
+
+    // the wavefront's share of a sub-tile: K (is_v = 0) or V^T of its page `pg`
+    const int is_v = wave & 1, pg = wave >> 1;
+    const unsigned ring_off = (unsigned)(size_t)(hs_gemm_detail::lds_ptr_t)ring + is_v * T::V + pg * T::PAGE;
+    unsigned from[CPW];   // where in the page's block a lane's 16 bytes of load i come from
 #pragma unroll
-    for (int t = 0; t < RTW; t++) {
-        int rt = un.rt0 + slot + 4 * t;
-        rt_on[t] = rt < nrt;
-        load_query_tile<HD>(a.q, a.anc_mask, r0, rt_on[t] ? rt : 0, rt_on[t] ? R : 0, G, a.hq, j, half, l32, qf[t], anc[t]);
+    for (int i = 0; i < CPW; i++) {
+        const int c = lane + 64 * i;
+        const int to_k = T::k_at(c / (HD / 8), c % (HD / 8)), to_v = T::v_at(c >> 1, c & 1);   // (both their own inverse)
+        from[i] = is_v ? to_v : to_k;
+    }
+
+    // Workgroups without wavefront units take the first ones by their number, all others what the counter hands out.
+    const int n_given = max(0, (int)gridDim.x - first_idle);
+    const bool more = n_units > n_given;
+    int it = (int)blockIdx.x - first_idle, par = 0;
+    if (it < 0) {
+        if (!more) return;
+        if (tid == 0) s_item[1] = n_given + atomicAdd(take, 1);
+        __syncthreads();   // (also: every private slice of the ring has been read)
+        it = __builtin_amdgcn_readfirstlane(s_item[1]);
+    }
+    if (it >= n_units) return;
+    AttnUnit cu = attn_unit_scalar(list, it), nu = cu;
+    bool have_n = false;
+
+    // fetches: the sub-tile after the last one asked for
+    const unsigned char* f_base = nullptr;
+    const int32_t* f_bt = nullptr;
+    int f_pos = 0, f_end = 0, f_total = 0, f_page = 0, f_slot = 0;
+    auto page_of = [&](int pos) __attribute__((always_inline)) {   // (see safe_page_lane)
+        const int p = pos >> 4;
+        const int page = scalar_word(f_bt + (pos < f_total && p < a.max_blocks ? p : 0));
+        return page >= 0 && page < a.n_blocks ? page : 0;
+    };
+    auto fetch_unit = [&](const AttnUnit& u) __attribute__((always_inline)) {
+        f_total = u.L + u.nn;
+        f_pos = u.part * a.part_keys;
+        f_end = min(f_total, f_pos + a.part_keys);
+        f_bt = a.block_table + (size_t)u.b * a.max_blocks;
+        f_base = reinterpret_cast<const unsigned char*>(is_v ? a.vc : a.kc) + (size_t)u.j * T::PAGE;
+        f_page = page_of(f_pos + 16 * pg);
+    };
+    // asks for one sub-tile and looks up the page of the one after it; false at the unit's end
+    auto fetch = [&]() __attribute__((always_inline)) {
+        if (f_pos >= f_end) return false;
+        const unsigned char* src = f_base + (size_t)f_page * page_bytes;
+        const unsigned dst = ring_off + f_slot * T::BYTES;
+#pragma unroll
+        for (int i = 0; i < CPW; i++) hs_gemm_detail::load_to_lds_16_stream(src, from[i], dst + i * 1024);
+        f_slot = (f_slot + 1) & (ATT_RING - 1);
+        f_pos += 32;
+        if (f_pos < f_end) f_page = page_of(f_pos + 16 * pg);
+        return true;
+    };
+    fetch_unit(cu);
+    int ahead = 0;   // sub-tiles asked for and not yet waited for
+    while (ahead < ATT_RING - 1 && fetch()) ahead++;
+    bool f_in_next = false;
+    int slot = 0;
+    for (;;) {
+        const int total = cu.L + cu.nn, R = cu.nn * G, nrt = (R + 31) >> 5;
+        const int k_begin = cu.part * a.part_keys, k_end = min(total, k_begin + a.part_keys);
+        const int my_rt = cu.rt0 + ((wave - (cu.part + cu.j + cu.b)) & 3);
+        const bool computes = my_rt < nrt;
+        const int k_put = max(k_begin, k_begin + ((k_end - k_begin - 1) & ~31) - 96);   // the claim is handed round here
+        const int k_claim = k_put - 64;                                                // ... and made here (or before the first)
+        int claim = 0;
+        if (more && k_claim < k_begin && tid == 0) claim = n_given + atomicAdd(take, 1);
+        bf16x8 qf[NKS];
+        uint64_t anc;
+        f32x16 o[NDT];
+        float m_run = -INFINITY, l_run = 0.f;
+        load_query_tile<HD>(a.q, a.anc_mask, cu.r0, computes ? my_rt : 0, computes ? R : 0, G, a.hq, cu.j, half, l32, qf, anc);
 #pragma unroll
         for (int dt = 0; dt < NDT; dt++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) o[t][dt][e] = 0.f;
-        m_run[t] = -INFINITY;
-        l_run[t] = 0.f;
-    }
-
-    // Staging.  A tile of TILE keys = TILE/16 pages, each 2*HD 16-byte chunks of K and as many of V^T.  A wavefront
-    // stages a run of whole pages.  With four live row tiles (NLIVE = 4) every wavefront stages a quarter of the
-    // tile; in a unit with fewer (a sequence of 33..96 query rows per KV head, or the last tile group of a longer
-    // one) the wavefronts without a row tile do nothing but stage, and take most of the pages off the ones that
-    // compute: loads, address arithmetic and LDS writes leave the instruction streams that carry the softmax and
-    // the MFMAs.  The two kinds of wavefront run separate loops (so that the staging registers of the one and the
-    // accumulators of the other do not add up) with the same two barriers per tile.
-    //   pages per tile = TILE/16 = 8:   4 live tiles (or 1): 2 pages each;  3: 1 each + 5;  2: 1 each + 3 + 3
-    // NLIVE = 4: every wavefront stages a quarter; NLIVE = 2: two or three live tiles (n_live), one routine for both.
-    constexpr int NPG = TILE / 16;
-    constexpr int PC = NLIVE == 4 ? NPG / 4 : NPG / 8;                            // pages of a computing wavefront
-    constexpr int PI = NLIVE == 4 ? 1 : NPG - 3 * PC;                             // most pages of a staging-only one
-    constexpr int CPP = 2 * HD / 64;                                              // 64-lane chunk rows per page
-    const int n_live = NLIVE == 4 ? 4 : min(4, nrt - un.rt0);
-    const int npi = __builtin_amdgcn_readfirstlane(NLIVE == 4 ? 0 : (NPG - n_live * PC) / (4 - n_live));
-    const bool computes = slot < n_live;
-    const int page0 = __builtin_amdgcn_readfirstlane(computes ? slot * PC : n_live * PC + (slot - n_live) * npi);
-    // lane p: the page of the partition's keys 16 p .. 16 p + 15 (a partition has at most 64 pages); one vector
-    // load per unit instead of a scalar load per page and tile
-    const int my_page = safe_page_lane(bt, k_begin + 16 * lane, total, a.max_blocks, a.n_blocks);
-    // lane parts of the addresses: chunk row r of a page holds chunks 64 r .. 64 r + 63
-    const int lane_g = lane * 8;                                              // elements, global side
-    const int lane_k = (lane / (HD / 8)) * KS + (lane % (HD / 8)) * 8;        // sK: 64 / (HD/8) keys per chunk row
-    const int lane_v = (lane >> 1) * VS + (lane & 1) * 8;                     // sV: 32 dims per chunk row
-#define HS_G_FETCH(KB, NP, NPRT)   /* NP: compile-time bound, NPRT: the wavefront's pages (>= 3 when guarded) */  \
-    {                                                                                                             \
-        _Pragma("unroll") for (int pg = 0; pg < NP; pg++) {                                                       \
-            if (pg >= 3 && pg >= (NPRT)) break;                                                                   \
-            const size_t pofs = (size_t)__builtin_amdgcn_readlane(my_page, (((KB) - k_begin) >> 4) + page0 + pg) * page_stride; \
-            _Pragma("unroll") for (int r = 0; r < CPP; r++) {                                                     \
-                rk[pg * CPP + r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kbase_ptr + pofs + r * 512 + lane_g)); \
-                rv[pg * CPP + r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vbase_ptr + pofs + r * 512 + lane_g)); \
-            }                                                                                                     \
-        }                                                                                                         \
-    }
-#define HS_G_STAGE(NP, NPRT)                                                                                      \
-    {                                                                                                             \
-        bf16_t* pk = sK + page0 * 16 * KS + lane_k;                                                               \
-        bf16_t* pv = sV + page0 * HD * VS + lane_v;                                                               \
-        _Pragma("unroll") for (int pg = 0; pg < NP; pg++)                                                         \
-            _Pragma("unroll") for (int r = 0; r < CPP; r++) {                                                     \
-                if (pg >= 3 && pg >= (NPRT)) break;                                                     \
-                *reinterpret_cast<u32x4*>(pk + (pg * 16 + r * (512 / HD)) * KS) = rk[pg * CPP + r];               \
-                u32x2* dst = reinterpret_cast<u32x2*>(pv + (pg * HD + r * 32) * VS);                              \
-                dst[0] = u32x2{rv[pg * CPP + r].x, rv[pg * CPP + r].y};                                           \
-                dst[1] = u32x2{rv[pg * CPP + r].z, rv[pg * CPP + r].w};                                           \
-            }                                                                                                     \
-    }
-    if (!computes) {
-        // staging only: no row tile, nothing to store at the end
-        u32x4 rk[PI * CPP], rv[PI * CPP];
-        HS_G_FETCH(k_begin, PI, npi)
-        for (int kbase = k_begin; kbase < k_end; kbase += TILE) {
-            __syncthreads();  // previous tile (or previous unit) fully consumed
-            HS_G_STAGE(PI, npi)
-            __syncthreads();
-            if (kbase + TILE < k_end) HS_G_FETCH(kbase + TILE, PI, npi)
-        }
-        return;
-    }
-    u32x4 rk[PC * CPP], rv[PC * CPP];
-    HS_G_FETCH(k_begin, PC, PC)
-    for (int kbase = k_begin; kbase < k_end; kbase += TILE) {
-        __syncthreads();  // previous tile (or previous unit) fully consumed
-        HS_G_STAGE(PC, PC)
-        __syncthreads();
-        if (kbase + TILE < k_end) HS_G_FETCH(kbase + TILE, PC, PC)
+            for (int e = 0; e < 16; e++) o[dt][e] = 0.f;
+        // (waited for here: inside the loop the wait would be for every load in flight, each time round)
 #pragma unroll
-        for (int sub = 0; sub < TILE / 32; sub++) {
-            const int kb = kbase + 32 * sub;
-            if (kb >= k_end) break;
-#pragma unroll
-            for (int t = 0; t < RTW; t++) {
-                if (!rt_on[t]) continue;
-                attn_subtile<HD>(sK + sub * 32 * KS, sV + sub * 2 * HD * VS, qf[t], o[t], m_run[t], l_run[t], anc[t],
-                                 kb, L, total, a.scale_log2, half, l32);
+        for (int ks = 0; ks < NKS; ks++) asm volatile("" : "+v"(qf[ks]));
+        asm volatile("" : "+v"(anc));
+        // waits for the wavefront's own part of the sub-tile at the head of what it asked for (what was asked for later may
+        // still be on its way), then for everybody's
+        auto landed = [&](bool take_one) __attribute__((always_inline)) {
+            if (take_one) {
+                ahead--;
+                if (ahead >= 2) HS_WAIT_VMCNT(2 * CPW);
+                else if (ahead == 1) HS_WAIT_VMCNT(CPW);
+                else HS_WAIT_VMCNT(0);
             }
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        };
+        landed(!is_v);        // the first keys
+        while (ahead < ATT_RING - 1 && fetch()) ahead++;
+        f32x16 sc = {};
+        if (computes) {
+            bf16x8 ka[NKS];
+            load_keys<HD>(ring + slot * T::BYTES, ka, half, l32);
+            sc = scores<HD>(ka, qf);
         }
-    }
-#undef HS_G_STAGE
-#undef HS_G_FETCH
+        for (int kb = k_begin; kb < k_end; kb += 32) {
+            if (more && kb == k_put && tid == 0) s_item[par] = claim;
+            landed(is_v || kb + 32 < k_end);     // this sub-tile's values, the next one's keys
+            if (more && kb == k_claim && tid == 0) claim = n_given + atomicAdd(take, 1);
+            if (more && kb == k_put) {
+                const int n = __builtin_amdgcn_readfirstlane(s_item[par]);
+                have_n = n < n_units;
+                if (have_n) nu = attn_unit_scalar(list, n);
+                par ^= 1;
+            }
+            if (f_pos >= f_end && have_n && !f_in_next && kb >= k_put) {
+                fetch_unit(nu);
+                f_in_next = true;
+            }
+            while (ahead < ATT_RING - 1 && fetch()) ahead++;
+            if (computes) {
+                bf16x8 ka[NKS], pb[2], va[2 * NDT];
+                load_keys<HD>(ring + ((slot + 1) & (ATT_RING - 1)) * T::BYTES, ka, half, l32);
 #pragma unroll
-    for (int t = 0; t < RTW; t++) {
-        if (!rt_on[t]) continue;
-        store_partial<HD>(o[t], m_run[t], l_run[t], a.part_o, a.part_ml, r0, un.rt0 + slot + 4 * t, R, G, a.hq, j,
-                          a.max_parts, part, half, l32);
+                for (int i = 0; i < 2 * NDT; i++) va[i] = load_values<HD>(ring + slot * T::BYTES, i, half, l32);
+                take_maximum<HD>(sc, o, m_run, l_run, anc, kb, cu.L, total, a.scale_log2, half);
+                const f32x16 next = scores<HD>(ka, qf);     // (of the last sub-tile: of whatever lies there, not used)
+                probabilities(sc, m_run, l_run, a.scale_log2, pb);
+#pragma unroll
+                for (int i = 0; i < 2 * NDT; i++)
+                    o[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pb[i / NDT], o[i % NDT], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < NKS; i++) {             // a product, its share of the exponentials
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x402, 64 / NKS, 0);
+                }
+                sc = next;
+            }
+            slot = (slot + 1) & (ATT_RING - 1);
+        }
+        if (computes)
+            store_partial<HD>(o, m_run, l_run, a.part_o, a.part_ml, cu.r0, my_rt, R, G, a.hq, cu.j, a.max_parts, cu.part, half,
+                              l32);
+        if (!have_n) break;
+        cu = nu;
+        have_n = f_in_next = false;   // (the fetches got into it at the latest with its predecessor's last sub-tile)
     }
 }
 
-// The unit's number of live row tiles (1..4; a group of four tiles per unit) selects the staging split.
-template <int HD, int RTW>
-__device__ inline void attn_unit_wg(const AttnArgs& a, const AttnUnit& un, bf16_t* sK, bf16_t* sV, int tid) {
-    const int nrt = (un.nn * (a.hq / a.hkv) + 31) >> 5;
-    const int n_live = RTW == 1 ? min(4, nrt - un.rt0) : 4;
-    if (n_live == 3 || n_live == 2) attn_unit_wg_n<HD, RTW, 2>(a, un, sK, sV, tid);
-    else attn_unit_wg_n<HD, RTW, 4>(a, un, sK, sV, tid);   // also a single live tile: everyone stages a quarter
-}
-
-// Persistent launch: exactly as many workgroups as the chip holds at once.  First every wavefront streams its share
+// Persistent launch: exactly as many workgroups as are resident at once.  First every wavefront streams its share
 // of the wavefront units (wavefront w of workgroup g: units 4 g + w, 4 g + w + 4 gridDim.x, ... -- dealt out
 // statically, so that nothing but K/V tiles is ever waited for); then the workgroups take the workgroup units one by
-// one through a counter (`take`, zeroed by the list kernel).  These are short -- four wavefronts share one partition
-// -- and fill the ragged end of the first phase: a workgroup that had less to stream takes more of them.  The claim
-// for the next unit is issued before the current one is computed.  No workgroup is launched for work that does not
+// one through a counter.  These are short -- four wavefronts share one partition -- and fill the ragged end of the first
+// phase: a workgroup that had less to stream takes more of them.  No workgroup is launched for work that does not
 // exist, and which workgroup computes a unit has no influence on the unit's result.
-template <int HD, int RTW>
-__global__ __launch_bounds__(256, (RTW == 1 ? 2 : 1)) void attn_verify_mfma(AttnArgs a, const int32_t* __restrict__ work,
-                                                                            int32_t* __restrict__ take,
-                                                                            const int4* __restrict__ list_a,
-                                                                            const int4* __restrict__ list_b) {
-    constexpr int KS = HD + 8;        // sK row stride (bf16)
-    constexpr int VS = 20;            // sV row stride (bf16): 16 tokens + pad, 40 bytes
-    // 128 keys of K and 8 pages of V^T: four private 32-key slices (wavefront units) or tiles of 64 keys shared by
-    // the workgroup (workgroup units)
-    __shared__ __attribute__((aligned(16))) bf16_t sK[128 * KS];
-    __shared__ __attribute__((aligned(16))) bf16_t sV[8 * HD * VS];
+template <int HD>
+__global__ __launch_bounds__(256, 2) void attn_verify_mfma(AttnArgs a, const int32_t* __restrict__ work,
+                                                           int32_t* __restrict__ take, const int4* __restrict__ list_a,
+                                                           const int4* __restrict__ list_b) {
+    // four private sub-tiles (wavefront units) or the ring of them shared by the workgroup (workgroup units)
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[ATT_RING * sub_tile<HD>::BYTES];
     __shared__ int s_item[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_a = work[0], n_b = work[1];
-    attn_wave_stream<HD>(a, list_b, n_b, blockIdx.x * 4 + wave, gridDim.x * 4, sK + wave * 32 * KS,
-                         sV + wave * 2 * HD * VS, lane);
+    attn_wave_stream<HD>(a, list_b, n_b, blockIdx.x * 4 + wave, gridDim.x * 4, ring + wave * sub_tile<HD>::BYTES, lane);
     if (n_a == 0) return;
-    if (tid == 0) s_item[0] = atomicAdd(take, 1);
-    __syncthreads();   // also: every private slice is consumed before shared tiles are written
-    int it = s_item[0], slot = 0;
-    while (it < n_a) {
-        if (tid == 0) s_item[slot ^ 1] = atomicAdd(take, 1);
-        const AttnUnit un = attn_unit_from(list_a[2 * it], list_a[2 * it + 1]);
-        attn_unit_wg<HD, RTW>(a, un, sK, sV, tid);
-        __syncthreads();
-        slot ^= 1;
-        it = s_item[slot];
-    }
+    attn_wg_stream<HD>(a, list_a, n_a, (n_b + 3) / 4, take, ring, s_item, tid);
 }
 
 // Prefill of a chunk of consecutive tokens per sequence (KV recomputation of a resumed rollout): token i of the chunk
@@ -837,7 +909,7 @@ __global__ __launch_bounds__(64) void attn_verify_plain(
     if (lane + 64 < hd) plain_st(op + lane + 64, (double)(o1 / l));
 }
 
-template <int HD, int RTW>
+template <int HD>
 void launch_mfma(const hs_ctx* ctx, int layer, size_t layer_off, const hs_kv_cache* cache, const hs_seq_state* seq,
                  const hs_step* step, const bf16_t* q, hipStream_t st) {
     const hs_model_desc& d = ctx->desc;
@@ -865,13 +937,13 @@ void launch_mfma(const hs_ctx* ctx, int layer, size_t layer_off, const hs_kv_cac
     static int per_cu = 0;
     if (per_cu == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)attn_verify_mfma<HD, RTW>, 256, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)attn_verify_mfma<HD>, 256, 0) != hipSuccess ||
             n < 1)
             n = 1;
         per_cu = n;
     }
     dim3 grid(ctx->n_cu * per_cu);
-    hipLaunchKernelGGL((attn_verify_mfma<HD, RTW>), grid, dim3(256), 0, st, a, work, work + 2 + layer, list_a, list_b);
+    hipLaunchKernelGGL((attn_verify_mfma<HD>), grid, dim3(256), 0, st, a, work, work + 2 + layer, list_a, list_b);
 }
 
 }  // namespace
@@ -900,8 +972,8 @@ void hs_launch_attention(const hs_ctx* ctx, int layer, const hs_kv_cache* cache,
     const bf16_t* q = (const bf16_t*)q_any;
     // one row tile per wavefront, two workgroups per compute unit, whatever the longest draft: a sequence with more
     // than 128 query rows per KV head comes as several units (see hs_worklist.h)
-    if (d.head_dim == 128) launch_mfma<128, 1>(ctx, layer, layer_off, cache, seq, step, q, st);
-    else launch_mfma<64, 1>(ctx, layer, layer_off, cache, seq, step, q, st);
+    if (d.head_dim == 128) launch_mfma<128>(ctx, layer, layer_off, cache, seq, step, q, st);
+    else launch_mfma<64>(ctx, layer, layer_off, cache, seq, step, q, st);
 }
 
 size_t hs_attention_max_units(const hs_ctx* ctx) {

@@ -109,50 +109,53 @@ __device__ __forceinline__ float block_max_f32(float v, float* red) {
 //
 // A decision at a node needs the node's largest logit and the sum of exp((logit - largest) / T) over the vocabulary:
 // some 20 operations, most of them fp64, for each of up to 152064 tokens, which is what bounds this path.  The walk from
-// node to node is a chain, but the sums do not depend on it: a first launch computes them for all rows side by side, cut
+// node to node is a chain, but the sums of different nodes are independent: they are computed by launches of their own, cut
 // into slices of SLICE tokens (a workgroup keeps a slice in registers, so every logit is read once), and the walk that
-// follows only combines the slices of the rows it visits.  64 trees of 17 rows over 152064 tokens: 0.16 to 0.2 ms for the sums
-// (3 to 4 TB/s of logits) and 0.03 ms for the walk; with everything in one workgroup per sequence, two passes over the
-// vocabulary per visited node and one lane that walked 594 tokens at the end, it was 2.6 to 3.4 ms.  Slices of 8192
+// follows only combines the slices of the rows it visits.  64 trees of 17 rows over 152064 tokens: 0.15 ms for the sums
+// of all rows (4.3 TB/s of logits) and 0.025 ms for the walk; with everything in one workgroup per sequence, two passes over
+// the vocabulary per visited node and one lane that walked 594 tokens at the end, it was 2.6 to 3.4 ms.  Slices of 8192
 // tokens took 5 % longer (twice the registers, half the wavefronts).
-// With very many rows most of them are never visited: beyond STATS_ALL_ROWS only the roots and their children are
-// computed ahead (2048 rows of 152064 tokens take 0.4 ms, about what the walk needs for six rows by itself), and the
-// walk computes the rest of what it visits.
+// Most rows of a large batch are never visited: a walk leaves its tree where a draft is rejected.  So the sums of many rows
+// come in stages: the roots; then, time and again, a small kernel takes every walk as far as the sums go and says what the
+// next launch sums for it: the node reached and the ones below it, 2, 4, 8 ... levels at a time, as fewer and fewer walks
+// are still under way.
 // Another rejection-sampling call of the context may run at the same time on another stream, with rows of its own and the
-// same place in the workspace.  So every sum carries a word made of itself and the number of the call that wrote it; the
-// walk takes what carries its own call's number and computes anything else itself, into LDS.
+// same place in the workspace.  So every sum and plan carries a word made of itself and the number of the call that wrote
+// it.  Where a stage finds anything but its own call's, it sums all nodes of its sequence (a call replayed from a graph has
+// the number of its earlier replays: nothing that is visited may be left over from those); where the last walk does, it
+// computes the sums itself, into LDS.
 constexpr int SLICE = HS_REJECT_SLICE, PER = SLICE / 256;   // tokens of a slice; of a slice, per thread
-constexpr int STATS_ALL_ROWS = 2048;
 
-__device__ __forceinline__ bool stats_ahead(int m, int pos, int root_pos) { return m <= STATS_ALL_ROWS || pos - root_pos <= 1; }
-
-// exp((l - ref) / T) in fp64 for l <= ref, with c = 16 / (T ln 2): (l - ref) c = n + f, |f| <= 1/2, and the result is
-// 2^(n >> 4) tab[n & 15] exp(f ln2/16), tab[j] = 2^(j/16) -- the table method of P. T. P. Tang (ACM TOMS 15, 1989) -- the
-// last factor by its Taylor series to the seventh power (remainder 1.3e-18).  15 fp64 operations against about 30 of the
+// exp((l - ref) / T) in fp64 for l <= ref, with c = 32 / (T ln 2): (l - ref) c = n + f, |f| <= 1/2, and the result is
+// 2^(n >> 5) tab[n & 31] exp(f ln2/32), tab[j] = 2^(j/32) -- the table method of P. T. P. Tang (ACM TOMS 15, 1989) -- the
+// last factor by its Taylor series to the sixth power (remainder 3.4e-18).  14 fp64 operations against about 30 of the
 // library's exp, and the sums are bound by them.  Error: c is a rounded product of a rounded constant, 2^-52 |x| of the
-// result x = (l - ref) / T, plus 2 ulp for the factors.  The sixteen table entries cover the 32 LDS banks once: no lookup
-// conflicts with another.  Differences below -746 T, -inf among them, are taken as -746 T, where the result is
-// 0; a NaN comes out as such a value, too, so callers look for NaNs themselves.
-// (The clamp is on the fp64 difference: at a low temperature -746 T is less than an fp32 logit resolves.)
+// result x = (l - ref) / T, plus 2 ulp for the factors.  The table's entries cover the 64 LDS banks once: no lookup
+// conflicts with another.  Differences below `low` are taken as that; a NaN comes out as such a value, too, so callers look
+// for NaNs themselves.  (The clamp is on the fp64 difference: at a low temperature it is less than an fp32 logit resolves.)
 struct exp_scale { double low, c; };
-__device__ __forceinline__ exp_scale make_scale(double inv_temp) { return {-746.0 / inv_temp, inv_temp * 23.083120654223414}; }
-__device__ __forceinline__ double exp_diff(float l, float ref, const exp_scale& k, const double* tab) {
+__device__ __forceinline__ exp_scale make_scale(double inv_temp, double least) { return {-least / inv_temp, inv_temp * 46.16624130844683}; }
+struct exp_parts { int n; double p; };     // 2^(n/32) p
+__device__ __forceinline__ exp_parts exp_split(float l, float ref, const exp_scale& k) {
     const double d = fmax((double)l - (double)ref, k.low);
     const double t = __builtin_fma(d, k.c, 6755399441055744.0);      // + 1.5 2^52: n in the low bits
-    const int n = __double2loint(t);
     const double f = __builtin_fma(d, k.c, -(t - 6755399441055744.0));
-    double p = 5.682086126528621e-14;
-    p = __builtin_fma(p, f, 9.181219573844438e-12);
-    p = __builtin_fma(p, f, 1.2715871950558131e-09);
-    p = __builtin_fma(p, f, 1.467610032291943e-07);
-    p = __builtin_fma(p, f, 1.3550807779497457e-05);
-    p = __builtin_fma(p, f, 0.0009383847928089872);
-    p = __builtin_fma(p, f, 0.04332169878499658);
-    p = __builtin_fma(p, f, 1.0);
-    return __builtin_amdgcn_ldexp(p * tab[n & 15], n >> 4);
+    double p = 1.4345655584131934e-13;
+    p = __builtin_fma(p, f, 3.973709984549416e-11);
+    p = __builtin_fma(p, f, 9.172562701824643e-09);
+    p = __builtin_fma(p, f, 1.693850972437182e-06);
+    p = __builtin_fma(p, f, 0.0002345961982022468);
+    p = __builtin_fma(p, f, 0.02166084939249829);
+    return {__double2loint(t), __builtin_fma(p, f, 1.0)};
+}
+// With a clamp at -746 T, -inf among what it takes, the result there is 0.
+__device__ __forceinline__ exp_scale exact_scale(double inv_temp) { return make_scale(inv_temp, 746.0); }
+__device__ __forceinline__ double exp_diff(float l, float ref, const exp_scale& k, const double* tab) {
+    const exp_parts e = exp_split(l, ref, k);
+    return __builtin_amdgcn_ldexp(e.p * tab[e.n & 31], e.n >> 5);
 }
 __device__ __forceinline__ void fill_exp_table(double* tab) {
-    if (threadIdx.x < 16) tab[threadIdx.x] = exp2((double)threadIdx.x * 0.0625);
+    if (threadIdx.x < 32) tab[threadIdx.x] = exp2((double)threadIdx.x * 0.03125);
     __syncthreads();
 }
 
@@ -178,18 +181,45 @@ __device__ __forceinline__ void load_slice(const float* __restrict__ lg, int voc
     }
 }
 
-// Sum of exp((logit - ref) / T) over a thread's logits; excluded ones (-inf) add nothing, a NaN makes it NaN.
+// Sum of exp((logit - ref) / T) over a thread's logits; a NaN makes it NaN.
+__device__ __forceinline__ double check_sum(const float (&v)[PER], float ref, double s) {
+    bool nan = ref == INFINITY;
+#pragma unroll
+    for (int j = 0; j < PER; j++) nan |= __builtin_isnan(v[j]);
+    return nan ? NAN : ref != -INFINITY ? s : 0.0;
+}
+// Excluded ones (-inf) add nothing.
 __device__ __forceinline__ double sum_weights(const float (&v)[PER], float ref, double inv_temp, const double* tab) {
-    const exp_scale k = make_scale(inv_temp);
+    const exp_scale k = exact_scale(inv_temp);
     double s = 0.0;
-    unsigned worst = 0u;
+#pragma unroll
+    for (int j = 0; j < PER; j++) s += exp_diff(v[j], ref, k, tab);
+    return check_sum(v, ref, s);
+}
+// The same where ref is the largest logit of a slice, so that the slice's sum is at least 1 and weights of e^-700 don't
+// show in it: excluded ones add that much, and a weight's power of two is an addition to its exponent.
+__device__ __forceinline__ double sum_slice(const float (&v)[PER], float largest, double inv_temp, const double* tab) {
+    const exp_scale k = make_scale(inv_temp, 700.0);
+    double s = 0.0;
 #pragma unroll
     for (int j = 0; j < PER; j++) {
-        s += exp_diff(v[j], ref, k, tab);
-        worst = max(worst, __float_as_uint(v[j]) << 1);
+        const exp_parts e = exp_split(v[j], largest, k);
+        const double t = tab[e.n & 31];
+        s = __builtin_fma(__hiloint2double(__double2hiint(t) + ((e.n & ~31) << 15), __double2loint(t)), e.p, s);
     }
-    return ref == -INFINITY && worst <= 0xFF000000u ? 0.0 : worst > 0xFF000000u || ref == INFINITY ? NAN : s;
+    return check_sum(v, largest, s);
 }
+
+// The sums come in stages from so many megabytes of logits on, by the hint or, of contexts with two candidates, by the
+// limits (trees of 17 rows over 152064 tokens, all rows at once against stages: 16 sequences, 165 MB, 64.5 against 67.7 us;
+// 24, 79 against 71; 32, 105 against 81; 64, 177 against 121; where nearly all drafts are accepted 176 against 127).
+// Chains mostly have far fewer rows than the limits allow (64 chains of 9 rows: 104 against 108; 64 sequences of one row, 26
+// against 46), so there the limits only speak from the second figure on, where stages cost little against all the rows
+// that there might be.
+#ifndef HS_REJECT_STAGED_MB
+#define HS_REJECT_STAGED_MB 200
+#define HS_REJECT_STAGED_UNKNOWN_MB 1200
+#endif
 
 // Largest logit and sum of one slice, relative to that largest logit, by a workgroup of 256 threads.
 // A slice in which every token is excluded (-inf) has the sum 0; a NaN anywhere makes the sum NaN.
@@ -201,7 +231,7 @@ __device__ __forceinline__ slice_stat slice_stats(const float (&v)[PER], double 
 #pragma unroll
     for (int j = 0; j < PER; j++) mx = fmaxf(mx, v[j]);
     mx = block_max_f32(mx, redf);
-    const double s = block_sum_f64(sum_weights(v, mx, inv_temp, tab), redd);
+    const double s = block_sum_f64(sum_slice(v, mx, inv_temp, tab), redd);
     // (the same in every lane: in scalar registers from here on)
     return {__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(mx))),
             __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(s)), __builtin_amdgcn_readfirstlane(__double2loint(s)))};
@@ -229,35 +259,187 @@ __device__ __forceinline__ bool get_stat(const hs_reject_stat* src, uint32_t cal
     return take_stat(*reinterpret_cast<const uint4*>(src), call, v);
 }
 
-// grid (sequences, slices, row split): a workgroup takes rows blockIdx.z, blockIdx.z + gridDim.z, ... of its sequence,
-// the next row's logits on their way while it sums the current one's.
-__global__ __launch_bounds__(256, 5) void reject_stats_kernel(const int32_t* __restrict__ row_off,
-                                                            const int32_t* __restrict__ pos,
-                                                            const float* __restrict__ logits, int vocab, int batch,
-                                                            double inv_temp, uint32_t call,
-                                                            hs_reject_stat* __restrict__ stats) {
-    __shared__ double tab[16];
+// A row's largest logit and sum, put together by half a wavefront from its slices: slice(s, v) gets one, false if it
+// cannot be used.
+template <typename Slice>
+__device__ __forceinline__ bool row_total(Slice slice, int n_slices, double inv_temp, int lane, float& mx, double& z) {
+    bool ok = true;
+    slice_stat v;
+    mx = -INFINITY;
+    for (int s = lane & 31; s < n_slices; s += 32) { ok &= slice(s, v); mx = fmaxf(mx, v.m); }
+    mx = wave_max_f32<32>(mx);
+    z = 0.0;
+    for (int s = lane & 31; s < n_slices; s += 32) { ok &= slice(s, v); z += v.s * exp(((double)v.m - (double)mx) * inv_temp); }
+    z = wave_sum_f64<32>(z);
+    return (__ballot(ok) >> (lane & 32) & 0xFFFFFFFFull) == 0xFFFFFFFFull;
+}
+
+// What a walk may ask of a sequence's nodes, a node per lane: parent, token, position and the token's logit at the parent.
+struct node_lanes { int par, tok, pos; float lg; };
+__device__ __forceinline__ node_lanes load_nodes(int r0, int nn, int vocab, const int32_t* __restrict__ tok,
+                                                 const int32_t* __restrict__ parent, const int32_t* __restrict__ pos,
+                                                 const float* __restrict__ logits, int lane) {
+    node_lanes n = {-2, 0, pos[r0], -INFINITY};
+    if (lane < nn) {
+        n.par = parent[r0 + lane];
+        n.tok = tok[r0 + lane];
+        n.pos = pos[r0 + lane];
+        // (a drafted id outside the vocabulary has no logit: it is a token of weight 0, rejected like any other)
+        if (lane > 0 && n.par >= 0 && n.par < nn && n.tok >= 0 && n.tok < vocab)
+            n.lg = logits[(size_t)(r0 + n.par) * vocab + n.tok];
+    }
+    return n;
+}
+
+// The decision at node cur, whose largest logit is mx and whose sum z, by a wavefront: its children are tried in node order.
+// Returns the accepted one or -1; lane q < nrej holds the q-th rejected token.
+__device__ __forceinline__ int try_children(const node_lanes& n, int cur, int nn, float mx, double z, double inv_temp,
+                                            uint64_t seed, uint64_t sid, int lane, int& nrej, int& rej) {
+    const bool child = lane > 0 && lane < nn && n.par == cur;
+    const double my_w = child ? exp(((double)n.lg - (double)mx) * inv_temp) : 0.0;
+    const uint32_t position = (uint32_t)(__shfl(n.pos, cur) + 1);
+    int next = -1, tried = 0;
+    double zr = z;
+    for (unsigned long long todo = __ballot(child); todo && next < 0; todo &= todo - 1) {
+        const int q = __ffsll(todo) - 1;
+        const int t = __shfl(n.tok, q);
+        double w = __hiloint2double(__shfl(__double2hiint(my_w), q), __shfl(__double2loint(my_w), q));
+        if (__any(lane < nrej && rej == t)) w = 0.0;
+        const double u = uniform01(seed, sid, position, (uint32_t)tried);
+        if (u < w / zr) {
+            next = q;
+        } else if (nrej < 8) {
+            if (lane == nrej) rej = t;
+            nrej++;
+            zr -= w;
+        }
+        tried++;
+    }
+    return next;
+}
+
+// Where a sequence's walk stands between two stages (node cur, a drafts accepted), and the nodes that the next one sums: none
+// once the walk has ended.
+struct walk_plan { unsigned long long todo; int cur, a; };
+__device__ __forceinline__ uint4 pack_plan(const walk_plan& w, uint32_t call) {
+    uint4 u = make_uint4((uint32_t)w.todo, (uint32_t)(w.todo >> 32), (uint32_t)(w.cur | w.a << 8), 0u);
+    uint32_t h = u.x * 0x9E3779B1u;
+    h = (h ^ (h >> 15)) + u.y;
+    h *= 0x85EBCA6Bu;
+    h = (h ^ (h >> 13)) + u.z;
+    h *= 0xC2B2AE35u;
+    u.w = h ^ (h >> 16) ^ call;
+    return u;
+}
+// (read by one thread for the workgroup: another call may be writing here, and barriers depend on what it says)
+__device__ __forceinline__ bool get_plan(const uint4* src, uint32_t call, walk_plan& w) {
+    __shared__ uint4 s_plan;
+    if (threadIdx.x == 0) s_plan = *src;
+    __syncthreads();
+    const uint4 u = s_plan;
+    w = {(unsigned long long)u.y << 32 | u.x, (int)(u.z & 255u), (int)(u.z >> 8 & 255u)};
+    return u.w == pack_plan(w, call).w && u.z <= 0xFFFFu;
+}
+
+// Node cur and what lies at most levels - 1 below it, a bit per node.
+__device__ __forceinline__ unsigned long long nodes_below(const node_lanes& n, int cur, int nn, int levels, int lane) {
+    unsigned long long in = 1ull << cur;
+    for (int l = 1; l < levels; l++) {
+        const unsigned long long more = in | __ballot(lane > 0 && lane < nn && n.par >= 0 && n.par < nn && (in >> (n.par & 63) & 1ull));
+        if (more == in) break;
+        in = more;
+    }
+    return in;
+}
+
+struct reject_stage_args {
+    const int32_t *row_off, *tok, *parent, *pos;
+    const float* logits;
+    int batch, vocab, n_slices, k_stride;
+    const uint64_t* seq_id;
+    double inv_temp;
+    uint64_t seed;
+    uint32_t call;
+    hs_reject_stat* stats;
+    uint4* plan;          // per sequence
+    int all_rows;         // up to so many rows the first stage sums all of them
+};
+
+__device__ __forceinline__ unsigned long long node_bits(int nn) { return nn < 64 ? (1ull << nn) - 1 : ~0ull; }
+
+// grid (sequences, slices, node split): a workgroup sums a slice of the nodes number blockIdx.z, blockIdx.z + gridDim.z,
+// ... of those that its stage computes, the next one's logits on their way while it sums the current one's.
+__global__ __launch_bounds__(256, 5) void reject_stats_kernel(reject_stage_args p, int first) {
+    __shared__ double tab[32];
+    const int b = blockIdx.x, n_slices = p.n_slices, slice = blockIdx.y;
+    const int r0 = p.row_off[b], nn = min(p.row_off[b + 1] - r0, HS_MAX_NODES);
+    if (nn <= 0) return;
+    unsigned long long todo = node_bits(nn);
+    if (first) {
+        if (p.row_off[p.batch] > p.all_rows) todo = 1ull;
+    } else {
+        walk_plan w;
+        if (get_plan(p.plan + b, p.call, w)) todo &= w.todo;
+    }
+    for (int q = 0; q < (int)blockIdx.z; q++) todo &= todo - 1;
+    todo = (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(todo >> 32)) << 32 | __builtin_amdgcn_readfirstlane((unsigned)todo);
+    if (!todo) return;
     fill_exp_table(tab);
-    const int b = blockIdx.x, n_slices = gridDim.y, slice = blockIdx.y, m = row_off[batch];
-    const int r0 = row_off[b], r1 = row_off[b + 1];
-    const bool vec = (vocab & 3) == 0 && ((unsigned long long)logits & 15ull) == 0;
-    auto next_row = [&](int r) {      // the first row from r on that is computed ahead
-        while (r < r1 && !stats_ahead(m, pos[r], pos[r0])) r += gridDim.z;
-        return r;
-    };
-    int r = next_row(r0 + blockIdx.z);
-    if (r >= r1) return;
+    const bool vec = (p.vocab & 3) == 0 && ((unsigned long long)p.logits & 15ull) == 0;
+    int i = __ffsll(todo) - 1;
     float v[PER], w[PER];
-    load_slice(logits + (size_t)r * vocab, vocab, slice, vec, v);
-    while (r < r1) {
-        const int rn = next_row(r + gridDim.z);
-        if (rn < r1) load_slice(logits + (size_t)rn * vocab, vocab, slice, vec, w);
-        const slice_stat sum = slice_stats(v, inv_temp, tab);
-        if (threadIdx.x == 0) put_stat(stats + (size_t)r * n_slices + slice, sum, call);
+    load_slice(p.logits + (size_t)(r0 + i) * p.vocab, p.vocab, slice, vec, v);
+    while (todo) {
+        for (int q = 0; q < (int)gridDim.z; q++) todo &= todo - 1;
+        const int next = __ffsll(todo) - 1;
+        if (todo) load_slice(p.logits + (size_t)(r0 + next) * p.vocab, p.vocab, slice, vec, w);
+        const slice_stat sum = slice_stats(v, p.inv_temp, tab);
+        if (threadIdx.x == 0) put_stat(p.stats + (size_t)(r0 + i) * n_slices + slice, sum, p.call);
 #pragma unroll
         for (int j = 0; j < PER; j++) v[j] = w[j];
-        r = rn;
+        i = next;
     }
+}
+
+// Between two stages: a workgroup per sequence takes its walk through the nodes that have been summed and plans the `levels`
+// from where it arrives.
+__global__ __launch_bounds__(256) void reject_plan_kernel(reject_stage_args p, int first, int levels) {
+    __shared__ float node_max[HS_MAX_NODES];
+    __shared__ double node_sum[HS_MAX_NODES];
+    __shared__ int node_ok[HS_MAX_NODES];
+    const int b = blockIdx.x, n_slices = p.n_slices, lane = threadIdx.x & 63;
+    const int r0 = p.row_off[b], nn = min(p.row_off[b + 1] - r0, HS_MAX_NODES);
+    if (nn <= 0) return;
+    walk_plan w = {1ull, 0, 0};
+    bool known = true;
+    if (first) { if (p.row_off[p.batch] <= p.all_rows) w.todo = 0ull; }
+    else known = get_plan(p.plan + b, p.call, w);
+    if (!known) w = {node_bits(nn), 0, 0};
+    else if (w.todo == node_bits(nn) && nn > 1) w.todo = 0ull;   // (everything has been summed)
+    else if (w.todo) {
+        const node_lanes n = load_nodes(r0, nn, p.vocab, p.tok, p.parent, p.pos, p.logits, lane);
+        for (int i = threadIdx.x >> 5; i < nn; i += 8) {
+            if (!(w.todo >> i & 1ull)) continue;
+            const hs_reject_stat* st = p.stats + (size_t)(r0 + i) * n_slices;
+            float mx;
+            double z;
+            const bool ok = row_total([&](int s, slice_stat& v) __attribute__((always_inline)) { return get_stat(st + s, p.call, v); },
+                                      n_slices, p.inv_temp, lane, mx, z);
+            if ((lane & 31) == 0) { node_max[i] = mx; node_sum[i] = z; node_ok[i] = ok; }
+        }
+        __syncthreads();
+        const uint64_t sid = p.seq_id[b];
+        bool ended = false;
+        while (!ended && known && (w.todo >> w.cur & 1ull)) {      // (a child's number need not be above its parent's,
+            known = node_ok[w.cur];                                //  but a walk of k_stride steps is over)
+            int nrej = 0, rej = -1;
+            const int next = try_children(n, w.cur, nn, node_max[w.cur], node_sum[w.cur], p.inv_temp, p.seed, sid, lane, nrej, rej);
+            if (next >= 0 && w.a + 1 < p.k_stride) { w.cur = next; w.a++; }
+            else ended = true;
+        }
+        w.todo = !known ? node_bits(nn) : ended ? 0ull : nodes_below(n, w.cur, nn, levels, lane);
+    }
+    if (threadIdx.x == 0) p.plan[b] = pack_plan(w, p.call);
 }
 
 // Sum over the lanes up to and including this one, in lane order by a fixed tree.
@@ -273,7 +455,7 @@ __device__ __forceinline__ double wave_prefix_f64(double v, int lane) {
 // Rejection sampling of one sequence by its workgroup (nn > 0).  The four wavefronts take every decision redundantly:
 // same values, same order, no exchange.
 __device__ __forceinline__ void accept_rejection_seq(
-    int b, int r0, int nn, int m_rows, int vocab, const int32_t* __restrict__ tok,
+    int b, int r0, int nn, int vocab, const int32_t* __restrict__ tok,
     const int32_t* __restrict__ parent, const int32_t* __restrict__ pos, const float* __restrict__ logits,
     const hs_reject_stat* __restrict__ stats, int n_slices, uint32_t call,
     const uint64_t* __restrict__ seq_id, double inv_temp, uint64_t seed, int k_stride,
@@ -283,7 +465,7 @@ __device__ __forceinline__ void accept_rejection_seq(
     slice_stat* own = reinterpret_cast<slice_stat*>(dyn_lds);   // [n_slices]: the sums of the node at hand
     __shared__ double wave_tot[4];
     __shared__ int s_first, s_last, s_pick;
-    __shared__ double tab[16];
+    __shared__ double tab[32];
     __shared__ float node_max[HS_MAX_NODES];
     __shared__ double node_sum[HS_MAX_NODES];
     __shared__ int node_ok[HS_MAX_NODES];
@@ -291,45 +473,18 @@ __device__ __forceinline__ void accept_rejection_seq(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t sid = seq_id[b];
     const bool vec = (vocab & 3) == 0 && ((unsigned long long)logits & 15ull) == 0;
-    const int root_pos = pos[r0];
     nn = min(nn, HS_MAX_NODES);   // (a draft tree has no more: hs_create)
-    // a drafted id outside the vocabulary has no logit: it is a token of weight 0, rejected like any other
     auto in_vocab = [&](int t) { return t >= 0 && t < vocab; };
-    // a row's largest logit and sum, put together by half a wavefront from its slices: slice(s, v) gets one, false if it
-    // cannot be used
-    auto row_total = [&](auto slice, float& mx, double& z) __attribute__((always_inline)) {
-        bool ok = true;
-        slice_stat v;
-        mx = -INFINITY;
-        for (int s = lane & 31; s < n_slices; s += 32) { ok &= slice(s, v); mx = fmaxf(mx, v.m); }
-        mx = wave_max_f32<32>(mx);
-        z = 0.0;
-        for (int s = lane & 31; s < n_slices; s += 32) { ok &= slice(s, v); z += v.s * exp(((double)v.m - (double)mx) * inv_temp); }
-        z = wave_sum_f64<32>(z);
-        return (__ballot(ok) >> (lane & 32) & 0xFFFFFFFFull) == 0xFFFFFFFFull;
-    };
-    // Everything that the walk may ask of the nodes, fetched side by side instead of node after node: lane i holds node i's
-    // parent, position, token and that token's logit at the parent.
+    // Everything that the walk may ask of the nodes, fetched side by side instead of node after node.
     for (int i = tid >> 5; i < nn; i += 8) {
-        bool ok = stats_ahead(m_rows, pos[r0 + i], root_pos);
-        if (ok) {
-            const hs_reject_stat* st = stats + (size_t)(r0 + i) * n_slices;
-            float mx;
-            double z;
-            ok = row_total([&](int s, slice_stat& v) __attribute__((always_inline)) { return get_stat(st + s, call, v); }, mx, z);
-            if ((lane & 31) == 0) { node_max[i] = mx; node_sum[i] = z; }
-        }
-        if ((lane & 31) == 0) node_ok[i] = ok;
+        const hs_reject_stat* st = stats + (size_t)(r0 + i) * n_slices;
+        float mx;
+        double z;
+        const bool ok = row_total([&](int s, slice_stat& v) __attribute__((always_inline)) { return get_stat(st + s, call, v); },
+                                  n_slices, inv_temp, lane, mx, z);
+        if ((lane & 31) == 0) { node_max[i] = mx; node_sum[i] = z; node_ok[i] = ok; }
     }
-    int pre_par = -2, pre_tok = 0, pre_pos = root_pos;
-    float pre_lg = -INFINITY;
-    if (lane < nn) {
-        pre_par = parent[r0 + lane];
-        pre_tok = tok[r0 + lane];
-        pre_pos = pos[r0 + lane];
-        if (lane > 0 && pre_par >= 0 && pre_par < nn && in_vocab(pre_tok))
-            pre_lg = logits[(size_t)(r0 + pre_par) * vocab + pre_tok];
-    }
+    const node_lanes n = load_nodes(r0, nn, vocab, tok, parent, pos, logits, lane);
     __syncthreads();
     int cur = 0, a = 0;
     if (tid == 0) path_row[(size_t)b * k_stride] = 0;
@@ -386,33 +541,13 @@ __device__ __forceinline__ void accept_rejection_seq(
             }
             if (any) __syncthreads();
         }
-        const uint32_t position = (uint32_t)(__shfl(pre_pos, cur) + 1);
         if (!last) {
             double z;
-            if (all) row_total([&](int s, slice_stat& v) __attribute__((always_inline)) { v = own[s]; return true; }, mx, z);
+            if (all) row_total([&](int s, slice_stat& v) __attribute__((always_inline)) { v = own[s]; return true; }, n_slices, inv_temp, lane, mx, z);
             else { mx = node_max[cur]; z = node_sum[cur]; }
-            // children in node order, a node per lane
-            const bool child = lane > 0 && lane < nn && pre_par == cur;
-            const double my_w = child ? exp(((double)pre_lg - (double)mx) * inv_temp) : 0.0;
-            int next = -1, next_tok = 0, tried = 0;
-            double zr = z;
-            for (unsigned long long todo = __ballot(child); todo && next < 0; todo &= todo - 1) {
-                const int q = __ffsll(todo) - 1;
-                const int t = __shfl(pre_tok, q);
-                double w = __hiloint2double(__shfl(__double2hiint(my_w), q), __shfl(__double2loint(my_w), q));
-                if (__any(lane < nrej && rej == t)) w = 0.0;
-                const double u = uniform01(seed, sid, position, (uint32_t)tried);
-                if (u < w / zr) {
-                    next = q;
-                    next_tok = t;
-                } else if (nrej < 8) {
-                    if (lane == nrej) rej = t;
-                    nrej++;
-                    zr -= w;
-                }
-                tried++;
-            }
+            const int next = try_children(n, cur, nn, mx, z, inv_temp, seed, sid, lane, nrej, rej);
             if (next >= 0 && a + 1 < k_stride) {
+                const int next_tok = __shfl(n.tok, next);
                 if (tid == 0) {
                     out_tok[(size_t)b * k_stride + a] = next_tok;
                     path_row[(size_t)b * k_stride + a + 1] = next;
@@ -428,6 +563,7 @@ __device__ __forceinline__ void accept_rejection_seq(
             continue;
         }
         // Final sample from the remaining distribution, in token-id order.
+        const uint32_t position = (uint32_t)(__shfl(n.pos, cur) + 1);
         auto slice_weight = [&](int s) __attribute__((always_inline)) { return s < n_slices ? own[s].s * exp(((double)own[s].m - (double)mx) * inv_temp) : 0.0; };
         double zt = 0.0;
         for (int s0 = 0; s0 < n_slices; s0 += 64) {
@@ -485,7 +621,7 @@ __device__ __forceinline__ void accept_rejection_seq(
                 bool in = lane < PER && i < vocab;
                 for (int q = 0; q < nrej; q++) in = in && __shfl(rej, q) != i;
                 const float l = in ? lg[i] : -INFINITY;
-                const double w = exp_diff(l, mx, make_scale(inv_temp), tab);
+                const double w = exp_diff(l, mx, exact_scale(inv_temp), tab);
                 const double cum = __hiloint2double(__shfl(__double2hiint(base), owner & 63), __shfl(__double2loint(base), owner & 63)) +
                                    wave_prefix_f64(w, lane);
                 const unsigned long long nz = __ballot(w > 0.0), hit = __ballot(w > 0.0 && cum >= target);
@@ -640,7 +776,7 @@ __global__ __launch_bounds__(256, REJECT ? 1 : 7) void accept_commit_kernel(acce
                 __syncthreads();   // the walk reads argmax[] written by the other wavefronts
             }
             if (REJECT) {
-                accept_rejection_seq(b, r0, nn, p.row_off[p.batch], p.vocab, p.tok, p.parent, p.pos, p.logits,
+                accept_rejection_seq(b, r0, nn, p.vocab, p.tok, p.parent, p.pos, p.logits,
                                      p.stats, p.n_slices, p.call, p.seq_id, p.inv_temp, p.seed, p.k_stride, p.accept_len,
                                      p.n_out, p.out_tok, p.path_row);
             } else if (tid == 0) {
@@ -666,6 +802,32 @@ __global__ __launch_bounds__(256) void philox_debug_kernel(const uint32_t* __res
     uint32_t o[4];
     philox4x32_10(ctr[4 * i], ctr[4 * i + 1], ctr[4 * i + 2], ctr[4 * i + 3], k0, k1, o);
     out[4 * i] = o[0]; out[4 * i + 1] = o[1]; out[4 * i + 2] = o[2]; out[4 * i + 3] = o[3];
+}
+
+// The sums of a rejection-sampling call.  rows_hint: an estimate of the number of rows, or 0 (no result depends on it).
+void launch_reject_stats(const hs_ctx* ctx, const accept_commit_args& a, int batch, int rows_hint, hs_reject_stat* stats, hipStream_t st) {
+    reject_stage_args p = {a.row_off, a.tok, a.parent, a.pos, a.logits, batch, a.vocab, a.n_slices, a.k_stride, a.seq_id,
+                           a.inv_temp, a.seed, a.call, stats, reinterpret_cast<uint4*>(ctx->ws + ctx->lay.reject_walk), 0};
+    const int depth = ctx->lim.k_max + 1, nodes = 1 + ctx->lim.c_max * ctx->lim.k_max;
+    const double row_mb = a.vocab * 4e-6;
+    double mb = (double)batch * nodes * row_mb;
+    if (rows_hint > 0) mb = std::min(mb, rows_hint * row_mb);
+    // enough workgroups to fill the chip: small batches split a sequence's rows, too
+    auto split = [&](int per_seq) { return dim3(batch, a.n_slices, std::max(1, std::min(2048 / (a.n_slices * batch), per_seq))); };
+    if (depth < 3 || mb < (rows_hint > 0 || ctx->lim.c_max > 1 ? HS_REJECT_STAGED_MB : HS_REJECT_STAGED_UNKNOWN_MB)) {
+        p.all_rows = INT32_MAX;
+        hipLaunchKernelGGL(reject_stats_kernel, split(nodes), dim3(256), 0, st, p, 1);
+        return;
+    }
+    p.all_rows = (int)(HS_REJECT_STAGED_MB / 2 / row_mb);
+    hipLaunchKernelGGL(reject_stats_kernel, split(1), dim3(256), 0, st, p, 1);
+    for (int done = 1, levels = 2; done < depth; done += levels, levels *= 2) {
+        if (depth - done - levels <= levels / 2) levels = depth - done;
+        hipLaunchKernelGGL(reject_plan_kernel, dim3(batch), dim3(256), 0, st, p, done == 1, levels);
+        dim3 grid = split(levels);
+        grid.z = std::max<int>(grid.z, std::min(levels, 4));     // (few walks are left)
+        hipLaunchKernelGGL(reject_stats_kernel, grid, dim3(256), 0, st, p, 0);
+    }
 }
 
 }  // namespace
@@ -706,12 +868,7 @@ void hs_launch_accept_commit(const hs_ctx* ctx, const hs_accept_args* args, cons
         p.stats = stats;
         p.n_slices = hs_reject_slices(d.vocab);
         p.call = ctx->reject_calls.fetch_add(1, std::memory_order_relaxed);
-        // enough workgroups to fill the chip: small batches split a sequence's rows, too
-        const int nodes = 1 + ctx->lim.c_max * ctx->lim.k_max;
-        int split = 2048 / (p.n_slices * p.batch);
-        split = split < 1 ? 1 : (split > nodes ? nodes : split);
-        hipLaunchKernelGGL(reject_stats_kernel, dim3(p.batch, p.n_slices, split), dim3(256), 0, st, p.row_off, p.pos,
-                           logits, p.vocab, p.batch, p.inv_temp, p.call, stats);
+        launch_reject_stats(ctx, p, seq->batch, step->rows_hint, stats, st);
     }
     p.accept_len = step->accept_len; p.n_out = step->n_out; p.out_tok = step->out_tok; p.path_row = step->path_row;
     if (policy) {

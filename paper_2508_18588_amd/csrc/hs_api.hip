@@ -55,6 +55,7 @@ void layout_workspace(hs_ctx* ctx) {
     w.pf_len = take((size_t)l.max_batch * 4);
     w.att_work = take((size_t)(2 + d.n_layers) * 4);
     w.att_list = take(2 * hs_attention_max_units(ctx) * 32);
+    w.reject_walk = take((size_t)l.max_batch * 16);
     w.reject_stats = take(M * (size_t)hs_reject_slices(d.vocab) * sizeof(hs_reject_stat));
     w.total = off;
 }

@@ -26,7 +26,7 @@ struct alignas(16) hs_reject_stat { float m; uint32_t check; double s; };
 static inline int hs_reject_slices(int vocab) { return (vocab + HS_REJECT_SLICE - 1) / HS_REJECT_SLICE; }
 
 struct hs_workspace_layout {
-    size_t x, xn, qkv, q, attn, act, part_o, part_ml, logits, logits_bytes, rowmax, draft_best, gemm_part, gemm_part_bytes, err, pf_len, att_work, att_list, reject_stats, total;
+    size_t x, xn, qkv, q, attn, act, part_o, part_ml, logits, logits_bytes, rowmax, draft_best, gemm_part, gemm_part_bytes, err, pf_len, att_work, att_list, reject_stats, reject_walk, total;
 };
 
 struct hs_ctx {

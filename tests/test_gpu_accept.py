@@ -229,8 +229,7 @@ def test_philox_words_equal_the_oracles_on_a_million_counters():
 def test_rejection_over_several_vocabulary_slices(toy, V, B, k, rows_big):
     """The sampler sums the vocabulary in slices of 4096 tokens: widths at a slice's edge, one that is not a multiple of 4
     (rows then are not 16-byte aligned), rejected tokens in the first, a middle and the last slice, whole slices masked
-    with -inf; and with more than 2048 rows the launch that computes sums ahead, which then covers the roots and their
-    children only.  Same logits, seed and ids as the oracle: the same decisions, unless the oracle's margin is below 1e-9."""
+    with -inf; and more than 2048 rows.  Same logits, seed and ids as the oracle: the same decisions, unless the oracle's margin is below 1e-9."""
     from paper_2508_18588_amd import HS_ACCEPT_REJECTION
     from paper_2508_18588_amd.runtime import Engine
     from hs_inputs import ModelShape
@@ -465,3 +464,74 @@ def test_overlapping_rejection_sampling_of_one_context_on_two_streams(toy):
 def hs_workspace_bytes_of(eng):
     from paper_2508_18588_amd import hs_workspace_bytes
     return hs_workspace_bytes(eng.ctx)
+
+
+@pytest.mark.parametrize("V,B,k,two", [(16401, 70, 31, True), (16400, 1000, 4, False)])
+def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, two):
+    """Many rows (here by the context's limits) are summed in stages, each for the nodes that the walks have reached: trees of
+    every depth from none to k, on which the walks end at every level.  The decisions are the oracle's (unless its
+    margin is below 1e-9) and those of one launch for all rows (which a hint of few rows asks for), also in a captured graph
+    replayed with other logits, and while another stream overwrites sums and states."""
+    from paper_2508_18588_amd import HS_ACCEPT_REJECTION
+    from paper_2508_18588_amd.runtime import Engine
+    from hs_inputs import ModelShape
+    shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
+    rng = np.random.default_rng(V)
+    eng = Engine(shape, make_weights(shape, 3), rope_table(64, 64), max_batch=B, k_max=k, c_max=2 if two else 1, max_len=80)
+    assert B * (1 + eng.c_max * k) * V * 4 >= 250e6
+    ids = rng.integers(0, 2 ** 62, B)
+    eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B, seq_ids=ids.astype(np.int64))
+    trees = random_trees(rng, B, k, V, two)
+    m = eng.set_rows([dict(tok=t["tok"], parent=t["parent"], pos=t["pos"]) for t in trees])
+    at = torch.tensor([(o + int(t["parent"][i])) * V + int(t["tok"][i])
+                       for t, o in zip(trees, np.cumsum([0] + [len(t["tok"]) for t in trees])) for i in range(1, len(t["tok"]))],
+                      device="cuda:0")
+    def logits(seed):
+        g = torch.Generator(device="cuda:0").manual_seed(seed)
+        eng.logits.copy_(torch.randn(eng.logits.shape, generator=g, device="cuda:0"))
+        eng.logits.view(-1)[at] = np.log(V) + 3.0 + torch.randn(len(at), generator=g, device="cuda:0")
+    def accept(hint):
+        eng.set_rows_hint(hint)
+        eng.accept(HS_ACCEPT_REJECTION, 1.0, 1234)
+    logits(1)
+    accept(0)
+    torch.cuda.synchronize()
+    want, lg, st, r, depths = results_of(eng.st), np_of(eng.logits[:m]), {n: np_of(v) for n, v in eng.st.items()}, 0, set()
+    for b, t in enumerate(trees):
+        n = len(t["tok"])
+        a, out, path, margin = oracle.accept_stochastic(t["tok"], t["parent"], t["pos"], lg[r:r + n].astype(np.float64), 1.0, 1234, int(ids[b]))
+        g = st["n_out"][b]
+        got = (int(st["accept_len"][b]), st["out_tok"][b, :g].tolist(), st["path_row"][b, :g].tolist())
+        assert got == (a, out.tolist(), path.tolist()) or margin < 1e-9, (b, got, a, out, path, margin)
+        depths.add(a)
+        r += n
+    assert depths >= set(range(min(k, 10)))
+    accept(1)
+    torch.cuda.synchronize()
+    live = lambda res: [(int(n), o[:n].tolist(), q[:n].tolist()) for n, o, q in zip(res[1], res[2], res[3])]
+    assert live(results_of(eng.st)) == live(want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        accept(0)
+    for seed in (2, 3, 1):
+        logits(seed)
+        accept(1)
+        torch.cuda.synchronize()
+        eager = live(results_of(eng.st))
+        eng.st["out_tok"].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert live(results_of(eng.st)) == eager
+    side = torch.cuda.Stream()
+    end = eng._ws_ptr - eng.workspace.data_ptr() + hs_workspace_bytes_of(eng)
+    slices = (V + 4095) // 4096
+    place = eng.workspace[end - eng.max_rows * slices * 16 - 32 * B - 512 & ~3:end & ~3].view(torch.int32)
+    for _ in range(10):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(40):
+                place.random_()
+        accept(0)
+        torch.cuda.synchronize()
+        assert live(results_of(eng.st)) == live(want)
+    eng.close()

@@ -35,7 +35,7 @@ def sources():
 def build(force: bool = True) -> str:
     """Compile every HIP source for gfx950 into libhistospec.so (in-tree)."""
     srcs = sources()
-    deps = srcs + [os.path.join(_CSRC, h) for h in ("hs_internal.h", "hs_gemm_common.h", "hs_worklist.h", "hs_lanes.h")] + [os.path.join(_ROOT, "include", "histospec.h")]
+    deps = srcs + [os.path.join(_CSRC, h) for h in ("hs_internal.h", "hs_gemm_common.h", "hs_gemm_stream.h", "hs_worklist.h", "hs_lanes.h")] + [os.path.join(_ROOT, "include", "histospec.h")]
     if not force and os.path.exists(LIB_PATH) and all(os.path.getmtime(LIB_PATH) >= os.path.getmtime(d) for d in deps):
         return LIB_PATH
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -19,27 +19,27 @@ __device__ __forceinline__ int swz(int r) { return (((r >> 1) & 3) << 1) | ((r >
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// 16 bytes per lane from global memory straight into LDS: lane i's data lands at LDS byte offset lds_off + 16 * i
-// (lds_off is wavefront-uniform and travels in M0).  Counted by vmcnt like any other load.  Issued as inline
+// 16 bytes per lane from global memory straight into LDS: lane i's data lands at LDS byte offset lds_off + add + 16 * i
+// (lds_off is wavefront-uniform, add a constant; their sum travels in M0).  Counted by vmcnt like any other load.  Issued as inline
 // assembly so that the compiler's wait-count bookkeeping does not see it: told about such a load it treats every
 // later LDS read as possibly returning out of order and waits for all of them at once, which serialises fragment
 // reads and matrix-core work; the kernels place the vmcnt waits for these loads themselves.  Any wait the compiler
 // inserts for its own loads can only be stricter than needed, because loads complete in issue order.
 // The source address is a wavefront-uniform base (scalar registers) plus a 32-bit unsigned byte offset per lane.
-__device__ __forceinline__ void load_to_lds_16(const unsigned char* base, unsigned off, unsigned lds_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+__device__ __forceinline__ __attribute__((always_inline)) void load_to_lds_16(const unsigned char* base, unsigned off, unsigned lds_off, const int add = 0) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
-                 : "s"(lds_off), "v"(off), "s"(base)
-                 : "memory", "m0");
+                 : "s"(lds_off), "v"(off), "s"(base), "i"(add)
+                 : "memory", "m0", "scc");
 }
 
 // The same for data that is read once per launch (the weight stream): non-temporal, so that it does not evict the
 // activation tile that every workgroup re-reads from L2.
-__device__ __forceinline__ void load_to_lds_16_stream(const unsigned char* base, unsigned off, unsigned lds_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+__device__ __forceinline__ __attribute__((always_inline)) void load_to_lds_16_stream(const unsigned char* base, unsigned off, unsigned lds_off, const int add = 0) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                  :
-                 : "s"(lds_off), "v"(off), "s"(base)
-                 : "memory", "m0");
+                 : "s"(lds_off), "v"(off), "s"(base), "i"(add)
+                 : "memory", "m0", "scc");
 }
 
 }  // namespace hs_gemm_detail

@@ -1,0 +1,605 @@
+// The bf16 MFMA GEMM of the projections:  C[M,N] (+)= A[M,K] . W[N,K]^T,  built for the row counts of a verify
+// step (a few hundred draft-tree rows) and run in row passes for more (prefill, wide drafts).
+//
+// At a verify step's row count a projection is bound by streaming its weights from HBM exactly once, with the
+// matrix cores needed at roughly half their rate just to keep up (220 rows: 220 flop per weight byte).  The kernel
+// is laid out around the weight stream:
+//   * One workgroup per (group of NU 32-row weight units, K chunk, row pass); unit and chunk counts are chosen by
+//     the host so that one round of workgroups covers the 256 compute units.  A workgroup holds all rows of its
+//     pass (up to 128*MT) against its weight slab, so with one pass every weight byte is fetched once.
+//   * Eight wavefronts, two per SIMD: row tile t (32 rows) belongs to wavefronts t % 4 and 4 + t % 4, the first of which
+//     multiplies it against the first half of the NU weight units, the second against the others.  A wavefront
+//     multiplies only the row tiles that exist (M is read on the device); its accumulators stay in registers for the
+//     whole chunk.
+//   * Tiles (64 deep in K) travel from global memory straight into LDS (global_load_lds_dwordx4) through an
+//     SA-stage activation ring and an SW-stage weight ring.
+//   * A wavefront issues one instruction at a time, about one per eight clocks when it is alone on its SIMD, and an MFMA
+//     takes 32: with four wavefronts (all units each, 28 instead of 36 KB of fragment reads per k-step at 220 rows) the
+//     200 instructions of a tile's 40 MFMAs were what a tile took.  With a second wavefront on the SIMD to issue from,
+//     every shape gains, those with few rows most (four 1.5B layers: 7 rows 320 -> 300 us, 264 rows 640 -> 605 us; a 7B
+//     layer with its attention at 220 rows 679 -> 662 us, prefill of 8 x 4096 tokens 21.6 -> 20.3 ms; with the choice of
+//     units below), same bits.
+//   * The loop is software-pipelined over k-steps of 16: the fragments of step s+1 are read while step s is multiplied,
+//     across tile boundaries, one by one behind single MFMAs, and the steady state carries no modulo arithmetic and as
+//     few guards as possible.  The tile hand-over (wait for the loads of the next tile, workgroup barrier, issue of new
+//     loads) sits before a tile's last k-step, after the last fragment read of the tile has been issued.
+//   * A read's or load's constant distances (weight unit, row tile, stage slot) lie in the instruction itself: a fragment is
+//     one ds_read, a load one scalar add (into m0), a nop and the load.  (With an address computation and a guard at each,
+//     a tile of the four-wavefront kernel was 302 instructions for its 64 MFMAs and took 1.15 times as long as the
+//     eight-wavefront one; at 188 it takes less.  The eight-wavefront one gained 1 %: LDS binds it.)
+//   * Four wavefronts (hs_gemm_wide.hip) of 4 x 4 tiles, 256 rows x 8 units per workgroup, for many rows: a fragment is
+//     used four times, not three or two and a half, so that an MFMA costs 0.75 instead of 1.07 KB through LDS, less of
+//     the chip's power and fewer rounds of workgroups.  7B gate/up at 4096 rows 942 -> 890 us (1250 TFLOP/s), at 2048 rows
+//     490 -> 446; down at 4096 674 -> 615.  Without its loads 816, without its MFMAs 628: at the clock that this load leaves
+//     the chip (1.4 to 1.5 GHz) the matrix cores bind it.
+//   * Passes of 64 rows and six activation stages (MT = 0) for up to 48 rows expected: with two, an activation tile was asked
+//     for one tile (a third of a microsecond) before its use.  7 rows of 1536, gate/up 15.4 -> 14.3 us, head 16.0 -> 14.7;
+//     12 rows of 3584, head of 16448 29.3 -> 25.9.  (Split K: chunks are too short, 9.2 -> 11.2; five units: 42.4 -> 44.3, the
+//     weight stream at 6.4 TB/s either way.)
+//   * What bounds it now: at up to 128 rows the weight stream (271 MB of gate/up weights in 50 us); at 220 rows LDS (184 KB a
+//     tile are 1440 clocks, its MFMAs 1280; without its loads the head takes 210 of 285 us, without its MFMAs 258; a
+//     deeper weight ring changes nothing), with a prologue and an epilogue that nothing overlaps.  A third activation stage made
+//     every such shape slower (71 -> 77 us), the row pitch of the operands (55 to 65 lines of 128 bytes) is worth 5 % either way.
+// SwiGLU pairs the gate and up rows of 16 output columns in one 32-row weight unit, so that both pre-activations of
+// a column meet in one MFMA tile (lanes c and c+16).
+#pragma once
+#include <algorithm>
+#include <type_traits>
+
+#include "hs_gemm_common.h"
+#include "hs_lanes.h"
+
+using namespace hs_gemm_detail;
+
+namespace {
+
+constexpr int TILE_BYTES = 32 * ROW_BYTES;  // a 32-row tile of either operand, 64 deep: 4 KB
+
+// A fragment at an LDS byte address.
+__device__ __forceinline__ bf16x8 lds_fragment(unsigned at) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(at);
+}
+
+// A pointer known to be the same in every lane, moved to scalar registers.
+__device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char* p) {
+    const unsigned long long v = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return (const unsigned char*)(((unsigned long long)hi << 32) | lo);
+}
+
+struct stream_args {
+    const unsigned char* A;
+    const unsigned char* wb[2];  // weight matrices (gate, up) or (W, W)
+    void* Cout;
+    float* part;
+    int M, m_max, N, K, n0, m0, kt0, kt1, chunk, group, n_groups;
+    int w_once;  // the launch reads every weight byte once (one row pass): non-temporal weight loads
+    int w_pre;   // the weight-only part of the prologue has been issued already (by the kernel, before M was known)
+};
+
+// Rows of a pass: 128 MT, or 64 (MT = 0).
+template <int MT>
+struct pass_shape {
+    static constexpr int ROWS = MT ? 128 * MT : 64, TILES = ROWS / 32;
+};
+
+// The weight units of a wavefront group: group 0 multiplies units 0 .. NU0-1, group 1 the others.
+template <int NU, int GRP>
+struct wave_units {
+    static constexpr int NU0 = (NU + 1) / 2, U0 = GRP ? NU0 : 0, N = GRP ? NU - NU0 : NU0;
+};
+
+// How the work of a workgroup lies on its WV wavefronts (8 or 4).  Two groups share the weight units; RG row groups share
+// the row tiles (tile t: row group t % RG), at most MI of them each.  Each wavefront fetches quarter `quad` (8 of 32 rows, a
+// 1 KB block) of weight units and row tiles: with eight wavefronts of its own group's units and of every second row
+// tile, with four of all.
+template <int NU, int MT, int GRP, int WV>
+struct wave_shape {
+    static constexpr int RG = WV / 2, MI = (pass_shape<MT>::TILES + RG - 1) / RG;
+    static constexpr int FETCH_U0 = WV == 8 ? wave_units<NU, GRP>::U0 : 0, FETCH_U = WV == 8 ? wave_units<NU, GRP>::N : NU;
+    static constexpr int FETCH_A = WV == 8 ? pass_shape<MT>::TILES / 2 : pass_shape<MT>::TILES;   // row tiles fetched ...
+    static constexpr int FETCH_A0 = WV == 8 ? GRP : 0, FETCH_AS = WV == 8 ? 2 : 1;                 // ... first, stride
+};
+
+// The 1 KB blocks of weight tile kt that a wavefront fetches, into stage kt % SW of the weight ring.  (A SwiGLU unit holds 16
+// gate rows then the 16 up rows of the same columns, so a wavefront's blocks are all gate rows -- quarters 0, 1 -- or all
+// up rows -- 2, 3.)
+template <int NU, int MT, int SA, int SW, int GRP, int WV>
+__device__ __forceinline__ void issue_weight_tile(const stream_args& p, const unsigned char* w_mine, unsigned smem_off,
+                                                  const unsigned (&w_off)[wave_shape<NU, MT, GRP, WV>::FETCH_U], int quad, int kt) {
+    constexpr int W_RING = SA * pass_shape<MT>::TILES * TILE_BYTES, W_STAGE = NU * TILE_BYTES;
+    const unsigned dst = smem_off + W_RING + (kt % SW) * W_STAGE + wave_shape<NU, MT, GRP, WV>::FETCH_U0 * TILE_BYTES + quad * 1024;
+    const unsigned char* base = w_mine + (size_t)kt * ROW_BYTES;
+#pragma unroll
+    for (int j = 0; j < wave_shape<NU, MT, GRP, WV>::FETCH_U; j++) {
+        if (WV == 8 && p.w_once) load_to_lds_16_stream(base, w_off[j], dst, j * 4096);
+        else load_to_lds_16(base, w_off[j], dst, j * 4096);
+    }
+}
+
+// One K chunk of one row pass for a wavefront of group GRP and row group rg that owns NMI live row tiles (0 = loads and
+// barriers only).
+template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int NMI, int WV>
+__device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char* smem, unsigned smem_off,
+                                             const unsigned (&w_off)[wave_shape<NU, MT, GRP, WV>::FETCH_U], int quad, int rg, int lane) {
+    using WS = wave_shape<NU, MT, GRP, WV>;
+    static_assert(SA >= 2 && SW > SA && (SA == 2 || (MT < 2 && WV == 8)), "the wait counts below");
+    constexpr int A_STAGE = pass_shape<MT>::TILES * TILE_BYTES, W_STAGE = NU * TILE_BYTES, W_RING = SA * A_STAGE;
+    constexpr int NUW = wave_units<NU, GRP>::N, U0 = wave_units<NU, GRP>::U0;
+    constexpr int NLW = WS::FETCH_U;   // 1 KB load instructions per weight tile and wavefront
+    constexpr int NSA = WS::FETCH_A;   // and at most this many per activation tile
+    constexpr int NM = NMI > 0 ? NMI : 1;
+    const int lrow = lane >> 3, lpos = lane & 7;
+    const int l32 = lane & 31, g = lane >> 5, fl = swz(l32);
+    const int frag_row = l32 * ROW_BYTES;
+    const unsigned a_chunk = (unsigned)((lpos ^ swz(8 * quad + lrow)) << 4);
+    const int a_row = p.m0 + 32 * WS::FETCH_A0 + 8 * quad + lrow;
+    const unsigned row_pitch = (unsigned)p.K * 2u;
+    // 8-row blocks of the activation tile this wavefront fetches, one per row tile FETCH_A0, FETCH_A0 + FETCH_AS, ...; blocks
+    // past the last row are not fetched.
+    constexpr int A_ROWS = 32 * WS::FETCH_AS, A_BYTES = WS::FETCH_AS * TILE_BYTES;
+    int n_a = 0;
+#pragma unroll
+    for (int l = 0; l < NSA; l++)
+        if (p.m0 + 32 * WS::FETCH_A0 + 8 * quad + A_ROWS * l < p.M) n_a = l + 1;
+    n_a = __builtin_amdgcn_readfirstlane(n_a);
+    unsigned a_off[NSA];
+#pragma unroll
+    for (int l = 0; l < NSA; l++) a_off[l] = (unsigned)min(a_row + A_ROWS * l, p.M - 1) * row_pitch + a_chunk;
+    const unsigned a_dst0 = smem_off + WS::FETCH_A0 * TILE_BYTES + quad * 1024;              // + stage + l * A_BYTES
+    const unsigned w_dst0 = smem_off + W_RING + WS::FETCH_U0 * TILE_BYTES + quad * 1024;     // + stage + j * 4096
+
+    auto issue_a = [&](int kt) {
+        const unsigned char* base = p.A + (size_t)kt * ROW_BYTES;
+#pragma unroll
+        for (int l = 0; l < NSA; l++)
+            if (l < n_a) load_to_lds_16(base, a_off[l], a_dst0 + (kt % SA) * A_STAGE, l * A_BYTES);
+    };
+    const unsigned char* w_mine = uniform_ptr((EPI == HS_EPI_SWIGLU_BF16 && quad >= 2) ? p.wb[1] : p.wb[0]);
+    auto issue_w = [&](int kt) { issue_weight_tile<NU, MT, SA, SW, GRP, WV>(p, w_mine, smem_off, w_off, quad, kt); };
+    // Hand-over number h (h < kt0 before the loop, then in the last quarter of tile h): first the activation tile h+SA,
+    // then the weight tile h+SW.  The issue order fixes the wait counts below.
+    auto issue_for = [&](int h) {
+        if (h + SA >= p.kt0 && h + SA < p.kt1) issue_a(h + SA);
+        if (h + SW >= p.kt0 && h + SW < p.kt1) issue_w(h + SW);
+    };
+    // Loads complete in issue order.  Tile t is awaited in tile t-1, when the hand-overs up to t-2 have been made.  Its
+    // activation part was issued at hand-over t-SA, its weight part at t-SW (earlier).  What may still be outstanding is
+    // what was issued after the activation part: the weight tiles of hand-overs t-SA to t-2 and the activation tiles of
+    // t-SA+1 to t-2, as far as there are such tiles.
+    auto wait_tile = [&](int t) {
+        int n = 0;
+#pragma unroll
+        for (int h = -SA; h <= -2; h++) {
+            if (t + h + SW < p.kt1) n += NLW;
+            if (h > -SA && t + h + SA < p.kt1) n += n_a;
+        }
+        switch (n) {   // (at most 5 x 3 + 4)
+#define HS_CASE(i) case i: HS_WAIT_VMCNT(i); break;
+            HS_CASE(1) HS_CASE(2) HS_CASE(3) HS_CASE(4) HS_CASE(5) HS_CASE(6) HS_CASE(7) HS_CASE(8) HS_CASE(9) HS_CASE(10)
+            HS_CASE(11) HS_CASE(12) HS_CASE(13) HS_CASE(14) HS_CASE(15) HS_CASE(16) HS_CASE(17) HS_CASE(18) HS_CASE(19)
+#undef HS_CASE
+            default: HS_WAIT_VMCNT(0);
+        }
+    };
+
+    f32x16 acc[NM][NUW];
+#pragma unroll
+    for (int i = 0; i < NM; i++)
+#pragma unroll
+        for (int j = 0; j < NUW; j++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+
+    // prologue: the hand-overs a longer-running loop would have made before tile kt0; of the last one only the
+    // activation part (its weight part goes out during the first half of tile kt0, see below)
+    // (its first SW - SA hand-overs carry weight tiles only: the kernel issues those itself before it knows M)
+#pragma unroll
+    for (int h = -SW; h < -1; h++)
+        if (h >= -SA || !p.w_pre) issue_for(p.kt0 + h);
+    wait_tile(p.kt0);
+    __builtin_amdgcn_s_barrier();
+    if (p.kt0 - 1 + SA < p.kt1) issue_a(p.kt0 - 1 + SA);
+
+    // Ring positions, kept incrementally: scalar instructions between MFMAs (a modulo, a guard, an address) are issued by
+    // the same wavefront that should issue the next MFMA.
+    int a_cur = (int)((unsigned)p.kt0 % SA) * A_STAGE;                   // stage of tile kt ...
+    int w_cur = (int)((unsigned)p.kt0 % SW) * W_STAGE;
+    int w_nxt = w_cur + W_STAGE == SW * W_STAGE ? 0 : w_cur + W_STAGE;   // ... and of tile kt+1
+    int w_prv = w_cur == 0 ? (SW - 1) * W_STAGE : w_cur - W_STAGE;       // stage of tile kt-1 = of tile kt-1+SW
+    const unsigned char* a_src = p.A + (size_t)(p.kt0 + SA) * ROW_BYTES;          // activation tile of hand-over kt
+    const unsigned char* w_src = w_mine + (size_t)(p.kt0 - 1 + SW) * ROW_BYTES;   // weight tile of hand-over kt-1
+
+    bf16x8 fa[2][NM], fb[2][NUW];
+    // Fragment r (weight units, then row tiles) of the k-step whose addresses are at_a / at_w: lane l reads tile row l%32,
+    // k-chunk 2 ks + l/32, at its swizzled position; units and row tiles are constant distances, within a read's offset.
+    unsigned at_ks[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) at_ks[ks] = smem_off + frag_row + (((2 * ks + g) ^ fl) << 4);
+    const int a_mine = rg * TILE_BYTES, w_mine_off = W_RING + U0 * TILE_BYTES;
+    auto frag = [&](int set, int r, unsigned at_a, unsigned at_w) __attribute__((always_inline)) {
+        if (r < NUW) fb[set][r < NUW ? r : 0] = lds_fragment(at_w + r * TILE_BYTES);
+        else fa[set][r >= NUW ? r - NUW : 0] = lds_fragment(at_a + WS::RG * (r - NUW) * TILE_BYTES);
+    };
+    // One k-step in a pinned order: behind each MFMA of the step that is in set KS % 2 come its share of the next step's
+    // fragment reads and of the NLD loads that `load(l)` issues.
+    // (a, w: the stages that the next step's fragments lie in; READ: there is a next step)
+    auto step = [&](auto ks_c, auto read_c, int a, int w, auto nld_c, auto load) __attribute__((always_inline)) {
+        constexpr int KS = decltype(ks_c)::value, NLD = decltype(nld_c)::value, NMF = NM * NUW, NR = NM + NUW;
+        constexpr int set = KS & 1, kr = (KS + 1) & 3;
+        constexpr bool READ = decltype(read_c)::value;
+        const unsigned at_a = at_ks[kr] + (unsigned)(a + a_mine), at_w = at_ks[kr] + (unsigned)(w + w_mine_off);
+#pragma unroll
+        for (int q = 0; q < NMF; q++) {
+            const int mi = q / NUW, ni = q % NUW;
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mi], fb[set][ni], acc[mi][ni], 0, 0, 0);
+            if (READ) {
+#pragma unroll
+                for (int r = q * NR / NMF; r < (q + 1) * NR / NMF; r++) frag(set ^ 1, r, at_a, at_w);
+            }
+#pragma unroll
+            for (int l = q * NLD / NMF; l < (q + 1) * NLD / NMF; l++) load(l);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto no_load = [](int) __attribute__((always_inline)) {};
+    if (NMI > 0) {
+#pragma unroll
+        for (int r = 0; r < NM + NUW; r++) frag(0, r, at_ks[0] + (unsigned)(a_cur + a_mine), at_ks[0] + (unsigned)(w_cur + w_mine_off));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    int kt = p.kt0;
+    // One tile of the k-loop.  k-steps 0 to 2, each reading the next step's fragments; meanwhile the weight blocks of
+    // hand-over kt-1 (tile kt-1+SW, into the stage that tile kt-1 left).
+    // Hand-over: every fragment read of tile kt has been issued; once they have returned (lgkmcnt) and all wavefronts have
+    // met, the activation stage of tile kt is free to be refilled.  Tile kt+1 must have landed: each wavefront waits for
+    // its own part before the barrier (a bare barrier: a fenced one would wait for the tiles in flight as well).
+    // k-step 3 then reads the first fragments of tile kt+1 and issues the activation blocks of this hand-over (tile
+    // kt+SA, into the stage of tile kt).
+    // The steady state (kt + SW < kt1: every load of both parts exists, the wait count is a constant) comes in two forms:
+    // G = 0 for a wavefront whose activation slots are all live (no guard at all), G = 2 with one guard per slot.  G = 1:
+    // the last tiles, with every load guarded.
+    auto tile = [&](auto g_c) __attribute__((always_inline)) {
+        constexpr int G = decltype(g_c)::value;
+        const bool w_on = G == 1 ? kt - 1 + SW < p.kt1 : true;
+        const unsigned w_dst = w_dst0 + w_prv, a_dst = a_dst0 + a_cur;
+        const int a_nxt = a_cur + A_STAGE == SA * A_STAGE ? 0 : a_cur + A_STAGE;   // stage of tile kt+1
+        auto load_w = [&](int l) __attribute__((always_inline)) {
+            if (w_on) {
+                if (WV == 8 && p.w_once) load_to_lds_16_stream(w_src, w_off[l], w_dst, l * 4096);
+                else load_to_lds_16(w_src, w_off[l], w_dst, l * 4096);
+            }
+        };
+        int na_eff = G == 0 ? NSA : G == 2 ? n_a : (kt + SA < p.kt1 ? n_a : 0);
+        if (G) asm volatile("" : "+s"(na_eff)); /* one scalar compare per slot, not a mask expression */
+        auto load_a = [&](int l) __attribute__((always_inline)) {
+            if (l < na_eff) load_to_lds_16(a_src, a_off[l], a_dst, l * A_BYTES);
+        };
+        if (NMI > 0) {
+            step(std::integral_constant<int, 0>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, NLW>{}, load_w);
+            step(std::integral_constant<int, 1>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, 0>{}, no_load);
+            step(std::integral_constant<int, 2>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, 0>{}, no_load);
+        } else {
+#pragma unroll
+            for (int l = 0; l < NLW; l++) load_w(l);
+        }
+        if (G == 1) wait_tile(kt + 1);
+        else if (SA == 2) HS_WAIT_VMCNT(NLW);
+        else if (G == 0) HS_WAIT_VMCNT((SA - 1) * NLW + (SA - 2) * NSA);
+        else if (NSA == 2 && n_a == 1) HS_WAIT_VMCNT((SA - 1) * NLW + (SA - 2));
+        else HS_WAIT_VMCNT((SA - 1) * NLW);
+        __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8)); /* lgkmcnt(0) */
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (NMI > 0) {
+            step(std::integral_constant<int, 3>{}, std::true_type{}, a_nxt, w_nxt, std::integral_constant<int, NSA>{}, load_a);
+        } else {
+#pragma unroll
+            for (int l = 0; l < NSA; l++) load_a(l);
+        }
+        a_cur = a_nxt;
+        w_prv = w_cur;
+        w_cur = w_nxt;
+        w_nxt = w_nxt + W_STAGE == SW * W_STAGE ? 0 : w_nxt + W_STAGE;
+        a_src += ROW_BYTES;
+        w_src += ROW_BYTES;
+    };
+    if (n_a == NSA) {
+        for (; kt + SW < p.kt1; kt++) tile(std::integral_constant<int, 0>{});
+    } else {
+        for (; kt + SW < p.kt1; kt++) tile(std::integral_constant<int, 2>{});
+    }
+    for (; kt + 1 < p.kt1; kt++) tile(std::integral_constant<int, 1>{});
+    // last tile of the chunk: nothing follows it
+    if (NMI > 0) {
+        step(std::integral_constant<int, 0>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, 0>{}, no_load);
+        step(std::integral_constant<int, 1>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, 0>{}, no_load);
+        step(std::integral_constant<int, 2>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, 0>{}, no_load);
+        step(std::integral_constant<int, 3>{}, std::false_type{}, 0, 0, std::integral_constant<int, 0>{}, no_load);
+    }
+
+    // (the lane number anew: values derived from it would otherwise stay in registers, or spill, through the whole loop)
+    int lane_e;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane_e));
+    // Epilogue.  Accumulator element e of a 32x32 tile: row 8*(e/4) + 4*(lane/32) + e%4, column lane%32.
+    if (EPI == HS_EPI_ROWMAX) {
+        // Each row's largest value among this workgroup's columns, as a key that orders by value and then by lower column:
+        // first over the lane's columns, then over the 32 lanes that hold the row, then over the two wavefronts that share
+        // it: every wavefront leaves its keys in LDS (every fragment has been read), a thread per row takes the larger.
+        // (152064 columns of K = 3584 at 220 and 2176 rows: one group after the other, with exchanges through the LDS unit,
+        // 310 and 2276 us; as it is 276 and 1987; four wavefronts with all units each, 295 and 2105.)
+        constexpr int ROWS = pass_shape<MT>::ROWS;
+        unsigned long long* keys = reinterpret_cast<unsigned long long*>(p.Cout);
+        unsigned long long* wave_keys = reinterpret_cast<unsigned long long*>(smem);   // [2][ROWS]
+        const int lr = 4 * (lane_e >> 5), lc = lane_e & 31;
+        __syncthreads();
+        if (NMI > 0) {
+#pragma unroll
+            for (int mi = 0; mi < NMI; mi++) {
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    unsigned long long key = 0ull;
+#pragma unroll
+                    for (int ni = 0; ni < NUW; ni++) {
+                        const int col = p.n0 + 32 * (U0 + ni) + lc;
+                        unsigned u = __float_as_uint(acc[mi][ni][e]);
+                        u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+                        const unsigned long long k2 = ((unsigned long long)u << 32) | (0xFFFFFFFFu - (unsigned)col);
+                        if (col < p.N && k2 > key) key = k2;
+                    }
+                    auto take = [&](unsigned lo, unsigned hi) __attribute__((always_inline)) {
+                        const unsigned long long other = ((unsigned long long)hi << 32) | lo;
+                        if (other > key) key = other;
+                    };
+                    take(lane_xor<16>((unsigned)key), lane_xor<16>((unsigned)(key >> 32)));
+                    take(lane_xor<8>((unsigned)key), lane_xor<8>((unsigned)(key >> 32)));
+                    take(lane_xor<4>((unsigned)key), lane_xor<4>((unsigned)(key >> 32)));
+                    take(lane_xor<2>((unsigned)key), lane_xor<2>((unsigned)(key >> 32)));
+                    take(lane_xor<1>((unsigned)key), lane_xor<1>((unsigned)(key >> 32)));
+                    __builtin_amdgcn_sched_barrier(0);   // (one row at a time: the accumulators leave few registers)
+                    if (lc == 0) wave_keys[GRP * ROWS + 32 * (rg + WS::RG * mi) + lr + 8 * (e >> 2) + (e & 3)] = key;
+                }
+            }
+        }
+        __syncthreads();
+        const int row = (GRP * WS::RG + rg) * 64 + lane_e;  // within the pass
+        if (row < ROWS && p.m0 + row < p.M) {
+            const unsigned long long k0 = wave_keys[row], k1 = wave_keys[ROWS + row];
+            keys[(size_t)(p.m0 + row) * p.n_groups + p.group] = k0 > k1 ? k0 : k1;
+        }
+        return;
+    }
+    if (NMI > 0) {
+        const int lr = 4 * (lane_e >> 5), lc = lane_e & 31;
+#pragma unroll
+        for (int mi = 0; mi < NMI; mi++) {
+            const int row0 = p.m0 + 32 * (rg + WS::RG * mi) + lr;
+            if (EPI == HS_EPI_SWIGLU_BF16) {
+                // Lanes c (gate) and c+16 (up) hold the two pre-activations of output column c.  Elements are taken
+                // in pairs: the gate lanes finish the row of element e and the up lanes the row of element e+1, so
+                // every lane computes an output.  One v_permlane16_swap does the exchange: it swaps the odd
+                // 16-lane rows of its first operand (element e: the up values) with the even rows of its second
+                // (element e+1: the gate values), after which the first holds every lane's gate and the second
+                // every lane's up.  (32-bit element offsets: the host checks that the output stays below 4 GiB.)
+                bf16_t* C = reinterpret_cast<bf16_t*>(p.Cout);
+                const bool up_lane = (lc & 16) != 0;
+                const int rbase = row0 + (up_lane ? 1 : 0);
+#pragma unroll
+                for (int ni = 0; ni < NUW; ni++) {
+                    const int col = p.n0 + 16 * (U0 + ni) + (lc & 15);
+#pragma unroll
+                    for (int e = 0; e < 16; e += 2) {
+                        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[mi][ni][e]),
+                                                                         __float_as_uint(acc[mi][ni][e + 1]), false, false);
+                        const float gate = __uint_as_float(sw[0]), up = __uint_as_float(sw[1]);
+                        const int row = rbase + 8 * (e >> 2) + (e & 3);
+                        if (col < p.N && row < p.M) {
+                            const float s = gate * __builtin_amdgcn_rcpf(1.f + __expf(-gate));
+                            C[(unsigned)row * (unsigned)p.N + (unsigned)col] = f32_to_bf16(s * up);
+                        }
+                    }
+                }
+            } else {
+                float* C = PARTIAL ? p.part + (size_t)p.chunk * p.m_max * p.N : reinterpret_cast<float*>(p.Cout);
+                // A row tile that lies wholly below M (all but the last one of a pass) is stored without row checks,
+                // through a wavefront-uniform row pointer plus a 32-bit lane offset.
+                const int tile_row = p.m0 + 32 * (rg + WS::RG * mi);
+                unsigned char* tile = reinterpret_cast<unsigned char*>(C + (size_t)tile_row * p.N);
+                __builtin_amdgcn_sched_barrier(0);
+                const unsigned lane_bytes = ((unsigned)lr * (unsigned)p.N + (unsigned)(p.n0 + 32 * U0 + lc)) * 4u;
+                if (tile_row + 32 <= p.M) {
+#pragma unroll
+                    for (int ni = 0; ni < NUW; ni++) {
+                        if (p.n0 + 32 * (U0 + ni) + lc >= p.N) continue;
+                        // (adding: all of a tile's loads before its first store -- element by element each load waited for
+                        // the one before it, 17 us of a launch with 16 rows)
+                        float old[16];
+                        if (!PARTIAL && EPI == HS_EPI_ADD_F32) {
+#pragma unroll
+                            for (int e = 0; e < 16; e++)
+                                old[e] = *reinterpret_cast<float*>(tile + (size_t)(8 * (e >> 2) + (e & 3)) * p.N * 4 +
+                                                                   (lane_bytes + 128u * ni));
+                        }
+#pragma unroll
+                        for (int e = 0; e < 16; e++) {
+                            unsigned char* rowp = tile + (size_t)(8 * (e >> 2) + (e & 3)) * p.N * 4;
+                            float* dst = reinterpret_cast<float*>(rowp + (lane_bytes + 128u * ni));
+                            if (!PARTIAL && EPI == HS_EPI_ADD_F32) *dst = old[e] + acc[mi][ni][e];
+                            else *dst = acc[mi][ni][e];
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int ni = 0; ni < NUW; ni++) {
+                        const int col = p.n0 + 32 * (U0 + ni) + lc;
+                        if (col >= p.N) continue;
+                        float old[16];
+                        if (!PARTIAL && EPI == HS_EPI_ADD_F32) {
+#pragma unroll
+                            for (int e = 0; e < 16; e++)   // (rows beyond M: the last row's element, not stored)
+                                old[e] = C[(size_t)min(row0 + 8 * (e >> 2) + (e & 3), p.M - 1) * p.N + col];
+                        }
+#pragma unroll
+                        for (int e = 0; e < 16; e++) {
+                            const int row = row0 + 8 * (e >> 2) + (e & 3);
+                            if (row < p.M) {
+                                float* dst = &C[(size_t)row * p.N + col];
+                                if (!PARTIAL && EPI == HS_EPI_ADD_F32) *dst = old[e] + acc[mi][ni][e];
+                                else *dst = acc[mi][ni][e];
+                            }
+                        }
+                    }
+                }
+            }
+        }
+    }
+}
+
+}  // namespace
+
+namespace {
+
+// What a wavefront of group GRP does: the row passes of its workgroup.
+template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int WV>
+__device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem, unsigned smem_off, int quad, int rg, int lane,
+                                             int pass, int n_pass) {
+    using WS = wave_shape<NU, MT, GRP, WV>;
+    // Weight loader geometry: instruction j of quarter w fills the 1 KB block of rows 8w..8w+7 of unit FETCH_U0 + j; lane i
+    // lands on row i/8, chunk position i%8 and therefore fetches chunk (i%8) ^ swz(row).  Rows beyond N are clamped to
+    // the last valid row: their products are computed and never stored.
+    // (32-bit byte offsets: the host checks that every operand stays below 4 GiB.)
+    const int lrow = lane >> 3, lpos = lane & 7;
+    unsigned w_off[WS::FETCH_U];
+#pragma unroll
+    for (int j = 0; j < WS::FETCH_U; j++) {
+        const int row = 8 * quad + lrow, unit = WS::FETCH_U0 + j;  // (row within the unit)
+        const int gn = (EPI == HS_EPI_SWIGLU_BF16) ? p.n0 + 16 * unit + 8 * (quad & 1) + lrow : p.n0 + 32 * unit + row;
+        w_off[j] = (unsigned)min(gn, p.N - 1) * (unsigned)(p.K * 2) + ((lpos ^ swz(row)) << 4);
+    }
+    // The weight-only hand-overs of the first chunk's prologue go out now: they do not depend on the row count,
+    // whose load from device memory (the kernel's first statement) is still on its way -- nothing has used it yet.
+    {
+        const unsigned char* w_mine = uniform_ptr((EPI == HS_EPI_SWIGLU_BF16 && quad >= 2) ? p.wb[1] : p.wb[0]);
+#pragma unroll
+        for (int h = -SW; h < -SA; h++)
+            if (p.kt0 + h + SW < p.kt1) issue_weight_tile<NU, MT, SA, SW, GRP, WV>(p, w_mine, smem_off, w_off, quad, p.kt0 + h + SW);
+    }
+    p.w_pre = 1;
+    for (p.m0 = pass * pass_shape<MT>::ROWS; p.m0 < p.M; p.m0 += n_pass * pass_shape<MT>::ROWS) {
+        int nmi = 0;
+#pragma unroll
+        for (int s = 0; s < WS::MI; s++)
+            if (rg + WS::RG * s < pass_shape<MT>::TILES && p.m0 + 32 * (rg + WS::RG * s) < p.M) nmi = s + 1;
+        nmi = __builtin_amdgcn_readfirstlane(nmi);
+#define HS_CHUNK(N) stream_chunk<EPI, PARTIAL, NU, MT, SA, SW, GRP, (N <= WS::MI ? N : 1), WV>(p, smem, smem_off, w_off, quad, rg, lane)
+        if (nmi == 0) HS_CHUNK(0);
+        else if (nmi == 1) HS_CHUNK(1);
+        else if (WS::MI >= 2 && nmi == 2) HS_CHUNK(2);
+        else if (WS::MI >= 3 && nmi == 3) HS_CHUNK(3);
+        else if (WS::MI >= 4) HS_CHUNK(4);
+#undef HS_CHUNK
+        __syncthreads();  // the rings are reused by the next row pass
+        p.w_pre = 0;
+    }
+    HS_WAIT_VMCNT(0);     // (a workgroup without rows leaves with its early weight loads landed)
+}
+
+}  // namespace
+
+namespace {
+
+// The kernel, for WV wavefronts.
+template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int WV>
+__device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
+                                              const bf16_t* __restrict__ W2, void* __restrict__ Cout,
+                                              float* __restrict__ part, const int32_t* __restrict__ m_dev,
+                                              int m_max, int N, int K, int tpc, int n_groups, int n_pass) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const unsigned smem_off = (unsigned)(size_t)(lds_ptr_t)smem;
+    constexpr int NCOLS = (EPI == HS_EPI_SWIGLU_BF16) ? 16 * NU : 32 * NU;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    stream_args p;
+    p.M = *m_dev;
+    p.A = reinterpret_cast<const unsigned char*>(A);
+    p.wb[0] = reinterpret_cast<const unsigned char*>(W);
+    p.wb[1] = reinterpret_cast<const unsigned char*>(EPI == HS_EPI_SWIGLU_BF16 ? W2 : W);
+    p.Cout = Cout;
+    p.part = part;
+    p.m_max = m_max;
+    p.N = N;
+    p.K = K;
+    // Workgroup id -> (weight group, row pass): ids are dealt round-robin to the 8 XCDs (each with its own L2).
+    // Unsplit K: an XCD takes a weight group and runs its row passes back to back, so that the passes which stream
+    // the same weight slab meet in one L2.
+    // (With a single pass the id is the group: no padding of the grid, a workgroup that only exits still has to
+    // wait for a compute unit with this kernel's LDS free.)
+    int group = blockIdx.x, pass = 0, chunk = blockIdx.y;
+    if (gridDim.y > 1) {
+        // Split-K: the workgroups that land on one XCD (ids congruent mod 8) take consecutive (chunk, group, pass)
+        // triples, pass fastest, i.e. one or two K chunks -- the slices of the activations they re-read then fit that
+        // XCD's L2 (all chunks together, e.g. 8 MB for the down projection at 220 rows and 27 MB at 720, do not), and
+        // the row passes that stream the same weight slice run side by side.  (grid.x = groups x passes, no padding.)
+        const int total = gridDim.x * gridDim.y, id = blockIdx.x + gridDim.x * blockIdx.y;
+        const int xcd = id & 7, slot = id >> 3;
+        const int full = total >> 3, extra = total & 7;          // XCDs 0 .. extra-1 hold one workgroup more
+        const int w = xcd * full + min(xcd, extra) + slot;
+        chunk = w / (int)gridDim.x;
+        const int rem = w - chunk * (int)gridDim.x;
+        group = rem / n_pass;
+        pass = rem - group * n_pass;
+    } else if (n_pass > 1) {
+        const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+        group = (local / n_pass) * 8 + xcd;
+        pass = local % n_pass;
+    }
+    if (group >= n_groups) return;
+    p.n0 = group * NCOLS;
+    p.group = group;
+    p.n_groups = n_groups;
+    p.chunk = chunk;
+    p.w_once = n_pass == 1;
+    const int nk = K / BK;
+    p.kt0 = chunk * tpc;
+    p.kt1 = min(nk, p.kt0 + tpc);
+
+    if constexpr (WV == 8) {
+        if (wave < 4) stream_group<EPI, PARTIAL, NU, MT, SA, SW, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, n_pass);
+        else stream_group<EPI, PARTIAL, NU, MT, SA, SW, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, n_pass);
+    } else {
+        if (wave < 2) stream_group<EPI, PARTIAL, NU, MT, SA, SW, 0, 4>(p, smem, smem_off, wave, wave, lane, pass, n_pass);
+        else stream_group<EPI, PARTIAL, NU, MT, SA, SW, 1, 4>(p, smem, smem_off, wave, wave - 2, lane, pass, n_pass);
+    }
+}
+
+}  // namespace
+
+namespace {
+
+// Launches a kernel of the shape <EPI, NU, MT, SA, SW>.
+template <int EPI, int NU, int MT, int SA, int SW, int THREADS, typename Kernel>
+void launch_shape(Kernel kernel, bool& configured, const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, float* part,
+                  const int32_t* m_dev, int m_max, int n, int k, int chunks, int tpc, int rows_hint, hipStream_t st) {
+    constexpr int NCOLS = (EPI == HS_EPI_SWIGLU_BF16) ? 16 * NU : 32 * NU, ROWS = pass_shape<MT>::ROWS;
+    constexpr size_t lds = (size_t)(SA * pass_shape<MT>::TILES + SW * NU) * TILE_BYTES;
+    static_assert(lds <= 160 * 1024, "LDS of one compute unit");
+    if (!configured) {      // more than 64 KB of dynamic LDS has to be asked for once per kernel
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        configured = true;
+    }
+    // row passes in the grid: what the hint calls for (rows beyond are reached by the pass loop of the kernel)
+    const int n_groups = (n + NCOLS - 1) / NCOLS;
+    int n_pass = (rows_hint + ROWS - 1) / ROWS;
+    if (n_pass < 1) n_pass = 1;
+    if (n_pass > (m_max + ROWS - 1) / ROWS) n_pass = (m_max + ROWS - 1) / ROWS;
+    dim3 grid(chunks > 1 ? n_groups * n_pass : (n_pass > 1 ? ((n_groups + 7) / 8) * 8 * n_pass : n_groups), chunks);
+    hipLaunchKernelGGL(kernel, grid, dim3(THREADS), lds, st, a, w, w2, c, part, m_dev, m_max, n, k, tpc, n_groups, n_pass);
+}
+
+}  // namespace
+
+// The same work in workgroups of 256 rows x 8 weight units (hs_gemm_wide.hip).
+void hs_launch_gemm_wide(int epi, bool partial, const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, float* part,
+                         const int32_t* m_dev, int m_max, int n, int k, int chunks, int tpc, int rows_hint, hipStream_t st);

@@ -204,3 +204,36 @@ def test_a_square_projection_of_the_feed_forward_width_has_room_for_its_partial_
     want = a.double() @ w.double().T.contiguous()
     assert float((c.double() - want).abs().max()) <= 2e-5 * (float(want.abs().max()) + 1.0)
     eng.close()
+
+
+@pytest.mark.parametrize("epi,n,k,hint", [(2, 1910, 1088, 4096), (1, 3810, 1088, 4096), (0, 10290, 192, 1280), (1, 10290, 192, 1280),
+                                          (2, 12810, 1024, 1280)])
+def test_four_wavefront_workgroups_and_passes_of_64_rows(epi, n, k, hint):
+    """Shapes at which a hint of many rows selects workgroups of 256 rows x 8 units (from three k-tiles, as many as the rings
+    hold, to 17; unsplit and split K; the last unit and the last group ragged), and a hint of one row passes of 64 rows: at
+    row counts around the edges of either, the product's definition (fp64 on the same operands) and the bits of the other
+    launch shapes, and nothing beyond the live rows."""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=1, d_model=3840, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ffn=1088, vocab=12864)
+    eng = Engine(shape, make_weights(shape, 1), rope_table(64, 128), max_batch=1, k_max=0, c_max=1, max_len=32, max_rows=hint, keep_logits=False)
+    g = torch.Generator(device="cuda:0").manual_seed(n + epi)
+    rnd = lambda r, s: (torch.randn(r, k, device="cuda:0", generator=g) * s).to(torch.bfloat16)
+    a, w, w2 = rnd(hint, 1.0), rnd(n, 0.05), rnd(n, 0.05) if epi == 2 else None
+    bits = lambda t: None if t is None else t.view(torch.int16)
+    for m in (1, 33, 64, 65, 255, 257, 700, hint):
+        want = a[:m].double() @ w.double().T
+        if epi == 2:
+            want = want * torch.sigmoid(want) * (a[:m].double() @ w2.double().T)
+        outs = []
+        for h in (100, 1, hint):
+            c = torch.full((hint, n), 15.0, device="cuda:0", dtype=torch.bfloat16 if epi == 2 else torch.float32)
+            m_dev = torch.full((1,), m, dtype=torch.int32, device="cuda:0")
+            eng.gemm(epi, bits(a), bits(w), bits(w2), bits(c) if epi == 2 else c, m_dev, hint, h)
+            torch.cuda.synchronize()
+            assert (c[m:] == 15.0).all(), (m, h, "rows beyond M were written")
+            outs.append(c[:m])
+        # fp32 sums of at most 1088 products; one bf16 rounding of the result (SwiGLU)
+        tol = (2.0 ** -8 if epi == 2 else 2e-5) * (want.abs().max() + 1.0)
+        assert (outs[0].double() - want - (15.0 if epi == 1 else 0.0)).abs().max() <= tol, m
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (m, "row hint changed the bits")
+    eng.close()

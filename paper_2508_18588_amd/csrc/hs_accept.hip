@@ -212,7 +212,7 @@ __device__ __forceinline__ double sum_slice(const float (&v)[PER], float largest
 
 // The sums come in stages from so many megabytes of logits on, by the hint or, of contexts with two candidates, by the
 // limits (trees of 17 rows over 152064 tokens, all rows at once against stages: 16 sequences, 165 MB, 64.5 against 67.7 us;
-// 24, 79 against 71; 32, 105 against 81; 64, 177 against 121; where nearly all drafts are accepted 176 against 127).
+// 24, 79 against 67; 32, 105 against 71; 64, 177 against 104; where more drafts are accepted 176 against 134).
 // Chains mostly have far fewer rows than the limits allow (64 chains of 9 rows: 104 against 108; 64 sequences of one row, 26
 // against 46), so there the limits only speak from the second figure on, where stages cost little against all the rows
 // that there might be.
@@ -371,7 +371,9 @@ __device__ __forceinline__ unsigned long long node_bits(int nn) { return nn < 64
 // ... of those that its stage computes, the next one's logits on their way while it sums the current one's.
 __global__ __launch_bounds__(256, 5) void reject_stats_kernel(reject_stage_args p, int first) {
     __shared__ double tab[32];
-    const int b = blockIdx.x, n_slices = p.n_slices, slice = blockIdx.y;
+    // (workgroups are dealt round-robin to the eight XCDs: a sequence's slices go to all of them, or those of the walks that
+    // are still under way would share a few: 64 trees 122 -> 105 us)
+    const int n_slices = p.n_slices, slice = blockIdx.y, b = (int)((blockIdx.x + blockIdx.y) % gridDim.x);
     const int r0 = p.row_off[b], nn = min(p.row_off[b + 1] - r0, HS_MAX_NODES);
     if (nn <= 0) return;
     unsigned long long todo = node_bits(nn);
@@ -825,7 +827,7 @@ void launch_reject_stats(const hs_ctx* ctx, const accept_commit_args& a, int bat
         if (depth - done - levels <= levels / 2) levels = depth - done;
         hipLaunchKernelGGL(reject_plan_kernel, dim3(batch), dim3(256), 0, st, p, done == 1, levels);
         dim3 grid = split(levels);
-        grid.z = std::max<int>(grid.z, std::min(levels, 4));     // (few walks are left)
+        grid.z = std::max(grid.z, 2u);     // (half of the walks are over: 32 trees 77 -> 71 us; four instead of two, 121 -> 123 of 64)
         hipLaunchKernelGGL(reject_stats_kernel, grid, dim3(256), 0, st, p, 0);
     }
 }

@@ -12,7 +12,7 @@
 // A = K tile from LDS, B = Q^T held in registers), so that each lane owns one query row -- the online-softmax
 // statistics are per-lane scalars and the exponentiated scores are already in the register layout the second
 // product O^T = V^T . P^T needs as its B operand.  V is stored in the cache with the token index fastest so V^T
-// tiles are plain 8-byte LDS reads.
+// tiles are plain 16-byte LDS reads (see attn_subtile).
 //
 // Two ways to run a unit (= one partition of one (sequence, KV head)), chosen per sequence by its number of query
 // rows R = G * nn:
@@ -940,7 +940,7 @@ void launch_mfma(const hs_ctx* ctx, int layer, size_t layer_off, const hs_kv_cac
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)attn_verify_mfma<HD>, 256, 0) != hipSuccess ||
             n < 1)
             n = 1;
-        per_cu = n;
+        per_cu = n < 2 ? n : 2;   // (a third would fit at head size 64: two toy layers are launches of idle workgroups then)
     }
     dim3 grid(ctx->n_cu * per_cu);
     hipLaunchKernelGGL((attn_verify_mfma<HD>), grid, dim3(256), 0, st, a, work, work + 2 + layer, list_a, list_b);

@@ -30,9 +30,9 @@
 //   * Four wavefronts (hs_gemm_wide.hip) of 4 x 4 tiles, 256 rows x 8 units per workgroup, for many rows: a fragment is
 //     used four times, not three or two and a half, so that an MFMA costs 0.75 instead of 1.07 KB through LDS, less of
 //     the chip's power and fewer rounds of workgroups.  7B gate/up at 4096 rows 942 -> 890 us (1250 TFLOP/s), at 2048 rows
-//     490 -> 446; down at 4096 674 -> 615.  Without its loads 816, without its MFMAs 628: at the clock that this load leaves
-//     the chip (1.4 to 1.5 GHz) the matrix cores bind it.
-//   * Passes of 64 rows and six activation stages (MT = 0) for up to 48 rows expected: with two, an activation tile was asked
+//     490 -> 446; down at 4096 674 -> 615.  Without its loads 816, without its MFMAs 628; counters: matrix cores busy 65 % of the
+//     cycles at the 1.76 GHz that this load leaves the chip, LDS 32 %.
+//   * Passes of 64 rows and six activation stages (MT = 0) for up to 32 rows expected: with two, an activation tile was asked
 //     for one tile (a third of a microsecond) before its use.  7 rows of 1536, gate/up 15.4 -> 14.3 us, head 16.0 -> 14.7;
 //     12 rows of 3584, head of 16448 29.3 -> 25.9.  (Split K: chunks are too short, 9.2 -> 11.2; five units: 42.4 -> 44.3, the
 //     weight stream at 6.4 TB/s either way.)
@@ -551,9 +551,13 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
         group = rem / n_pass;
         pass = rem - group * n_pass;
     } else if (n_pass > 1) {
-        const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-        group = (local / n_pass) * 8 + xcd;
-        pass = local % n_pass;
+        // (With many passes four groups side by side, the passes one after the other: the 32 workgroups of an XCD then share
+        // the operand tiles of 8 passes and 4 groups, 12 of them, where 16 passes and 2 groups are 18: 152064 columns of K = 3584 at 2176 rows 1966 -> 1897 us.)
+        const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, per_xcd = (n_groups + 7) >> 3;
+        const int side = n_pass >= 8 ? 4 : 1, first = local / (side * n_pass) * side, n_side = min(side, per_xcd - first);
+        const int rem = local - first * n_pass;
+        pass = side > 1 ? rem / n_side : rem;
+        group = (first + (side > 1 ? rem - pass * n_side : 0)) * 8 + xcd;
     }
     if (group >= n_groups) return;
     p.n0 = group * NCOLS;

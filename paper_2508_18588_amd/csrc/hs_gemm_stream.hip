@@ -21,8 +21,9 @@ void launch_stream(const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, 
                                            m_max, n, k, chunks, tpc, rows_hint, st);
 }
 
+// Passes of 64 rows up to this hint: a step with twice the rows expected still takes one.
 #ifndef HS_FEW_ROWS
-#define HS_FEW_ROWS 48
+#define HS_FEW_ROWS 32
 #endif
 constexpr int HS_WIDE_KERNEL_ROWS = 512;
 #ifndef HS_WIDE_GROUP_ROWS

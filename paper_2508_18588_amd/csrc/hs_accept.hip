@@ -121,9 +121,9 @@ __device__ __forceinline__ float block_max_f32(float v, float* red) {
 // are still under way.
 // Another rejection-sampling call of the context may run at the same time on another stream, with rows of its own and the
 // same place in the workspace.  So every sum and plan carries a word made of itself and the number of the call that wrote
-// it.  Where a stage finds anything but its own call's, it sums all nodes of its sequence (a call replayed from a graph has
-// the number of its earlier replays: nothing that is visited may be left over from those); where the last walk does, it
-// computes the sums itself, into LDS.
+// it.  Where a workgroup of a stage finds anything but its own call's plan, it sums all nodes of its sequence, whatever the
+// others of its slice have found (a call replayed from a graph has the number of its earlier replays: nothing that is visited
+// may be left over from those); where the last walk finds another call's sum, it computes the node's sums itself, into LDS.
 constexpr int SLICE = HS_REJECT_SLICE, PER = SLICE / 256;   // tokens of a slice; of a slice, per thread
 
 // exp((l - ref) / T) in fp64 for l <= ref, with c = 32 / (T ln 2): (l - ref) c = n + f, |f| <= 1/2, and the result is
@@ -377,13 +377,17 @@ __global__ __launch_bounds__(256, 5) void reject_stats_kernel(reject_stage_args 
     const int r0 = p.row_off[b], nn = min(p.row_off[b + 1] - r0, HS_MAX_NODES);
     if (nn <= 0) return;
     unsigned long long todo = node_bits(nn);
+    int skip = (int)blockIdx.z, stride = (int)gridDim.z;
     if (first) {
         if (p.row_off[p.batch] > p.all_rows) todo = 1ull;
     } else {
         walk_plan w;
         if (get_plan(p.plan + b, p.call, w)) todo &= w.todo;
+        // (not the call's own plan: the other workgroups of this slice may have read it before it was overwritten and count
+        // other nodes, so this one leaves none to them)
+        else { skip = 0; stride = 1; }
     }
-    for (int q = 0; q < (int)blockIdx.z; q++) todo &= todo - 1;
+    for (int q = 0; q < skip; q++) todo &= todo - 1;
     todo = (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(todo >> 32)) << 32 | __builtin_amdgcn_readfirstlane((unsigned)todo);
     if (!todo) return;
     fill_exp_table(tab);
@@ -392,7 +396,7 @@ __global__ __launch_bounds__(256, 5) void reject_stats_kernel(reject_stage_args 
     float v[PER], w[PER];
     load_slice(p.logits + (size_t)(r0 + i) * p.vocab, p.vocab, slice, vec, v);
     while (todo) {
-        for (int q = 0; q < (int)gridDim.z; q++) todo &= todo - 1;
+        for (int q = 0; q < stride; q++) todo &= todo - 1;
         const int next = __ffsll(todo) - 1;
         if (todo) load_slice(p.logits + (size_t)(r0 + next) * p.vocab, p.vocab, slice, vec, w);
         const slice_stat sum = slice_stats(v, p.inv_temp, tab);

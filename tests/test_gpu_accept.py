@@ -535,3 +535,64 @@ def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, 
         torch.cuda.synchronize()
         assert live(results_of(eng.st)) == live(want)
     eng.close()
+
+
+def test_a_replayed_call_in_stages_while_its_plans_are_overwritten(toy):
+    """A call replayed from a graph finds the sums of its earlier replays in the workspace, and their check words are its own.
+    Whatever another call overwrites between two workgroups' reads of a plan (here a second stream that keeps rewriting all
+    plans), a stage must not leave out a node of it: the walk would take the earlier replay's sum for it.  Two sets of logits
+    in turn, so that what is left over is wrong."""
+    from paper_2508_18588_amd import HS_ACCEPT_REJECTION
+    from paper_2508_18588_amd.runtime import Engine
+    from hs_inputs import ModelShape
+    V, B, k = 65540, 64, 8
+    shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
+    rng = np.random.default_rng(12)
+    eng = Engine(shape, make_weights(shape, 3), rope_table(64, 64), max_batch=B, k_max=k, c_max=2, max_len=80)
+    eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B, seq_ids=rng.integers(0, 2 ** 62, B).astype(np.int64))
+    trees = [oracle.build_tree([rng.integers(0, V, k), rng.integers(0, V, k)], 0, 50) for _ in range(B)]
+    m = eng.set_rows([dict(tok=t["tok"], parent=t["parent"], pos=t["pos"]) for t in trees])
+    at = torch.tensor([(o + int(t["parent"][i])) * V + int(t["tok"][i])
+                       for t, o in zip(trees, np.cumsum([0] + [len(t["tok"]) for t in trees])) for i in range(1, len(t["tok"]))],
+                      device="cuda:0")
+    eng.set_rows_hint(m)
+    assert m * V * 4e-6 >= 250            # in stages
+    live = lambda res: [(int(n), o[:n].tolist(), q[:n].tolist()) for n, o, q in zip(res[1], res[2], res[3])]
+    sets, want = [], []
+    for seed in (1, 2):
+        g = torch.Generator(device="cuda:0").manual_seed(seed)
+        lg = torch.randn(eng.logits.shape, generator=g, device="cuda:0")
+        lg.view(-1)[at] = np.log(V) + 2.0 + torch.randn(len(at), generator=g, device="cuda:0")
+        eng.logits.copy_(lg)
+        eng.accept(HS_ACCEPT_REJECTION, 1.0, 1234)
+        torch.cuda.synchronize()
+        sets.append(lg)
+        want.append(live(results_of(eng.st)))
+    assert want[0] != want[1]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        eng.accept(HS_ACCEPT_REJECTION, 1.0, 1234)
+    # the plans are 16 bytes per sequence in front of the sums, the workspace's last region
+    up = lambda n: (n + 255) // 256 * 256
+    end = eng._ws_ptr - eng.workspace.data_ptr() + hs_workspace_bytes_of(eng) - up(eng.max_rows * ((V + 4095) // 4096) * 16)
+    plans = eng.workspace[end - up(16 * B):end - up(16 * B) + 16 * B].view(torch.int32)
+    noise = torch.randint(-2 ** 31, 2 ** 31, (4 * B,), dtype=torch.int32, device="cuda:0")
+    rewrite, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    other = torch.zeros(64, dtype=torch.int32, device="cuda:0")
+    with torch.cuda.graph(rewrite):
+        for i in range(40):
+            torch.add(noise, 7919 * i, out=plans)
+            for _ in range(1 + i * 5 % 11):     # (a while without: a stage reads some of its plans before, some after)
+                other.add_(1)
+    wrong = []
+    for trial in range(60):
+        eng.logits.copy_(sets[trial % 2])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            rewrite.replay()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = live(results_of(eng.st))
+        wrong += [(trial, b) for b in range(B) if got[b] != want[trial % 2][b]]
+    eng.close()
+    assert not wrong, (len(wrong), wrong[:10])

@@ -214,7 +214,7 @@ typedef struct hs_accept_args {
 /* Validates the shape and copies the descriptors.  Supported: head_dim 64 or 128, kv_block 16, n_q_heads a
  * multiple of n_kv_heads with at most 8 query heads per KV head, d_model / d_ffn / n_q_heads*head_dim multiples
  * of 64, d_model at most 16384.  The norm weight vectors must be 16-byte aligned (HS_ERR_INVALID_ARG otherwise).
- * The length of the attention's split-KV partitions (128 to 2048 keys) is chosen here from the limits
+ * The length of the attention's split-KV partitions (128, 256, 512 or 1024 keys) is chosen here from the limits
  * alone -- results of contexts created with different limits can differ in the last bits. */
 hs_status hs_create(const hs_model_desc* desc, const hs_weights* weights, const hs_limits* limits, hs_ctx** out);
 void hs_destroy(hs_ctx* ctx);

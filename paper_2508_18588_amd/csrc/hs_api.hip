@@ -170,29 +170,30 @@ hs_status hs_create(const hs_model_desc* desc, const hs_weights* w, const hs_lim
         ctx->norm1.push_back(w->norm1[i]);
         ctx->norm2.push_back(w->norm2[i]);
     }
-    // Split-KV partition length (a multiple of 32 keys): a function of the context's limits only, so results are identical
-    // across calls.  Longer partitions mean fewer partial results, which are written into the middle of the K/V read
-    // stream (98 of 2250 MB cost 73 of 396 us where every sequence verifies 17 rows of 5 heads) and read back by the merge;
-    // shorter ones keep a small batch spread over the whole chip.  So: the longest that still cuts a full batch at maximum
-    // length into enough partitions per layer.
-    // With two candidates per draft the partial results are many and a unit of work has four wavefronts: 512 partitions
-    // are enough, one for every resident workgroup (trees of 17 nodes; 64 sequences of 8192 tokens, 8 heads, 1024 against
-    // 2048 keys: step 1383 -> 1360 us; 32 of them 770 -> 762; 32 of 4000 to 8000 tokens, 2 heads, in 256, 512 and 1024 keys: 430, 413,
-    // 387).  With chains most sequences have one row or a few, and a unit one wavefront: 4096 partitions, and 8192 for 2048 keys,
-    // whose longer chains leave a longer tail (128 sequences, 4608 partitions of 2048 keys: 650 -> 656 us; 256 with
-    // 17408: 1332 -> 1312).  Where 256 keys give fewer than 1024 partitions there is at most one for every second wavefront, and
-    // the launch lasts as long as one wavefront's chain of 32-key steps: 128 keys (7 sequences of up to 2600 tokens, four
-    // 1.5B layers: 300 -> 285 us).  With 1408 partitions of 256 keys 128 were 0.6 % slower.  (Not where a context made for large prefill calls would need
-    // more than 512 MB for the partial results.)
+    // Split-KV partition length (a multiple of 32 keys, at most 64 pages): a function of the context's limits only,
+    // so results are identical across calls.  The longest of 1024 / 512 / 256 keys that still cuts a full batch at
+    // maximum length into 4096 partitions per layer (256: 1024 partitions): longer partitions mean fewer partial results, which
+    // are written into the middle of the K/V read stream and read back by the merge, shorter ones keep a small batch spread
+    // over the whole chip.  Where 256 keys give fewer than
+    // 1024 partitions there is at most one for every second wavefront, and the launch lasts as long as one wavefront's
+    // chain of 32-key steps: 128 keys (7 sequences of up to 2600 tokens, four 1.5B layers: 300 -> 285 us; 4 short ones
+    // through the two toy layers: 113 -> 110 us).  With 1408 partitions 128 keys were 0.6 % slower.  (Not where a context
+    // made for large prefill calls would need more than 512 MB for the partial results.)
+    // Longer ones were tried and are not worth it, because the limits do not say how long the sequences are now nor how many
+    // rows they have, and up to 32 query rows are one wavefront's work.  2048 keys from 8192 partitions on (256 sequences, limits
+    // for 32768 tokens, a 7B layer): drafting 948 -> 929 us at 2000 tokens and 1353 -> 1339 with a long tail, but plain decoding
+    // 474 -> 501, 559 -> 603 at 3000 tokens and 777 -> 805.  Half a thousand partitions for two candidates per draft: trees of
+    // 17 nodes over 8192 keys, a 14B layer, 64 sequences 1410 -> 1395 us, with matches for one in six 695 -> 734, for none 590 ->
+    // 606; four heads of one query head each, 64 sequences of 1024 tokens 135 -> 157.  The error grows, too, since a partition's
+    // largest probability is exactly 1: against 64 bits, 1024 and 2048 keys, 0.006309 and 0.006336 (long tail), 0.007712 and 0.007730.
     {
         const long long keys = (long long)l.max_blocks_per_seq * 16;
         ctx->att_part = 256;
-        for (int part : {2048, 1024, 512, 256, 128}) {
+        for (int part : {1024, 512, 256, 128}) {
             const long long parts = (keys + part - 1) / part, total = parts * l.max_batch * d.n_kv_heads;
             if (part == 128 && (long long)l.max_rows * d.n_q_heads * parts * d.head_dim * 2 > (512ll << 20)) break;
             ctx->att_part = part;
-            const int enough = l.c_max > 1 ? 512 : part == 2048 ? 8192 : part == 256 ? 1024 : 4096;
-            if (total >= enough) break;
+            if (total >= (part == 256 ? 1024 : 4096)) break;
         }
     }
     const long long max_keys = (long long)l.max_blocks_per_seq * 16;

@@ -348,7 +348,7 @@ __device__ inline void attn_wave_stream(const AttnArgs& a, const int4* __restric
     int k_end = min(total, k_begin + a.part_keys);
     const bf16_t* kbase_ptr = a.kc + (size_t)cu.j * 16 * HD;   // + page * page_stride
     const bf16_t* vbase_ptr = a.vc + (size_t)cu.j * HD * 16;
-    // the unit's page numbers, 64 at a time: lane l holds the page of positions 16 l .. + 15 of 1024, handed out by
+    // the unit's page numbers: lane l holds the page of positions k_begin + 16 l .. + 15 (at most 64 pages), handed out by
     // readlane -- no table look-up sits between two sub-tiles
     int my_page = safe_page_lane(a.block_table + (size_t)cu.b * a.max_blocks, k_begin + 16 * lane, total, a.max_blocks,
                                  a.n_blocks);
@@ -404,29 +404,19 @@ __device__ inline void attn_wave_stream(const AttnArgs& a, const int4* __restric
                 *reinterpret_cast<u32x4*>(tile + v_put + pp * T::PAGE + ii * 1024) = rv[pp * NCP + ii];
             }
         const bool last = kb + 32 >= k_end;
-        const bool last_page = last || ((kb + 32 - k_begin) & 1023) == 0;   // my_page ends with this sub-tile
-        if (!n_ready && (last_page || ((kb - k_begin) & 1023) != 0)) {
-            const int k_more = k_begin + ((kb - k_begin) & ~1023) + 1024;
-            if (k_more < k_end) {
-                my_page_n = safe_page_lane(a.block_table + (size_t)cu.b * a.max_blocks, k_more + 16 * lane, total, a.max_blocks,
-                                           a.n_blocks);
-                n_ready = true;
-            } else if (have_n) {
-                nu = attn_unit_from(en0, en1);
-                total_n = nu.L + nu.nn;
-                k_begin_n = nu.part * a.part_keys;
-                k_end_n = min(total_n, k_begin_n + a.part_keys);
-                kbase_n = a.kc + (size_t)nu.j * 16 * HD;
-                vbase_n = a.vc + (size_t)nu.j * HD * 16;
-                my_page_n = safe_page_lane(a.block_table + (size_t)nu.b * a.max_blocks, k_begin_n + 16 * lane, total_n,
-                                           a.max_blocks, a.n_blocks);
-                n_ready = true;
-            }
+        if (!n_ready && have_n && (last || kb > k_begin)) {
+            nu = attn_unit_from(en0, en1);
+            total_n = nu.L + nu.nn;
+            k_begin_n = nu.part * a.part_keys;
+            k_end_n = min(total_n, k_begin_n + a.part_keys);
+            kbase_n = a.kc + (size_t)nu.j * 16 * HD;
+            vbase_n = a.vc + (size_t)nu.j * HD * 16;
+            my_page_n = safe_page_lane(a.block_table + (size_t)nu.b * a.max_blocks, k_begin_n + 16 * lane, total_n,
+                                       a.max_blocks, a.n_blocks);
+            n_ready = true;
         }
-        if (!last) {
-            if (last_page) { my_page = my_page_n; n_ready = false; }
-            HS_W_FETCH(my_page, kbase_ptr, vbase_ptr, ((kb + 32 - k_begin) >> 4) & 63)
-        } else if (have_n) HS_W_FETCH(my_page_n, kbase_n, vbase_n, 0)
+        if (!last) HS_W_FETCH(my_page, kbase_ptr, vbase_ptr, (kb + 32 - k_begin) >> 4)
+        else if (have_n) HS_W_FETCH(my_page_n, kbase_n, vbase_n, 0)
         attn_subtile<HD>(tile, qf, o, m_run, l_run, anc, kb, cu.L, total, a.scale_log2, half, l32);
         kb += 32;
         if (last) {
@@ -478,8 +468,8 @@ __device__ inline AttnUnit attn_unit_scalar(const int4* list, int it) {
 // The keys run one sub-tile ahead of the values, so that the next sub-tile's first product is issued between this one's
 // exponentials: an instruction takes a wavefront about eight clocks, and there are two of them on a SIMD.
 // Steps with a 128-key tile at a time and now (us; launches of the first 45 -> 40): 64 sequences of 2560 tokens, a third of
-// them with 9 rows, four 1.5B layers 579 -> 560; 64 trees of 17 rows over 8192 keys, one 14B layer 1413 -> 1390, with
-// partitions of 2048 keys (hs_create) 1368; 256 sequences with a long tail of lengths, a 7B layer 1338 -> 1315.  What is
+// them with 9 rows, four 1.5B layers 579 -> 560; 64 trees of 17 rows over 8192 keys, one 14B layer 1413 -> 1390;
+// 256 sequences with a long tail of lengths, a 7B layer 1348 -> 1332.  What is
 // left there: without its arithmetic the 14B launch takes 400 us of 470, without its loads 250, and the partial results
 // (see hs_create) are 70 of the 400.
 template <int HD>

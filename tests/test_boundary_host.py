@@ -79,6 +79,46 @@ def test_create_validates_shape_and_limits(lib):
     assert lib.hs_create(None, None, None, None) == hs.HS_ERR_INVALID_ARG
 
 
+def _partitions(batch, hq, hkv, hd, c_max, k_max, blocks):
+    """Split-KV partitions of a sequence of maximum length, from what one more row takes of the workspace: per partition and
+    query head an output of head_dim fp16 values, a maximum and a sum."""
+    L = 2
+    desc = hs.hs_model_desc(L, 256, hq, hkv, hd, 1024, 4096, 16, 1e-6)
+    arr = (C.c_void_p * L)(0x1000, 0x1000)
+    p = C.cast(arr, C.POINTER(C.c_void_p))
+    w = hs.hs_weights(0x1000, 0x1000, 0x1000, p, p, p, p, p, p, p, 0x1000)
+
+    def bytes_of_256_rows(blocks):
+        n = []
+        rows = -(-batch * (1 + c_max * k_max) // 256) * 256
+        for m in (rows, rows + 256):
+            ctx = hs.hs_create(desc, w, hs.hs_limits(batch, k_max, c_max, m, blocks, 512, 8))
+            n.append(hs.hs_workspace_bytes(ctx))
+            hs.hs_destroy(ctx)
+        return n[1] - n[0]
+    parts, rest = divmod(bytes_of_256_rows(blocks) - bytes_of_256_rows(1), 256 * hq * (2 * hd + 8))
+    assert rest == 0
+    return 1 + parts
+
+
+@pytest.mark.parametrize("shape,part_keys", [
+    # (batch, query heads, KV heads, head size, candidates, longest draft, pages per sequence)
+    ((256, 28, 4, 128, 1, 32, 2048), 1024),     # 32768 tokens: no longer than a wavefront's 64 page numbers, however many there are
+    ((64, 40, 8, 128, 2, 8, 512), 1024),
+    ((32, 40, 8, 128, 2, 8, 512), 512),         # two candidates per draft: like one, as most sequences may find no match
+    ((16, 40, 8, 128, 2, 8, 512), 256),
+    ((64, 12, 2, 128, 2, 8, 512), 256),
+    ((64, 4, 4, 64, 2, 8, 64), 256),
+    ((64, 12, 2, 128, 2, 8, 161), 256),
+    ((8, 8, 2, 128, 2, 22, 16440), 1024),
+    ((7, 12, 2, 128, 1, 16, 164), 128),
+])
+def test_partition_lengths_of_the_verify_attention(lib, shape, part_keys):
+    """A function of the limits alone: the longest of 1024, 512 and 256 keys with at least 4096 (256: 1024) partitions per layer,
+    else 128."""
+    assert _partitions(*shape) == -(-shape[-1] * 16 // part_keys)
+
+
 def test_calls_reject_bad_arguments_without_launching(lib):
     desc, w, lim, keep = _good()
     ctx = hs.hs_create(desc, w, lim)

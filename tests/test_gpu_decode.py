@@ -396,9 +396,9 @@ def test_workgroup_attention_units_with_one_to_four_live_row_tiles(head_dim):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("head_dim", [64, 128])
-def test_attention_partitions_of_2048_keys(head_dim):
-    """A context whose limits allow one very long sequence cuts the keys into partitions of 2048: units of more than 64
-    pages (a wavefront unit looks up its page numbers 64 at a time), some with a handful of keys, next to each other
+def test_attention_partitions_of_1024_keys(head_dim):
+    """A context whose limits allow one very long sequence cuts the keys into partitions of 1024, the longest there are: units
+    of all 64 pages that a wavefront unit can look up, some with a handful of keys, next to each other
     as wavefront units (1 or 5 rows of 4 heads) and workgroup units (13 and 23 rows).  Two steps in lock-step with the oracle."""
     from paper_2508_18588_amd.runtime import Engine, Policy
     shape = ModelShape(n_layers=1, d_model=256, n_q_heads=8, n_kv_heads=2, head_dim=head_dim, d_ffn=384, vocab=512)
@@ -413,7 +413,7 @@ def test_attention_partitions_of_2048_keys(head_dim):
     cands = [[np.concatenate([t[-6:], rng.integers(0, shape.vocab, k)]).astype(np.int32) if k else none, none]
              for t, k in zip(toks, draft_lens)]
     pol = Policy(window=6, m_min=3, k_fixed=22, k_max=22)
-    eng = Engine(shape, w, rope, max_batch=8, k_max=22, c_max=2, max_len=2200, seq_caps=[70000] + [2200] * 7,
+    eng = Engine(shape, w, rope, max_batch=8, k_max=22, c_max=2, max_len=2200, seq_caps=[263000] + [2200] * 7,
                  shuffle_pages_seed=73)
     eng.load_sequences(toks, budgets=[40] * 8)
     eng.set_history(cands)
@@ -421,10 +421,9 @@ def test_attention_partitions_of_2048_keys(head_dim):
     ob = OracleBatch(model, toks, [40] * 8, 2300)
     stats = lockstep(eng, ob, cands, pol, max_steps=2)
     eng.close()
-    print("2048-key partitions", head_dim, stats)
+    print("1024-key partitions", head_dim, stats)
     assert stats["steps"] == 2
     assert stats["rows"] >= 16 + sum(draft_lens)
-
 
 
 def test_split_and_serial_gemm_execution_agree_bitwise():

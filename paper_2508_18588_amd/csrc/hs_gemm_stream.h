@@ -460,6 +460,13 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
 
 namespace {
 
+// Weight stages of the 256-row passes that a 64-row instance falls back to: those of the 256-row instance.
+template <int NU>
+struct few_rows_fallback {
+    static constexpr int SW = NU == 3 ? 7 : 5;
+    static_assert(NU == 3 || NU == 4, "the 64-row instances");
+};
+
 // What a wavefront of group GRP does: the row passes of its workgroup.
 template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int WV>
 __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem, unsigned smem_off, int quad, int rg, int lane,
@@ -486,6 +493,17 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
             if (p.kt0 + h + SW < p.kt1) issue_weight_tile<NU, MT, SA, SW, GRP, WV>(p, w_mine, smem_off, w_off, quad, p.kt0 + h + SW);
     }
     p.w_pre = 1;
+    if constexpr (MT == 0) {
+        // More rows than the hint let expect: passes of 256 after all (of 64 they would read the weights four times as often:
+        // 16448 columns of K = 3584 with 990 rows 460 us, 185 in passes of 256).  The early loads land first, they lie elsewhere.
+        if (p.M > pass_shape<0>::ROWS) {
+            HS_WAIT_VMCNT(0);
+            __syncthreads();
+            p.w_pre = 0;
+            stream_group<EPI, PARTIAL, NU, 2, 2, few_rows_fallback<NU>::SW, GRP, WV>(p, smem, smem_off, quad, rg, lane, pass, n_pass);
+            return;
+        }
+    }
     for (p.m0 = pass * pass_shape<MT>::ROWS; p.m0 < p.M; p.m0 += n_pass * pass_shape<MT>::ROWS) {
         int nmi = 0;
 #pragma unroll
@@ -589,6 +607,8 @@ void launch_shape(Kernel kernel, bool& configured, const bf16_t* a, const bf16_t
     constexpr int NCOLS = (EPI == HS_EPI_SWIGLU_BF16) ? 16 * NU : 32 * NU, ROWS = pass_shape<MT>::ROWS;
     constexpr size_t lds = (size_t)(SA * pass_shape<MT>::TILES + SW * NU) * TILE_BYTES;
     static_assert(lds <= 160 * 1024, "LDS of one compute unit");
+    if constexpr (MT == 0)
+        static_assert((2 * pass_shape<2>::TILES + few_rows_fallback<NU>::SW * NU) * TILE_BYTES <= lds, "the fallback's rings");
     if (!configured) {      // more than 64 KB of dynamic LDS has to be asked for once per kernel
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         configured = true;

@@ -21,7 +21,8 @@ void launch_stream(const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, 
                                            m_max, n, k, chunks, tpc, rows_hint, st);
 }
 
-// Passes of 64 rows up to this hint: a step with twice the rows expected still takes one.
+// Passes of 64 rows up to this hint: a step with twice the rows expected still takes one.  (With more the same launch takes
+// passes of 256: drafting can bring any number of rows after a step that had few.)
 #ifndef HS_FEW_ROWS
 #define HS_FEW_ROWS 32
 #endif

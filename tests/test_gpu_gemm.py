@@ -237,3 +237,64 @@ def test_four_wavefront_workgroups_and_passes_of_64_rows(epi, n, k, hint):
         assert (outs[0].double() - want - (15.0 if epi == 1 else 0.0)).abs().max() <= tol, m
         assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (m, "row hint changed the bits")
     eng.close()
+
+
+def _launch_us(call, n=10):
+    """Median time of a launch in microseconds, five times n of them in a row."""
+    times = []
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(n):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) / n * 1e3)
+    return sorted(times[1:])[2]
+
+
+@pytest.mark.parametrize("epi,n,k,m,hint,most", [(0, 16448, 3584, 990, 30, 2.2), (2, 13824, 3584, 990, 30, 2.2)])
+def test_a_wrong_row_hint_costs_little(epi, n, k, m, hint, most):
+    """The hint is the caller's guess, and drafting makes the row count swing: launched for `hint` rows, m rows may take at most
+    `most` times what they take with the right hint.  (30 for 990: 1.4 as measured, the passes being of 256 rows instead of
+    384; 3.6 if they were of 64.)"""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=1, d_model=3584, n_q_heads=28, n_kv_heads=4, head_dim=128, d_ffn=13824, vocab=16448)
+    eng = Engine(shape, make_weights(shape, 1), rope_table(64, 128), max_batch=1, k_max=0, c_max=1, max_len=32, max_rows=1024, keep_logits=False)
+    g = torch.Generator(device="cuda:0").manual_seed(n)
+    rnd = lambda r, s: (torch.randn(r, k, device="cuda:0", generator=g) * s).to(torch.bfloat16).view(torch.int16)
+    a, w, w2 = rnd(1024, 1.0), rnd(n, 0.05), rnd(n, 0.05) if epi == 2 else None
+    c = torch.zeros(1024, n, device="cuda:0", dtype=torch.int16 if epi == 2 else torch.float32)
+    m_dev = torch.full((1,), m, dtype=torch.int32, device="cuda:0")
+    right, wrong = (_launch_us(lambda: eng.gemm(epi, a, w, w2, c, m_dev, 1024, h)) for h in (m, hint))
+    eng.close()
+    assert wrong <= most * right, (right, wrong)
+
+
+def test_row_maxima_of_more_rows_than_the_hint_of_few():
+    """The LM head's keys (epi 3), launched for one row and for 300: the same bits from one row to several passes."""
+    from paper_2508_18588_amd import lib
+    from paper_2508_18588_amd.runtime import Engine
+    n, k = 12810, 1024
+    shape = ModelShape(n_layers=1, d_model=k, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ffn=1088, vocab=n)
+    eng = Engine(shape, make_weights(shape, 1), rope_table(64, 128), max_batch=1, k_max=0, c_max=1, max_len=32, max_rows=704, keep_logits=False)
+    g = torch.Generator(device="cuda:0").manual_seed(8)
+    a = torch.randn(704, k, device="cuda:0", generator=g).to(torch.bfloat16)
+    w = (torch.randn(n, k, device="cuda:0", generator=g) * 0.05).to(torch.bfloat16)
+    groups = lib().hs_debug_rowmax_groups(n)
+    for m in (1, 64, 65, 256, 257, 700):
+        m_dev = torch.full((1,), m, dtype=torch.int32, device="cuda:0")
+        keys = []
+        for hint in (1, 300):
+            c = torch.zeros(704, groups, dtype=torch.int64, device="cuda:0")
+            eng.gemm(3, a.view(torch.int16), w.view(torch.int16), None, c, m_dev, 704, hint)
+            torch.cuda.synchronize()
+            assert (c[m:] == 0).all()
+            keys.append(np_of(c[:m]).view(np.uint64))
+        assert (keys[0] == keys[1]).all(), m
+        want = (a[:m].float() @ w.float().T)
+        best = (0xFFFFFFFF - (keys[0].max(1) & 0xFFFFFFFF)).astype(np.int64)
+        got = want[torch.arange(m, device="cuda:0"), torch.from_numpy(best).cuda()]
+        # (two fp32 sums of 1024 products in another order: the named column is within their rounding of the largest)
+        assert (want.max(1).values - got <= 2e-4).all(), m
+    eng.close()

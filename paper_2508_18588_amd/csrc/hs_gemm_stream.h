@@ -126,7 +126,7 @@ template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int NM
 __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char* smem, unsigned smem_off,
                                              const unsigned (&w_off)[wave_shape<NU, MT, GRP, WV>::FETCH_U], int quad, int rg, int lane) {
     using WS = wave_shape<NU, MT, GRP, WV>;
-    static_assert(SA >= 2 && SW > SA && (SA == 2 || (MT < 2 && WV == 8)), "the wait counts below");
+    static_assert(SA >= 2 && SW > SA && (SA == 2 || (MT == 0 && WV == 8)), "the wait counts below (n_a is 0 or NSA = 1 where SA > 2)");
     constexpr int A_STAGE = pass_shape<MT>::TILES * TILE_BYTES, W_STAGE = NU * TILE_BYTES, W_RING = SA * A_STAGE;
     constexpr int NUW = wave_units<NU, GRP>::N, U0 = wave_units<NU, GRP>::U0;
     constexpr int NLW = WS::FETCH_U;   // 1 KB load instructions per weight tile and wavefront
@@ -294,7 +294,6 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
         if (G == 1) wait_tile(kt + 1);
         else if (SA == 2) HS_WAIT_VMCNT(NLW);
         else if (G == 0) HS_WAIT_VMCNT((SA - 1) * NLW + (SA - 2) * NSA);
-        else if (NSA == 2 && n_a == 1) HS_WAIT_VMCNT((SA - 1) * NLW + (SA - 2));
         else HS_WAIT_VMCNT((SA - 1) * NLW);
         __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8)); /* lgkmcnt(0) */
         __builtin_amdgcn_s_barrier();

@@ -473,6 +473,13 @@ struct few_rows_fallback {
     static_assert(NU == 3 || NU == 4, "the 64-row instances");
 };
 
+// Weight stages of the four-wavefront kernel's smaller shares of a group's units: as many as LDS holds, at most 8.
+template <int NU>
+struct wide_share {
+    static constexpr int SW = NU == 4 ? 6 : 8;
+    static_assert((2 * pass_shape<2>::TILES + SW * NU) * TILE_BYTES <= 160 * 1024, "LDS of one compute unit");
+};
+
 // What a wavefront of group GRP does: the row passes of its workgroup.
 template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int WV>
 __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem, unsigned smem_off, int quad, int rg, int lane,
@@ -560,31 +567,55 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
     // the same weight slab meet in one L2.
     // (With a single pass the id is the group: no padding of the grid, a workgroup that only exits still has to
     // wait for a compute unit with this kernel's LDS free.)
-    int group = blockIdx.x, pass = 0, chunk = blockIdx.y;
+    // Four wavefronts: there may be fewer rows than the hint let expect (or there was none).  Then the first ids take the
+    // passes that have rows -- ids n_pass apart would lie on a few of the chip's shader engines -- and the others share their
+    // units, in halves or quarters of a group, where that takes less time: by rounds of 256 workgroups, each units + 3 (with
+    // 2 to 6 the choice is within 1 % of the best of the three, 64 to 1536 rows of the 1.5B and 7B shapes with hints of 3000).
+    // us at hints of 990 and of 2048 or more, before there was this kernel / with every pass in its place and whole / now: 14B
+    // gate/up at 64 rows 56, 105 / 150, 84 / 55, 55, at 220 rows 83, 146 / 203, 111 / 79, 79; 7B down at 220 rows 60, 65 /
+    // 95, 96 / 45, 46; QKV 23, 28 / 37, 38 / 24, 25.  (For this the count is waited for first, half a microsecond.)
+    int passes = n_pass, units = NU;
+    if constexpr (WV == 4) {
+        p.M = __builtin_amdgcn_readfirstlane(p.M);
+        const int live = (p.M + pass_shape<MT>::ROWS - 1) / pass_shape<MT>::ROWS, wgs = n_groups * (int)gridDim.y * live;
+        if (live <= 0) return;
+        if (live < n_pass) {
+            auto cost = [&](int u) { return (wgs * (NU / u) + 255) / 256 * (u + 3); };
+            if (live * 2 <= n_pass && cost(NU / 2) < cost(units)) units = NU / 2;
+            if (live * 4 <= n_pass && cost(NU / 4) < cost(units)) units = NU / 4;
+            passes = live;
+        }
+    }
+    const int slots = passes * (NU / units);    // workgroups of a group: its passes, then its other shares' ...
+    int group = blockIdx.x, slot = 0, chunk = blockIdx.y;
     if (gridDim.y > 1) {
         // Split-K: the workgroups that land on one XCD (ids congruent mod 8) take consecutive (chunk, group, pass)
         // triples, pass fastest, i.e. one or two K chunks -- the slices of the activations they re-read then fit that
         // XCD's L2 (all chunks together, e.g. 8 MB for the down projection at 220 rows and 27 MB at 720, do not), and
         // the row passes that stream the same weight slice run side by side.  (grid.x = groups x passes, no padding.)
-        const int total = gridDim.x * gridDim.y, id = blockIdx.x + gridDim.x * blockIdx.y;
-        const int xcd = id & 7, slot = id >> 3;
+        const int per_chunk = n_groups * slots, total = per_chunk * gridDim.y, id = blockIdx.x + gridDim.x * blockIdx.y;
+        const int xcd = id & 7, nth = id >> 3;
         const int full = total >> 3, extra = total & 7;          // XCDs 0 .. extra-1 hold one workgroup more
-        const int w = xcd * full + min(xcd, extra) + slot;
-        chunk = w / (int)gridDim.x;
-        const int rem = w - chunk * (int)gridDim.x;
-        group = rem / n_pass;
-        pass = rem - group * n_pass;
+        if (WV == 4 && nth >= full + (xcd < extra ? 1 : 0)) return;
+        const int w = xcd * full + min(xcd, extra) + nth;
+        chunk = w / per_chunk;
+        const int rem = w - chunk * per_chunk;
+        group = rem / slots;
+        slot = rem - group * slots;
     } else if (n_pass > 1) {
         // (With many passes four groups side by side, the passes one after the other: the 32 workgroups of an XCD then share
         // the operand tiles of 8 passes and 4 groups, 12 of them, where 16 passes and 2 groups are 18: 152064 columns of K = 3584 at 2176 rows 1966 -> 1897 us.)
         const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, per_xcd = (n_groups + 7) >> 3;
-        const int side = n_pass >= 8 ? 4 : 1, first = local / (side * n_pass) * side, n_side = min(side, per_xcd - first);
-        const int rem = local - first * n_pass;
-        pass = side > 1 ? rem / n_side : rem;
-        group = (first + (side > 1 ? rem - pass * n_side : 0)) * 8 + xcd;
+        if (WV == 4 && local >= per_xcd * slots) return;
+        const int side = slots >= 8 || 2 * passes <= n_pass ? 4 : 1, first = local / (side * slots) * side, n_side = min(side, per_xcd - first);
+        const int rem = local - first * slots;
+        slot = side > 1 ? rem / n_side : rem;
+        group = (first + (side > 1 ? rem - slot * n_side : 0)) * 8 + xcd;
     }
     if (group >= n_groups) return;
-    p.n0 = group * NCOLS;
+    const int share = WV == 4 && units < NU ? slot / passes : 0, pass = slot - share * passes;
+    p.n0 = group * NCOLS + share * units * (NCOLS / NU);
+    if (WV == 4 && p.n0 >= N) return;
     p.group = group;
     p.n_groups = n_groups;
     p.chunk = chunk;
@@ -594,11 +625,17 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
     p.kt1 = min(nk, p.kt0 + tpc);
 
     if constexpr (WV == 8) {
-        if (wave < 4) stream_group<EPI, PARTIAL, NU, MT, SA, SW, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, n_pass);
-        else stream_group<EPI, PARTIAL, NU, MT, SA, SW, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, n_pass);
+        if (wave < 4) stream_group<EPI, PARTIAL, NU, MT, SA, SW, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, passes);
+        else stream_group<EPI, PARTIAL, NU, MT, SA, SW, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, passes);
     } else {
-        if (wave < 2) stream_group<EPI, PARTIAL, NU, MT, SA, SW, 0, 4>(p, smem, smem_off, wave, wave, lane, pass, n_pass);
-        else stream_group<EPI, PARTIAL, NU, MT, SA, SW, 1, 4>(p, smem, smem_off, wave, wave - 2, lane, pass, n_pass);
+        auto run = [&](auto nu_c, auto sw_c) __attribute__((always_inline)) {
+            constexpr int U = decltype(nu_c)::value, S = decltype(sw_c)::value;
+            if (wave < 2) stream_group<EPI, PARTIAL, U, MT, SA, S, 0, 4>(p, smem, smem_off, wave, wave, lane, pass, passes);
+            else stream_group<EPI, PARTIAL, U, MT, SA, S, 1, 4>(p, smem, smem_off, wave, wave - 2, lane, pass, passes);
+        };
+        if (units == NU) run(std::integral_constant<int, NU>{}, std::integral_constant<int, SW>{});
+        else if (units == NU / 2) run(std::integral_constant<int, NU / 2>{}, std::integral_constant<int, wide_share<NU / 2>::SW>{});
+        else run(std::integral_constant<int, NU / 4>{}, std::integral_constant<int, wide_share<NU / 4>::SW>{});
     }
 }
 

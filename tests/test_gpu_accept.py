@@ -348,12 +348,12 @@ def test_rejection_at_an_infinite_temperature_is_uniform_over_the_tokens_that_ar
     eng.close()
 
 
-@pytest.mark.parametrize("V,B,k", [(4096, 5, 4), (4097, 5, 4), (12290, 3, 8), (8192, 70, 31)])
+@pytest.mark.parametrize("V,B,k", [(4096, 5, 4), (4097, 5, 4), (12290, 3, 8), (8192, 70, 31), (24576, 70, 31)])
 def test_a_drafted_id_outside_the_vocabulary_is_a_token_of_weight_zero(toy, V, B, k):
     """Histories are the caller's: an id that the model does not know (negative, the vocabulary's size, far beyond) is
     rejected like a token whose logit is -inf, and the other rows of the batch are decided as if it were not there.  The
-    oracle gets the logits with one more column, all -inf, and that column's id for every such token.  The last shape has
-    more than 2048 rows (sums of deeper nodes computed by the walk itself)."""
+    oracle gets the logits with one more column, all -inf, and that column's id for every such token.  The last two shapes have
+    2240 rows: all summed at once, and, 220 MB of logits, in stages."""
     from paper_2508_18588_amd import HS_ACCEPT_REJECTION
     from paper_2508_18588_amd.runtime import Engine
     from hs_inputs import ModelShape
@@ -466,9 +466,13 @@ def hs_workspace_bytes_of(eng):
     return hs_workspace_bytes(eng.ctx)
 
 
-@pytest.mark.parametrize("V,B,k,two", [(16401, 70, 31, True), (16400, 1000, 4, False)])
-def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, two):
-    """Many rows (here by the context's limits) are summed in stages, each for the nodes that the walks have reached: trees of
+@pytest.mark.parametrize("V,B,k,two,drafting", [
+    (16401, 70, 31, True, 70), (16404, 70, 31, True, 70),       # rows that are not, and that are 16-byte aligned
+    (16400, 1000, 4, False, 1000),                              # chains
+    (16400, 1000, 4, False, 100),                               # so few live rows that the first stage sums them all
+])
+def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, two, drafting):
+    """Many rows (here by the hint) are summed in stages, each for the nodes that the walks have reached: trees of
     every depth from none to k, on which the walks end at every level.  The decisions are the oracle's (unless its
     margin is below 1e-9) and those of one launch for all rows (which a hint of few rows asks for), also in a captured graph
     replayed with other logits, and while another stream overwrites sums and states."""
@@ -478,11 +482,15 @@ def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, 
     shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=V)
     rng = np.random.default_rng(V)
     eng = Engine(shape, make_weights(shape, 3), rope_table(64, 64), max_batch=B, k_max=k, c_max=2 if two else 1, max_len=80)
-    assert B * (1 + eng.c_max * k) * V * 4 >= 250e6
+    # the host's rule: from 200 MB of logits by the hint, no more than the limits allow; the first stage sums all of up to 100 MB
+    many = B * (1 + eng.c_max * k)
+    assert many * V * 4e-6 >= 200 > V * 4e-6
     ids = rng.integers(0, 2 ** 62, B)
     eng.load_sequences([np.array([0], np.int32)] * B, budgets=[99] * B, seq_ids=ids.astype(np.int64))
     trees = random_trees(rng, B, k, V, two)
+    trees[drafting:] = [oracle.build_tree([np.zeros(0, np.int64)], 1, 50) for _ in range(B - drafting)]
     m = eng.set_rows([dict(tok=t["tok"], parent=t["parent"], pos=t["pos"]) for t in trees])
+    assert (m * V * 4e-6 > 100) == (drafting == B)
     at = torch.tensor([(o + int(t["parent"][i])) * V + int(t["tok"][i])
                        for t, o in zip(trees, np.cumsum([0] + [len(t["tok"]) for t in trees])) for i in range(1, len(t["tok"]))],
                       device="cuda:0")
@@ -494,7 +502,7 @@ def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, 
         eng.set_rows_hint(hint)
         eng.accept(HS_ACCEPT_REJECTION, 1.0, 1234)
     logits(1)
-    accept(0)
+    accept(many)
     torch.cuda.synchronize()
     want, lg, st, r, depths = results_of(eng.st), np_of(eng.logits[:m]), {n: np_of(v) for n, v in eng.st.items()}, 0, set()
     for b, t in enumerate(trees):
@@ -512,7 +520,7 @@ def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, 
     assert live(results_of(eng.st)) == live(want)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        accept(0)
+        accept(many)
     for seed in (2, 3, 1):
         logits(seed)
         accept(1)
@@ -531,7 +539,7 @@ def test_sums_in_stages_equal_the_oracle_and_the_sums_of_all_rows(toy, V, B, k, 
         with torch.cuda.stream(side):
             for _ in range(40):
                 place.random_()
-        accept(0)
+        accept(many)
         torch.cuda.synchronize()
         assert live(results_of(eng.st)) == live(want)
     eng.close()

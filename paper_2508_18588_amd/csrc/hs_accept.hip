@@ -210,12 +210,12 @@ __device__ __forceinline__ double sum_slice(const float (&v)[PER], float largest
     return check_sum(v, largest, s);
 }
 
-// The sums come in stages from so many megabytes of logits on, by the hint or, of contexts with two candidates, by the
-// limits (trees of 17 rows over 152064 tokens, all rows at once against stages: 16 sequences, 165 MB, 64.5 against 67.7 us;
-// 24, 79 against 67; 32, 105 against 71; 64, 177 against 104; where more drafts are accepted 176 against 134).
-// Chains mostly have far fewer rows than the limits allow (64 chains of 9 rows: 104 against 108; 64 sequences of one row, 26
-// against 46), so there the limits only speak from the second figure on, where stages cost little against all the rows
-// that there might be.
+// The sums come in stages from so many megabytes of logits on, by the hint (trees of 17 rows over 152064 tokens, all rows at
+// once against stages: 16 sequences, 165 MB, 64.5 against 67.7 us; 24, 79 against 67; 32, 105 against 71; 64, 177 against 104;
+// where more drafts are accepted 176 against 134).  Without a hint there is only the most that the limits allow, and there may
+// be far fewer rows: 64 sequences of one row take 27 us at once and 40 in stages, four launches of which find nothing to do.
+// So the limits only speak from the second figure on, where stages cost little against all the rows that there might be (64
+// chains of 9 rows: 104 against 108).
 #ifndef HS_REJECT_STAGED_MB
 #define HS_REJECT_STAGED_MB 200
 #define HS_REJECT_STAGED_UNKNOWN_MB 1200
@@ -820,7 +820,7 @@ void launch_reject_stats(const hs_ctx* ctx, const accept_commit_args& a, int bat
     if (rows_hint > 0) mb = std::min(mb, rows_hint * row_mb);
     // enough workgroups to fill the chip: small batches split a sequence's rows, too
     auto split = [&](int per_seq) { return dim3(batch, a.n_slices, std::max(1, std::min(2048 / (a.n_slices * batch), per_seq))); };
-    if (depth < 3 || mb < (rows_hint > 0 || ctx->lim.c_max > 1 ? HS_REJECT_STAGED_MB : HS_REJECT_STAGED_UNKNOWN_MB)) {
+    if (depth < 3 || mb < (rows_hint > 0 ? HS_REJECT_STAGED_MB : HS_REJECT_STAGED_UNKNOWN_MB)) {
         p.all_rows = INT32_MAX;
         hipLaunchKernelGGL(reject_stats_kernel, split(nodes), dim3(256), 0, st, p, 1);
         return;

@@ -102,6 +102,7 @@ class Engine:
                         parr(w["wo"]), parr(w["wgate"]), parr(w["wup"]), parr(w["wdown"]), parr(w["norm1"]),
                         parr(w["norm2"]), self.rope.data_ptr())
         self.g_max = g_max
+        self.rows_hint, self._laid_out = 0, False
         lim = hs_limits(max_batch, k_max, c_max, self.max_rows, self.max_blocks, self.max_pos, w_max, g_max)
         self.ctx = hs_create(desc, hw, lim)
         self.flags = (HS_FLAG_FP32_ACTIVATIONS if precise else 0) | (HS_FLAG_WORKSPACE_LOGITS if workspace_logits else 0)
@@ -157,7 +158,7 @@ class Engine:
                               s["parent"].data_ptr(), s["anc_mask"].data_ptr(), s["row2seq"].data_ptr(),
                               self.logits.data_ptr() if self.logits is not None else None, s["argmax"].data_ptr(),
                               s["accept_len"].data_ptr(), s["n_out"].data_ptr(), s["out_tok"].data_ptr(),
-                              s["path_row"].data_ptr(), getattr(self, "rows_hint", 0), s["draft_src"].data_ptr())
+                              s["path_row"].data_ptr(), self.rows_hint, s["draft_src"].data_ptr())
 
     def close(self):
         if self.ctx:
@@ -215,6 +216,7 @@ class Engine:
     # ---------------------------------------------------------------- the four calls
 
     def draft(self, policy: Policy):
+        self._caller_hint()
         args = hs_draft_args(self.n_cand, self.hist.data_ptr(), self.hist_off.data_ptr(), policy.c())
         hs_draft(self.ctx, args, self.c_seq, self.c_step, self.stream())
 
@@ -234,6 +236,7 @@ class Engine:
         self.greward = _dev(np.asarray(rew, np.int32))
 
     def draft_group(self, policy: Policy):
+        self._caller_hint()
         args = hs_group_draft_args(self.n_resp, self.ghist.data_ptr(), self.ghist_off.data_ptr(),
                                    self.greward.data_ptr(), policy.c())
         hs_draft_group(self.ctx, args, self.c_seq, self.c_step, self.stream())
@@ -245,8 +248,12 @@ class Engine:
 
     def set_rows_hint(self, rows: int):
         """Tell the library how many rows to expect (a launch-shape hint; results do not depend on it)."""
-        self.rows_hint = int(rows)
-        self.c_step.rows_hint = self.rows_hint
+        self.rows_hint = self.c_step.rows_hint = int(rows)
+
+    def _caller_hint(self):
+        """The rows of set_rows are replaced by a draft's: their number is no hint any more."""
+        if self.rows_hint == 0 and self._laid_out:
+            self.c_step.rows_hint, self._laid_out = 0, False
 
     def verify(self):
         hs_verify(self.ctx, self.c_cache, self.c_seq, self.c_step, self.stream())
@@ -355,6 +362,9 @@ class Engine:
         s["parent"].copy_(torch.from_numpy(par))
         s["row2seq"].copy_(torch.from_numpy(r2s))
         s["anc_mask"].copy_(torch.from_numpy(anc.view(np.int64)))
+        # laid out here, the rows are known and not only expected (until the next draft, or the caller's own hint)
+        if self.rows_hint == 0:
+            self.c_step.rows_hint, self._laid_out = r, True
         return r
 
     def prefill(self, token_lists):
@@ -380,6 +390,7 @@ class Engine:
             self.set_rows(rows)
             self.verify()
         self.seq_len.copy_(saved)
+        self._caller_hint()
         torch.cuda.synchronize()
 
     def prefill_chunked(self, chunk: int = 512, kv_done=None):

@@ -1,4 +1,4 @@
-"""Register budgets of the two hot kernels, read from the compiler's own resource report (no GPU needed).
+"""Register budgets of the hot kernels, read from the compiler's own resource report (no GPU needed).
 
 The verify attention runs two workgroups per compute unit, i.e. 256 registers per wavefront, and its streaming loop
 uses every one of them: a change anywhere in the kernel that makes the register allocator spill puts scratch
@@ -8,6 +8,7 @@ import os
 import re
 import subprocess
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -39,8 +40,16 @@ def resource_report(source):
     return report
 
 
-def test_verify_attention_keeps_two_workgroups_per_compute_unit_without_scratch():
-    rep = resource_report("hs_attention.hip")
+@pytest.fixture(scope="module")
+def reports():
+    """The sources' reports, compiled side by side (a GEMM source takes minutes)."""
+    names = ("hs_gemm_stream.hip", "hs_gemm_wide.hip", "hs_accept.hip", "hs_attention.hip")
+    with ThreadPoolExecutor(len(names)) as ex:
+        return dict(zip(names, ex.map(resource_report, names)))
+
+
+def test_verify_attention_keeps_two_workgroups_per_compute_unit_without_scratch(reports):
+    rep = reports["hs_attention.hip"]
     kernels = {k: v for k, v in rep.items() if "attn_verify_mfma" in k}
     assert len(kernels) == 2, sorted(rep)                      # head_dim 128 and 64
     for name, r in kernels.items():
@@ -49,13 +58,16 @@ def test_verify_attention_keeps_two_workgroups_per_compute_unit_without_scratch(
         assert r["LDS Size [bytes/block]"] <= 80 * 1024, (name, r)
 
 
-def test_hot_gemm_instances_use_no_scratch():
-    rep = resource_report("hs_gemm_stream.hip")
+def test_hot_gemm_instances_use_no_scratch(reports):
+    rep = reports["hs_gemm_stream.hip"]
     # <EPI, PARTIAL, NU, MT, SA, SW> of a 7B-shape speculative step: gate/up, down, QKV and O, LM head (row maximum);
-    # and the same at 128 rows (the one-token steps)
+    # and the same at 128 rows (the one-token steps); then the passes of 64 rows: gate/up, O and down where K is not split, a
+    # head that keeps logits, the row maximum
     hot = ["ILi2ELb0ELi5ELi3ELi2ELi3EE", "ILi0ELb1ELi4ELi3ELi2ELi4EE", "ILi0ELb1ELi2ELi3ELi2ELi6EE",
            "ILi3ELb0ELi5ELi3ELi2ELi3EE", "ILi2ELb0ELi5ELi2ELi2ELi4EE", "ILi0ELb1ELi4ELi2ELi2ELi5EE",
-           "ILi0ELb1ELi2ELi2ELi2ELi8EE", "ILi3ELb0ELi5ELi2ELi2ELi4EE"]
+           "ILi0ELb1ELi2ELi2ELi2ELi8EE", "ILi3ELb0ELi5ELi2ELi2ELi4EE",
+           "ILi2ELb0ELi3ELi0ELi6ELi9EE", "ILi2ELb0ELi4ELi0ELi6ELi7EE", "ILi1ELb0ELi3ELi0ELi6ELi9EE", "ILi1ELb0ELi4ELi0ELi6ELi7EE",
+           "ILi0ELb0ELi3ELi0ELi6ELi9EE", "ILi0ELb0ELi4ELi0ELi6ELi7EE", "ILi3ELb0ELi4ELi0ELi6ELi7EE"]
     for tag in hot:
         names = [k for k in rep if "hs_gemm_stream" + tag in k]
         assert len(names) == 1, (tag, sorted(rep))
@@ -63,10 +75,19 @@ def test_hot_gemm_instances_use_no_scratch():
         assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (names[0], r)
 
 
-def test_greedy_acceptance_and_commit_fill_a_compute_unit():
+def test_the_gemm_for_many_rows_uses_no_scratch(reports):
+    """Four wavefronts with 256 accumulator registers and some 150 others each: one per SIMD, of 512."""
+    rep = {k: v for k, v in reports["hs_gemm_wide.hip"].items() if "hs_gemm_wide" in k}
+    assert len(rep) == 4, sorted(rep)                          # gate/up, split K, added, stored
+    for name, r in rep.items():
+        assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
+        assert r["VGPRs"] + r["AGPRs"] <= 512 and r["AGPRs"] == 256, (name, r)
+
+
+def test_greedy_acceptance_and_commit_fill_a_compute_unit(reports):
     """hs_accept_commit of a thousand sequences is one workgroup each: seven or eight of them per compute unit, not the one
     that the sampler's registers would leave."""
-    rep = resource_report("hs_accept.hip")
+    rep = reports["hs_accept.hip"]
     kernels = {k: v for k, v in rep.items() if "accept_commit_kernel" in k and "Lb0E" in k}
     assert len(kernels) == 2, sorted(rep)                      # bf16 and float caches
     for name, r in kernels.items():

@@ -301,3 +301,31 @@ def test_row_maxima_of_more_rows_than_the_hint_of_few():
         # (two fp32 sums of 1024 products in another order: the named column is within their rounding of the largest)
         assert (want.max(1).values - got <= 2e-4).all(), m
     eng.close()
+
+
+@pytest.mark.parametrize("n", [6380, 10316])
+def test_groups_side_by_side(n):
+    """Eight and more passes: an XCD runs four groups side by side, and the rest of its groups after them -- seven groups of
+    four units (eight wavefronts), six of eight units of which most XCDs have five (four wavefronts).  The product's
+    definition and the bits of launches with two passes, with all passes full, the last one ragged, and half of them empty."""
+    from paper_2508_18588_amd.runtime import Engine
+    k, hint = 192, 3072
+    shape = ModelShape(n_layers=1, d_model=192, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=192, vocab=10368)
+    eng = Engine(shape, make_weights(shape, 1), rope_table(64, 64), max_batch=1, k_max=0, c_max=1, max_len=32, max_rows=hint, keep_logits=False)
+    g = torch.Generator(device="cuda:0").manual_seed(n)
+    rnd = lambda r, s: (torch.randn(r, k, device="cuda:0", generator=g) * s).to(torch.bfloat16)
+    a, w = rnd(hint, 1.0), rnd(n, 0.05)
+    for m in (hint, 2825, 1500):
+        want = a[:m].double() @ w.double().T
+        outs = []
+        for h in (500, hint):
+            c = torch.full((hint, n), 15.0, device="cuda:0")
+            m_dev = torch.full((1,), m, dtype=torch.int32, device="cuda:0")
+            eng.gemm(0, a.view(torch.int16), w.view(torch.int16), None, c, m_dev, hint, h)
+            torch.cuda.synchronize()
+            assert (c[m:] == 15.0).all(), (m, h, "rows beyond M were written")
+            outs.append(c[:m])
+        # fp32 sums of 192 products
+        assert (outs[1].double() - want).abs().max() <= 2e-5 * (want.abs().max() + 1.0), m
+        assert torch.equal(outs[0], outs[1]), (m, "row hint changed the bits")
+    eng.close()

@@ -26,9 +26,10 @@
 //   * A load's constant distances (weight unit, row tile, stage slot) lie in the instruction itself: one scalar add (into m0), a
 //     nop and the load.  So do a fragment's, which then is one ds_read.  (With an address computation and a guard at each,
 //     a tile of the four-wavefront kernel was 302 instructions for its 64 MFMAs and took 1.15 times as long as the
-//     eight-wavefront one; at 188 it takes less.)  Only eight wavefronts with passes of 384 rows, which LDS binds, compute a
-//     fragment's address: it spaces their reads.  16448 columns of K = 3584, us at 256, 320, 352 and 384 rows: 47.6, 52.7, 58.2
-//     and 60.7, as single instructions 49.0, 56.0, 60.6 and 62.8; the 5 us of a split-K launch with few rows, 0.1 more.
+//     eight-wavefront one; at 188 it takes less.)  Only eight wavefronts with passes of 384 rows, which LDS binds, and fewer than five
+//     units compute a fragment's address: it spaces their reads.  16448 columns of K = 3584, us at 256, 320, 352 and 384
+//     rows: 47.6, 52.7, 58.2 and 60.7, as single instructions 49.0, 56.0, 60.6 and 62.8.  Five units are the same from 288 rows
+//     on and gain with single instructions below: 152064 columns at 220 rows 285 -> 281; the 5 us of a split-K launch with few rows 0.1.
 //   * Four wavefronts (hs_gemm_wide.hip) of 4 x 4 tiles, 256 rows x 8 units per workgroup, for many rows: a fragment is
 //     used four times, not three or two and a half, so that an MFMA costs 0.75 instead of 1.07 KB through LDS, less of
 //     the chip's power and fewer rounds of workgroups.  7B gate/up at 4096 rows 942 -> 890 us (1250 TFLOP/s), at 2048 rows
@@ -221,7 +222,7 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
     for (int ks = 0; ks < 4; ks++) at_ks[ks] = smem_off + frag_row + (((2 * ks + g) ^ fl) << 4);
     const int a_mine = rg * TILE_BYTES, w_mine_off = W_RING + U0 * TILE_BYTES;
     auto frag = [&](int set, int r, unsigned at_a, unsigned at_w) __attribute__((always_inline)) {
-        if constexpr (WV == 4 || MT < 3) {
+        if constexpr (WV == 4 || MT < 3 || NU == 5) {
             if (r < NUW) fb[set][r < NUW ? r : 0] = lds_fragment(at_w + r * TILE_BYTES);
             else fa[set][r >= NUW ? r - NUW : 0] = lds_fragment(at_a + WS::RG * (r - NUW) * TILE_BYTES);
         } else {

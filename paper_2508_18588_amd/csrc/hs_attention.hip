@@ -12,7 +12,7 @@
 // A = K tile from LDS, B = Q^T held in registers), so that each lane owns one query row -- the online-softmax
 // statistics are per-lane scalars and the exponentiated scores are already in the register layout the second
 // product O^T = V^T . P^T needs as its B operand.  V is stored in the cache with the token index fastest so V^T
-// tiles are plain 16-byte LDS reads (see attn_subtile).
+// operands are two plain 8-byte LDS reads (see load_values).
 //
 // Two ways to run a unit (= one partition of one (sequence, KV head)), chosen per sequence by its number of query
 // rows R = G * nn:
@@ -48,8 +48,9 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // A 32-key sub-tile (two pages) in LDS: K as 32 rows of HD elements, then V^T as two pages of HD rows of 16 tokens, both
 // without padding, so that a page's K or V^T block is one contiguous run that a load into LDS can fill.  16-byte chunks are
-// permuted instead, within a row of K and within a pair of V^T, so that 16 consecutive rows read at the same chunk
-// cover the 64 banks once (and a write of consecutive chunks does anyway).
+// permuted instead: within a row of K, so that 16 consecutive rows read at the same chunk cover the 64 banks once; of 16 rows of
+// V^T first the first halves, then the second ones, so that an operand is two 8-byte pieces a constant distance apart, and
+// 16 rows' pieces lie on different banks.
 template <int HD>
 struct sub_tile {
     static constexpr int PAGE = 32 * HD, V = 2 * PAGE, BYTES = 4 * PAGE;   // a page's K (or V^T) block, V^T's place, all
@@ -58,18 +59,21 @@ struct sub_tile {
     }
     // what 1 KB further on changes in the permutation
     static constexpr int k_step(int i) { return (HD == 128 ? 4 * i & 15 : 4 * i & 7) << 4; }
-    static __device__ __forceinline__ int v_at(int dim, int chunk) { return dim * 32 + ((chunk ^ ((dim >> 3) & 1)) << 4); }
+    static constexpr int V_HALF = 256;   // from a row's first to its second half
+    static __device__ __forceinline__ int v_at(int dim, int chunk) { return (dim >> 4) * 512 + chunk * V_HALF + (dim & 15) * 16; }
+    // where in a page's V^T block the 16 bytes that belong at 16 c of it in LDS come from
+    static __device__ __forceinline__ int v_from(int c) { return ((c >> 5) * 16 + (c & 15)) * 32 + ((c >> 4) & 1) * 16; }
 };
 
 // One 32-key sub-tile for one 32-row query tile: S^T = K.Q^T, online softmax per lane, O^T += V^T.P^T.
 // Every query row's arithmetic is independent of which other rows are in flight.
-// Row i of the A operand is not key i but key pi(i), bits 2 and 3 exchanged: element e of a lane's scores is then key
-// 16 (e / 8) + 8 half + e % 8, so that the eight probabilities of a page that a lane feeds to the second product belong to
-// eight consecutive tokens -- one 16-byte piece of a V^T row instead of two of 8 bytes.
+// Element e of a lane's scores is key 8 (e / 4) + 4 half + e % 4: the eight probabilities of a page that a lane feeds to the
+// second product belong to two runs of four tokens, and so do the V^T operand's two pieces.  (With the A operand's rows
+// permuted so that they are one run and the operand one 16-byte piece, the launch was 0 to 0.4 % shorter and every output
+// differed, by 0.002 to 0.003 of its size: the sums' order is kept.)
 template <int HD>
 __device__ __forceinline__ void load_keys(const unsigned char* tile, bf16x8 (&ka)[HD / 16], int half, int l32) {
-    const int krow = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
-    int k0 = sub_tile<HD>::k_at(krow, half);  // chunk 2 ks + half: the permutation is an exclusive or, and so is 2 ks
+    int k0 = sub_tile<HD>::k_at(l32, half);  // chunk 2 ks + half: the permutation is an exclusive or, and so is 2 ks
     asm volatile("" : "+v"(k0));              // (eight addresses kept across the caller's loop would spill)
 #pragma unroll
     for (int ks = 0; ks < HD / 16; ks++) ka[ks] = *reinterpret_cast<const bf16x8*>(tile + (k0 ^ (ks << 5)));
@@ -87,14 +91,15 @@ __device__ __forceinline__ f32x16 scores(const bf16x8 (&ka)[HD / 16], const bf16
 // Masks the scores (in tiles that reach past the cached prefix) and moves the running maximum.  (A maximum that only moves
 // where a score exceeds it by 2^8 spares most of the rescales, 1 % of a step with trees, but its probabilities are no longer
 // exactly 1 at the maximum: the error of a layer against 64 bits grew by 3 %.)
+// Returns what the sum so far is to be scaled by.
 template <int HD>
-__device__ __forceinline__ void take_maximum(f32x16& s, f32x16 (&o)[HD / 32], float& m_run, float& l_run, uint64_t anc,
-                                              int kbase, int L, int total, float scale_log2, int half) {
+__device__ __forceinline__ float take_maximum(f32x16& s, f32x16 (&o)[HD / 32], float& m_run, uint64_t anc, int kbase, int L,
+                                               int total, float scale_log2, int half) {
     // query row = this lane's.  Only tiles that reach past the cached prefix need the tree mask.
     if (kbase + 32 > L) {
 #pragma unroll
         for (int e = 0; e < 16; e++) {
-            const int kp = kbase + 16 * (e >> 3) + 8 * half + (e & 7);
+            const int kp = kbase + 8 * (e >> 2) + 4 * half + (e & 3);
             const bool vis = (kp < L) | ((kp < total) & (bool)((anc >> ((kp - L) & 63)) & 1ull));
             s[e] = vis ? s[e] : -INFINITY;
         }
@@ -111,19 +116,21 @@ __device__ __forceinline__ void take_maximum(f32x16& s, f32x16 (&o)[HD / 32], fl
     }
     const float m_new = fmaxf(m_run, tmax);
     // where it does not move for any of the 32 rows, multiplying by exactly 1 is skipped
+    float alpha = 1.f;
     if (__any(m_new != m_run)) {
-        const float alpha = fast_exp2(m_run - (m_new == -INFINITY ? 0.f : m_new));
+        alpha = fast_exp2(m_run - (m_new == -INFINITY ? 0.f : m_new));
         m_run = m_new;
-        l_run *= alpha;
 #pragma unroll
         for (int dt = 0; dt < HD / 32; dt++)
 #pragma unroll
             for (int e = 0; e < 16; e++) o[dt][e] *= alpha;
     }
+    return alpha;
 }
 
 // Probabilities of a sub-tile, as the second product's operand, and their sum.
-__device__ __forceinline__ void probabilities(const f32x16& s, float m_run, float& l_run, float scale_log2, bf16x8 (&pb)[2]) {
+__device__ __forceinline__ void probabilities(const f32x16& s, float m_run, float alpha, float& l_run, float scale_log2,
+                                              bf16x8 (&pb)[2]) {
     const float m_safe = (m_run == -INFINITY) ? 0.f : m_run;
     float psum = 0.f;
 #pragma unroll
@@ -133,14 +140,18 @@ __device__ __forceinline__ void probabilities(const f32x16& s, float m_run, floa
         pb[e >> 3][e & 7] = (__bf16)p;
     }
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(psum), __float_as_uint(psum), false, false);
-    l_run += __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    l_run = __builtin_fmaf(l_run, alpha, __uint_as_float(sw[0]) + __uint_as_float(sw[1]));
 }
 
 template <int HD>
 __device__ __forceinline__ bf16x8 load_values(const unsigned char* tile, int i, int half, int l32) {
     using T = sub_tile<HD>;
     constexpr int NDT = HD / 32;
-    return *reinterpret_cast<const bf16x8*>(tile + T::V + T::v_at(l32, half) + (i / NDT) * T::PAGE + (i % NDT) * 1024);
+    const unsigned char* at = tile + T::V + T::v_at(l32, 0) + 8 * half + (i / NDT) * T::PAGE + (i % NDT) * 1024;
+    union { u32x2 u[2]; bf16x8 v; } va;
+    va.u[0] = *reinterpret_cast<const u32x2*>(at);
+    va.u[1] = *reinterpret_cast<const u32x2*>(at + T::V_HALF);
+    return va.v;
 }
 
 template <int HD>
@@ -151,8 +162,8 @@ __device__ inline void attn_subtile(const unsigned char* tile, const bf16x8 (&qf
     bf16x8 ka[HD / 16], pb[2];
     load_keys<HD>(tile, ka, half, l32);
     f32x16 s = scores<HD>(ka, qf);
-    take_maximum<HD>(s, o, m_run, l_run, anc, kbase, L, total, scale_log2, half);
-    probabilities(s, m_run, l_run, scale_log2, pb);
+    const float alpha = take_maximum<HD>(s, o, m_run, anc, kbase, L, total, scale_log2, half);
+    probabilities(s, m_run, alpha, l_run, scale_log2, pb);
 #pragma unroll
     for (int i = 0; i < 2 * NDT; i++)
         o[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_values<HD>(tile, i, half, l32), pb[i / NDT], o[i % NDT], 0, 0, 0);
@@ -394,7 +405,7 @@ __device__ inline void attn_wave_stream(const AttnArgs& a, const int4* __restric
     int kb = k_begin;
     for (;;) {
         int k_to = k_put;
-        asm volatile("" : "+v"(k_to));   // (see attn_subtile)
+        asm volatile("" : "+v"(k_to));   // (see load_keys)
 #pragma unroll
         for (int pp = 0; pp < 2; pp++)
 #pragma unroll
@@ -490,8 +501,7 @@ __device__ inline void attn_wg_stream(const AttnArgs& a, const int4* __restrict_
 #pragma unroll
     for (int i = 0; i < CPW; i++) {
         const int c = lane + 64 * i;
-        const int to_k = T::k_at(c / (HD / 8), c % (HD / 8)), to_v = T::v_at(c >> 1, c & 1);   // (both their own inverse)
-        from[i] = is_v ? to_v : to_k;
+        from[i] = is_v ? T::v_from(c) : T::k_at(c / (HD / 8), c % (HD / 8));   // (K's permutation is its own inverse)
     }
 
     // Workgroups without wavefront units take the first ones by their number, all others what the counter hands out.
@@ -603,9 +613,9 @@ __device__ inline void attn_wg_stream(const AttnArgs& a, const int4* __restrict_
                 load_keys<HD>(ring + ((slot + 1) & (ATT_RING - 1)) * T::BYTES, ka, half, l32);
 #pragma unroll
                 for (int i = 0; i < 2 * NDT; i++) va[i] = load_values<HD>(ring + slot * T::BYTES, i, half, l32);
-                take_maximum<HD>(sc, o, m_run, l_run, anc, kb, cu.L, total, a.scale_log2, half);
+                const float alpha = take_maximum<HD>(sc, o, m_run, anc, kb, cu.L, total, a.scale_log2, half);
                 const f32x16 next = scores<HD>(ka, qf);     // (of the last sub-tile: of whatever lies there, not used)
-                probabilities(sc, m_run, l_run, a.scale_log2, pb);
+                probabilities(sc, m_run, alpha, l_run, a.scale_log2, pb);
 #pragma unroll
                 for (int i = 0; i < 2 * NDT; i++)
                     o[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pb[i / NDT], o[i % NDT], 0, 0, 0);

@@ -478,9 +478,9 @@ __device__ inline AttnUnit attn_unit_scalar(const int4* list, int it) {
 // about as many units as workgroups an early claim gives some of them two and others none.
 // The keys run one sub-tile ahead of the values, so that the next sub-tile's first product is issued between this one's
 // exponentials: an instruction takes a wavefront about eight clocks, and there are two of them on a SIMD.
-// Steps with a 128-key tile at a time and now (us; launches of the first 45 -> 40): 64 sequences of 2560 tokens, a third of
-// them with 9 rows, four 1.5B layers 579 -> 560; 64 trees of 17 rows over 8192 keys, one 14B layer 1413 -> 1390;
-// 256 sequences with a long tail of lengths, a 7B layer 1348 -> 1332.  What is
+// Steps with a 128-key tile at a time and now (us; launches of the first 45 -> 42): 64 sequences of 2560 tokens, a third of
+// them with 9 rows, four 1.5B layers 573 -> 553; 64 trees of 17 rows over 8192 keys, one 14B layer 1404 -> 1378;
+// 256 sequences with a long tail of lengths, a 7B layer 1335 -> 1323.  What is
 // left there: without its arithmetic the 14B launch takes 400 us of 470, without its loads 250, and the partial results
 // (see hs_create) are 70 of the 400.
 template <int HD>

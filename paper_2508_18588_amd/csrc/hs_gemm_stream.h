@@ -605,7 +605,7 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
         slot = rem - group * slots;
     } else if (n_pass > 1) {
         // (With many passes four groups side by side, the passes one after the other: the 32 workgroups of an XCD then share
-        // the operand tiles of 8 passes and 4 groups, 12 of them, where 16 passes and 2 groups are 18: 152064 columns of K = 3584 at 2176 rows 1966 -> 1897 us.)
+        // the operand tiles of 8 passes and 4 groups, 12 of them, where 16 passes and 2 groups are 18: 152064 columns of K = 3584 at 2176 rows, stored, 1966 -> 1897 us.)
         const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3, per_xcd = (n_groups + 7) >> 3;
         if (WV == 4 && local >= per_xcd * slots) return;
         const int side = slots >= 8 || 2 * passes <= n_pass ? 4 : 1, first = local / (side * slots) * side, n_side = min(side, per_xcd - first);

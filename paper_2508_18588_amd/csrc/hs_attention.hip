@@ -49,8 +49,9 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // A 32-key sub-tile (two pages) in LDS: K as 32 rows of HD elements, then V^T as two pages of HD rows of 16 tokens, both
 // without padding, so that a page's K or V^T block is one contiguous run that a load into LDS can fill.  16-byte chunks are
 // permuted instead: within a row of K, so that 16 consecutive rows read at the same chunk cover the 64 banks once; of 16 rows of
-// V^T first the first halves, then the second ones, so that an operand is two 8-byte pieces a constant distance apart, and
-// 16 rows' pieces lie on different banks.
+// V^T first the first halves, then the second ones, so that an operand is two 8-byte pieces a constant distance apart.  (32 lanes
+// read the same half of their chunks, so two of them meet on each bank: the counters show LDS busy 50 % of the cycles, 20 of
+// them conflicts, where single 16-byte pieces had 23 % and none; a 14B step with trees 1388 -> 1391 us.)
 template <int HD>
 struct sub_tile {
     static constexpr int PAGE = 32 * HD, V = 2 * PAGE, BYTES = 4 * PAGE;   // a page's K (or V^T) block, V^T's place, all

@@ -348,7 +348,7 @@ hs_status hs_gate_table_build(const float* ms, const int32_t* rows, int32_t n_po
  * max(tau(group 0, max_wks), t_train); d is bisected in [0, (tau(last group, min_wks) - t0) / (n_groups - 1)] down
  * to `precision`; for a given d a group takes the fewest workers that meet its target time.  Writes plan[n_groups]
  * and *d_out (the gradient the plan was computed for).  HS_ERR_CAPACITY: even the upper end of the interval needs
- * more than `wks` workers (plan untouched).  No device work; one GPU machine never runs it for more than one worker --
+ * more than `wks` workers (plan untouched).  No device work; a single GPU never needs it for more than one worker --
  * it pairs with the sequence-sharded layout described for several GPUs. */
 hs_status hs_plan_allocation(const double* tau, int32_t n_groups, int32_t min_wks, int32_t max_wks, int32_t wks,
                              double t_train, double precision, int32_t* plan, double* d_out);

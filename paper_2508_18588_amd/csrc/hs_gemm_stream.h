@@ -35,14 +35,21 @@
 //     the chip's power and fewer rounds of workgroups.  7B gate/up at 4096 rows 942 -> 890 us (1250 TFLOP/s), at 2048 rows
 //     490 -> 446; down at 4096 674 -> 615.  Without its loads 816, without its MFMAs 628; counters: matrix cores busy 65 % of the
 //     cycles at the 1.76 GHz that this load leaves the chip, LDS 32 %.
-//   * Passes of 64 rows and six activation stages (MT = 0) for up to 32 rows expected: with two, an activation tile was asked
-//     for one tile (a third of a microsecond) before its use.  7 rows of 1536, gate/up 15.4 -> 14.3 us, head 16.0 -> 14.7;
-//     12 rows of 3584, head of 16448 29.3 -> 25.9.  (Split K: chunks are too short, 9.2 -> 11.2; five units: 42.4 -> 44.3, the
-//     weight stream at 6.4 TB/s either way.)
-//   * What bounds it now: at up to 128 rows the weight stream (271 MB of gate/up weights in 50 us); at 220 rows LDS (184 KB a
+//   * Up to 160 rows expected (two to four units): three activation stages, and one wavefront group fetches the activations,
+//     the other the weights.  Loads count as landed in the order of their issue: while every wavefront fetched both, waiting for
+//     the next tile's activations, asked for last, meant waiting for weights asked for a tile before, and the weight ring
+//     was never more than that deep however many stages it had.  us, before and now: 1.5B gate/up at 7, 32, 64 and 100 rows
+//     13.9, 15.2, 16.5, 17.9 -> 12.0, 13.0, 15.0, 17.5; 16448 columns of K = 3584 at 7, 32, 64 and 128 rows 23.4, 25.3, 31.0,
+//     36.8 -> 22.1, 23.5, 27.0, 35.5; 14B gate/up at 7 and 32 rows 47.8, 52.2 -> 46.1, 50.1; 7B down at 64 rows 31.3 -> 30.2.
+//     Chunks of split K that are shorter than 16 tiles, five units (42 us either way) and passes of 384 rows (two activation
+//     stages are what LDS holds; 16448 columns at 217 rows 45.8, fetched apart 50.5) stay as they were.
+//   * Passes of 64 rows (MT = 0) for up to 32 rows expected: another 1 to 5 % (few_rows_rings).
+//   * What bounds it now: at up to 128 rows the weight stream (271 MB of gate/up weights in 50 us); from 160 rows on the two
+//     operands' ways into a compute unit, one after the other (1.5B gate/up at 165 rows, clocks a tile: weights alone 880, activations
+//     alone 820, both 1600, everything 1550, without either 1000); at 220 rows of a 7B shape LDS and the power they all draw (184 KB a
 //     tile are 1440 clocks, its MFMAs 1280; without its loads the head takes 210 of 285 us, without its MFMAs 258; a
-//     deeper weight ring changes nothing), with a prologue and an epilogue that nothing overlaps.  A third activation stage made
-//     every such shape slower (71 -> 77 us), the row pitch of the operands (55 to 65 lines of 128 bytes) is worth 5 % either way.
+//     deeper weight ring changes nothing), with a prologue and an epilogue that nothing overlaps.  A third activation stage in
+//     passes of 256 rows made every such shape slower (71 -> 77 us), the row pitch of the operands (55 to 65 lines of 128 bytes) is worth 5 % either way.
 // SwiGLU pairs the gate and up rows of 16 output columns in one 32-row weight unit, so that both pre-activations of
 // a column meet in one MFMA tile (lanes c and c+16).
 #pragma once
@@ -96,13 +103,21 @@ struct wave_units {
 // How the work of a workgroup lies on its WV wavefronts (8 or 4).  Two groups share the weight units; RG row groups share
 // the row tiles (tile t: row group t % RG), at most MI of them each.  Each wavefront fetches quarter `quad` (8 of 32 rows, a
 // 1 KB block) of weight units and row tiles: with eight wavefronts of its own group's units and of every second row
-// tile, with four of all.
-template <int NU, int MT, int GRP, int WV>
+// tile, with four of all.  With three and more activation stages (eight wavefronts) the first group fetches the row tiles
+// and the second the weight units: a wavefront's loads count as landed in the order they were issued, so where one
+// wavefront fetches both, waiting for the activations of the next tile (an L2 away, asked for last) means waiting for the
+// weights asked for just before them (a memory latency away) and the weight ring is never more than a tile deep.
+template <int NU, int MT, int SA, int GRP, int WV>
 struct wave_shape {
+    static constexpr bool SPLIT = SA > 2;
+    static_assert(!SPLIT || WV == 8, "four wavefronts fetch a quarter of everything each");
     static constexpr int RG = WV / 2, MI = (pass_shape<MT>::TILES + RG - 1) / RG;
-    static constexpr int FETCH_U0 = WV == 8 ? wave_units<NU, GRP>::U0 : 0, FETCH_U = WV == 8 ? wave_units<NU, GRP>::N : NU;
-    static constexpr int FETCH_A = WV == 8 ? pass_shape<MT>::TILES / 2 : pass_shape<MT>::TILES;   // row tiles fetched ...
-    static constexpr int FETCH_A0 = WV == 8 ? GRP : 0, FETCH_AS = WV == 8 ? 2 : 1;                 // ... first, stride
+    static constexpr bool OWN = WV == 8 && !SPLIT;                                                // own group's share of both
+    static constexpr int FETCH_U0 = OWN ? wave_units<NU, GRP>::U0 : 0;
+    static constexpr int FETCH_U = OWN ? wave_units<NU, GRP>::N : SPLIT && GRP == 0 ? 0 : NU;     // weight units fetched
+    static constexpr int FETCH_A = SPLIT && GRP == 1 ? 0 : pass_shape<MT>::TILES / (OWN ? 2 : 1); // row tiles fetched ...
+    static constexpr int FETCH_A0 = OWN ? GRP : 0, FETCH_AS = OWN ? 2 : 1;                         // ... first, stride
+    static constexpr int U_SIZE = FETCH_U ? FETCH_U : 1, A_SIZE = FETCH_A ? FETCH_A : 1;          // (of arrays)
 };
 
 // The 1 KB blocks of weight tile kt that a wavefront fetches, into stage kt % SW of the weight ring.  (A SwiGLU unit holds 16
@@ -110,12 +125,12 @@ struct wave_shape {
 // up rows -- 2, 3.)
 template <int NU, int MT, int SA, int SW, int GRP, int WV>
 __device__ __forceinline__ void issue_weight_tile(const stream_args& p, const unsigned char* w_mine, unsigned smem_off,
-                                                  const unsigned (&w_off)[wave_shape<NU, MT, GRP, WV>::FETCH_U], int quad, int kt) {
+                                                  const unsigned (&w_off)[wave_shape<NU, MT, SA, GRP, WV>::U_SIZE], int quad, int kt) {
     constexpr int W_RING = SA * pass_shape<MT>::TILES * TILE_BYTES, W_STAGE = NU * TILE_BYTES;
-    const unsigned dst = smem_off + W_RING + (kt % SW) * W_STAGE + wave_shape<NU, MT, GRP, WV>::FETCH_U0 * TILE_BYTES + quad * 1024;
+    const unsigned dst = smem_off + W_RING + (kt % SW) * W_STAGE + wave_shape<NU, MT, SA, GRP, WV>::FETCH_U0 * TILE_BYTES + quad * 1024;
     const unsigned char* base = w_mine + (size_t)kt * ROW_BYTES;
 #pragma unroll
-    for (int j = 0; j < wave_shape<NU, MT, GRP, WV>::FETCH_U; j++) {
+    for (int j = 0; j < wave_shape<NU, MT, SA, GRP, WV>::FETCH_U; j++) {
         if (WV == 8 && p.w_once) load_to_lds_16_stream(base, w_off[j], dst, j * 4096);
         else load_to_lds_16(base, w_off[j], dst, j * 4096);
     }
@@ -125,9 +140,9 @@ __device__ __forceinline__ void issue_weight_tile(const stream_args& p, const un
 // barriers only).
 template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int NMI, int WV>
 __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char* smem, unsigned smem_off,
-                                             const unsigned (&w_off)[wave_shape<NU, MT, GRP, WV>::FETCH_U], int quad, int rg, int lane) {
-    using WS = wave_shape<NU, MT, GRP, WV>;
-    static_assert(SA >= 2 && SW > SA && (SA == 2 || (MT == 0 && WV == 8)), "the wait counts below (n_a is 0 or NSA = 1 where SA > 2)");
+                                             const unsigned (&w_off)[wave_shape<NU, MT, SA, GRP, WV>::U_SIZE], int quad, int rg, int lane) {
+    using WS = wave_shape<NU, MT, SA, GRP, WV>;
+    static_assert(SA >= 2 && SW > SA, "the wait counts below");
     constexpr int A_STAGE = pass_shape<MT>::TILES * TILE_BYTES, W_STAGE = NU * TILE_BYTES, W_RING = SA * A_STAGE;
     constexpr int NUW = wave_units<NU, GRP>::N, U0 = wave_units<NU, GRP>::U0;
     constexpr int NLW = WS::FETCH_U;   // 1 KB load instructions per weight tile and wavefront
@@ -147,7 +162,7 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
     for (int l = 0; l < NSA; l++)
         if (p.m0 + 32 * WS::FETCH_A0 + 8 * quad + A_ROWS * l < p.M) n_a = l + 1;
     n_a = __builtin_amdgcn_readfirstlane(n_a);
-    unsigned a_off[NSA];
+    unsigned a_off[WS::A_SIZE];
 #pragma unroll
     for (int l = 0; l < NSA; l++) a_off[l] = (unsigned)min(a_row + A_ROWS * l, p.M - 1) * row_pitch + a_chunk;
     const unsigned a_dst0 = smem_off + WS::FETCH_A0 * TILE_BYTES + quad * 1024;              // + stage + l * A_BYTES
@@ -160,7 +175,7 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
             if (l < n_a) load_to_lds_16(base, a_off[l], a_dst0 + (kt % SA) * A_STAGE, l * A_BYTES);
     };
     const unsigned char* w_mine = uniform_ptr((EPI == HS_EPI_SWIGLU_BF16 && quad >= 2) ? p.wb[1] : p.wb[0]);
-    auto issue_w = [&](int kt) { issue_weight_tile<NU, MT, SA, SW, GRP, WV>(p, w_mine, smem_off, w_off, quad, kt); };
+    auto issue_w = [&](int kt) { if constexpr (NLW > 0) issue_weight_tile<NU, MT, SA, SW, GRP, WV>(p, w_mine, smem_off, w_off, quad, kt); };
     // Hand-over number h (h < kt0 before the loop, then in the last quarter of tile h): first the activation tile h+SA,
     // then the weight tile h+SW.  The issue order fixes the wait counts below.
     auto issue_for = [&](int h) {
@@ -169,19 +184,21 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
     };
     // Loads complete in issue order.  Tile t is awaited in tile t-1, when the hand-overs up to t-2 have been made.  Its
     // activation part was issued at hand-over t-SA, its weight part at t-SW (earlier).  What may still be outstanding is
-    // what was issued after the activation part: the weight tiles of hand-overs t-SA to t-2 and the activation tiles of
-    // t-SA+1 to t-2, as far as there are such tiles.
+    // what the wavefront issued after the last of its own parts of tile t: where it fetches activations, the weight tiles of
+    // hand-overs t-SA to t-2 and the activation tiles of t-SA+1 to t-2; where it fetches weights alone, the weight tiles of
+    // hand-overs t-SW+1 to t-2; as far as there are such tiles.
     auto wait_tile = [&](int t) {
         int n = 0;
 #pragma unroll
-        for (int h = -SA; h <= -2; h++) {
+        for (int h = NSA ? -SA : -SW + 1; h <= -2; h++) {
             if (t + h + SW < p.kt1) n += NLW;
             if (h > -SA && t + h + SA < p.kt1) n += n_a;
         }
-        switch (n) {   // (at most 5 x 3 + 4)
+        switch (n) {   // (at most 7 x 3)
 #define HS_CASE(i) case i: HS_WAIT_VMCNT(i); break;
             HS_CASE(1) HS_CASE(2) HS_CASE(3) HS_CASE(4) HS_CASE(5) HS_CASE(6) HS_CASE(7) HS_CASE(8) HS_CASE(9) HS_CASE(10)
-            HS_CASE(11) HS_CASE(12) HS_CASE(13) HS_CASE(14) HS_CASE(15) HS_CASE(16) HS_CASE(17) HS_CASE(18) HS_CASE(19)
+            HS_CASE(11) HS_CASE(12) HS_CASE(13) HS_CASE(14) HS_CASE(15) HS_CASE(16) HS_CASE(17) HS_CASE(18) HS_CASE(19) HS_CASE(20)
+            HS_CASE(21)
 #undef HS_CASE
             default: HS_WAIT_VMCNT(0);
         }
@@ -293,9 +310,10 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
             for (int l = 0; l < NLW; l++) load_w(l);
         }
         if (G == 1) wait_tile(kt + 1);
+        else if (!NSA) HS_WAIT_VMCNT((SW - 2) * NLW);
         else if (SA == 2) HS_WAIT_VMCNT(NLW);
-        else if (G == 0) HS_WAIT_VMCNT((SA - 1) * NLW + (SA - 2) * NSA);
-        else HS_WAIT_VMCNT((SA - 1) * NLW);
+        else if (G == 0) HS_WAIT_VMCNT((SA - 2) * NSA);
+        else wait_tile(kt + 1);
         __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4) | (0 << 8)); /* lgkmcnt(0) */
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -467,10 +485,12 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
 
 namespace {
 
-// Weight stages of the 256-row passes that a 64-row instance falls back to: those of the 256-row instance.
+// The rings of a 64-row instance.  Its LDS is that of the 256-row passes it falls back to (FALL_SA, FALL_SW stages, those of the
+// 256-row instance); of it, passes of 64 rows use SA and SW stages: with more on its way a launch takes longer (7 rows of
+// 3584, head of 16448 columns: 4 and 5 stages 22.1 us, 3 and 4 22.7, 5 and 6 22.9, 6 and 9 25.3).
 template <int NU>
-struct few_rows_fallback {
-    static constexpr int SW = NU == 3 ? 7 : 5;
+struct few_rows_rings {
+    static constexpr int SA = NU == 3 ? 4 : 3, SW = NU == 3 ? 5 : 4, FALL_SA = 3, FALL_SW = NU == 3 ? 5 : 4;
     static_assert(NU == 3 || NU == 4, "the 64-row instances");
 };
 
@@ -485,13 +505,13 @@ struct wide_share {
 template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int WV>
 __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem, unsigned smem_off, int quad, int rg, int lane,
                                              int pass, int n_pass) {
-    using WS = wave_shape<NU, MT, GRP, WV>;
+    using WS = wave_shape<NU, MT, SA, GRP, WV>;
     // Weight loader geometry: instruction j of quarter w fills the 1 KB block of rows 8w..8w+7 of unit FETCH_U0 + j; lane i
     // lands on row i/8, chunk position i%8 and therefore fetches chunk (i%8) ^ swz(row).  Rows beyond N are clamped to
     // the last valid row: their products are computed and never stored.
     // (32-bit byte offsets: the host checks that every operand stays below 4 GiB.)
     const int lrow = lane >> 3, lpos = lane & 7;
-    unsigned w_off[WS::FETCH_U];
+    unsigned w_off[WS::U_SIZE];
 #pragma unroll
     for (int j = 0; j < WS::FETCH_U; j++) {
         const int row = 8 * quad + lrow, unit = WS::FETCH_U0 + j;  // (row within the unit)
@@ -500,7 +520,7 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
     }
     // The weight-only hand-overs of the first chunk's prologue go out now: they do not depend on the row count,
     // whose load from device memory (the kernel's first statement) is still on its way -- nothing has used it yet.
-    {
+    if constexpr (WS::FETCH_U > 0) {
         const unsigned char* w_mine = uniform_ptr((EPI == HS_EPI_SWIGLU_BF16 && quad >= 2) ? p.wb[1] : p.wb[0]);
 #pragma unroll
         for (int h = -SW; h < -SA; h++)
@@ -514,7 +534,7 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
             HS_WAIT_VMCNT(0);
             __syncthreads();
             p.w_pre = 0;
-            stream_group<EPI, PARTIAL, NU, 2, 2, few_rows_fallback<NU>::SW, GRP, WV>(p, smem, smem_off, quad, rg, lane, pass, n_pass);
+            stream_group<EPI, PARTIAL, NU, 2, few_rows_rings<NU>::FALL_SA, few_rows_rings<NU>::FALL_SW, GRP, WV>(p, smem, smem_off, quad, rg, lane, pass, n_pass);
             return;
         }
     }
@@ -626,8 +646,13 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
     p.kt1 = min(nk, p.kt0 + tpc);
 
     if constexpr (WV == 8) {
-        if (wave < 4) stream_group<EPI, PARTIAL, NU, MT, SA, SW, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, passes);
-        else stream_group<EPI, PARTIAL, NU, MT, SA, SW, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, passes);
+        auto run = [&](auto sa_c, auto sw_c) __attribute__((always_inline)) {
+            constexpr int A_STAGES = decltype(sa_c)::value, W_STAGES = decltype(sw_c)::value;
+            if (wave < 4) stream_group<EPI, PARTIAL, NU, MT, A_STAGES, W_STAGES, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, passes);
+            else stream_group<EPI, PARTIAL, NU, MT, A_STAGES, W_STAGES, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, passes);
+        };
+        if constexpr (MT == 0) run(std::integral_constant<int, few_rows_rings<NU>::SA>{}, std::integral_constant<int, few_rows_rings<NU>::SW>{});
+        else run(std::integral_constant<int, SA>{}, std::integral_constant<int, SW>{});
     } else {
         auto run = [&](auto nu_c, auto sw_c) __attribute__((always_inline)) {
             constexpr int U = decltype(nu_c)::value, S = decltype(sw_c)::value;
@@ -652,7 +677,8 @@ void launch_shape(Kernel kernel, bool& configured, const bf16_t* a, const bf16_t
     constexpr size_t lds = (size_t)(SA * pass_shape<MT>::TILES + SW * NU) * TILE_BYTES;
     static_assert(lds <= 160 * 1024, "LDS of one compute unit");
     if constexpr (MT == 0)
-        static_assert((2 * pass_shape<2>::TILES + few_rows_fallback<NU>::SW * NU) * TILE_BYTES <= lds, "the fallback's rings");
+        static_assert((few_rows_rings<NU>::FALL_SA * pass_shape<2>::TILES + few_rows_rings<NU>::FALL_SW * NU) * TILE_BYTES <= lds &&
+                          few_rows_rings<NU>::SA <= SA && few_rows_rings<NU>::SW <= SW, "the rings of either pass");
     if (!configured) {      // more than 64 KB of dynamic LDS has to be asked for once per kernel
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         configured = true;

@@ -1,7 +1,8 @@
 // Instances of the bf16 MFMA GEMM (hs_gemm_stream.h) with eight wavefronts per workgroup, and the choice of an instance.
 #include "hs_gemm_stream.h"
 
-// NU weight units per workgroup, MT row tiles per wavefront pair (128*MT rows per pass; 64 for MT = 0), SA / SW ring stages.
+// NU weight units per workgroup, MT row tiles per wavefront pair (128*MT rows per pass; 64 for MT = 0), SA / SW ring stages
+// (three and more activation stages: the two operands are fetched by a wavefront group each).
 // (External linkage: the host takes the kernel's address to raise its dynamic LDS limit.)
 template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW>
 __global__ __launch_bounds__(512) void hs_gemm_stream(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
@@ -26,6 +27,9 @@ void launch_stream(const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, 
 #ifndef HS_FEW_ROWS
 #define HS_FEW_ROWS 32
 #endif
+// Split K in chunks of at least this many k-tiles fetches the two operands apart (7B down, 33 tiles: 1 to 4 %; QKV of the 1.5B
+// shape, in chunks of 4, would take 5.4 us instead of 5.1, its down projection, in chunks of 14, the same either way).
+constexpr int HS_APART_TILES = 16;
 constexpr int HS_WIDE_KERNEL_ROWS = 512;
 #ifndef HS_WIDE_GROUP_ROWS
 #define HS_WIDE_GROUP_ROWS 352   // measured cross-over at the 7B shape: 33 vs 40 us at 300 rows, 49 vs 37 us at 385
@@ -93,12 +97,13 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
         if constexpr (EPI != HS_EPI_ROWMAX) {
             if (tall) launch_stream<EPI, PARTIAL, 3, 3, 2, 5>(HS_ARGS);
             else if (few) { if constexpr (!PARTIAL) launch_stream<EPI, PARTIAL, 3, 0, 6, 9>(HS_ARGS); }
-            else launch_stream<EPI, PARTIAL, 3, 2, 2, 7>(HS_ARGS);
+            else launch_stream<EPI, PARTIAL, 3, 2, 3, 5>(HS_ARGS);
         }
     } else {
         if (tall) launch_stream<EPI, PARTIAL, 4, 3, 2, 4>(HS_ARGS);
         else if (few) { if constexpr (!PARTIAL) launch_stream<EPI, PARTIAL, 4, 0, 6, 7>(HS_ARGS); }
-        else launch_stream<EPI, PARTIAL, 4, 2, 2, 5>(HS_ARGS);
+        else if (PARTIAL && tpc < HS_APART_TILES) { if constexpr (PARTIAL) launch_stream<EPI, PARTIAL, 4, 2, 2, 5>(HS_ARGS); }
+        else launch_stream<EPI, PARTIAL, 4, 2, 3, 4>(HS_ARGS);
     }
 #undef HS_ARGS
 }

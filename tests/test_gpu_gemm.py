@@ -329,3 +329,40 @@ def test_groups_side_by_side(n):
         assert (outs[1].double() - want).abs().max() <= 2e-5 * (want.abs().max() + 1.0), m
         assert torch.equal(outs[0], outs[1]), (m, "row hint changed the bits")
     eng.close()
+
+
+@pytest.mark.parametrize("epi,n,k", [(0, 1616, 64), (2, 1616, 128), (0, 1616, 192), (1, 1616, 320), (2, 1616, 448), (0, 28832, 320),
+                                     (0, 3600, 18432), (1, 3600, 18432)])
+def test_operands_fetched_by_a_wavefront_group_each(epi, n, k):
+    """Launches for up to 160 expected rows fetch activations and weights in different wavefronts, each group with waits of its
+    own: fewer k-tiles than either ring has stages, as many, more; three and four units to a group, split K; row counts around
+    the edges of 8-row blocks, tiles and passes, below and above the hint.  The product's definition in fp64, and the bits of
+    the launch for many rows."""
+    from paper_2508_18588_amd.runtime import Engine
+    rows = 300
+    shape = ModelShape(n_layers=1, d_model=3648 if k > 448 else 448, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ffn=max(k, 448),
+                       vocab=max(n, 512))
+    eng = Engine(shape, make_weights(shape, 1), rope_table(64, 128), max_batch=1, k_max=0, c_max=1, max_len=32, max_rows=rows,
+                 keep_logits=False)
+    g = torch.Generator(device="cuda:0").manual_seed(n + k)
+    rnd = lambda r, s: (torch.randn(r, k, device="cuda:0", generator=g) * s).to(torch.bfloat16)
+    a, w, w2 = rnd(rows, 1.0), rnd(n, 0.05), rnd(n, 0.05) if epi == 2 else None
+    bits = lambda t: None if t is None else t.view(torch.int16)
+    for m in (1, 7, 9, 32, 63, 65, 160, 257, rows):
+        want = a[:m].double() @ w.double().T
+        if epi == 2:
+            want = want * torch.sigmoid(want) * (a[:m].double() @ w2.double().T)
+        outs = []
+        for h in (300, 1, 32, 33, 160):
+            c = torch.full((rows, n), 15.0, device="cuda:0", dtype=torch.bfloat16 if epi == 2 else torch.float32)
+            m_dev = torch.full((1,), m, dtype=torch.int32, device="cuda:0")
+            eng.gemm(epi, bits(a), bits(w), bits(w2), bits(c) if epi == 2 else c, m_dev, rows, h)
+            torch.cuda.synchronize()
+            assert (c[m:] == 15.0).all(), (m, h, "rows beyond M were written")
+            outs.append(c[:m])
+        # fp32 sums of k products of size 0.05: an error of 2^-24 each, at most sqrt(k) of them in a row's favour times ten;
+        # one bf16 rounding of the result (SwiGLU)
+        tol = 2.0 ** -8 * (want.abs().max() + 1.0) if epi == 2 else 10 * 2.0 ** -24 * k ** 0.5 * (float(want.abs().max()) + 15.0)
+        assert (outs[0].double() - want - (15.0 if epi == 1 else 0.0)).abs().max() <= tol, m
+        assert all(torch.equal(outs[0], o) for o in outs[1:]), (m, "row hint changed the bits")
+    eng.close()

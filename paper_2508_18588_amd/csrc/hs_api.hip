@@ -53,6 +53,7 @@ void layout_workspace(hs_ctx* ctx) {
     w.gemm_part_bytes = M * part_cols * 4;
     w.gemm_part = take(w.gemm_part_bytes);
     w.pf_len = take((size_t)l.max_batch * 4);
+    w.row_info = take(M * sizeof(hs_row_info));
     w.att_work = take((size_t)(2 + d.n_layers) * 4);
     w.att_list = take(2 * hs_attention_max_units(ctx) * 32);
     w.reject_walk = take((size_t)l.max_batch * 16);
@@ -325,6 +326,7 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
     const int nqkv = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
     // Few rows expected: run the narrow projections split over K (same arithmetic, more workgroups).
     const int hint = step->rows_hint > 0 ? step->rows_hint : m_max;
+    const int expected = step->rows_hint > 0 ? std::min(step->rows_hint, m_max) : 0;   // (no estimate: the limits are none)
     const size_t cap_slot = capture_slot_bytes(ctx), cap_xn = hs_fp32_activations(ctx) ? cap_slot : cap_slot / 2;
 
     (void)hipGetLastError();
@@ -339,8 +341,8 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
     int pend = 0;
     for (int l = 0; l < d.n_layers; l++) {
         pr.begin(3);
-        if (l == 0) hs_launch_embed_norm(ctx, seq, step, seq->batch, x, ctx->norm1[0], xn, st);
-        else hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, st);
+        if (l == 0) hs_launch_embed_norm(ctx, cache, seq, step, true, x, ctx->norm1[0], xn, st);
+        else hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, expected, st);
         pr.end();
         if (ctx->capture && l + 1 == d.n_layers) {
             (void)hipMemcpyAsync(ctx->capture, xn, cap_xn, hipMemcpyDeviceToDevice, st);
@@ -351,19 +353,19 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
                        &pend);
         pr.end();
         pr.begin(3);
-        hs_launch_rope_kv(ctx, l, cache, seq, step, qkv, q, pend, st);
+        hs_launch_rope_kv(ctx, l, cache, seq, step, qkv, q, pend, expected, st);
         pr.end();
         pr.begin(0, l % 4 == 0);
         hs_launch_attention(ctx, l, cache, seq, step, q, attn, st);
         pr.end();
         pr.begin(3);
-        hs_launch_attention_merge(ctx, seq, step, attn, st);
+        hs_launch_attention_merge(ctx, seq, step, attn, expected, st);
         pr.end();
         pr.begin(1);
         hs_launch_gemm(ctx, HS_EPI_ADD_F32, attn, ctx->wo[l], nullptr, x, m_dev, m_max, d.d_model, qh, hint, st, &pend);
         pr.end();
         pr.begin(3);
-        hs_launch_rmsnorm(ctx, x, ctx->norm2[l], xn, m_dev, pend, st);
+        hs_launch_rmsnorm(ctx, x, ctx->norm2[l], xn, m_dev, pend, expected, st);
         pr.end();
         if (ctx->capture && l + 1 == d.n_layers) {
             (void)hipMemcpyAsync(ctx->capture + 2 * cap_slot, xn, cap_xn, hipMemcpyDeviceToDevice, st);
@@ -378,7 +380,7 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
         pr.end();
     }
     pr.begin(3);
-    hs_launch_rmsnorm(ctx, x, ctx->norm_f, xn, m_dev, pend, st);
+    hs_launch_rmsnorm(ctx, x, ctx->norm_f, xn, m_dev, pend, expected, st);
     pr.end();
     if (head_fused) {
         // no [rows][vocab] array: the LM head leaves one (largest value, column) key per row and column group,
@@ -393,7 +395,7 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
                        st);
         pr.end();
         pr.begin(3);
-        hs_launch_argmax(ctx, logits, step->argmax, m_dev, st);
+        hs_launch_argmax(ctx, logits, step->argmax, m_dev, expected, st);
         pr.end();
     }
     if (ctx->profile) {
@@ -429,24 +431,25 @@ hs_status hs_prefill(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* 
     const int qh = d.n_q_heads * d.head_dim;
     const int nqkv = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
     const int hint = args->rows_hint > 0 ? args->rows_hint : m_max;
+    const int expected = args->rows_hint > 0 ? std::min(args->rows_hint, m_max) : 0;
     // the row kernels place a row at slot (sequence length - 1 + its index): here that is kv_done + i
     hs_seq_state pf = *seq;
     pf.seq_len = len_plus1;
 
     (void)hipGetLastError();
-    hs_launch_prefill_rows(ctx, seq, args->kv_done, args->chunk, step, len_plus1, st);
+    hs_launch_prefill_rows(ctx, cache, seq, args->kv_done, args->chunk, step, len_plus1, st);
     int pend = 0;
     for (int l = 0; l < d.n_layers; l++) {
-        if (l == 0) hs_launch_embed_norm(ctx, nullptr, step, seq->batch, x, ctx->norm1[0], xn, st);
-        else hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, st);
+        if (l == 0) hs_launch_embed_norm(ctx, cache, &pf, step, false, x, ctx->norm1[0], xn, st);
+        else hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, expected, st);
         hs_launch_gemm(ctx, HS_EPI_STORE_F32, xn, ctx->wqkv[l], nullptr, qkv, m_dev, m_max, nqkv, d.d_model, hint, st,
                        &pend);
-        hs_launch_rope_kv(ctx, l, cache, &pf, step, qkv, q, pend, st);
+        hs_launch_rope_kv(ctx, l, cache, &pf, step, qkv, q, pend, expected, st);
         pend = 0;
         if (l + 1 == d.n_layers) break;   // the last layer's K/V are written: nothing downstream is needed
         hs_launch_attention_prefill(ctx, l, cache, &pf, len_plus1, step, q, attn, args->chunk, st);
         hs_launch_gemm(ctx, HS_EPI_ADD_F32, attn, ctx->wo[l], nullptr, x, m_dev, m_max, d.d_model, qh, hint, st, &pend);
-        hs_launch_rmsnorm(ctx, x, ctx->norm2[l], xn, m_dev, pend, st);
+        hs_launch_rmsnorm(ctx, x, ctx->norm2[l], xn, m_dev, pend, expected, st);
         hs_launch_gemm(ctx, HS_EPI_SWIGLU_BF16, xn, ctx->wgate[l], ctx->wup[l], act, m_dev, m_max, d.d_ffn, d.d_model, hint, st);
         hs_launch_gemm(ctx, HS_EPI_ADD_F32, act, ctx->wdown[l], nullptr, x, m_dev, m_max, d.d_model, d.d_ffn, hint, st,
                        &pend);

@@ -788,60 +788,83 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
 // Combine the partitions of one (row, query head) in partition order: one wavefront per (row, head), four per
 // workgroup; rows are strided over the grid's x dimension (the row count is only known on the device).  Lane p
 // holds partition p's (max, sum); weights are broadcast from there.
+// A chain of memory round trips per row: the number of partitions (one load, written once per pass; the next row's is asked
+// for a row ahead), then the weights and the first eight partitions' outputs together, in 4-byte pieces of two elements.
+// With few rows expected the first row's loads do not wait for the number of partitions either (up to max_parts, in bounds).
+constexpr int HS_MERGE_EARLY_ROWS = 32;
 template <int HD>
-__global__ __launch_bounds__(256) void attn_merge(const _Float16* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                   const int32_t* __restrict__ row2seq, const int32_t* __restrict__ row_off,
-                                                   const int32_t* __restrict__ seq_len, int batch, int max_parts,
-                                                   int part_keys, int hq, bf16_t* __restrict__ out) {
+__global__ __launch_bounds__(256) void attn_merge(const _Float16* part_o, const float* part_ml,
+                                                  const hs_row_info* infos, const int32_t* m_dev,
+                                                  int max_parts, int max_rows, int hq, bf16_t* __restrict__ out, int expected) {
+    constexpr int E = HD / 64, AHEAD = 8;      // elements of a lane: E * lane, ...
+    typedef _Float16 piece __attribute__((ext_vector_type(E)));
     const int head = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (head >= hq) return;
-    const int m = row_off[batch];
-    for (int row = blockIdx.x; row < m; row += gridDim.x) {
-        const int b = row2seq[row];
-        const int total = seq_len[b] - 1 + (row_off[b + 1] - row_off[b]);
-        const int nparts = min(max_parts, (total + part_keys - 1) / part_keys);
+    int row = blockIdx.x, lim = max_parts;
+    if (row >= expected || expected > HS_MERGE_EARLY_ROWS) {
+        if (row >= *m_dev) return;
+        lim = infos[row].parts;
+    }
+    for (;;) {
+        const unsigned zero = hs_opaque_zero();     // (all of a row's loads inside the loop: one in front of it would be waited for there)
+        const int m_lane = m_dev[zero], parts_lane = infos[row + zero].parts;
+        const int next = min(row + (int)gridDim.x, max_rows - 1);
         const size_t prow = ((size_t)row * hq + head) * max_parts;
+        const float2* ml = reinterpret_cast<const float2*>(part_ml) + prow;
+        const _Float16* po = part_o + prow * HD + E * lane;
+        const float2 ml0 = ml[min(lane, lim - 1)];
+        piece v[AHEAD];
+#pragma unroll
+        for (int q = 0; q < AHEAD; q++) v[q] = *reinterpret_cast<const piece*>(po + (size_t)min(q, lim - 1) * HD);
+        const int next_lane = infos[next + zero].parts;
+        hs_loads_issued();
+        const int m = hs_uniform(m_lane), nparts = hs_uniform(parts_lane);
+        if (row >= m) return;
         float mg = -INFINITY;
         for (int p0 = 0; p0 < nparts; p0 += 64) {
-            float mp = (p0 + lane < nparts) ? part_ml[(prow + p0 + lane) * 2] : -INFINITY;
+            float mp = p0 + lane < nparts ? (p0 == 0 ? ml0.x : ml[p0 + lane].x) : -INFINITY;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) mp = fmaxf(mp, __shfl_xor(mp, o));
             mg = fmaxf(mg, mp);
         }
-        float den = 0.f, acc[HD / 64];
+        float den = 0.f, acc[E];
 #pragma unroll
-        for (int i = 0; i < HD / 64; i++) acc[i] = 0.f;
+        for (int i = 0; i < E; i++) acc[i] = 0.f;
         for (int p0 = 0; p0 < nparts; p0 += 64) {
             float wl = 0.f, ll = 0.f;
             if (p0 + lane < nparts) {
-                wl = fast_exp2(part_ml[(prow + p0 + lane) * 2] - mg);
-                ll = part_ml[(prow + p0 + lane) * 2 + 1];
+                const float2 t = p0 == 0 ? ml0 : ml[p0 + lane];
+                wl = fast_exp2(t.x - mg);
+                ll = t.y;
             }
             const int n = min(64, nparts - p0);
             // partition order; the values of eight partitions are fetched before the first is added, so that the loop
             // waits for memory once per eight partitions instead of once per partition
-            for (int pb = 0; pb < n; pb += 8) {
-                _Float16 v[8][HD / 64];
+            for (int pb = 0; pb < n; pb += AHEAD) {
+                if (p0 + pb > 0) {
 #pragma unroll
-                for (int q = 0; q < 8; q++) {
-                    const _Float16* po = part_o + (prow + p0 + min(pb + q, n - 1)) * HD;
-#pragma unroll
-                    for (int i = 0; i < HD / 64; i++) v[q][i] = po[lane + 64 * i];
+                    for (int q = 0; q < AHEAD; q++) v[q] = *reinterpret_cast<const piece*>(po + (size_t)(p0 + min(pb + q, n - 1)) * HD);
                 }
 #pragma unroll
-                for (int q = 0; q < 8; q++) {
+                for (int q = 0; q < AHEAD; q++) {
                     if (pb + q < n) {
                         // the partition's weight in the whole: exp2(m_p - m) l_p; its output is stored normalised
                         const float w = __shfl(wl, pb + q) * __shfl(ll, pb + q);
                         den += w;
 #pragma unroll
-                        for (int i = 0; i < HD / 64; i++) acc[i] += w * (float)v[q][i];
+                        for (int i = 0; i < E; i++) acc[i] += w * (float)v[q][i];
                     }
                 }
             }
         }
-#pragma unroll
-        for (int i = 0; i < HD / 64; i++) out[((size_t)row * hq + head) * HD + lane + 64 * i] = f32_to_bf16(acc[i] / den);
+        bf16_t* dst = out + ((size_t)row * hq + head) * HD + E * lane;
+        if constexpr (E == 2)
+            *reinterpret_cast<uint32_t*>(dst) = (uint32_t)f32_to_bf16(acc[0] / den) | ((uint32_t)f32_to_bf16(acc[E - 1] / den) << 16);
+        else
+            *dst = f32_to_bf16(acc[0] / den);
+        row += gridDim.x;
+        if (row >= m) return;
+        lim = hs_uniform(next_lane);
     }
 }
 
@@ -1019,17 +1042,18 @@ void hs_launch_attention_prefill(const hs_ctx* ctx, int layer, const hs_kv_cache
 }
 
 void hs_launch_attention_merge(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, void* out_any,
-                               hipStream_t st) {
+                               int expected, hipStream_t st) {
     if (hs_plain_kernels(ctx)) return;  // the plain kernel writes the final output itself
     bf16_t* out = (bf16_t*)out_any;
     const hs_model_desc& d = ctx->desc;
     const _Float16* part_o = reinterpret_cast<const _Float16*>(ctx->ws + ctx->lay.part_o);
     float* part_ml = reinterpret_cast<float*>(ctx->ws + ctx->lay.part_ml);
+    const hs_row_info* infos = reinterpret_cast<const hs_row_info*>(ctx->ws + ctx->lay.row_info);
     dim3 grid(hs_row_grid(ctx, 256, (d.n_q_heads + 3) / 4), (d.n_q_heads + 3) / 4);
     if (d.head_dim == 128)
-        hipLaunchKernelGGL((attn_merge<128>), grid, dim3(256), 0, st, part_o, part_ml, step->row2seq, step->row_off,
-                           seq->seq_len, seq->batch, ctx->max_parts, ctx->att_part, d.n_q_heads, out);
+        hipLaunchKernelGGL((attn_merge<128>), grid, dim3(256), 0, st, part_o, part_ml, infos, step->row_off + seq->batch,
+                           ctx->max_parts, ctx->lim.max_rows, d.n_q_heads, out, expected);
     else
-        hipLaunchKernelGGL((attn_merge<64>), grid, dim3(256), 0, st, part_o, part_ml, step->row2seq, step->row_off,
-                           seq->seq_len, seq->batch, ctx->max_parts, ctx->att_part, d.n_q_heads, out);
+        hipLaunchKernelGGL((attn_merge<64>), grid, dim3(256), 0, st, part_o, part_ml, infos, step->row_off + seq->batch,
+                           ctx->max_parts, ctx->lim.max_rows, d.n_q_heads, out, expected);
 }

@@ -90,10 +90,10 @@ template <typename OutT, int ITEMS>
 __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void embed_norm_kernel(
     const bf16_t* __restrict__ embed, const int32_t* __restrict__ tok, int vocab, float* __restrict__ x,
     const float* __restrict__ w, OutT* __restrict__ out, const int32_t* __restrict__ row_off, int batch, int d, float eps,
-    int list_groups, hs_attn_lists lists, const int32_t* __restrict__ seq_len) {
+    int list_groups, hs_attn_lists lists, const int32_t* __restrict__ seq_len, hs_row_places places) {
     __shared__ float red[NORM_THREADS_MAX / 64];
     if ((int)blockIdx.x < list_groups) {
-        hs_write_worklist(lists, seq_len, row_off, batch, blockIdx.x, list_groups);
+        hs_write_worklist(lists, places, seq_len, row_off, batch, blockIdx.x, list_groups);
         return;
     }
     clear_sums(red);
@@ -128,28 +128,32 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void embed_no
 // other rows of a compute unit hide the chain; how many share one does not matter (rows of 3584 and of 5120 in
 // workgroups of 448 to 1024 threads: a step takes the same within 0.3 %).
 template <typename OutT, int ITEMS>
-__global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
-                                                       OutT* __restrict__ out, const int32_t* __restrict__ m_dev,
+__global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS == 1 ? 7 : ITEMS == 2 ? 8 : 4) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
+                                                       OutT* __restrict__ out, const int32_t* m_dev,
                                                        int d, float eps,
                                                        const float* __restrict__ part, int chunks,
-                                                       size_t chunk_stride) {
+                                                       size_t chunk_stride, int expected) {
     __shared__ float red[NORM_THREADS_MAX / 64];
     clear_sums(red);
-    const int m = *m_dev;
-    for (int row = blockIdx.x; row < m; row += gridDim.x) {
+    int row = blockIdx.x;
+    if (row >= expected && row >= *m_dev) return;
+    for (;;) {
+        // (all of a row's loads inside the loop: one that is moved in front of it is waited for there)
+        const unsigned zero = hs_opaque_zero();
+        const int m_lane = m_dev[zero];
         float* xr = x + (size_t)row * d;
         const float* pr = part + (size_t)row * d;
         float4 v[ITEMS], g[ITEMS];
         unsigned at[ITEMS]; // byte offsets (beyond the row's end its last elements': no branch between the loads)
 #pragma unroll
         for (int it = 0; it < ITEMS; it++) {
-            at[it] = min((int)(threadIdx.x + it * blockDim.x) * 4, d - 4) * 4u;
+            at[it] = min((int)(threadIdx.x + it * blockDim.x) * 4, d - 4) * 4u + zero;
             v[it] = load4<float4>(xr, at[it]);
             g[it] = load4<float4>(w, at[it]);
         }
         if (chunks > 0) {
             // PER partials of each element in flight at once (written out: left to itself the compiler waits for each)
-            constexpr int PER = ITEMS == 1 ? 5 : 2;
+            constexpr int PER = ITEMS == 1 ? 10 : ITEMS == 2 ? 3 : 2;
             float4 t[ITEMS];
             const float* pc = pr;
             for (int c0 = 0; c0 < chunks; c0 += PER) {
@@ -162,6 +166,7 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void rmsnorm_
                             q[j][it] = load4<f32x4>(pc, at[it]);
                         pc += chunk_stride;
                     }
+                hs_loads_issued();
 #pragma unroll
                 for (int j = 0; j < PER; j++)
                     if (c0 + j < chunks) {
@@ -178,7 +183,11 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void rmsnorm_
                 v[it].x += t[it].x; v[it].y += t[it].y; v[it].z += t[it].z; v[it].w += t[it].w;
             }
         }
+        const int m = hs_uniform(m_lane);
+        if (row >= m) return;
         norm_row<OutT, ITEMS>(v, g, chunks > 0, xr, out + (size_t)row * d, d, eps, red);
+        row += gridDim.x;
+        if (row >= m) return;
     }
 }
 
@@ -193,31 +202,29 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void rmsnorm_
 // for 2048 rows of 2048 in six; now 70, 25 and 21 (2.7 to 5 TB/s of partial sums).
 template <typename T>
 __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__ qkv, const float* __restrict__ rope_cs,
-                                                       const int32_t* __restrict__ pos, const int32_t* __restrict__ row2seq,
-                                                       const int32_t* __restrict__ row_off,
-                                                       const int32_t* __restrict__ seq_len,
-                                                       const int32_t* __restrict__ block_table, int max_blocks,
-                                                       int batch, T* __restrict__ q_out, T* __restrict__ kc,
-                                                       T* __restrict__ vc, size_t layer_off, int hq, int hkv,
-                                                       int h, int max_pos, int n_blocks,
-                                                       const float* __restrict__ part, int chunks,
-                                                       size_t chunk_stride) {
-    const int m = row_off[batch];
+                                                       const hs_row_info* infos, const int32_t* m_dev, T* __restrict__ q_out,
+                                                       T* __restrict__ kc, T* __restrict__ vc, size_t layer_off, int hq,
+                                                       int hkv, int h, const float* __restrict__ part, int chunks,
+                                                       size_t chunk_stride, int expected) {
     const int half = h >> 1, per_head = half >> 2;         // items of a q or k head
     const int n_rot = (hq + hkv) * per_head, n_items = n_rot + hkv * (h >> 2);
     const int nqkv = (hq + 2 * hkv) * h;
     const bool cs_vec = ((unsigned long long)rope_cs & 15ull) == 0;
-    // (the conditions that skip a row are the same for all threads of the workgroup)
-    for (int row = blockIdx.x; row < m; row += gridDim.x) {
+    int row = blockIdx.x;
+    if (row >= expected && row >= *m_dev) return;
+    for (;;) {
         const float* src = (chunks > 0 ? part : qkv) + (size_t)row * nqkv;
         const int n_src = chunks > 0 ? chunks : 1;
-        int b = -1, p = 0, slot = 0, page = -1;
+        int m = 0;      // (stays 0 for a wavefront without items; lane 0 has one if any lane has)
         for (int i = threadIdx.x; i < n_items; i += blockDim.x) {
+            const unsigned zero = hs_opaque_zero();     // (all of an item's loads inside the loop, as in the norm)
+            const int m_lane = m_dev[zero];
+            const hs_row_info info = infos[row + zero];
             const bool rot = i < n_rot;
             const int head = rot ? i / per_head : hq + hkv + (i - n_rot) / (h >> 2);      // head of the QKV vector
             const int j = rot ? 4 * (i % per_head) : 4 * ((i - n_rot) % (h >> 2));        // first element in it
             // PER chunks in flight at once (v items load their elements twice: no branch between the loads)
-            constexpr int PER = 3;
+            constexpr int PER = 6;
             const unsigned at = (unsigned)(head * h + j) * 4u, at_y = at + (rot ? (unsigned)half * 4u : 0u);
             const float* pc = src;
             float4 x, y;
@@ -230,6 +237,7 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
                         qy[c] = load4<f32x4>(pc, at_y);
                         pc += chunk_stride;
                     }
+                hs_loads_issued();
 #pragma unroll
                 for (int c = 0; c < PER; c++)
                     if (c0 + c < n_src) {
@@ -243,21 +251,17 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
                         }
                     }
             }
-            if (b < 0) {
-                b = row2seq[row];
-                p = pos[row];
-                slot = seq_len[b] - 1 + (row - row_off[b]);
-                page = (slot >= 0 && (slot >> 4) < max_blocks) ? block_table[(size_t)b * max_blocks + (slot >> 4)] : -1;
-            }
-            // (a position flagged by the draft step, a slot beyond the block table, a missing page: nothing is written)
-            if (p < 0 || p >= max_pos || page < 0 || page >= n_blocks) break;
-            const int in_page = slot & 15;
+            // (no such row, or one that writes nothing: the same for all threads of the workgroup)
+            const int place = hs_uniform(info.slot);
+            m = hs_uniform(m_lane);
+            if (row >= m || place < 0) break;
+            const int page = place >> 4, in_page = place & 15;
             if (!rot) {   // v head -> cache [page][kv head][h][16]
                 T* dst = vc + layer_off + (((size_t)page * hkv + (head - hq - hkv)) * h + j) * 16 + in_page;
                 put(dst, x.x); put(dst + 16, x.y); put(dst + 32, x.z); put(dst + 48, x.w);
                 continue;
             }
-            const float* cs = rope_cs + ((size_t)p * half + j) * 2;
+            const float* cs = rope_cs + ((size_t)hs_uniform(info.pos) * half + j) * 2;
             float4 c0, c1;   // (cos, sin) of pairs j, j + 1 and j + 2, j + 3
             if (cs_vec) {
                 c0 = *reinterpret_cast<const float4*>(cs);
@@ -279,17 +283,21 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
             put4(dst, lo);
             put4(dst + half, hi);
         }
+        row += gridDim.x;
+        if (row >= hs_uniform(m)) return;
     }
 }
 
 // One workgroup of 16 wavefronts per row; 16-byte loads where the row is aligned.  Ties resolve to the lowest id
 // at every level, so the result is the first maximum whatever the reduction shape.
 __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int32_t* __restrict__ out,
-                                                       const int32_t* __restrict__ m_dev, int vocab) {
+                                                       const int32_t* m_dev, int vocab, int expected) {
     __shared__ float sv[16];
     __shared__ int si[16];
-    const int m = *m_dev;
-    for (int row = blockIdx.x; row < m; row += gridDim.x) {
+    int row = blockIdx.x;
+    if (row >= expected && row >= *m_dev) return;
+    for (;;) {
+        const int m_lane = m_dev[hs_opaque_zero()];
         if (row != (int)blockIdx.x) __syncthreads();  // the previous row's candidates have been read
         const float* l = logits + (size_t)row * vocab;
         float bv = -INFINITY;
@@ -297,13 +305,24 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
         auto take = [&](float v, int i) { if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; } };
         if ((vocab & 3) == 0) {
             const float4* l4 = reinterpret_cast<const float4*>(l);
-            for (int i = threadIdx.x; i < vocab / 4; i += 1024) {
-                float4 v = l4[i];
-                take(v.x, 4 * i); take(v.y, 4 * i + 1); take(v.z, 4 * i + 2); take(v.w, 4 * i + 3);
+            // (four loads on their way at once; beyond the row's end its last element again)
+            const int n4 = vocab / 4;
+            for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * 1024) {
+                float4 v[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) v[j] = l4[min(i0 + 1024 * j, n4 - 1)];
+                hs_loads_issued();
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int i = min(i0 + 1024 * j, n4 - 1);
+                    take(v[j].x, 4 * i); take(v[j].y, 4 * i + 1); take(v[j].z, 4 * i + 2); take(v[j].w, 4 * i + 3);
+                }
             }
         } else {
             for (int i = threadIdx.x; i < vocab; i += 1024) take(l[i], i);
         }
+        const int m = hs_uniform(m_lane);
+        if (row >= m) return;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             float ov = __shfl_xor(bv, o);
@@ -316,6 +335,8 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
             for (int w = 1; w < 16; w++) take(sv[w], si[w]);
             out[row] = bi;
         }
+        row += gridDim.x;
+        if (row >= m) return;
     }
 }
 
@@ -328,7 +349,7 @@ __global__ __launch_bounds__(1024) void prefill_rows_kernel(
     int tokens_stride, int batch, int chunk, int max_rows, int max_pos, const int32_t* __restrict__ block_table,
     int max_blocks, int32_t* __restrict__ row_off,
     int32_t* __restrict__ tok, int32_t* __restrict__ pos, int32_t* __restrict__ parent, int32_t* __restrict__ row2seq,
-    int32_t* __restrict__ len_plus1, uint32_t* __restrict__ err) {
+    int32_t* __restrict__ len_plus1, uint32_t* __restrict__ err, int n_blocks, hs_row_info* __restrict__ infos) {
     __shared__ int sw[16];
     __shared__ int s_first[1024], s_n[1024], s_done[1024];
     __shared__ int carry_s;
@@ -381,6 +402,7 @@ __global__ __launch_bounds__(1024) void prefill_rows_kernel(
                 pos[s0 + i] = dn + i;
                 parent[s0 + i] = i - 1;
                 row2seq[s0 + i] = b0 + q;
+                infos[s0 + i] = hs_place_row(block_table + (size_t)(b0 + q) * max_blocks, max_blocks, n_blocks, max_pos, dn + i, dn + i, 0);
             }
         }
         if (threadIdx.x == 1023) carry_s = before + incl;
@@ -391,13 +413,14 @@ __global__ __launch_bounds__(1024) void prefill_rows_kernel(
 
 }  // namespace
 
-void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_seq_state* seq, int32_t* kv_done, int chunk, hs_step* step,
+void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* seq, int32_t* kv_done, int chunk, hs_step* step,
                             int32_t* len_plus1, hipStream_t st) {
     hipLaunchKernelGGL(prefill_rows_kernel, dim3(1), dim3(1024), 0, st, seq->seq_len, kv_done, seq->tokens,
                        seq->tokens_stride, seq->batch, chunk, ctx->lim.max_rows, ctx->lim.max_pos, seq->block_table,
                        ctx->lim.max_blocks_per_seq, step->row_off,
                        step->tok, step->pos, step->parent, step->row2seq, len_plus1,
-                       reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.err));
+                       reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.err), cache->n_blocks,
+                       reinterpret_cast<hs_row_info*>(ctx->ws + ctx->lay.row_info));
 }
 
 // Rounds of a row's elements over its workgroup, and its threads: one round where 1024 threads hold the row, no more threads
@@ -413,56 +436,55 @@ static int norm_threads(int d) { return std::max(256, std::min(NORM_THREADS_MAX,
         default: hipLaunchKernelGGL((KERNEL<OUT, 4>), GRID, block, 0, st, __VA_ARGS__);                               \
     }
 
-void hs_launch_embed_norm(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, int batch, float* x,
-                          const float* w, void* out, hipStream_t st) {
+void hs_launch_embed_norm(const hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* seq, const hs_step* step,
+                          bool lists, float* x, const float* w, void* out, hipStream_t st) {
     const hs_model_desc& d = ctx->desc;
     static_assert(HS_LIST_THREADS == NORM_THREADS_MAX, "the list writers are workgroups of this launch");
-    const bool lists = seq && !hs_plain_kernels(ctx);
     const dim3 block(norm_threads(d.d_model));
     const int groups = lists ? hs_list_groups(block.x) : 0;
     const hs_attn_lists l = lists ? hs_attention_lists(ctx) : hs_attn_lists{};
     const dim3 grid(hs_row_grid(ctx, block.x) + groups);
-    const int32_t* len = seq ? seq->seq_len : nullptr;
+    const hs_row_places pl = hs_row_places_of(ctx, cache, seq, step);
     if (hs_fp32_activations(ctx)) {
         HS_NORM_LAUNCH(embed_norm_kernel, float, grid, ctx->embed, step->tok, d.vocab, x, w, (float*)out, step->row_off,
-                       batch, d.d_model, d.rms_eps, groups, l, len)
+                       seq->batch, d.d_model, d.rms_eps, groups, l, seq->seq_len, pl)
     } else {
         HS_NORM_LAUNCH(embed_norm_kernel, bf16_t, grid, ctx->embed, step->tok, d.vocab, x, w, (bf16_t*)out, step->row_off,
-                       batch, d.d_model, d.rms_eps, groups, l, len)
+                       seq->batch, d.d_model, d.rms_eps, groups, l, seq->seq_len, pl)
     }
 }
 
 void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, const int32_t* m_dev,
-                       int pending_chunks, hipStream_t st) {
+                       int pending_chunks, int expected, hipStream_t st) {
     const hs_model_desc& d = ctx->desc;
     const float* part = reinterpret_cast<const float*>(ctx->ws + ctx->lay.gemm_part);
     const size_t stride = (size_t)ctx->lim.max_rows * d.d_model;
     const dim3 block(norm_threads(d.d_model)), grid(hs_row_grid(ctx, block.x));
     if (hs_fp32_activations(ctx)) {
         HS_NORM_LAUNCH(rmsnorm_kernel, float, grid, x, w, (float*)out, m_dev, d.d_model, d.rms_eps, part, pending_chunks,
-                       stride)
+                       stride, expected)
     } else {
         HS_NORM_LAUNCH(rmsnorm_kernel, bf16_t, grid, x, w, (bf16_t*)out, m_dev, d.d_model, d.rms_eps, part,
-                       pending_chunks, stride)
+                       pending_chunks, stride, expected)
     }
 }
 #undef HS_NORM_LAUNCH
 
 void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
-                       const hs_step* step, const float* qkv, void* q, int pending_chunks, hipStream_t st) {
+                       const hs_step* step, const float* qkv, void* q, int pending_chunks, int expected,
+                       hipStream_t st) {
     const hs_model_desc& d = ctx->desc;
     size_t layer_off = (size_t)layer * cache->n_blocks * d.n_kv_heads * 16 * d.head_dim;
     const float* part = reinterpret_cast<const float*>(ctx->ws + ctx->lay.gemm_part);
+    const hs_row_info* infos = reinterpret_cast<const hs_row_info*>(ctx->ws + ctx->lay.row_info);
     const size_t nqkv = (size_t)(d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
     // an item per thread if a workgroup has that many, else as many rounds of equal size as it takes
     const int items = (d.n_q_heads + d.n_kv_heads) * (d.head_dim / 8) + d.n_kv_heads * (d.head_dim / 4);
     const int rounds = (items + 1023) / 1024, threads = ((items + rounds - 1) / rounds + 63) / 64 * 64;
     const dim3 grid(hs_row_grid(ctx, threads)), block(threads);
 #define HS_ROPE_ARGS(T)                                                                                          \
-    qkv, ctx->rope_cs, step->pos, step->row2seq, step->row_off, seq->seq_len, seq->block_table,                  \
-        ctx->lim.max_blocks_per_seq, seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off, d.n_q_heads,      \
-        d.n_kv_heads, d.head_dim, ctx->lim.max_pos, cache->n_blocks, part, pending_chunks,                       \
-        (size_t)ctx->lim.max_rows * nqkv
+    qkv, ctx->rope_cs, infos, step->row_off + seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off,          \
+        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, expected
     if (hs_fp32_activations(ctx))
         hipLaunchKernelGGL(rope_kv_kernel<float>, grid, block, 0, st, HS_ROPE_ARGS(float));
     else
@@ -471,7 +493,7 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
 }
 
 void hs_launch_argmax(const hs_ctx* ctx, const float* logits, int32_t* argmax, const int32_t* m_dev,
-                      hipStream_t st) {
+                      int expected, hipStream_t st) {
     hipLaunchKernelGGL(argmax_kernel, dim3(hs_row_grid(ctx, 1024)), dim3(1024), 0, st, logits, argmax, m_dev,
-                       ctx->desc.vocab);
+                       ctx->desc.vocab, expected);
 }

@@ -26,7 +26,7 @@ struct alignas(16) hs_reject_stat { float m; uint32_t check; double s; };
 static inline int hs_reject_slices(int vocab) { return (vocab + HS_REJECT_SLICE - 1) / HS_REJECT_SLICE; }
 
 struct hs_workspace_layout {
-    size_t x, xn, qkv, q, attn, act, part_o, part_ml, logits, logits_bytes, rowmax, draft_best, gemm_part, gemm_part_bytes, err, pf_len, att_work, att_list, reject_stats, reject_walk, total;
+    size_t x, xn, qkv, q, attn, act, part_o, part_ml, logits, logits_bytes, rowmax, draft_best, gemm_part, gemm_part_bytes, err, pf_len, row_info, att_work, att_list, reject_stats, reject_walk, total;
 };
 
 struct hs_ctx {
@@ -96,6 +96,21 @@ static inline int hs_row_grid(const hs_ctx* ctx, int threads, int per_row = 1) {
     return resident < 1 ? 1 : (resident < ctx->lim.max_rows ? resident : ctx->lim.max_rows);
 }
 
+// A zero that the compiler does not know: an index with it makes a load that all lanes share a vector load.  Such loads
+// return in the order of their issue, so that a row's data can be asked for behind the row count and both are waited for at
+// once; a scalar load's wait would hold up whatever is addressed by another scalar load.
+__device__ __forceinline__ unsigned hs_opaque_zero() {
+    unsigned z;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+    return z;
+}
+// What has been asked for above stays above.
+__device__ __forceinline__ void hs_loads_issued() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ int hs_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // ---- launchers (each enqueues on `st`; shapes have been validated by the caller) ----
 
 // GEMM family: C[M,N] (+)= A[M,K] . W[N,K]^T, A and W bf16, fp32 accumulation in a fixed k order.
@@ -115,23 +130,50 @@ void hs_launch_gemm(const hs_ctx* ctx, int epi, const void* a, const bf16_t* w, 
                     int* pending = nullptr);
 int hs_gemm_rowmax_groups(int n);   // column groups (= keys per row) of an HS_EPI_ROWMAX launch over n columns
 
-// Embedding gather into the residual stream and its first RMSNorm; with seq (hs_verify), the unit lists of the step's
-// attention are written by further workgroups of the same launch.
-void hs_launch_embed_norm(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, int batch, float* x,
-                          const float* w, void* out, hipStream_t st);
+// What a row's place in its sequence comes to, written once per pass (beside the attention's unit lists, or by the launch
+// that lays out a prefill's rows) and read by every layer: the row's K/V slot (page * 16 + slot in the page; -1: nothing is written), its position and the number of
+// attention partitions of its sequence.
+struct alignas(16) hs_row_info { int32_t slot, pos, parts, unused; };
+struct hs_row_places {
+    const int32_t *pos, *block_table;
+    int max_blocks, max_pos, n_blocks;
+    hs_row_info* info;
+};
+static inline hs_row_places hs_row_places_of(const hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* seq, const hs_step* step) {
+    return {step->pos, seq->block_table, ctx->lim.max_blocks_per_seq, ctx->lim.max_pos, cache->n_blocks,
+            reinterpret_cast<hs_row_info*>(ctx->ws + ctx->lay.row_info)};
+}
+// The row at `at` tokens from its sequence's start (a position flagged by the draft step, a slot beyond the block table, a
+// missing page: nothing is written).
+__device__ __forceinline__ hs_row_info hs_place_row(const int32_t* pages, int max_blocks, int n_blocks, int max_pos, int at,
+                                                    int pos, int parts) {
+    const int page = at >= 0 && (at >> 4) < max_blocks ? pages[at >> 4] : -1;
+    const bool none = pos < 0 || pos >= max_pos || page < 0 || page >= n_blocks;
+    return {none ? -1 : page * 16 + (at & 15), pos, parts, 0};
+}
+
+// In the row kernels below, `expected` is the host's estimate of the row count.  A workgroup whose first row lies below it
+// asks for the row's data before the count has arrived from memory (in bounds: never more than max_rows); the result does
+// not depend on it.
+
+// Embedding gather into the residual stream and its first RMSNorm; with lists (hs_verify), the rows' hs_row_info and the
+// unit lists of the step's attention are written by further workgroups of the same launch.
+void hs_launch_embed_norm(const hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* seq, const hs_step* step,
+                          bool lists, float* x, const float* w, void* out, hipStream_t st);
 // RMSNorm of the residual stream; with pending_chunks > 0 it first adds the pending chunk partials of the
 // preceding projection (in chunk order) to x.
 void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, const int32_t* m_dev,
-                       int pending_chunks, hipStream_t st);
+                       int pending_chunks, int expected, hipStream_t st);
 // Rotary embedding + KV write; with pending_chunks > 0 the QKV values are the chunk-ordered sums of the pending
 // partials instead of qkv.
 void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
-                       const hs_step* step, const float* qkv, void* q, int pending_chunks, hipStream_t st);
+                       const hs_step* step, const float* qkv, void* q, int pending_chunks, int expected,
+                       hipStream_t st);
 void hs_launch_attention(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
                          const hs_step* step, const void* q, void* out, hipStream_t st);
 // Chunked prefill: row arrays of one call (rows of sequence b = its next tokens from the token log) and the causal
 // attention over [0, kv_done + i] for token i of the chunk.  len_plus1[b] = cached positions + 1.
-void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_seq_state* seq, int32_t* kv_done, int chunk, hs_step* step,
+void hs_launch_prefill_rows(const hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* seq, int32_t* kv_done, int chunk, hs_step* step,
                             int32_t* len_plus1, hipStream_t st);
 void hs_launch_attention_prefill(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
                                  const int32_t* len_plus1, const hs_step* step, const bf16_t* q, bf16_t* out, int chunk,
@@ -145,9 +187,9 @@ struct hs_attn_lists {
 hs_attn_lists hs_attention_lists(const hs_ctx* ctx);
 size_t hs_attention_max_units(const hs_ctx* ctx);
 void hs_launch_attention_merge(const hs_ctx* ctx, const hs_seq_state* seq, const hs_step* step, void* out,
-                               hipStream_t st);
+                               int expected, hipStream_t st);
 void hs_launch_argmax(const hs_ctx* ctx, const float* logits, int32_t* argmax, const int32_t* m_dev,
-                      hipStream_t st);
+                      int expected, hipStream_t st);
 void hs_launch_draft(const hs_ctx* ctx, const hs_draft_args* args, const hs_seq_state* seq, hs_step* step,
                      hipStream_t st);
 // hs_draft_static: segment winners in a static device array of HS_DRAFT_STATIC_ENTRIES slots.  Returns false (with the

@@ -1,4 +1,4 @@
-// The unit lists of the verify attention, written on the device once per hs_verify call.
+// The unit lists of the verify attention and the rows' places, written on the device once per hs_verify call.
 #pragma once
 #include "hs_internal.h"
 
@@ -14,7 +14,7 @@ static inline int hs_list_groups(int threads) { return 256 * 64 / threads; }
 // prefix sum over the batch), a wavefront then writes the units of one sequence.  These workgroups are part of the launch
 // that gathers the embeddings, which needs nothing of the lists: one workgroup of four wavefronts in a launch of its own
 // took 8 us at 64 sequences, 14 at 128 and 26 at 256, with the rest of the chip idle.
-__device__ inline void hs_write_worklist(const hs_attn_lists& l, const int32_t* __restrict__ seq_len,
+__device__ inline void hs_write_worklist(const hs_attn_lists& l, const hs_row_places& pl, const int32_t* __restrict__ seq_len,
                                          const int32_t* __restrict__ row_off, int batch, int group, int groups) {
     constexpr int NW_MAX = HS_LIST_THREADS / 64;
     const int nt = blockDim.x, nw = nt >> 6;
@@ -67,6 +67,10 @@ __device__ inline void hs_write_worklist(const hs_attn_lists& l, const int32_t* 
         const int nb = min(nt, batch - b0);
         for (int i = group * nw + wave; i < nb; i += groups * nw) {
             const int n = s_nu[i], rows = s_nn[i];
+            const int parts = min(l.max_parts, (s_len[i] + rows + l.part_keys - 1) / l.part_keys);
+            for (int r = lane; r < rows; r += 64)
+                pl.info[s_r0[i] + r] = hs_place_row(pl.block_table + (size_t)(b0 + i) * pl.max_blocks, pl.max_blocks, pl.n_blocks,
+                                                    pl.max_pos, s_len[i] + r, pl.pos[s_r0[i] + r], parts);
             int4* dst = (n < 0 ? l.list_a : l.list_b) + 2 * (size_t)s_off[i];
             const int cnt = n < 0 ? -n : n, grp = n < 0 ? (rows * l.G + 127) / 128 : 1;
             for (int u = lane; u < cnt; u += 64) {

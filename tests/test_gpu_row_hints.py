@@ -1,0 +1,58 @@
+"""The row kernels ask for a row's data before the row count has arrived where the host's estimate covers the row: the result
+must not depend on the estimate, and rows that do not exist must leave no trace."""
+import numpy as np
+import pytest
+import torch
+
+from hs_inputs import ModelShape, make_weights, rope_table
+from gpu_common import np_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,hq,hkv,h,f", [(256, 4, 4, 64, 1024), (1536, 12, 2, 128, 1024), (5120, 8, 8, 128, 8192)])
+def test_a_step_does_not_depend_on_the_expected_rows(d, hq, hkv, h, f):
+    """One and two rounds per row of the norm, with and without pending partial sums (up to more chunks than are in flight at
+    once), heads of 64 and 128; estimates of no row, some, exactly all, more (and more than the merge asks ahead for).  A
+    sequence whose page is missing writes no K/V, whatever the estimate."""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=2, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=h, d_ffn=f, vocab=512)
+    rng, B = np.random.default_rng(d), 5
+    toks = [rng.integers(0, 512, n).astype(np.int32) for n in (40, 300, 17, 16, 700)]
+    w = make_weights(shape, 3)
+    eng = Engine(shape, w, rope_table(1024, h), max_batch=8, k_max=9, c_max=1, max_len=710)
+    eng.load_sequences(toks, [9] * B)
+    eng.prefill_chunked(256)
+    rows = []
+    for b, n in enumerate((1, 10, 3, 0, 5)):
+        t = np.concatenate([toks[b][-1:], rng.integers(0, 512, max(0, n - 1))]).astype(np.int32)
+        rows.append(dict(tok=t, parent=np.arange(-1, n - 1), pos=len(toks[b]) - 1 + np.arange(n)) if n else None)
+    m = eng.set_rows(rows)
+    assert m == 19
+    table = eng.block_table.clone()
+    eng.block_table[2, (len(toks[2]) - 1 + 2) // 16] = eng.n_blocks     # (beyond the cache: sequence 2's rows 0.. lie on that page)
+    kc, vc = eng.kc.clone(), eng.vc.clone()
+    outs = []
+    for hint in (0, 1, 7, m, 33, eng.max_rows):
+        eng.kc.copy_(kc)
+        eng.vc.copy_(vc)
+        eng.logits.zero_()
+        eng.c_step.rows_hint = hint
+        eng.verify()
+        torch.cuda.synchronize()
+        live = torch.cat([eng.logits[:11], eng.logits[14:m]])           # (the rows whose keys are all there)
+        outs.append((live.clone(), eng.kc.clone(), eng.vc.clone(), np_of(eng.st["argmax"])[:11].tolist()))
+        assert not eng.logits[m:].any()
+    for hint, o in zip((1, 7, m, 33, eng.max_rows), outs[1:]):
+        assert torch.equal(o[0], outs[0][0]) and o[3] == outs[0][3], hint
+        assert torch.equal(o[1], outs[0][1]) and torch.equal(o[2], outs[0][2]), hint
+    # exactly the live rows' slots changed: 16 rows of four sequences, in both layers
+    k2 = outs[0][1].view(2, eng.n_blocks, hkv, 16, h) != kc.view(2, eng.n_blocks, hkv, 16, h)
+    changed = k2.any(-1).any(2)
+    want = torch.zeros_like(changed)
+    for b, r in enumerate(rows):
+        for i in range(0 if r is None or b == 2 else len(r["tok"])):
+            slot = len(toks[b]) - 1 + i
+            want[:, int(table[b, slot // 16]), slot % 16] = True
+    assert torch.equal(changed, want)
+    eng.close()

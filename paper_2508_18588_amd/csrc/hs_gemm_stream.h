@@ -51,7 +51,7 @@
 //     deeper weight ring changes nothing), with a prologue and an epilogue that nothing overlaps.  A third activation stage in
 //     passes of 256 rows made every such shape slower (71 -> 77 us), the row pitch of the operands (55 to 65 lines of 128 bytes) is worth 5 % either way.
 // SwiGLU pairs the gate and up rows of 16 output columns in one 32-row weight unit, so that both pre-activations of
-// a column meet in one MFMA tile (lanes c and c+16).
+// a column meet in one MFMA tile.
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -204,6 +204,10 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
         }
     };
 
+    // A SwiGLU tile is computed transposed (weights as the first operand): a lane then holds a row's gate and up values of
+    // the same columns, four columns in a row, and stores 8 bytes.  (As lanes c and c + 16 of a row, exchanged and stored by 2
+    // bytes: 7B gate/up at 4096 rows 885 us, now 857, at 300 to 1000 rows 1 %, with fewer the same.)  Same products, same order, same bits.
+    constexpr bool TRANSPOSED = EPI == HS_EPI_SWIGLU_BF16;
     f32x16 acc[NM][NUW];
 #pragma unroll
     for (int i = 0; i < NM; i++)
@@ -258,7 +262,8 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
 #pragma unroll
         for (int q = 0; q < NMF; q++) {
             const int mi = q / NUW, ni = q % NUW;
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mi], fb[set][ni], acc[mi][ni], 0, 0, 0);
+            if (TRANSPOSED) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][ni], fa[set][mi], acc[mi][ni], 0, 0, 0);
+            else acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mi], fb[set][ni], acc[mi][ni], 0, 0, 0);
             if (READ) {
 #pragma unroll
                 for (int r = q * NR / NMF; r < (q + 1) * NR / NMF; r++) frag(set ^ 1, r, at_a, at_w);
@@ -401,27 +406,33 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
         for (int mi = 0; mi < NMI; mi++) {
             const int row0 = p.m0 + 32 * (rg + WS::RG * mi) + lr;
             if (EPI == HS_EPI_SWIGLU_BF16) {
-                // Lanes c (gate) and c+16 (up) hold the two pre-activations of output column c.  Elements are taken
-                // in pairs: the gate lanes finish the row of element e and the up lanes the row of element e+1, so
-                // every lane computes an output.  One v_permlane16_swap does the exchange: it swaps the odd
-                // 16-lane rows of its first operand (element e: the up values) with the even rows of its second
-                // (element e+1: the gate values), after which the first holds every lane's gate and the second
-                // every lane's up.  (32-bit element offsets: the host checks that the output stays below 4 GiB.)
+                // Element e of the transposed tile: row of the weight unit 8*(e/4) + 4*(lane/32) + e%4, of which 0 to 15 are gate
+                // rows and 16 to 31 the up rows of the same columns, activation row lane%32.  (32-bit element offsets: the
+                // host checks that the output stays below 4 GiB.)
                 bf16_t* C = reinterpret_cast<bf16_t*>(p.Cout);
-                const bool up_lane = (lc & 16) != 0;
-                const int rbase = row0 + (up_lane ? 1 : 0);
+                const int row = p.m0 + 32 * (rg + WS::RG * mi) + lc;
+                const bool whole = (p.N & 3) == 0 && ((unsigned long long)C & 7ull) == 0;    // four columns end within N, 8-byte stores
+                if (row < p.M) {
 #pragma unroll
-                for (int ni = 0; ni < NUW; ni++) {
-                    const int col = p.n0 + 16 * (U0 + ni) + (lc & 15);
+                    for (int ni = 0; ni < NUW; ni++) {
 #pragma unroll
-                    for (int e = 0; e < 16; e += 2) {
-                        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[mi][ni][e]),
-                                                                         __float_as_uint(acc[mi][ni][e + 1]), false, false);
-                        const float gate = __uint_as_float(sw[0]), up = __uint_as_float(sw[1]);
-                        const int row = rbase + 8 * (e >> 2) + (e & 3);
-                        if (col < p.N && row < p.M) {
-                            const float s = gate * __builtin_amdgcn_rcpf(1.f + __expf(-gate));
-                            C[(unsigned)row * (unsigned)p.N + (unsigned)col] = f32_to_bf16(s * up);
+                        for (int q = 0; q < 2; q++) {
+                            const int col = p.n0 + 16 * (U0 + ni) + 8 * q + lr;
+                            bf16_t v[4];
+#pragma unroll
+                            for (int e = 0; e < 4; e++) {
+                                const float gate = acc[mi][ni][4 * q + e], up = acc[mi][ni][8 + 4 * q + e];
+                                const float s = gate * __builtin_amdgcn_rcpf(1.f + __expf(-gate));
+                                v[e] = f32_to_bf16(s * up);
+                            }
+                            bf16_t* dst = C + ((unsigned)row * (unsigned)p.N + (unsigned)col);
+                            if (whole) {
+                                if (col < p.N) *reinterpret_cast<uint2*>(dst) = make_uint2((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16));
+                            } else {
+#pragma unroll
+                                for (int e = 0; e < 4; e++)
+                                    if (col + e < p.N) dst[e] = v[e];
+                            }
                         }
                     }
                 }

@@ -394,15 +394,34 @@ __global__ __launch_bounds__(1024) void prefill_rows_kernel(
             s_done[threadIdx.x] = done;
         }
         __syncthreads();
-        // a wavefront per sequence writes its rows
-        for (int q = wave; q < min(1024, batch - b0); q += 16) {
-            const int s0 = s_first[q], dn = s_done[q];
-            for (int i = lane; i < s_n[q]; i += 64) {
-                tok[s0 + i] = tokens[(size_t)(b0 + q) * tokens_stride + dn + i];
-                pos[s0 + i] = dn + i;
-                parent[s0 + i] = i - 1;
-                row2seq[s0 + i] = b0 + q;
-                infos[s0 + i] = hs_place_row(block_table + (size_t)(b0 + q) * max_blocks, max_blocks, n_blocks, max_pos, dn + i, dn + i, 0);
+        // A thread per row, four at a time, so that the rows' tokens and pages come in one trip to memory however few sequences
+        // there are; a row's sequence is the last one that starts at or before it (those without rows start where the next one does).
+        // (A wavefront per sequence: five sequences of 2048 rows 13.6 us, now 7.8; eight of 4096 10.1, now 9.3.)
+        const int nb = min(1024, batch - b0), end = s_first[nb - 1] + s_n[nb - 1];
+        for (int r0 = s_first[0] + threadIdx.x; r0 < end; r0 += 4 * 1024) {
+            int q[4], t[4];
+            hs_row_info info[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int r = min(r0 + 1024 * j, end - 1);
+                int lo = 0;
+                for (int step = 512; step > 0; step >>= 1)
+                    if (lo + step < nb && s_first[lo + step] <= r) lo += step;
+                const int at = s_done[lo] + r - s_first[lo];
+                q[j] = lo;
+                t[j] = tokens[(size_t)(b0 + lo) * tokens_stride + at];
+                info[j] = hs_place_row(block_table + (size_t)(b0 + lo) * max_blocks, max_blocks, n_blocks, max_pos, at, at, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int r = r0 + 1024 * j;
+                if (r < end) {
+                    tok[r] = t[j];
+                    pos[r] = info[j].pos;
+                    parent[r] = r - s_first[q[j]] - 1;
+                    row2seq[r] = b0 + q[j];
+                    infos[r] = info[j];
+                }
             }
         }
         if (threadIdx.x == 1023) carry_s = before + incl;

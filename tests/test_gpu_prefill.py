@@ -180,3 +180,36 @@ def test_prefill_7b_shape_two_layers():
     print("7B-shape prefill: max |dK|,|dV| =", worst, "tolerance", tol)
     assert worst <= tol
     eng.close()
+
+
+@pytest.mark.parametrize("batch,longest,chunk,max_rows", [(1, 1400, 1024, 1400), (3, 1500, 1024, 2100), (7, 900, 777, 4400), (1100, 6, 4, 2500)])
+def test_rows_of_one_call(toy, batch, longest, chunk, max_rows):
+    """The row arrays that a call lays out, row by row: one sequence, several thousand rows, more sequences than threads, some
+    with nothing to do, and a row limit that ends inside a sequence."""
+    from paper_2508_18588_amd import hs_prefill, hs_prefill_args
+    from paper_2508_18588_amd.runtime import Engine
+    shape, w, rope = toy
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(1, longest + 1, batch)
+    lens[0] = longest
+    toks = texts(rng, lens, shape.vocab)
+    eng = Engine(shape, w, rope, max_batch=batch, k_max=4, c_max=1, max_len=longest + 16, max_rows=max_rows, keep_logits=False)
+    eng.load_sequences(toks, budgets=[8] * batch)
+    done = np.minimum(rng.integers(0, 3, batch), lens - 1).astype(np.int32)
+    eng.kv_done = torch.from_numpy(done.copy()).cuda()
+    hs_prefill(eng.ctx, eng.c_cache, eng.c_seq, eng.c_step, hs_prefill_args(chunk, 0, eng.kv_done.data_ptr()), eng.stream())
+    torch.cuda.synchronize()
+    assert eng.poll_error() == 0
+    off, want = [0], {n: [] for n in ("tok", "pos", "parent", "row2seq")}
+    for b in range(batch):
+        n = min(chunk, lens[b] - 1 - done[b], max_rows - off[-1])
+        want["tok"] += toks[b][done[b]:done[b] + n].tolist()
+        want["pos"] += range(done[b], done[b] + n)
+        want["parent"] += range(-1, n - 1)
+        want["row2seq"] += [b] * n
+        off.append(off[-1] + n)
+    assert np_of(eng.st["row_off"])[:batch + 1].tolist() == off
+    assert np_of(eng.kv_done).tolist() == (done + np.diff(off)).tolist()
+    for name, rows in want.items():
+        assert np_of(eng.st[name])[:off[-1]].tolist() == rows, name
+    eng.close()

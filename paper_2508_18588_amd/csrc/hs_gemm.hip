@@ -5,7 +5,8 @@
 // chunk is accumulated by the matrix cores on its own, and the chunk sums are added left to right in fp32
 // (t = p0 + p1 + ...; then stored, or added to the residual).  A row's result therefore never depends on how many
 // other rows share the launch or on the launch shape the row hint selects -- which is what makes speculative and
-// one-token decoding agree bit for bit.  The MFMA kernel lives in hs_gemm_stream.hip; here are the ordered reduce
+// one-token decoding agree bit for bit.  (With many rows a workgroup takes all chunks of its tile in turn, same sums in the
+// same order: hs_gemm_folded.hip.)  The MFMA kernel lives in hs_gemm_stream.hip; here are the ordered reduce
 // of the chunk partials (used when no following kernel takes them over), the plain kernels (debugging, fp32
 // activations), and the shape rules.
 #include "hs_gemm_common.h"
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(256) void gemm_plain(const AT* __restrict__ A, cons
 
 template <int EPI>
 void launch(const hs_ctx* ctx, const void* a_any, const bf16_t* w, const bf16_t* w2, void* c, const int32_t* m_dev,
-            int m_max, int n, int k, int rows_hint, hipStream_t st, int* pending) {
+            int m_max, int n, int k, int rows_hint, hipStream_t st, int* pending, int fold_k) {
     if (pending) *pending = 0;
     if (hs_plain_kernels(ctx)) {
         dim3 grid((n + 4 * PC - 1) / (4 * PC), (m_max + PR - 1) / PR);
@@ -165,6 +166,9 @@ void launch(const hs_ctx* ctx, const void* a_any, const bf16_t* w, const bf16_t*
     int chunks = (EPI == HS_EPI_SWIGLU_BF16 || EPI == HS_EPI_ROWMAX) ? 1 : hs_gemm_chunks(n, k);
     const int tpc = (nk + chunks - 1) / chunks;
     chunks = (nk + tpc - 1) / tpc;  // no empty chunk
+    if constexpr (EPI == HS_EPI_STORE_F32 || EPI == HS_EPI_ADD_F32) {
+        if (chunks > 1 && k <= fold_k && hs_launch_gemm_folded(EPI, a, w, c, m_dev, m_max, n, k, chunks, tpc, rows_hint, st)) return;
+    }
     float* part = reinterpret_cast<float*>(ctx->ws + ctx->lay.gemm_part);
     hs_launch_gemm_stream(EPI, a, w, w2, c, part, m_dev, m_max, n, k, chunks, tpc, rows_hint, st);
     if (chunks > 1) {
@@ -206,19 +210,19 @@ int hs_gemm_chunks(int n, int k, bool narrow) {
 }
 
 void hs_launch_gemm(const hs_ctx* ctx, int epi, const void* a, const bf16_t* w, const bf16_t* w2, void* c,
-                    const int32_t* m_dev, int m_max, int n, int k, int rows_hint, hipStream_t st, int* pending) {
+                    const int32_t* m_dev, int m_max, int n, int k, int rows_hint, hipStream_t st, int* pending, int fold_k) {
     switch (epi) {
         case HS_EPI_STORE_F32:
-            launch<HS_EPI_STORE_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending);
+            launch<HS_EPI_STORE_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
             break;
         case HS_EPI_ADD_F32:
-            launch<HS_EPI_ADD_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending);
+            launch<HS_EPI_ADD_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
             break;
         case HS_EPI_ROWMAX:
-            launch<HS_EPI_ROWMAX>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending);
+            launch<HS_EPI_ROWMAX>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
             break;
         default:
-            launch<HS_EPI_SWIGLU_BF16>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending);
+            launch<HS_EPI_SWIGLU_BF16>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
             break;
     }
 }

@@ -52,3 +52,11 @@ bool hs_gemm_narrow_groups(int n, int k);
 void hs_launch_gemm_stream(int epi, const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, float* part,
                            const int32_t* m_dev, int m_max, int n, int k, int chunks, int tpc, int rows_hint,
                            hipStream_t st);
+
+// Microseconds that the split execution is expected to take, the reading of its partial sums by the next kernel included.
+double hs_gemm_split_us(bool add, int n, int chunks, int tpc, int rows);
+
+// A split-K projection with all chunks of a tile in one workgroup (hs_gemm_folded.hip): no partial sums, the epilogue (store or
+// add) applied.  Returns false, with nothing launched, where the split execution is expected to be faster.
+bool hs_launch_gemm_folded(int epi, const bf16_t* a, const bf16_t* w, void* c, const int32_t* m_dev, int m_max, int n, int k,
+                           int chunks, int tpc, int rows_hint, hipStream_t st);

@@ -35,6 +35,7 @@
 //     the chip's power and fewer rounds of workgroups.  7B gate/up at 4096 rows 942 -> 890 us (1250 TFLOP/s), at 2048 rows
 //     490 -> 446; down at 4096 674 -> 615.  Without its loads 816, without its MFMAs 628; counters: matrix cores busy 65 % of the
 //     cycles at the 1.76 GHz that this load leaves the chip, LDS 32 %.
+//   * Split K with many rows: a workgroup takes all chunks of its tile in turn (FOLD, hs_gemm_folded.hip), no partial sums.
 //   * Up to 160 rows expected (two to four units): three activation stages, and one wavefront group fetches the activations,
 //     the other the weights.  Loads count as landed in the order of their issue: while every wavefront fetched both, waiting for
 //     the next tile's activations, asked for last, meant waiting for weights asked for a tile before, and the weight ring
@@ -85,6 +86,7 @@ struct stream_args {
     float* part;
     int M, m_max, N, K, n0, m0, kt0, kt1, chunk, group, n_groups;
     int w_once;  // the launch reads every weight byte once (one row pass): non-temporal weight loads
+    int fold;    // FOLD: k-tiles of a chunk
     int w_pre;   // the weight-only part of the prologue has been issued already (by the kernel, before M was known)
 };
 
@@ -136,9 +138,9 @@ __device__ __forceinline__ void issue_weight_tile(const stream_args& p, const un
     }
 }
 
-// One K chunk of one row pass for a wavefront of group GRP and row group rg that owns NMI live row tiles (0 = loads and
+// One K chunk (FOLD: all of them, p.fold k-tiles each) of one row pass for a wavefront of group GRP and row group rg that owns NMI live row tiles (0 = loads and
 // barriers only).
-template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int NMI, int WV>
+template <int EPI, bool PARTIAL, bool FOLD, int NU, int MT, int SA, int SW, int GRP, int NMI, int WV>
 __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char* smem, unsigned smem_off,
                                              const unsigned (&w_off)[wave_shape<NU, MT, SA, GRP, WV>::U_SIZE], int quad, int rg, int lane) {
     using WS = wave_shape<NU, MT, SA, GRP, WV>;
@@ -215,6 +217,32 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
         for (int j = 0; j < NUW; j++)
 #pragma unroll
             for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+    // FOLD: the chunks of split K one after the other, their sums added left to right as the ordered reduce adds them.
+    f32x16 sum[FOLD ? NM : 1][FOLD ? NUW : 1];
+    int left = p.fold;      // k-tiles of the chunk still to come
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int i = 0; i < NM; i++)
+#pragma unroll
+            for (int j = 0; j < NUW; j++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) sum[i][j][e] = -0.f;    // (the first chunk's sum stays as it is)
+    }
+    auto fold = [&]() __attribute__((always_inline)) {
+        if constexpr (FOLD) {
+            if (--left == 0) {
+                left = p.fold;
+                if (NMI > 0) {
+#pragma unroll
+                    for (int i = 0; i < NM; i++)
+#pragma unroll
+                        for (int j = 0; j < NUW; j++)
+#pragma unroll
+                            for (int e = 0; e < 16; e++) { sum[i][j][e] += acc[i][j][e]; acc[i][j][e] = 0.f; }
+                }
+            }
+        }
+    };
 
     // prologue: the hand-overs a longer-running loop would have made before tile kt0; of the last one only the
     // activation part (its weight part goes out during the first half of tile kt0, see below)
@@ -334,6 +362,7 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
         w_nxt = w_nxt + W_STAGE == SW * W_STAGE ? 0 : w_nxt + W_STAGE;
         a_src += ROW_BYTES;
         w_src += ROW_BYTES;
+        fold();
     };
     if (n_a == NSA) {
         for (; kt + SW < p.kt1; kt++) tile(std::integral_constant<int, 0>{});
@@ -347,6 +376,15 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
         step(std::integral_constant<int, 1>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, 0>{}, no_load);
         step(std::integral_constant<int, 2>{}, std::true_type{}, a_cur, w_cur, std::integral_constant<int, 0>{}, no_load);
         step(std::integral_constant<int, 3>{}, std::false_type{}, 0, 0, std::integral_constant<int, 0>{}, no_load);
+    }
+
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int i = 0; i < NM; i++)
+#pragma unroll
+            for (int j = 0; j < NUW; j++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[i][j][e] = sum[i][j][e] + acc[i][j][e];
     }
 
     // (the lane number anew: values derived from it would otherwise stay in registers, or spill, through the whole loop)
@@ -513,7 +551,7 @@ struct wide_share {
 };
 
 // What a wavefront of group GRP does: the row passes of its workgroup.
-template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int GRP, int WV>
+template <int EPI, bool PARTIAL, bool FOLD, int NU, int MT, int SA, int SW, int GRP, int WV>
 __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem, unsigned smem_off, int quad, int rg, int lane,
                                              int pass, int n_pass) {
     using WS = wave_shape<NU, MT, SA, GRP, WV>;
@@ -545,7 +583,7 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
             HS_WAIT_VMCNT(0);
             __syncthreads();
             p.w_pre = 0;
-            stream_group<EPI, PARTIAL, NU, 2, few_rows_rings<NU>::FALL_SA, few_rows_rings<NU>::FALL_SW, GRP, WV>(p, smem, smem_off, quad, rg, lane, pass, n_pass);
+            stream_group<EPI, PARTIAL, FOLD, NU, 2, few_rows_rings<NU>::FALL_SA, few_rows_rings<NU>::FALL_SW, GRP, WV>(p, smem, smem_off, quad, rg, lane, pass, n_pass);
             return;
         }
     }
@@ -555,7 +593,7 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
         for (int s = 0; s < WS::MI; s++)
             if (rg + WS::RG * s < pass_shape<MT>::TILES && p.m0 + 32 * (rg + WS::RG * s) < p.M) nmi = s + 1;
         nmi = __builtin_amdgcn_readfirstlane(nmi);
-#define HS_CHUNK(N) stream_chunk<EPI, PARTIAL, NU, MT, SA, SW, GRP, (N <= WS::MI ? N : 1), WV>(p, smem, smem_off, w_off, quad, rg, lane)
+#define HS_CHUNK(N) stream_chunk<EPI, PARTIAL, FOLD, NU, MT, SA, SW, GRP, (N <= WS::MI ? N : 1), WV>(p, smem, smem_off, w_off, quad, rg, lane)
         if (nmi == 0) HS_CHUNK(0);
         else if (nmi == 1) HS_CHUNK(1);
         else if (WS::MI >= 2 && nmi == 2) HS_CHUNK(2);
@@ -572,8 +610,8 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
 
 namespace {
 
-// The kernel, for WV wavefronts.
-template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW, int WV>
+// The kernel, for WV wavefronts.  (FOLD: a single grid row, tpc k-tiles per chunk.)
+template <int EPI, bool PARTIAL, bool FOLD, int NU, int MT, int SA, int SW, int WV>
 __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                               const bf16_t* __restrict__ W2, void* __restrict__ Cout,
                                               float* __restrict__ part, const int32_t* __restrict__ m_dev,
@@ -653,22 +691,23 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
     p.chunk = chunk;
     p.w_once = n_pass == 1;
     const int nk = K / BK;
-    p.kt0 = chunk * tpc;
-    p.kt1 = min(nk, p.kt0 + tpc);
+    p.kt0 = FOLD ? 0 : chunk * tpc;
+    p.kt1 = FOLD ? nk : min(nk, p.kt0 + tpc);
+    p.fold = tpc;
 
     if constexpr (WV == 8) {
         auto run = [&](auto sa_c, auto sw_c) __attribute__((always_inline)) {
             constexpr int A_STAGES = decltype(sa_c)::value, W_STAGES = decltype(sw_c)::value;
-            if (wave < 4) stream_group<EPI, PARTIAL, NU, MT, A_STAGES, W_STAGES, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, passes);
-            else stream_group<EPI, PARTIAL, NU, MT, A_STAGES, W_STAGES, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, passes);
+            if (wave < 4) stream_group<EPI, PARTIAL, FOLD, NU, MT, A_STAGES, W_STAGES, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, passes);
+            else stream_group<EPI, PARTIAL, FOLD, NU, MT, A_STAGES, W_STAGES, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, passes);
         };
         if constexpr (MT == 0) run(std::integral_constant<int, few_rows_rings<NU>::SA>{}, std::integral_constant<int, few_rows_rings<NU>::SW>{});
         else run(std::integral_constant<int, SA>{}, std::integral_constant<int, SW>{});
     } else {
         auto run = [&](auto nu_c, auto sw_c) __attribute__((always_inline)) {
             constexpr int U = decltype(nu_c)::value, S = decltype(sw_c)::value;
-            if (wave < 2) stream_group<EPI, PARTIAL, U, MT, SA, S, 0, 4>(p, smem, smem_off, wave, wave, lane, pass, passes);
-            else stream_group<EPI, PARTIAL, U, MT, SA, S, 1, 4>(p, smem, smem_off, wave, wave - 2, lane, pass, passes);
+            if (wave < 2) stream_group<EPI, PARTIAL, FOLD, U, MT, SA, S, 0, 4>(p, smem, smem_off, wave, wave, lane, pass, passes);
+            else stream_group<EPI, PARTIAL, FOLD, U, MT, SA, S, 1, 4>(p, smem, smem_off, wave, wave - 2, lane, pass, passes);
         };
         if (units == NU) run(std::integral_constant<int, NU>{}, std::integral_constant<int, SW>{});
         else if (units == NU / 2) run(std::integral_constant<int, NU / 2>{}, std::integral_constant<int, wide_share<NU / 2>::SW>{});

@@ -9,7 +9,7 @@ __global__ __launch_bounds__(512) void hs_gemm_stream(const bf16_t* __restrict__
                                                       const bf16_t* __restrict__ W2, void* __restrict__ Cout,
                                                       float* __restrict__ part, const int32_t* __restrict__ m_dev,
                                                       int m_max, int N, int K, int tpc, int n_groups, int n_pass) {
-    stream_kernel<EPI, PARTIAL, NU, MT, SA, SW, 8>(A, W, W2, Cout, part, m_dev, m_max, N, K, tpc, n_groups, n_pass);
+    stream_kernel<EPI, PARTIAL, false, NU, MT, SA, SW, 8>(A, W, W2, Cout, part, m_dev, m_max, N, K, tpc, n_groups, n_pass);
 }
 
 namespace {
@@ -30,7 +30,9 @@ void launch_stream(const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, 
 // Split K in chunks of at least this many k-tiles fetches the two operands apart (7B down, 33 tiles: 1 to 4 %; QKV of the 1.5B
 // shape, in chunks of 4, would take 5.4 us instead of 5.1, its down projection, in chunks of 14, the same either way).
 constexpr int HS_APART_TILES = 16;
-constexpr int HS_WIDE_KERNEL_ROWS = 512;
+constexpr int HS_TALL_ROWS = 160, HS_WIDE_KERNEL_ROWS = 512;
+// A round of 256 workgroups takes this long per k-tile (four wavefronts; eight, for each unit).
+constexpr int HS_WIDE_TILE_NS = 1600, HS_UNIT_TILE_NS = 305;
 #ifndef HS_WIDE_GROUP_ROWS
 #define HS_WIDE_GROUP_ROWS 352   // measured cross-over at the 7B shape: 33 vs 40 us at 300 rows, 49 vs 37 us at 385
 #endif
@@ -63,7 +65,7 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
     // Rows per pass: 256 leaves LDS for a deeper weight ring; 384 once the hint is within a factor 1.6 of 256 (the
     // row count of a speculative step swings by a third around its mean), so that a step above its average does
     // not pay a second pass over the weights.  Row tiles that do not exist cost nothing in either shape.
-    const bool tall = rows_hint > 160, few = rows_hint <= HS_FEW_ROWS && !PARTIAL && k >= 16 * BK;
+    const bool tall = rows_hint > HS_TALL_ROWS, few = rows_hint <= HS_FEW_ROWS && !PARTIAL && k >= 16 * BK;
     const int unit_cols = (EPI == HS_EPI_SWIGLU_BF16) ? 16 : 32, pass_rows = tall ? 384 : 256;
     const int passes = std::max(1, (std::min(rows_hint, m_max) + pass_rows - 1) / pass_rows);
     const int nu = EPI == HS_EPI_ROWMAX ? rowmax_units(n) : choose_units((n + unit_cols - 1) / unit_cols, chunks, passes);
@@ -77,7 +79,7 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
         const int units = (n + unit_cols - 1) / unit_cols;
         const long long wgs = (long long)((units + nu - 1) / nu) * chunks * passes;
         const long long wide_wgs = (long long)((units + 7) / 8) * chunks * ((std::min(rows_hint, m_max) + 255) / 256);
-        if ((wide_wgs + 255) / 256 * 1600 < (wgs + 255) / 256 * 305 * nu) {
+        if ((wide_wgs + 255) / 256 * HS_WIDE_TILE_NS < (wgs + 255) / 256 * HS_UNIT_TILE_NS * nu) {
             hs_launch_gemm_wide(EPI, PARTIAL, HS_ARGS);
             return;
         }
@@ -113,6 +115,18 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
 int hs_gemm_rowmax_groups(int n) {
     const int nu = rowmax_units(n);
     return (n + 32 * nu - 1) / (32 * nu);
+}
+
+// By the rounds of the kernel that launch_stream_shape takes at this many rows (512 and more): what its k-tiles take and about 8 us for
+// a round's first tiles and its stores, and the partial sums read back at 5.5 TB/s (7B shape, 4096 rows, us: QKV 148 and 27 for
+// 152 and 34, O 117 and 53 for 120 and 53, down 486 and 107 for 491 and 107; 14B at 1088: 89, 65, 156 for 92, 68, 158).
+double hs_gemm_split_us(bool add, int n, int chunks, int tpc, int rows) {
+    const int units = (n + 31) / 32, passes = (rows + 383) / 384, nu = choose_units(units, chunks, passes);
+    const int rounds = ((units + nu - 1) / nu * chunks * passes + 255) / 256;
+    const int wide_rounds = ((units + 7) / 8 * chunks * ((rows + 255) / 256) + 255) / 256;
+    const bool wide = wide_rounds * HS_WIDE_TILE_NS < rounds * HS_UNIT_TILE_NS * nu;
+    const double gemm = wide ? wide_rounds * (tpc * 1e-3 * HS_WIDE_TILE_NS + 8.) : rounds * (tpc * 1e-3 * HS_UNIT_TILE_NS * nu + 8.);
+    return gemm + (add ? chunks + 1 : chunks - 1) * 4e-6 * rows * n / 5.5;
 }
 
 void hs_launch_gemm_stream(int epi, const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, float* part,

@@ -7,7 +7,7 @@ __global__ __launch_bounds__(256, 1) void hs_gemm_wide(const bf16_t* __restrict_
                                                        const bf16_t* __restrict__ W2, void* __restrict__ Cout,
                                                        float* __restrict__ part, const int32_t* __restrict__ m_dev, int m_max,
                                                        int N, int K, int tpc, int n_groups, int n_pass) {
-    stream_kernel<EPI, PARTIAL, NU, 2, 2, 3, 4>(A, W, W2, Cout, part, m_dev, m_max, N, K, tpc, n_groups, n_pass);
+    stream_kernel<EPI, PARTIAL, false, NU, 2, 2, 3, 4>(A, W, W2, Cout, part, m_dev, m_max, N, K, tpc, n_groups, n_pass);
 }
 
 namespace {

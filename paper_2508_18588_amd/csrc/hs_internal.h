@@ -125,9 +125,11 @@ enum { HS_EPI_STORE_F32 = 0, HS_EPI_ADD_F32 = 1, HS_EPI_SWIGLU_BF16 = 2, HS_EPI_
 // pending: if not null and the split execution was chosen, the ordered reduce is NOT launched: *pending receives the
 // number of chunk partials left in the workspace ([chunk][m_max][n] floats at lay.gemm_part) for the next kernel in
 // line to add up in chunk order and apply the epilogue (store / add to c); otherwise *pending = 0.
+// fold_k: the largest K whose chunks may run one after the other in a workgroup where that is expected to be faster (0 where
+// rows_hint is only a limit: with far fewer rows than expected it is the slower execution, and the more so the longer K is).
 void hs_launch_gemm(const hs_ctx* ctx, int epi, const void* a, const bf16_t* w, const bf16_t* w2, void* c,
                     const int32_t* m_dev, int m_max, int n, int k, int rows_hint, hipStream_t st,
-                    int* pending = nullptr);
+                    int* pending = nullptr, int fold_k = 0);
 int hs_gemm_rowmax_groups(int n);   // column groups (= keys per row) of an HS_EPI_ROWMAX launch over n columns
 
 // What a row's place in its sequence comes to, written once per pass (beside the attention's unit lists, or by the launch

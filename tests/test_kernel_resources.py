@@ -43,7 +43,7 @@ def resource_report(source):
 @pytest.fixture(scope="module")
 def reports():
     """The sources' reports, compiled side by side (a GEMM source takes minutes)."""
-    names = ("hs_gemm_stream.hip", "hs_gemm_wide.hip", "hs_accept.hip", "hs_attention.hip")
+    names = ("hs_gemm_stream.hip", "hs_gemm_wide.hip", "hs_gemm_folded.hip", "hs_accept.hip", "hs_attention.hip")
     with ThreadPoolExecutor(len(names)) as ex:
         return dict(zip(names, ex.map(resource_report, names)))
 
@@ -82,6 +82,14 @@ def test_the_gemm_for_many_rows_uses_no_scratch(reports):
     for name, r in rep.items():
         assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
         assert r["VGPRs"] + r["AGPRs"] <= 512 and r["AGPRs"] == 256, (name, r)
+
+
+def test_folded_gemm_uses_no_scratch(reports):
+    """Two sets of up to 64 accumulators in wavefronts of 256 registers."""
+    rep = {k: v for k, v in reports["hs_gemm_folded.hip"].items() if "hs_gemm_folded" in k}
+    assert len(rep) == 6, sorted(rep)                          # stored and added, 2 to 4 units
+    for name, r in rep.items():
+        assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
 
 
 def test_greedy_acceptance_and_commit_fill_a_compute_unit(reports):

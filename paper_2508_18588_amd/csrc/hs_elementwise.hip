@@ -205,12 +205,14 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
                                                        const hs_row_info* infos, const int32_t* m_dev, T* __restrict__ q_out,
                                                        T* __restrict__ kc, T* __restrict__ vc, size_t layer_off, int hq,
                                                        int hkv, int h, const float* __restrict__ part, int chunks,
-                                                       size_t chunk_stride, int expected) {
+                                                       size_t chunk_stride, int expected, int by_page) {
     const int half = h >> 1, per_head = half >> 2;         // items of a q or k head
     const int n_rot = (hq + hkv) * per_head, n_items = n_rot + hkv * (h >> 2);
     const int nqkv = (hq + 2 * hkv) * h;
     const bool cs_vec = ((unsigned long long)rope_cs & 15ull) == 0;
+    // by_page: of 128 neighbouring rows 16 at a time go to one XCD (workgroups are dealt to the eight of them in turn).
     int row = blockIdx.x;
+    if (by_page) row = (row & ~127) | (row & 7) << 4 | (row >> 3 & 15);
     if (row >= expected && row >= *m_dev) return;
     for (;;) {
         const float* src = (chunks > 0 ? part : qkv) + (size_t)row * nqkv;
@@ -489,6 +491,12 @@ void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, c
 }
 #undef HS_NORM_LAUNCH
 
+// From this many expected rows on, neighbouring rows go to one XCD in sets of 16.  A page of V holds 16 positions side by side, 2
+// bytes each: rows of a sequence that are dealt to eight XCDs write parts of the same 32 bytes into eight L2s, and each goes to
+// memory on its own.  us, dealt in turn and in sets: 4096 rows of 4608 columns 32.4, 27.0; 1078 rows 14.2, 11.6; 1088 of 7168
+// 21.4, 18.8; 2048 of 2048 9.8, 8.3.  (With few rows sets of 16 would leave XCDs without any.)
+constexpr int HS_PAGE_ROWS = 512;
+
 void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
                        const hs_step* step, const float* qkv, void* q, int pending_chunks, int expected,
                        hipStream_t st) {
@@ -501,9 +509,10 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
     const int items = (d.n_q_heads + d.n_kv_heads) * (d.head_dim / 8) + d.n_kv_heads * (d.head_dim / 4);
     const int rounds = (items + 1023) / 1024, threads = ((items + rounds - 1) / rounds + 63) / 64 * 64;
     const dim3 grid(hs_row_grid(ctx, threads)), block(threads);
+    const int by_page = expected >= HS_PAGE_ROWS && grid.x % 128 == 0;
 #define HS_ROPE_ARGS(T)                                                                                          \
     qkv, ctx->rope_cs, infos, step->row_off + seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off,          \
-        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, expected
+        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, expected, by_page
     if (hs_fp32_activations(ctx))
         hipLaunchKernelGGL(rope_kv_kernel<float>, grid, block, 0, st, HS_ROPE_ARGS(float));
     else

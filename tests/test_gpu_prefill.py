@@ -213,3 +213,17 @@ def test_rows_of_one_call(toy, batch, longest, chunk, max_rows):
     for name, rows in want.items():
         assert np_of(eng.st[name])[:off[-1]].tolist() == rows, name
     eng.close()
+
+
+@pytest.mark.parametrize("longest", [130, 1000])
+def test_cache_does_not_depend_on_how_rows_are_dealt_to_workgroups(toy, longest):
+    """The rotary kernel deals rows to its workgroups in turn, or 16 neighbours at a time where its grid is a multiple of 128
+    (max_rows here) and 512 rows and more are expected: the same cache."""
+    shape, w, rope = toy
+    toks = texts(np.random.default_rng(longest), [longest, 700, 3, 611, 17], shape.vocab)
+    caches = []
+    for max_rows in (1279, 1280):
+        eng, _ = run_prefill(shape, w, rope, toks, 1024, max_rows, pages_seed=5)
+        caches.append((np_of(eng.kc).copy(), np_of(eng.vc).copy()))
+        eng.close()
+    assert (caches[0][0] == caches[1][0]).all() and (caches[0][1] == caches[1][1]).all()

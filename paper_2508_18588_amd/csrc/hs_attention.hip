@@ -173,11 +173,16 @@ __device__ inline void attn_subtile(const unsigned char* tile, const bf16x8 (&qf
 // A 64-key tile (four pages) of the prefill: the same steps with one maximum and one rescale per 64 keys and the two
 // halves' products independent of each other.  The rows are consecutive tokens: every row of the tile sees every key below
 // `all`, and the lane's own row the keys below `mine`.
+// A page's keys lie in LDS with bits 2 and 3 of their number exchanged (prefill_key_row): of a tile of scores a lane then holds
+// eight neighbouring keys of each page, and the values that belong to them are one 16-byte read.
+__device__ __forceinline__ int prefill_key_row(int key) { return (key & 3) | (key >> 1 & 4) | (key << 1 & 8); }
+// The half (of a row's 16 keys) that lies first is the other one in every second set of eight rows: no bank conflicts.
+__device__ __forceinline__ int prefill_value_at(int row, int half) { return row * 16 + ((half ^ (row >> 3)) & 1) * 8; }
 template <int HD>
 __device__ inline void attn_tile64(const bf16_t* sK, const bf16_t* sV, const bf16x8 (&qf)[HD / 16], f32x16 (&o)[HD / 32],
                                    float& m_run, float& l_run, int kbase, int all, int mine, float scale_log2, int half,
                                    int l32) {
-    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32;
+    constexpr int KS = HD + 8, NKS = HD / 16, NDT = HD / 32;
     f32x16 s[2];
 #pragma unroll
     for (int u = 0; u < 2; u++)
@@ -195,7 +200,7 @@ __device__ inline void attn_tile64(const bf16_t* sK, const bf16_t* sV, const bf1
         for (int u = 0; u < 2; u++)
 #pragma unroll
             for (int e = 0; e < 16; e++) {
-                const int kp = kbase + 32 * u + 8 * (e >> 2) + 4 * half + (e & 3);
+                const int kp = kbase + 32 * u + 16 * (e >> 3) + 8 * half + (e & 7);
                 s[u][e] = kp < all || kp < mine ? s[u][e] : -INFINITY;
             }
     }
@@ -238,12 +243,8 @@ __device__ inline void attn_tile64(const bf16_t* sK, const bf16_t* sV, const bf1
     for (int kk = 0; kk < 4; kk++)
 #pragma unroll
         for (int dt = 0; dt < NDT; dt++) {
-            const bf16_t* vrow = &sV[(kk * HD + dt * 32 + l32) * VS];
-            const u32x2 lo = *reinterpret_cast<const u32x2*>(vrow + 4 * half);
-            const u32x2 hi = *reinterpret_cast<const u32x2*>(vrow + 8 + 4 * half);
-            union { u32x4 u; bf16x8 v; } va;
-            va.u = u32x4{lo.x, lo.y, hi.x, hi.y};
-            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.v, pb[kk], o[dt], 0, 0, 0);
+            const bf16x8 va = *reinterpret_cast<const bf16x8*>(&sV[prefill_value_at(kk * HD + dt * 32 + l32, half)]);
+            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[kk], o[dt], 0, 0, 0);
         }
 }
 
@@ -673,13 +674,16 @@ __global__ __launch_bounds__(256, 2) void attn_verify_mfma(AttnArgs a, const int
 // tiles of keys in LDS (one barrier per tile instead of two, the next tile written while this one is multiplied), page
 // numbers held in a register and one softmax step per 64 keys: 190 and 38 us (630 TFLOP/s).  (One maximum per 64 instead of
 // 32 keys leaves fewer probabilities at exactly 1: the error against 64 bits grows by 0.1 to 0.2 %, 0.004629 to 0.004635.)
+// Those counters are of values in rows of 40 bytes, written and read in pieces of 8.  With the keys in the order that makes a lane's
+// values neighbours (prefill_key_row) they lie in rows of 32, in pieces of 16: 182 -> 178 us and 36.8 -> 33.3.  Multiplying
+// the next tile's keys between the exponentials needs 32 registers more than there are (182 and 42 us, with 10 spilled).
 template <int HD>
 __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, size_t layer_off,
     const int32_t* __restrict__ len_plus1, const int32_t* __restrict__ block_table, int max_blocks, int n_blocks,
     const int32_t* __restrict__ row_off, bf16_t* __restrict__ out, int hq, int hkv, float scale_log2, int batch, int nx) {
-    constexpr int KS = HD + 8, VS = 20, NKS = HD / 16, NDT = HD / 32, TILE = 64, NCK = HD / 32;
-    constexpr int K_BUF = TILE * KS, V_BUF = 4 * HD * VS;
+    constexpr int KS = HD + 8, NKS = HD / 16, NDT = HD / 32, TILE = 64, NCK = HD / 32;
+    constexpr int K_BUF = TILE * KS, V_BUF = 4 * HD * 16;
     __shared__ __attribute__((aligned(16))) bf16_t sK[2 * K_BUF];
     __shared__ __attribute__((aligned(16))) bf16_t sV[2 * V_BUF];
 
@@ -751,10 +755,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
 #pragma unroll
         for (int i = 0; i < NCK; i++) {
             const int c = lane + 64 * i;
-            *reinterpret_cast<u32x4*>(&sK[buf * K_BUF + (wave * 16 + c / (HD / 8)) * KS + (c % (HD / 8)) * 8]) = rk[i];
-            u32x2* dst = reinterpret_cast<u32x2*>(&sV[buf * V_BUF + (wave * HD + (c >> 1)) * VS + (c & 1) * 8]);
-            dst[0] = u32x2{rv[i].x, rv[i].y};
-            dst[1] = u32x2{rv[i].z, rv[i].w};
+            *reinterpret_cast<u32x4*>(&sK[buf * K_BUF + (wave * 16 + prefill_key_row(c / (HD / 8))) * KS + (c % (HD / 8)) * 8]) = rk[i];
+            *reinterpret_cast<u32x4*>(&sV[buf * V_BUF + prefill_value_at(wave * HD + (c >> 1), c & 1)]) = rv[i];
         }
     };
     fetch(0);

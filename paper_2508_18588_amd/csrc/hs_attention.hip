@@ -173,10 +173,9 @@ __device__ inline void attn_subtile(const unsigned char* tile, const bf16x8 (&qf
 // A 64-key tile (four pages) of the prefill: the same steps with one maximum and one rescale per 64 keys and the two
 // halves' products independent of each other.  The rows are consecutive tokens: every row of the tile sees every key below
 // `all`, and the lane's own row the keys below `mine`.
-// A page's keys lie in LDS with bits 2 and 3 of their number exchanged (prefill_key_row): of a tile of scores a lane then holds
-// eight neighbouring keys of each page, and the values that belong to them are one 16-byte read.
-__device__ __forceinline__ int prefill_key_row(int key) { return (key & 3) | (key >> 1 & 4) | (key << 1 & 8); }
-// The half (of a row's 16 keys) that lies first is the other one in every second set of eight rows: no bank conflicts.
+// A page's keys are in order: of a tile of scores a lane of half h holds keys 4h .. 4h+3 and 8+4h .. 8+4h+3 of each page.  The values
+// that belong to them lie together in LDS, where in a row's 16 prefill_value_at says: one 16-byte read.  The half that
+// lies first is the other one in every second set of eight rows, so that no two lanes meet in a bank.
 __device__ __forceinline__ int prefill_value_at(int row, int half) { return row * 16 + ((half ^ (row >> 3)) & 1) * 8; }
 template <int HD>
 __device__ inline void attn_tile64(const bf16_t* sK, const bf16_t* sV, const bf16x8 (&qf)[HD / 16], f32x16 (&o)[HD / 32],
@@ -200,7 +199,7 @@ __device__ inline void attn_tile64(const bf16_t* sK, const bf16_t* sV, const bf1
         for (int u = 0; u < 2; u++)
 #pragma unroll
             for (int e = 0; e < 16; e++) {
-                const int kp = kbase + 32 * u + 16 * (e >> 3) + 8 * half + (e & 7);
+                const int kp = kbase + 32 * u + 8 * (e >> 2) + 4 * half + (e & 3);
                 s[u][e] = kp < all || kp < mine ? s[u][e] : -INFINITY;
             }
     }
@@ -674,8 +673,9 @@ __global__ __launch_bounds__(256, 2) void attn_verify_mfma(AttnArgs a, const int
 // tiles of keys in LDS (one barrier per tile instead of two, the next tile written while this one is multiplied), page
 // numbers held in a register and one softmax step per 64 keys: 190 and 38 us (630 TFLOP/s).  (One maximum per 64 instead of
 // 32 keys leaves fewer probabilities at exactly 1: the error against 64 bits grows by 0.1 to 0.2 %, 0.004629 to 0.004635.)
-// Those counters are of values in rows of 40 bytes, written and read in pieces of 8.  With the keys in the order that makes a lane's
-// values neighbours (prefill_key_row) they lie in rows of 32, in pieces of 16: 182 -> 178 us and 36.8 -> 33.3.  Multiplying
+// Those counters are of values in rows of 40 bytes, read in two pieces of 8.  Now they lie in rows of 32 in the order in which a lane
+// needs them (prefill_value_at), written in pieces of 8 and read in one of 16: 182 -> 176 and 41 -> 38, same bits.  (With a
+// page's keys in another order in LDS the writes are one piece, too: 174 and 35, but every sum of probabilities is another one.)  Multiplying
 // the next tile's keys between the exponentials needs 32 registers more than there are (182 and 42 us, with 10 spilled).
 template <int HD>
 __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
@@ -755,8 +755,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma(
 #pragma unroll
         for (int i = 0; i < NCK; i++) {
             const int c = lane + 64 * i;
-            *reinterpret_cast<u32x4*>(&sK[buf * K_BUF + (wave * 16 + prefill_key_row(c / (HD / 8))) * KS + (c % (HD / 8)) * 8]) = rk[i];
-            *reinterpret_cast<u32x4*>(&sV[buf * V_BUF + prefill_value_at(wave * HD + (c >> 1), c & 1)]) = rv[i];
+            *reinterpret_cast<u32x4*>(&sK[buf * K_BUF + (wave * 16 + c / (HD / 8)) * KS + (c % (HD / 8)) * 8]) = rk[i];
+            bf16_t* dst = &sV[buf * V_BUF + (c & 1) * 4];
+            *reinterpret_cast<u32x2*>(dst + prefill_value_at(wave * HD + (c >> 1), 0)) = u32x2{rv[i].x, rv[i].y};
+            *reinterpret_cast<u32x2*>(dst + prefill_value_at(wave * HD + (c >> 1), 1)) = u32x2{rv[i].z, rv[i].w};
         }
     };
     fetch(0);

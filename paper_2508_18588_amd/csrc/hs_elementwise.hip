@@ -132,11 +132,11 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS == 1 ? 7 : ITEMS == 2 ? 8 :
                                                        OutT* __restrict__ out, const int32_t* m_dev,
                                                        int d, float eps,
                                                        const float* __restrict__ part, int chunks,
-                                                       size_t chunk_stride, int expected) {
+                                                       size_t chunk_stride, int early) {
     __shared__ float red[NORM_THREADS_MAX / 64];
     clear_sums(red);
     int row = blockIdx.x;
-    if (row >= expected && row >= *m_dev) return;
+    if (row >= early && row >= *m_dev) return;
     for (;;) {
         // (all of a row's loads inside the loop: one that is moved in front of it is waited for there)
         const unsigned zero = hs_opaque_zero();
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
                                                        const hs_row_info* infos, const int32_t* m_dev, T* __restrict__ q_out,
                                                        T* __restrict__ kc, T* __restrict__ vc, size_t layer_off, int hq,
                                                        int hkv, int h, const float* __restrict__ part, int chunks,
-                                                       size_t chunk_stride, int expected, int by_page) {
+                                                       size_t chunk_stride, int early, int by_page) {
     const int half = h >> 1, per_head = half >> 2;         // items of a q or k head
     const int n_rot = (hq + hkv) * per_head, n_items = n_rot + hkv * (h >> 2);
     const int nqkv = (hq + 2 * hkv) * h;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
     // by_page: of 128 neighbouring rows 16 at a time go to one XCD (workgroups are dealt to the eight of them in turn).
     int row = blockIdx.x;
     if (by_page) row = (row & ~127) | (row & 7) << 4 | (row >> 3 & 15);
-    if (row >= expected && row >= *m_dev) return;
+    if (row >= early && row >= *m_dev) return;
     for (;;) {
         const float* src = (chunks > 0 ? part : qkv) + (size_t)row * nqkv;
         const int n_src = chunks > 0 ? chunks : 1;
@@ -293,11 +293,11 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
 // One workgroup of 16 wavefronts per row; 16-byte loads where the row is aligned.  Ties resolve to the lowest id
 // at every level, so the result is the first maximum whatever the reduction shape.
 __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int32_t* __restrict__ out,
-                                                       const int32_t* m_dev, int vocab, int expected) {
+                                                       const int32_t* m_dev, int vocab, int early) {
     __shared__ float sv[16];
     __shared__ int si[16];
     int row = blockIdx.x;
-    if (row >= expected && row >= *m_dev) return;
+    if (row >= early && row >= *m_dev) return;
     for (;;) {
         const int m_lane = m_dev[hs_opaque_zero()];
         if (row != (int)blockIdx.x) __syncthreads();  // the previous row's candidates have been read
@@ -307,20 +307,22 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
         auto take = [&](float v, int i) { if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; } };
         if ((vocab & 3) == 0) {
             const float4* l4 = reinterpret_cast<const float4*>(l);
-            // (four loads on their way at once; beyond the row's end its last element again)
+            // (four loads on their way at once; beyond the row's end its last element again.  Behind the first four the count has
+            // arrived: of a row that does not exist 64 KB are read, not all of its vocabulary.)
             const int n4 = vocab / 4;
             for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * 1024) {
                 float4 v[4];
 #pragma unroll
                 for (int j = 0; j < 4; j++) v[j] = l4[min(i0 + 1024 * j, n4 - 1)];
                 hs_loads_issued();
+                if (row >= hs_uniform(m_lane)) break;
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
                     const int i = min(i0 + 1024 * j, n4 - 1);
                     take(v[j].x, 4 * i); take(v[j].y, 4 * i + 1); take(v[j].z, 4 * i + 2); take(v[j].w, 4 * i + 3);
                 }
             }
-        } else {
+        } else if (row < hs_uniform(m_lane)) {
             for (int i = threadIdx.x; i < vocab; i += 1024) take(l[i], i);
         }
         const int m = hs_uniform(m_lane);
@@ -481,12 +483,13 @@ void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, c
     const float* part = reinterpret_cast<const float*>(ctx->ws + ctx->lay.gemm_part);
     const size_t stride = (size_t)ctx->lim.max_rows * d.d_model;
     const dim3 block(norm_threads(d.d_model)), grid(hs_row_grid(ctx, block.x));
+    const int early = hs_early_rows(expected);
     if (hs_fp32_activations(ctx)) {
         HS_NORM_LAUNCH(rmsnorm_kernel, float, grid, x, w, (float*)out, m_dev, d.d_model, d.rms_eps, part, pending_chunks,
-                       stride, expected)
+                       stride, early)
     } else {
         HS_NORM_LAUNCH(rmsnorm_kernel, bf16_t, grid, x, w, (bf16_t*)out, m_dev, d.d_model, d.rms_eps, part,
-                       pending_chunks, stride, expected)
+                       pending_chunks, stride, early)
     }
 }
 #undef HS_NORM_LAUNCH
@@ -512,7 +515,7 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
     const int by_page = expected >= HS_PAGE_ROWS && grid.x % 128 == 0;
 #define HS_ROPE_ARGS(T)                                                                                          \
     qkv, ctx->rope_cs, infos, step->row_off + seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off,          \
-        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, expected, by_page
+        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, hs_early_rows(expected), by_page
     if (hs_fp32_activations(ctx))
         hipLaunchKernelGGL(rope_kv_kernel<float>, grid, block, 0, st, HS_ROPE_ARGS(float));
     else
@@ -523,5 +526,5 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
 void hs_launch_argmax(const hs_ctx* ctx, const float* logits, int32_t* argmax, const int32_t* m_dev,
                       int expected, hipStream_t st) {
     hipLaunchKernelGGL(argmax_kernel, dim3(hs_row_grid(ctx, 1024)), dim3(1024), 0, st, logits, argmax, m_dev,
-                       ctx->desc.vocab, expected);
+                       ctx->desc.vocab, hs_early_rows(expected));
 }

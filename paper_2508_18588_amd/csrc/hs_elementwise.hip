@@ -125,22 +125,26 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS <= 2 ? 8 : 4) void embed_no
 // OutT = bf16_t (rounded activations) or float (fp32-activation mode).
 // The kernel is a chain of memory round trips, not a stream: a thread keeps its (up to NORM_ITEMS x 4) elements in
 // registers from the first load to the normalised store, and the norm weights are fetched with them.  With many rows the
-// other rows of a compute unit hide the chain; how many share one does not matter (rows of 3584 and of 5120 in
-// workgroups of 448 to 1024 threads: a step takes the same within 0.3 %).
-template <typename OutT, int ITEMS>
-__global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS == 1 ? 7 : ITEMS == 2 ? 8 : 4) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
+// other rows of a compute unit hide the chain: 64 registers and eight wavefronts per SIMD, so that two workgroups of 1024 threads
+// share one and the grid (hs_row_grid) is resident.  EARLY, for a few rows (hs_early_rows), hides it by what is on its way at
+// once: the row count, the row and ten partials of it, in 70 registers.  us, 64 registers and 70: 1078 rows of 3584 with nine
+// partials 29.0 and 33.3, of 4096 with seven 30.1 and 33.6, of 3584 with none 7.6 and 10.2; 540 rows 17.2 and 19.0; 7 rows
+// of 1536 with ten 4.3 and 3.7.
+template <typename OutT, int ITEMS, bool EARLY>
+__global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS > 2 ? 4 : EARLY && ITEMS == 1 ? 7 : 8) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
                                                        OutT* __restrict__ out, const int32_t* m_dev,
                                                        int d, float eps,
                                                        const float* __restrict__ part, int chunks,
                                                        size_t chunk_stride, int early) {
     __shared__ float red[NORM_THREADS_MAX / 64];
     clear_sums(red);
-    int row = blockIdx.x;
-    if (row >= early && row >= *m_dev) return;
+    int row = blockIdx.x, m = EARLY && row < early ? INT32_MAX : *m_dev;
+    if (row >= m) return;
     for (;;) {
-        // (all of a row's loads inside the loop: one that is moved in front of it is waited for there)
-        const unsigned zero = hs_opaque_zero();
-        const int m_lane = m_dev[zero];
+        // (EARLY: all of a row's loads inside the loop; one that is moved in front of it is waited for there)
+        const unsigned zero = EARLY ? hs_opaque_zero() : 0u;
+        int m_lane = m;
+        if constexpr (EARLY) m_lane = m_dev[zero];
         float* xr = x + (size_t)row * d;
         const float* pr = part + (size_t)row * d;
         float4 v[ITEMS], g[ITEMS];
@@ -153,7 +157,7 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS == 1 ? 7 : ITEMS == 2 ? 8 :
         }
         if (chunks > 0) {
             // PER partials of each element in flight at once (written out: left to itself the compiler waits for each)
-            constexpr int PER = ITEMS == 1 ? 10 : ITEMS == 2 ? 3 : 2;
+            constexpr int PER = ITEMS == 1 ? (EARLY ? 10 : 5) : ITEMS == 2 ? 3 : 2;
             float4 t[ITEMS];
             const float* pc = pr;
             for (int c0 = 0; c0 < chunks; c0 += PER) {
@@ -183,13 +187,20 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS == 1 ? 7 : ITEMS == 2 ? 8 :
                 v[it].x += t[it].x; v[it].y += t[it].y; v[it].z += t[it].z; v[it].w += t[it].w;
             }
         }
-        const int m = hs_uniform(m_lane);
-        if (row >= m) return;
+        if constexpr (EARLY) {
+            m = hs_uniform(m_lane);
+            if (row >= m) return;
+        }
         norm_row<OutT, ITEMS>(v, g, chunks > 0, xr, out + (size_t)row * d, d, eps, red);
         row += gridDim.x;
         if (row >= m) return;
     }
 }
+
+template <typename OutT, int ITEMS>
+constexpr auto early_rmsnorm = &rmsnorm_kernel<OutT, ITEMS, true>;
+template <typename OutT, int ITEMS>
+constexpr auto counted_rmsnorm = &rmsnorm_kernel<OutT, ITEMS, false>;
 
 // Rotates q and k heads at the row's position (pairs i, i + h/2), writes q as bf16, K into its page row-major and V into
 // its page with the token index fastest.  T = bf16_t, or float in the fp32-activation mode (queries and cache entries
@@ -200,8 +211,12 @@ __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS == 1 ? 7 : ITEMS == 2 ? 8 :
 // slot -> page is followed.  Bound by the partial sums it reads.  With the row gathered in LDS by 1024 threads first:
 // 74 us for 4096 rows of 4608 in three chunks, 28 us for 1067 rows of 7168 in two, 28 us
 // for 2048 rows of 2048 in six; now 70, 25 and 21 (2.7 to 5 TB/s of partial sums).
-template <typename T>
-__global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__ qkv, const float* __restrict__ rope_cs,
+// EARLY as in the norm: with few rows six chunks in flight and 70 registers (74 where T is float), else three and 64, for eight
+// wavefronts per SIMD: two workgroups of 1024 threads (40 and 8 heads of 128) share a compute unit.  us, 64 registers and 70:
+// 540 rows of that shape 12.5 and 12.9, 1078 rows 20.0 and 20.2, of 28 and 4 heads 10.6 and 11.1; 7 rows of 12 and 2 heads
+// in six chunks 4.4 and 3.7.
+template <typename T, bool EARLY>
+__global__ __launch_bounds__(1024, EARLY ? 4 : 8) void rope_kv_kernel(const float* __restrict__ qkv, const float* __restrict__ rope_cs,
                                                        const hs_row_info* infos, const int32_t* m_dev, T* __restrict__ q_out,
                                                        T* __restrict__ kc, T* __restrict__ vc, size_t layer_off, int hq,
                                                        int hkv, int h, const float* __restrict__ part, int chunks,
@@ -213,20 +228,22 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
     // by_page: of 128 neighbouring rows 16 at a time go to one XCD (workgroups are dealt to the eight of them in turn).
     int row = blockIdx.x;
     if (by_page) row = (row & ~127) | (row & 7) << 4 | (row >> 3 & 15);
-    if (row >= early && row >= *m_dev) return;
+    int m = EARLY && row < early ? INT32_MAX : *m_dev;
+    if (row >= m) return;
     for (;;) {
         const float* src = (chunks > 0 ? part : qkv) + (size_t)row * nqkv;
         const int n_src = chunks > 0 ? chunks : 1;
-        int m = 0;      // (stays 0 for a wavefront without items; lane 0 has one if any lane has)
+        if constexpr (EARLY) m = 0;      // (stays 0 for a wavefront without items; lane 0 has one if any lane has)
         for (int i = threadIdx.x; i < n_items; i += blockDim.x) {
-            const unsigned zero = hs_opaque_zero();     // (all of an item's loads inside the loop, as in the norm)
-            const int m_lane = m_dev[zero];
+            const unsigned zero = EARLY ? hs_opaque_zero() : 0u;     // (all of an item's loads inside the loop, as in the norm)
+            int m_lane = m;
+            if constexpr (EARLY) m_lane = m_dev[zero];
             const hs_row_info info = infos[row + zero];
             const bool rot = i < n_rot;
             const int head = rot ? i / per_head : hq + hkv + (i - n_rot) / (h >> 2);      // head of the QKV vector
             const int j = rot ? 4 * (i % per_head) : 4 * ((i - n_rot) % (h >> 2));        // first element in it
             // PER chunks in flight at once (v items load their elements twice: no branch between the loads)
-            constexpr int PER = 6;
+            constexpr int PER = EARLY ? 6 : 3;
             const unsigned at = (unsigned)(head * h + j) * 4u, at_y = at + (rot ? (unsigned)half * 4u : 0u);
             const float* pc = src;
             float4 x, y;
@@ -255,7 +272,7 @@ __global__ __launch_bounds__(1024) void rope_kv_kernel(const float* __restrict__
             }
             // (no such row, or one that writes nothing: the same for all threads of the workgroup)
             const int place = hs_uniform(info.slot);
-            m = hs_uniform(m_lane);
+            if constexpr (EARLY) m = hs_uniform(m_lane);
             if (row >= m || place < 0) break;
             const int page = place >> 4, in_page = place & 15;
             if (!rot) {   // v head -> cache [page][kv head][h][16]
@@ -484,13 +501,15 @@ void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, c
     const size_t stride = (size_t)ctx->lim.max_rows * d.d_model;
     const dim3 block(norm_threads(d.d_model)), grid(hs_row_grid(ctx, block.x));
     const int early = hs_early_rows(expected);
+#define HS_ARGS(T) x, w, (T*)out, m_dev, d.d_model, d.rms_eps, part, pending_chunks, stride, early
     if (hs_fp32_activations(ctx)) {
-        HS_NORM_LAUNCH(rmsnorm_kernel, float, grid, x, w, (float*)out, m_dev, d.d_model, d.rms_eps, part, pending_chunks,
-                       stride, early)
+        if (early) { HS_NORM_LAUNCH(early_rmsnorm, float, grid, HS_ARGS(float)) }
+        else { HS_NORM_LAUNCH(counted_rmsnorm, float, grid, HS_ARGS(float)) }
     } else {
-        HS_NORM_LAUNCH(rmsnorm_kernel, bf16_t, grid, x, w, (bf16_t*)out, m_dev, d.d_model, d.rms_eps, part,
-                       pending_chunks, stride, early)
+        if (early) { HS_NORM_LAUNCH(early_rmsnorm, bf16_t, grid, HS_ARGS(bf16_t)) }
+        else { HS_NORM_LAUNCH(counted_rmsnorm, bf16_t, grid, HS_ARGS(bf16_t)) }
     }
+#undef HS_ARGS
 }
 #undef HS_NORM_LAUNCH
 
@@ -512,14 +531,17 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
     const int items = (d.n_q_heads + d.n_kv_heads) * (d.head_dim / 8) + d.n_kv_heads * (d.head_dim / 4);
     const int rounds = (items + 1023) / 1024, threads = ((items + rounds - 1) / rounds + 63) / 64 * 64;
     const dim3 grid(hs_row_grid(ctx, threads)), block(threads);
-    const int by_page = expected >= HS_PAGE_ROWS && grid.x % 128 == 0;
+    const int by_page = expected >= HS_PAGE_ROWS && grid.x % 128 == 0, early = hs_early_rows(expected);
 #define HS_ROPE_ARGS(T)                                                                                          \
     qkv, ctx->rope_cs, infos, step->row_off + seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off,          \
-        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, hs_early_rows(expected), by_page
-    if (hs_fp32_activations(ctx))
-        hipLaunchKernelGGL(rope_kv_kernel<float>, grid, block, 0, st, HS_ROPE_ARGS(float));
-    else
-        hipLaunchKernelGGL(rope_kv_kernel<bf16_t>, grid, block, 0, st, HS_ROPE_ARGS(bf16_t));
+        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, early, by_page
+    if (hs_fp32_activations(ctx)) {
+        if (early) hipLaunchKernelGGL((rope_kv_kernel<float, true>), grid, block, 0, st, HS_ROPE_ARGS(float));
+        else hipLaunchKernelGGL((rope_kv_kernel<float, false>), grid, block, 0, st, HS_ROPE_ARGS(float));
+    } else {
+        if (early) hipLaunchKernelGGL((rope_kv_kernel<bf16_t, true>), grid, block, 0, st, HS_ROPE_ARGS(bf16_t));
+        else hipLaunchKernelGGL((rope_kv_kernel<bf16_t, false>), grid, block, 0, st, HS_ROPE_ARGS(bf16_t));
+    }
 #undef HS_ROPE_ARGS
 }
 

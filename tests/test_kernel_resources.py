@@ -43,7 +43,7 @@ def resource_report(source):
 @pytest.fixture(scope="module")
 def reports():
     """The sources' reports, compiled side by side (a GEMM source takes minutes)."""
-    names = ("hs_gemm_stream.hip", "hs_gemm_wide.hip", "hs_gemm_folded.hip", "hs_accept.hip", "hs_attention.hip")
+    names = ("hs_gemm_stream.hip", "hs_gemm_wide.hip", "hs_gemm_folded.hip", "hs_accept.hip", "hs_attention.hip", "hs_elementwise.hip")
     with ThreadPoolExecutor(len(names)) as ex:
         return dict(zip(names, ex.map(resource_report, names)))
 
@@ -104,4 +104,16 @@ def test_greedy_acceptance_and_commit_fill_a_compute_unit(reports):
     sampler = {k: v for k, v in rep.items() if "reject_stats_kernel" in k or ("accept_commit_kernel" in k and "Lb1E" in k)}
     assert len(sampler) == 3, sorted(rep)                      # the sums, and the walk for either cache
     for name, r in sampler.items():
+        assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
+
+
+def test_row_kernels_for_many_rows_let_two_workgroups_share_a_compute_unit(reports):
+    """hs_row_grid deals rows to 2048 threads per compute unit: eight wavefronts per SIMD, or a launch whose workgroups have 1024
+    threads runs in two rounds.  (The instances for a few rows, EARLY, trade that for more loads in flight.)"""
+    rep = reports["hs_elementwise.hip"]
+    many = [k for k in rep if re.search(r"rmsnorm_kernelI[tf]Li[12]ELb0E|rope_kv_kernelI[tf]Lb0E|argmax_kernel", k)]
+    assert len(many) >= 7, sorted(rep)
+    for name in many:
+        assert rep[name]["VGPRs"] <= 64 and rep[name]["Occupancy [waves/SIMD]"] == 8, (name, rep[name])
+    for name, r in rep.items():
         assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)

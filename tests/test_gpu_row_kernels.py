@@ -191,3 +191,27 @@ def test_tables_that_only_allow_narrow_loads():
             logits.append(last_row_logits(eng, list(prompts), "verify"))
             eng.close()
         assert (logits[0] == logits[1]).all() and (logits[0] == logits[2]).all()
+
+
+@pytest.mark.parametrize("vocab", [64, 4096, 16380, 16384, 16386, 16388, 36868])
+def test_argmax_is_the_first_of_the_largest_logits(vocab):
+    """The largest logit there three times; widths below, at and above the four loads of 1024 threads that are on their way at once, and one that allows no 16-byte
+    loads; with and without an estimate of the rows."""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=vocab)
+    w = make_weights(shape, vocab)
+    third = (vocab + 2) // 3
+    w["lm_head"] = np.concatenate([w["lm_head"][:third]] * 3)[:vocab].copy()
+    rng = np.random.default_rng(vocab)
+    eng = Engine(shape, w, rope_table(64, 64), max_batch=70, k_max=0, c_max=1, max_len=32)
+    eng.load_sequences([rng.integers(0, vocab, 20).astype(np.int32) for _ in range(70)], [9] * 70)
+    eng.set_rows([dict(tok=rng.integers(0, vocab, 1), parent=[-1], pos=[19]) for _ in range(70)])
+    for hint in (0, 3, 64, 70):
+        eng.c_step.rows_hint = hint
+        eng.st["argmax"].fill_(-1)
+        eng.verify()
+        torch.cuda.synchronize()
+        logits = np_of(eng.logits)[:70]
+        assert np_of(eng.st["argmax"]).tolist() == logits.argmax(1).tolist(), hint
+        assert (logits.argmax(1) < third).all()
+    eng.close()

@@ -304,11 +304,6 @@ hs_status hs_draft_group(hs_ctx* ctx, const hs_group_draft_args* args, const hs_
     return HS_OK;
 }
 
-// Largest K folded in a speculative step, whose row count swings around what is expected of it.  With 1078 rows expected and 64, 220,
-// 540, 1078 and 1300 there, us, split and its reduce against folded: 7B QKV 19, 25, 45, 59, 82 / 24, 35, 39, 43, 69, O 17, 22, 39, 54, 78
-// / 24, 39, 41, 44, 65; a down projection, three to five times as long, would take 180 us however few rows come, 45 split.
-static constexpr int HS_VERIFY_FOLD_K = 5120;
-
 hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* seq, hs_step* step, hs_stream stream) {
     if (!ctx) return HS_ERR_INVALID_ARG;
     if (!ctx->ws) return fail(ctx, HS_ERR_CAPACITY, "no workspace bound");
@@ -332,7 +327,7 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
     // Few rows expected: run the narrow projections split over K (same arithmetic, more workgroups).
     const int hint = step->rows_hint > 0 ? step->rows_hint : m_max;
     const int expected = step->rows_hint > 0 ? std::min(step->rows_hint, m_max) : 0;   // (no estimate: the limits are none)
-    const int fold_k = step->rows_hint > 0 ? HS_VERIFY_FOLD_K : 0;
+    const double fold = step->rows_hint > 0 ? HS_FOLD_GUESSED : 0.;
     const size_t cap_slot = capture_slot_bytes(ctx), cap_xn = hs_fp32_activations(ctx) ? cap_slot : cap_slot / 2;
 
     (void)hipGetLastError();
@@ -343,8 +338,8 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
 
     // A projection run in the split execution leaves its chunk partials for the next kernel in line (RMSNorm for
     // the residual projections, rotary/KV write for QKV), which adds them up in chunk order: one launch fewer per
-    // projection.  `pend` carries the number of chunks from the projection to that kernel.
-    int pend = 0;
+    // projection.  `pend` tells that kernel how many chunks there are, and up to how many rows.
+    hs_pending pend;
     for (int l = 0; l < d.n_layers; l++) {
         pr.begin(3);
         if (l == 0) hs_launch_embed_norm(ctx, cache, seq, step, true, x, ctx->norm1[0], xn, st);
@@ -356,7 +351,7 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
         }
         pr.begin(1);
         hs_launch_gemm(ctx, HS_EPI_STORE_F32, xn, ctx->wqkv[l], nullptr, qkv, m_dev, m_max, nqkv, d.d_model, hint, st,
-                       &pend, fold_k);
+                       &pend, fold);
         pr.end();
         pr.begin(3);
         hs_launch_rope_kv(ctx, l, cache, seq, step, qkv, q, pend, expected, st);
@@ -368,7 +363,7 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
         hs_launch_attention_merge(ctx, seq, step, attn, expected, st);
         pr.end();
         pr.begin(1);
-        hs_launch_gemm(ctx, HS_EPI_ADD_F32, attn, ctx->wo[l], nullptr, x, m_dev, m_max, d.d_model, qh, hint, st, &pend, fold_k);
+        hs_launch_gemm(ctx, HS_EPI_ADD_F32, attn, ctx->wo[l], nullptr, x, m_dev, m_max, d.d_model, qh, hint, st, &pend, fold);
         pr.end();
         pr.begin(3);
         hs_launch_rmsnorm(ctx, x, ctx->norm2[l], xn, m_dev, pend, expected, st);
@@ -382,7 +377,7 @@ hs_status hs_verify(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* s
         pr.end();
         pr.begin(1);
         hs_launch_gemm(ctx, HS_EPI_ADD_F32, act, ctx->wdown[l], nullptr, x, m_dev, m_max, d.d_model, d.d_ffn, hint, st,
-                       &pend, fold_k);
+                       &pend, fold);
         pr.end();
     }
     pr.begin(3);
@@ -438,28 +433,28 @@ hs_status hs_prefill(hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* 
     const int nqkv = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
     const int hint = args->rows_hint > 0 ? args->rows_hint : m_max;
     const int expected = args->rows_hint > 0 ? std::min(args->rows_hint, m_max) : 0;
-    const int fold_k = args->rows_hint > 0 ? INT32_MAX : 0;
+    const double fold = args->rows_hint > 0 ? HS_FOLD_KNOWN : 0.;
     // the row kernels place a row at slot (sequence length - 1 + its index): here that is kv_done + i
     hs_seq_state pf = *seq;
     pf.seq_len = len_plus1;
 
     (void)hipGetLastError();
     hs_launch_prefill_rows(ctx, cache, seq, args->kv_done, args->chunk, step, len_plus1, st);
-    int pend = 0;
+    hs_pending pend;
     for (int l = 0; l < d.n_layers; l++) {
         if (l == 0) hs_launch_embed_norm(ctx, cache, &pf, step, false, x, ctx->norm1[0], xn, st);
         else hs_launch_rmsnorm(ctx, x, ctx->norm1[l], xn, m_dev, pend, expected, st);
         hs_launch_gemm(ctx, HS_EPI_STORE_F32, xn, ctx->wqkv[l], nullptr, qkv, m_dev, m_max, nqkv, d.d_model, hint, st,
-                       &pend, fold_k);
+                       &pend, fold);
         hs_launch_rope_kv(ctx, l, cache, &pf, step, qkv, q, pend, expected, st);
-        pend = 0;
+        pend = {};
         if (l + 1 == d.n_layers) break;   // the last layer's K/V are written: nothing downstream is needed
         hs_launch_attention_prefill(ctx, l, cache, &pf, len_plus1, step, q, attn, args->chunk, st);
-        hs_launch_gemm(ctx, HS_EPI_ADD_F32, attn, ctx->wo[l], nullptr, x, m_dev, m_max, d.d_model, qh, hint, st, &pend, fold_k);
+        hs_launch_gemm(ctx, HS_EPI_ADD_F32, attn, ctx->wo[l], nullptr, x, m_dev, m_max, d.d_model, qh, hint, st, &pend, fold);
         hs_launch_rmsnorm(ctx, x, ctx->norm2[l], xn, m_dev, pend, expected, st);
         hs_launch_gemm(ctx, HS_EPI_SWIGLU_BF16, xn, ctx->wgate[l], ctx->wup[l], act, m_dev, m_max, d.d_ffn, d.d_model, hint, st);
         hs_launch_gemm(ctx, HS_EPI_ADD_F32, act, ctx->wdown[l], nullptr, x, m_dev, m_max, d.d_model, d.d_ffn, hint, st,
-                       &pend, fold_k);
+                       &pend, fold);
     }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail_hip(ctx, "hs_prefill", e);
     return HS_OK;
@@ -664,7 +659,7 @@ hs_status hs_debug_gemm(hs_ctx* ctx, int32_t epi, const void* a, const void* w, 
         return fail(ctx, HS_ERR_CAPACITY, "hs_debug_gemm: partial-sum scratch too small for this shape");
     (void)hipGetLastError();
     hs_launch_gemm(ctx, epi, (const bf16_t*)a, (const bf16_t*)w, (const bf16_t*)w2, c, m_dev, m_max, n, k,
-                   rows_hint > 0 ? rows_hint : m_max, (hipStream_t)stream, nullptr, rows_hint > 0 ? k : 0);
+                   rows_hint > 0 ? rows_hint : m_max, (hipStream_t)stream, nullptr, rows_hint > 0 ? HS_FOLD_KNOWN : 0.);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return fail_hip(ctx, "hs_debug_gemm", e);
     return HS_OK;
 }

@@ -134,12 +134,13 @@ template <typename OutT, int ITEMS, bool EARLY>
 __global__ __launch_bounds__(NORM_THREADS_MAX, ITEMS > 2 ? 4 : EARLY && ITEMS == 1 ? 7 : 8) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ w,
                                                        OutT* __restrict__ out, const int32_t* m_dev,
                                                        int d, float eps,
-                                                       const float* __restrict__ part, int chunks,
+                                                       const float* __restrict__ part, int chunks, int pending_rows,
                                                        size_t chunk_stride, int early) {
     __shared__ float red[NORM_THREADS_MAX / 64];
     clear_sums(red);
     int row = blockIdx.x, m = EARLY && row < early ? INT32_MAX : *m_dev;
     if (row >= m) return;
+    if (!EARLY && m > pending_rows) chunks = 0;     // (where few rows are expected, partials pend whatever their number)
     for (;;) {
         // (EARLY: all of a row's loads inside the loop; one that is moved in front of it is waited for there)
         const unsigned zero = EARLY ? hs_opaque_zero() : 0u;
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(1024, EARLY ? 4 : 8) void rope_kv_kernel(const floa
                                                        const hs_row_info* infos, const int32_t* m_dev, T* __restrict__ q_out,
                                                        T* __restrict__ kc, T* __restrict__ vc, size_t layer_off, int hq,
                                                        int hkv, int h, const float* __restrict__ part, int chunks,
-                                                       size_t chunk_stride, int early, int by_page) {
+                                                       int pending_rows, size_t chunk_stride, int early, int by_page) {
     const int half = h >> 1, per_head = half >> 2;         // items of a q or k head
     const int n_rot = (hq + hkv) * per_head, n_items = n_rot + hkv * (h >> 2);
     const int nqkv = (hq + 2 * hkv) * h;
@@ -230,6 +231,7 @@ __global__ __launch_bounds__(1024, EARLY ? 4 : 8) void rope_kv_kernel(const floa
     if (by_page) row = (row & ~127) | (row & 7) << 4 | (row >> 3 & 15);
     int m = EARLY && row < early ? INT32_MAX : *m_dev;
     if (row >= m) return;
+    if (!EARLY && m > pending_rows) chunks = 0;     // (where few rows are expected, partials pend whatever their number)
     for (;;) {
         const float* src = (chunks > 0 ? part : qkv) + (size_t)row * nqkv;
         const int n_src = chunks > 0 ? chunks : 1;
@@ -500,13 +502,13 @@ void hs_launch_embed_norm(const hs_ctx* ctx, const hs_kv_cache* cache, const hs_
 }
 
 void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, const int32_t* m_dev,
-                       int pending_chunks, int expected, hipStream_t st) {
+                       hs_pending pending, int expected, hipStream_t st) {
     const hs_model_desc& d = ctx->desc;
     const float* part = reinterpret_cast<const float*>(ctx->ws + ctx->lay.gemm_part);
     const size_t stride = (size_t)ctx->lim.max_rows * d.d_model;
     const dim3 block(norm_threads(d.d_model)), grid(hs_row_grid(ctx, block.x));
     const int early = hs_early_rows(expected);
-#define HS_ARGS(T) x, w, (T*)out, m_dev, d.d_model, d.rms_eps, part, pending_chunks, stride, early
+#define HS_ARGS(T) x, w, (T*)out, m_dev, d.d_model, d.rms_eps, part, pending.chunks, pending.rows, stride, early
     if (hs_fp32_activations(ctx)) {
         if (early) { HS_NORM_LAUNCH(early_rmsnorm, float, grid, HS_ARGS(float)) }
         else { HS_NORM_LAUNCH(counted_rmsnorm, float, grid, HS_ARGS(float)) }
@@ -525,7 +527,7 @@ void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, c
 constexpr int HS_PAGE_ROWS = 512;
 
 void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
-                       const hs_step* step, const float* qkv, void* q, int pending_chunks, int expected,
+                       const hs_step* step, const float* qkv, void* q, hs_pending pending, int expected,
                        hipStream_t st) {
     const hs_model_desc& d = ctx->desc;
     size_t layer_off = (size_t)layer * cache->n_blocks * d.n_kv_heads * 16 * d.head_dim;
@@ -539,7 +541,7 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
     const int by_page = expected >= HS_PAGE_ROWS && grid.x % 128 == 0, early = hs_early_rows(expected);
 #define HS_ROPE_ARGS(T)                                                                                          \
     qkv, ctx->rope_cs, infos, step->row_off + seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off,          \
-        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending_chunks, (size_t)ctx->lim.max_rows * nqkv, early, by_page
+        d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending.chunks, pending.rows, (size_t)ctx->lim.max_rows * nqkv, early, by_page
     if (hs_fp32_activations(ctx)) {
         if (early) hipLaunchKernelGGL((rope_kv_kernel<float, true>), grid, block, 0, st, HS_ROPE_ARGS(float));
         else hipLaunchKernelGGL((rope_kv_kernel<float, false>), grid, block, 0, st, HS_ROPE_ARGS(float));

@@ -5,8 +5,8 @@
 // chunk is accumulated by the matrix cores on its own, and the chunk sums are added left to right in fp32
 // (t = p0 + p1 + ...; then stored, or added to the residual).  A row's result therefore never depends on how many
 // other rows share the launch or on the launch shape the row hint selects -- which is what makes speculative and
-// one-token decoding agree bit for bit.  (With many rows a workgroup takes all chunks of its tile in turn, same sums in the
-// same order: hs_gemm_folded.hip.)  The MFMA kernel lives in hs_gemm_stream.hip; here are the ordered reduce
+// one-token decoding agree bit for bit.  (Where many rows are expected and there a workgroup takes all chunks of its tile in turn,
+// same sums in the same order: hs_gemm_folded.hip.)  The MFMA kernel lives in hs_gemm_stream.hip; here are the ordered reduce
 // of the chunk partials (used when no following kernel takes them over), the plain kernels (debugging, fp32
 // activations), and the shape rules.
 #include "hs_gemm_common.h"
@@ -149,8 +149,8 @@ __global__ __launch_bounds__(256) void gemm_plain(const AT* __restrict__ A, cons
 
 template <int EPI>
 void launch(const hs_ctx* ctx, const void* a_any, const bf16_t* w, const bf16_t* w2, void* c, const int32_t* m_dev,
-            int m_max, int n, int k, int rows_hint, hipStream_t st, int* pending, int fold_k) {
-    if (pending) *pending = 0;
+            int m_max, int n, int k, int rows_hint, hipStream_t st, hs_pending* pending, double fold) {
+    if (pending) *pending = {};
     if (hs_plain_kernels(ctx)) {
         dim3 grid((n + 4 * PC - 1) / (4 * PC), (m_max + PR - 1) / PR);
         if (hs_fp32_activations(ctx))
@@ -166,14 +166,18 @@ void launch(const hs_ctx* ctx, const void* a_any, const bf16_t* w, const bf16_t*
     int chunks = (EPI == HS_EPI_SWIGLU_BF16 || EPI == HS_EPI_ROWMAX) ? 1 : hs_gemm_chunks(n, k);
     const int tpc = (nk + chunks - 1) / chunks;
     chunks = (nk + tpc - 1) / tpc;  // no empty chunk
-    if constexpr (EPI == HS_EPI_STORE_F32 || EPI == HS_EPI_ADD_F32) {
-        if (chunks > 1 && k <= fold_k && hs_launch_gemm_folded(EPI, a, w, c, m_dev, m_max, n, k, chunks, tpc, rows_hint, st)) return;
-    }
     float* part = reinterpret_cast<float*>(ctx->ws + ctx->lay.gemm_part);
+    if constexpr (EPI == HS_EPI_STORE_F32 || EPI == HS_EPI_ADD_F32) {
+        int split_rows = 0;     // (without a kernel in line that would add partial sums up there are none, whatever the count)
+        if (chunks > 1 && fold > 0. && hs_launch_gemm_folded(EPI, a, w, c, part, m_dev, m_max, n, k, chunks, tpc, rows_hint, fold, st, pending ? &split_rows : nullptr)) {
+            if (split_rows > 0) *pending = {chunks, split_rows};
+            return;
+        }
+    }
     hs_launch_gemm_stream(EPI, a, w, w2, c, part, m_dev, m_max, n, k, chunks, tpc, rows_hint, st);
     if (chunks > 1) {
         if (pending) {
-            *pending = chunks;  // the next kernel in line adds the partials up
+            *pending = {chunks, m_max};  // the next kernel in line adds the partials up
         } else {
             const int rows = rows_hint < 1 ? 1 : (2 * rows_hint > m_max ? m_max : 2 * rows_hint);
             hipLaunchKernelGGL((gemm_split_reduce<EPI>), dim3(((n + 3) / 4 + 255) / 256, rows), dim3(256), 0, st, part,
@@ -210,19 +214,19 @@ int hs_gemm_chunks(int n, int k, bool narrow) {
 }
 
 void hs_launch_gemm(const hs_ctx* ctx, int epi, const void* a, const bf16_t* w, const bf16_t* w2, void* c,
-                    const int32_t* m_dev, int m_max, int n, int k, int rows_hint, hipStream_t st, int* pending, int fold_k) {
+                    const int32_t* m_dev, int m_max, int n, int k, int rows_hint, hipStream_t st, hs_pending* pending, double fold) {
     switch (epi) {
         case HS_EPI_STORE_F32:
-            launch<HS_EPI_STORE_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
+            launch<HS_EPI_STORE_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold);
             break;
         case HS_EPI_ADD_F32:
-            launch<HS_EPI_ADD_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
+            launch<HS_EPI_ADD_F32>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold);
             break;
         case HS_EPI_ROWMAX:
-            launch<HS_EPI_ROWMAX>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
+            launch<HS_EPI_ROWMAX>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold);
             break;
         default:
-            launch<HS_EPI_SWIGLU_BF16>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold_k);
+            launch<HS_EPI_SWIGLU_BF16>(ctx, a, w, w2, c, m_dev, m_max, n, k, rows_hint, st, pending, fold);
             break;
     }
 }

@@ -57,6 +57,8 @@ void hs_launch_gemm_stream(int epi, const bf16_t* a, const bf16_t* w, const bf16
 double hs_gemm_split_us(bool add, int n, int chunks, int tpc, int rows);
 
 // A split-K projection with all chunks of a tile in one workgroup (hs_gemm_folded.hip): no partial sums, the epilogue (store or
-// add) applied.  Returns false, with nothing launched, where the split execution is expected to be faster.
-bool hs_launch_gemm_folded(int epi, const bf16_t* a, const bf16_t* w, void* c, const int32_t* m_dev, int m_max, int n, int k,
-                           int chunks, int tpc, int rows_hint, hipStream_t st);
+// add) applied -- if there are more than *split_rows rows (set here; nullptr: none); with up to so many the partial sums are
+// left in `part` as by the split execution.  Returns false, with nothing launched, where the split execution is not expected to take
+// `gain` times as long.
+bool hs_launch_gemm_folded(int epi, const bf16_t* a, const bf16_t* w, void* c, float* part, const int32_t* m_dev, int m_max, int n,
+                           int k, int chunks, int tpc, int rows_hint, double gain, hipStream_t st, int* split_rows);

@@ -16,50 +16,74 @@ template <int EPI, int NU, int SW>
 __global__ __launch_bounds__(512) void hs_gemm_folded(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                       const bf16_t* __restrict__ W2, void* __restrict__ Cout,
                                                       float* __restrict__ part, const int32_t* __restrict__ m_dev, int m_max,
-                                                      int N, int K, int tpc, int n_groups, int n_pass) {
-    stream_kernel<EPI, false, true, NU, 2, 2, SW, 8>(A, W, W2, Cout, part, m_dev, m_max, N, K, tpc, n_groups, n_pass);
+                                                      int N, int K, int tpc, int n_groups, int n_pass, int split_rows) {
+    stream_kernel<EPI, false, true, NU, 2, 2, SW, 8>(A, W, W2, Cout, part, m_dev, m_max, N, K, tpc, n_groups, n_pass, split_rows);
 }
 
 namespace {
 
 template <int EPI, int NU, int SW>
-void launch_folded(const bf16_t* a, const bf16_t* w, void* c, const int32_t* m_dev, int m_max, int n, int k, int tpc,
-                   int rows_hint, hipStream_t st) {
+void launch_folded(const bf16_t* a, const bf16_t* w, void* c, float* part, const int32_t* m_dev, int m_max, int n, int k, int tpc,
+                   int rows_hint, int split_rows, hipStream_t st) {
     static bool configured = false;
-    launch_shape<EPI, NU, 2, 2, SW, 512>(&hs_gemm_folded<EPI, NU, SW>, configured, a, w, w, c, nullptr, m_dev, m_max, n, k, 1, tpc,
-                                         rows_hint, st);
+    launch_shape<EPI, NU, 2, 2, SW, 512>(&hs_gemm_folded<EPI, NU, SW>, configured, a, w, w, c, part, m_dev, m_max, n, k, 1, tpc,
+                                         rows_hint, st, split_rows);
 }
 
 template <int EPI>
-void launch_folded_units(int nu, const bf16_t* a, const bf16_t* w, void* c, const int32_t* m_dev, int m_max, int n, int k,
-                         int tpc, int rows_hint, hipStream_t st) {
-    if (nu == 2) launch_folded<EPI, 2, 8>(a, w, c, m_dev, m_max, n, k, tpc, rows_hint, st);
-    else if (nu == 3) launch_folded<EPI, 3, 6>(a, w, c, m_dev, m_max, n, k, tpc, rows_hint, st);
-    else launch_folded<EPI, 4, 5>(a, w, c, m_dev, m_max, n, k, tpc, rows_hint, st);
+void launch_folded_units(int nu, const bf16_t* a, const bf16_t* w, void* c, float* part, const int32_t* m_dev, int m_max, int n,
+                         int k, int tpc, int rows_hint, int split_rows, hipStream_t st) {
+#define HS_ARGS a, w, c, part, m_dev, m_max, n, k, tpc, rows_hint, split_rows, st
+    if (nu == 2) launch_folded<EPI, 2, 8>(HS_ARGS);
+    else if (nu == 3) launch_folded<EPI, 3, 6>(HS_ARGS);
+    else launch_folded<EPI, 4, 5>(HS_ARGS);
+#undef HS_ARGS
+}
+
+// Microseconds of a k-tile and round with this many units.
+constexpr double TILE_US[5] = {0, 0, 0.70, 0.77, 0.88};
+
+// What `passes` row passes take: rounds of an XCD's 32 compute units, which take whole weight groups, and what adding reads and
+// writes of the output; and with the chunks one to a workgroup: rounds of all compute units, and the partial sums.
+double folded_us(bool add, int n, int k, int nu, int passes, int rows) {
+    const int groups = ((n + 31) / 32 + nu - 1) / nu, rounds = ((groups + 7) / 8 * passes + 31) / 32;
+    return rounds * (k / BK * TILE_US[nu] + 5.) + (add ? 4e-6 * rows * n / 5.5 : 0.);
+}
+double chunks_apart_us(bool add, int n, int nu, int chunks, int tpc, int passes) {
+    const int groups = ((n + 31) / 32 + nu - 1) / nu, rounds = (groups * passes * chunks + 255) / 256;
+    return rounds * (tpc * TILE_US[nu] + 8.) + (add ? chunks + 1 : chunks - 1) * 4e-6 * 256 * passes * n / 5.5;
 }
 
 }  // namespace
 
-// Rounds count for more here than anywhere else (a round walks all of K): those of an XCD's 32 compute units, which take whole
-// weight groups, each k-tiles x the time above + 5 us.  Against the split execution's estimate with 8 % to spare: of 57 (shape,
-// projection, rows) measured in whole passes, 1.5B, 7B and 14B shapes at 600 to 4096 rows, what it takes is faster (7B O at 4096 rows 120
-// against 170 us, down 590 against 621; 14B O at 1500, 79 against 101) and what it leaves loses, gains less
-// than 8 us, or is the long K of the 14B shape in three rounds (4096 rows, 28 us of 2687 a pass).
-bool hs_launch_gemm_folded(int epi, const bf16_t* a, const bf16_t* w, void* c, const int32_t* m_dev, int m_max, int n, int k,
-                           int chunks, int tpc, int rows_hint, hipStream_t st) {
-    const int rows = std::min(rows_hint, m_max), passes = (rows + 255) / 256, units = (n + 31) / 32;
+// Rounds count for more here than anywhere else: a round walks all of K.  The split execution's estimate has to be `gain` times this
+// one's.  HS_FOLD_KNOWN: of 57 (shape, projection, rows) measured in whole passes, 1.5B, 7B and 14B shapes at 600 to 4096 rows,
+// what it takes is faster or within 1 % (7B O at 4096 rows 120 against 170 us, down 590 against 621; 14B O at 1500, 79 against
+// 101, at 2176 161 against 161) and what it leaves loses, gains less than 8 us, or is the long K of the 14B shape in three rounds
+// (4096 rows, 28 us of 2687 a pass).
+// Drafting makes the row count swing around what is expected, and a walk along all of K takes its time however few rows there are.
+// With up to split_rows rows, by the same estimates, the kernel leaves partial sums after all, and HS_FOLD_GUESSED asks for more.
+// us with 1078 expected and 64, 220, 300, 540, 1078, 1300 there, the next kernel included, split / always folded / now: 7B QKV 20, 29,
+// 33, 51, 69, 90 / 34, 51, 47, 50, 57, 85 / 20, 29, 46, 49, 57, 86; O, which is split (1.09 expected), 18, 24, 28, 42, 60, 85 / 33, 51, 47,
+// 49, 57, 83; O of 4096 columns 19, 26, 32, 52, 73, 92 / 36, 55, 50, 53, 65, 92 / 19, 27, 37, 52, 64, 90.
+bool hs_launch_gemm_folded(int epi, const bf16_t* a, const bf16_t* w, void* c, float* part, const int32_t* m_dev, int m_max, int n,
+                           int k, int chunks, int tpc, int rows_hint, double gain, hipStream_t st, int* split_rows) {
+    const int rows = std::min(rows_hint, m_max), passes = (rows + 255) / 256;
     if (rows < 512) return false;   // one or two passes: too few workgroups
     const bool add = epi == HS_EPI_ADD_F32;
-    constexpr double TILE_US[5] = {0, 0, 0.70, 0.77, 0.88};
-    double best = hs_gemm_split_us(add, n, chunks, tpc, rows) / 1.08;
+    double best = hs_gemm_split_us(add, n, chunks, tpc, rows) / gain;
     int nu = 0;
     for (int u : {2, 3, 4}) {
-        const int groups = (units + u - 1) / u, rounds = ((groups + 7) / 8 * passes + 31) / 32;
-        const double us = rounds * (k / BK * TILE_US[u] + 5.) + (add ? 4e-6 * rows * n / 5.5 : 0.);
+        const double us = folded_us(add, n, k, u, passes, rows);
         if (us < best) { best = us; nu = u; }
     }
     if (nu == 0) return false;
-    if (add) launch_folded_units<HS_EPI_ADD_F32>(nu, a, w, c, m_dev, m_max, n, k, tpc, rows_hint, st);
-    else launch_folded_units<HS_EPI_STORE_F32>(nu, a, w, c, m_dev, m_max, n, k, tpc, rows_hint, st);
+    int live = 0;       // passes up to which the chunks are taken apart
+    while (split_rows && live + 1 < passes && chunks_apart_us(add, n, nu, chunks, tpc, live + 1) < folded_us(add, n, k, nu, live + 1, 256 * (live + 1))) live++;
+    if (split_rows) *split_rows = 256 * live;
+#define HS_ARGS nu, a, w, c, part, m_dev, m_max, n, k, tpc, rows_hint, 256 * live, st
+    if (add) launch_folded_units<HS_EPI_ADD_F32>(HS_ARGS);
+    else launch_folded_units<HS_EPI_STORE_F32>(HS_ARGS);
+#undef HS_ARGS
     return true;
 }

@@ -610,12 +610,13 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
 
 namespace {
 
-// The kernel, for WV wavefronts.  (FOLD: a single grid row, tpc k-tiles per chunk.)
+// The kernel, for WV wavefronts.  (FOLD: a single grid row, tpc k-tiles per chunk; with up to split_rows rows the workgroups take the
+// chunks one each and leave partial sums.)
 template <int EPI, bool PARTIAL, bool FOLD, int NU, int MT, int SA, int SW, int WV>
 __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                               const bf16_t* __restrict__ W2, void* __restrict__ Cout,
                                               float* __restrict__ part, const int32_t* __restrict__ m_dev,
-                                              int m_max, int N, int K, int tpc, int n_groups, int n_pass) {
+                                              int m_max, int N, int K, int tpc, int n_groups, int n_pass, int split_rows = 0) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned smem_off = (unsigned)(size_t)(lds_ptr_t)smem;
     constexpr int NCOLS = (EPI == HS_EPI_SWIGLU_BF16) ? 16 * NU : 32 * NU;
@@ -632,6 +633,29 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
     p.m_max = m_max;
     p.N = N;
     p.K = K;
+    const int nk = K / BK;
+    if constexpr (FOLD) {
+        p.M = __builtin_amdgcn_readfirstlane(p.M);
+        if (p.M <= split_rows) {
+            // (chunk, group, pass) triples, pass fastest, an XCD's workgroups taking consecutive ones (as split K below)
+            const int live = (p.M + pass_shape<MT>::ROWS - 1) / pass_shape<MT>::ROWS, per_chunk = n_groups * live;
+            const int total = per_chunk * ((nk + tpc - 1) / tpc), full = total >> 3, extra = total & 7;
+            const int xcd = blockIdx.x & 7, share = full + (xcd < extra ? 1 : 0);
+            p.n_groups = n_groups;
+            p.w_once = live == 1;
+            for (int nth = blockIdx.x >> 3; nth < share; nth += gridDim.x >> 3) {
+                const int w = xcd * full + min(xcd, extra) + nth, rem = w % per_chunk;
+                p.chunk = w / per_chunk;
+                p.group = rem / live;
+                p.n0 = p.group * NCOLS;
+                p.kt0 = p.chunk * tpc;
+                p.kt1 = min(nk, p.kt0 + tpc);
+                if (wave < 4) stream_group<HS_EPI_STORE_F32, true, false, NU, MT, SA, SW, 0, 8>(p, smem, smem_off, wave, wave, lane, rem % live, live);
+                else stream_group<HS_EPI_STORE_F32, true, false, NU, MT, SA, SW, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, rem % live, live);
+            }
+            return;
+        }
+    }
     // Workgroup id -> (weight group, row pass): ids are dealt round-robin to the 8 XCDs (each with its own L2).
     // Unsplit K: an XCD takes a weight group and runs its row passes back to back, so that the passes which stream
     // the same weight slab meet in one L2.
@@ -690,7 +714,6 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
     p.n_groups = n_groups;
     p.chunk = chunk;
     p.w_once = n_pass == 1;
-    const int nk = K / BK;
     p.kt0 = FOLD ? 0 : chunk * tpc;
     p.kt1 = FOLD ? nk : min(nk, p.kt0 + tpc);
     p.fold = tpc;
@@ -720,9 +743,9 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
 namespace {
 
 // Launches a kernel of the shape <EPI, NU, MT, SA, SW>.
-template <int EPI, int NU, int MT, int SA, int SW, int THREADS, typename Kernel>
+template <int EPI, int NU, int MT, int SA, int SW, int THREADS, typename Kernel, typename... More>
 void launch_shape(Kernel kernel, bool& configured, const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, float* part,
-                  const int32_t* m_dev, int m_max, int n, int k, int chunks, int tpc, int rows_hint, hipStream_t st) {
+                  const int32_t* m_dev, int m_max, int n, int k, int chunks, int tpc, int rows_hint, hipStream_t st, More... more) {
     constexpr int NCOLS = (EPI == HS_EPI_SWIGLU_BF16) ? 16 * NU : 32 * NU, ROWS = pass_shape<MT>::ROWS;
     constexpr size_t lds = (size_t)(SA * pass_shape<MT>::TILES + SW * NU) * TILE_BYTES;
     static_assert(lds <= 160 * 1024, "LDS of one compute unit");
@@ -739,7 +762,7 @@ void launch_shape(Kernel kernel, bool& configured, const bf16_t* a, const bf16_t
     if (n_pass < 1) n_pass = 1;
     if (n_pass > (m_max + ROWS - 1) / ROWS) n_pass = (m_max + ROWS - 1) / ROWS;
     dim3 grid(chunks > 1 ? n_groups * n_pass : (n_pass > 1 ? ((n_groups + 7) / 8) * 8 * n_pass : n_groups), chunks);
-    hipLaunchKernelGGL(kernel, grid, dim3(THREADS), lds, st, a, w, w2, c, part, m_dev, m_max, n, k, tpc, n_groups, n_pass);
+    hipLaunchKernelGGL(kernel, grid, dim3(THREADS), lds, st, a, w, w2, c, part, m_dev, m_max, n, k, tpc, n_groups, n_pass, more...);
 }
 
 }  // namespace

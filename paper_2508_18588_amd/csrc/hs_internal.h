@@ -124,12 +124,15 @@ enum { HS_EPI_STORE_F32 = 0, HS_EPI_ADD_F32 = 1, HS_EPI_SWIGLU_BF16 = 2, HS_EPI_
 // (one workgroup per K chunk + an ordered reduce); results are identical whatever it is.
 // pending: if not null and the split execution was chosen, the ordered reduce is NOT launched: *pending receives the
 // number of chunk partials left in the workspace ([chunk][m_max][n] floats at lay.gemm_part) for the next kernel in
-// line to add up in chunk order and apply the epilogue (store / add to c); otherwise *pending = 0.
-// fold_k: the largest K whose chunks may run one after the other in a workgroup where that is expected to be faster (0 where
-// rows_hint is only a limit: with far fewer rows than expected it is the slower execution, and the more so the longer K is).
+// line to add up in chunk order and apply the epilogue (store / add to c) -- if there are at most `rows` rows; with more,
+// the epilogue has been applied.  No partials: chunks = 0.
+// fold: K chunks may run one after the other in a workgroup where that is expected to be so much faster, HS_FOLD_KNOWN or
+// HS_FOLD_GUESSED for row counts that are known to the caller or swing around rows_hint; 0 (never) where rows_hint is only a limit.
+struct hs_pending { int chunks = 0, rows = 0; };
+constexpr double HS_FOLD_KNOWN = 1.08, HS_FOLD_GUESSED = 1.2;
 void hs_launch_gemm(const hs_ctx* ctx, int epi, const void* a, const bf16_t* w, const bf16_t* w2, void* c,
                     const int32_t* m_dev, int m_max, int n, int k, int rows_hint, hipStream_t st,
-                    int* pending = nullptr, int fold_k = 0);
+                    hs_pending* pending = nullptr, double fold = 0.);
 int hs_gemm_rowmax_groups(int n);   // column groups (= keys per row) of an HS_EPI_ROWMAX launch over n columns
 
 // What a row's place in its sequence comes to, written once per pass (beside the attention's unit lists, or by the launch
@@ -167,14 +170,14 @@ static inline int hs_early_rows(int expected) { return expected <= HS_EARLY_ROWS
 // unit lists of the step's attention are written by further workgroups of the same launch.
 void hs_launch_embed_norm(const hs_ctx* ctx, const hs_kv_cache* cache, const hs_seq_state* seq, const hs_step* step,
                           bool lists, float* x, const float* w, void* out, hipStream_t st);
-// RMSNorm of the residual stream; with pending_chunks > 0 it first adds the pending chunk partials of the
+// RMSNorm of the residual stream; with partials pending it first adds the chunk partials of the
 // preceding projection (in chunk order) to x.
 void hs_launch_rmsnorm(const hs_ctx* ctx, float* x, const float* w, void* out, const int32_t* m_dev,
-                       int pending_chunks, int expected, hipStream_t st);
-// Rotary embedding + KV write; with pending_chunks > 0 the QKV values are the chunk-ordered sums of the pending
+                       hs_pending pending, int expected, hipStream_t st);
+// Rotary embedding + KV write; with partials pending the QKV values are the chunk-ordered sums of the pending
 // partials instead of qkv.
 void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
-                       const hs_step* step, const float* qkv, void* q, int pending_chunks, int expected,
+                       const hs_step* step, const float* qkv, void* q, hs_pending pending, int expected,
                        hipStream_t st);
 void hs_launch_attention(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, const hs_seq_state* seq,
                          const hs_step* step, const void* q, void* out, hipStream_t st);

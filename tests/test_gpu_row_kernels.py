@@ -195,8 +195,8 @@ def test_tables_that_only_allow_narrow_loads():
 
 @pytest.mark.parametrize("vocab", [64, 4096, 16380, 16384, 16386, 16388, 36868])
 def test_argmax_is_the_first_of_the_largest_logits(vocab):
-    """The largest logit there three times; widths below, at and above the four loads of 1024 threads that are on their way at once, and one that allows no 16-byte
-    loads; with and without an estimate of the rows."""
+    """The largest logit is there three times; widths below, at and above the four loads of 1024 threads that are on their way
+    at once, and one that allows no 16-byte loads; with and without an estimate of the rows."""
     from paper_2508_18588_amd.runtime import Engine
     shape = ModelShape(n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ffn=64, vocab=vocab)
     w = make_weights(shape, vocab)

@@ -36,15 +36,18 @@
 //     490 -> 446; down at 4096 674 -> 615.  Without its loads 816, without its MFMAs 628; counters: matrix cores busy 65 % of the
 //     cycles at the 1.76 GHz that this load leaves the chip, LDS 32 %.
 //   * Split K with many rows: a workgroup takes all chunks of its tile in turn (FOLD, hs_gemm_folded.hip), no partial sums.
-//   * Up to 160 rows expected (two to four units): three activation stages, and one wavefront group fetches the activations,
+//   * Up to 160 rows expected (three and four units): three activation stages, and one wavefront group fetches the activations,
 //     the other the weights.  Loads count as landed in the order of their issue: while every wavefront fetched both, waiting for
 //     the next tile's activations, asked for last, meant waiting for weights asked for a tile before, and the weight ring
 //     was never more than that deep however many stages it had.  us, before and now: 1.5B gate/up at 7, 32, 64 and 100 rows
 //     13.9, 15.2, 16.5, 17.9 -> 12.0, 13.0, 15.0, 17.5; 16448 columns of K = 3584 at 7, 32, 64 and 128 rows 23.4, 25.3, 31.0,
 //     36.8 -> 22.1, 23.5, 27.0, 35.5; 14B gate/up at 7 and 32 rows 47.8, 52.2 -> 46.1, 50.1; 7B down at 64 rows 31.3 -> 30.2.
-//     Chunks of split K that are shorter than 16 tiles, five units (42 us either way) and passes of 384 rows (two activation
-//     stages are what LDS holds; 16448 columns at 217 rows 45.8, fetched apart 50.5) stay as they were.
-//   * Passes of 64 rows (MT = 0) for up to 32 rows expected: another 1 to 5 % (few_rows_rings).
+//     Two units (the shapes with short chunks of split K: 1.5B QKV, chunks of 4 tiles, would take 5.4 us instead of 5.1, its down
+//     projection, of 14, the same either way), five units (42 us either way) and passes of 384 rows (two activation
+//     stages are what LDS holds; 16448 columns at 217 rows 45.8, fetched apart 50.5) stay as they were.  From 96 rows on the gain
+//     is what a shape makes of it: 16448 columns at 128 rows, K = 1536, 3584, 4096, 5120: 18.6, 38.7, 42.8, 54.2 -> 19.3, 38.2,
+//     40.8, 55.7.  With more rows than expected, 217 to 990, nothing is lost (14B gate/up at 990: 339 -> 325).
+//   * Passes of 64 rows (MT = 0) for up to 32 rows expected: another 1 to 5 %.
 //   * What bounds it now: at up to 128 rows the weight stream (271 MB of gate/up weights in 50 us); from 160 rows on the two
 //     operands' ways into a compute unit, one after the other (1.5B gate/up at 165 rows, clocks a tile: weights alone 880, activations
 //     alone 820, both 1600, everything 1550, without either 1000); at 220 rows of a 7B shape LDS and the power they all draw (184 KB a
@@ -196,11 +199,10 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
             if (t + h + SW < p.kt1) n += NLW;
             if (h > -SA && t + h + SA < p.kt1) n += n_a;
         }
-        switch (n) {   // (at most 7 x 3)
+        static_assert((NSA ? (SA - 1) * NLW + (SA - 2) * NSA : (SW - 2) * NLW) <= 9, "the cases below");
+        switch (n) {
 #define HS_CASE(i) case i: HS_WAIT_VMCNT(i); break;
-            HS_CASE(1) HS_CASE(2) HS_CASE(3) HS_CASE(4) HS_CASE(5) HS_CASE(6) HS_CASE(7) HS_CASE(8) HS_CASE(9) HS_CASE(10)
-            HS_CASE(11) HS_CASE(12) HS_CASE(13) HS_CASE(14) HS_CASE(15) HS_CASE(16) HS_CASE(17) HS_CASE(18) HS_CASE(19) HS_CASE(20)
-            HS_CASE(21)
+            HS_CASE(1) HS_CASE(2) HS_CASE(3) HS_CASE(4) HS_CASE(5) HS_CASE(6) HS_CASE(7) HS_CASE(8) HS_CASE(9)
 #undef HS_CASE
             default: HS_WAIT_VMCNT(0);
         }
@@ -534,12 +536,12 @@ __device__ __forceinline__ void stream_chunk(const stream_args& p, unsigned char
 
 namespace {
 
-// The rings of a 64-row instance.  Its LDS is that of the 256-row passes it falls back to (FALL_SA, FALL_SW stages, those of the
-// 256-row instance); of it, passes of 64 rows use SA and SW stages: with more on its way a launch takes longer (7 rows of
-// 3584, head of 16448 columns: 4 and 5 stages 22.1 us, 3 and 4 22.7, 5 and 6 22.9, 6 and 9 25.3).
+// What a 64-row instance falls back to: passes of 256 rows with the rings of the 256-row instance.  They need more LDS than its own
+// rings, which are no deeper than this: with more on its way a launch takes longer (7 rows of 3584, head of 16448 columns, three
+// units: 4 and 5 stages 22.1 us, 3 and 4 22.7, 5 and 6 22.9, 6 and 9 25.3).
 template <int NU>
-struct few_rows_rings {
-    static constexpr int SA = NU == 3 ? 4 : 3, SW = NU == 3 ? 5 : 4, FALL_SA = 3, FALL_SW = NU == 3 ? 5 : 4;
+struct few_rows_fallback {
+    static constexpr int SA = 3, SW = NU == 3 ? 5 : 4;
     static_assert(NU == 3 || NU == 4, "the 64-row instances");
 };
 
@@ -583,7 +585,7 @@ __device__ __forceinline__ void stream_group(stream_args& p, unsigned char* smem
             HS_WAIT_VMCNT(0);
             __syncthreads();
             p.w_pre = 0;
-            stream_group<EPI, PARTIAL, FOLD, NU, 2, few_rows_rings<NU>::FALL_SA, few_rows_rings<NU>::FALL_SW, GRP, WV>(p, smem, smem_off, quad, rg, lane, pass, n_pass);
+            stream_group<EPI, PARTIAL, FOLD, NU, 2, few_rows_fallback<NU>::SA, few_rows_fallback<NU>::SW, GRP, WV>(p, smem, smem_off, quad, rg, lane, pass, n_pass);
             return;
         }
     }
@@ -719,13 +721,8 @@ __device__ __forceinline__ void stream_kernel(const bf16_t* __restrict__ A, cons
     p.fold = tpc;
 
     if constexpr (WV == 8) {
-        auto run = [&](auto sa_c, auto sw_c) __attribute__((always_inline)) {
-            constexpr int A_STAGES = decltype(sa_c)::value, W_STAGES = decltype(sw_c)::value;
-            if (wave < 4) stream_group<EPI, PARTIAL, FOLD, NU, MT, A_STAGES, W_STAGES, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, passes);
-            else stream_group<EPI, PARTIAL, FOLD, NU, MT, A_STAGES, W_STAGES, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, passes);
-        };
-        if constexpr (MT == 0) run(std::integral_constant<int, few_rows_rings<NU>::SA>{}, std::integral_constant<int, few_rows_rings<NU>::SW>{});
-        else run(std::integral_constant<int, SA>{}, std::integral_constant<int, SW>{});
+        if (wave < 4) stream_group<EPI, PARTIAL, FOLD, NU, MT, SA, SW, 0, 8>(p, smem, smem_off, wave, wave, lane, pass, passes);
+        else stream_group<EPI, PARTIAL, FOLD, NU, MT, SA, SW, 1, 8>(p, smem, smem_off, wave - 4, wave - 4, lane, pass, passes);
     } else {
         auto run = [&](auto nu_c, auto sw_c) __attribute__((always_inline)) {
             constexpr int U = decltype(nu_c)::value, S = decltype(sw_c)::value;
@@ -747,11 +744,14 @@ template <int EPI, int NU, int MT, int SA, int SW, int THREADS, typename Kernel,
 void launch_shape(Kernel kernel, bool& configured, const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, float* part,
                   const int32_t* m_dev, int m_max, int n, int k, int chunks, int tpc, int rows_hint, hipStream_t st, More... more) {
     constexpr int NCOLS = (EPI == HS_EPI_SWIGLU_BF16) ? 16 * NU : 32 * NU, ROWS = pass_shape<MT>::ROWS;
-    constexpr size_t lds = (size_t)(SA * pass_shape<MT>::TILES + SW * NU) * TILE_BYTES;
-    static_assert(lds <= 160 * 1024, "LDS of one compute unit");
-    if constexpr (MT == 0)
-        static_assert((few_rows_rings<NU>::FALL_SA * pass_shape<2>::TILES + few_rows_rings<NU>::FALL_SW * NU) * TILE_BYTES <= lds &&
-                          few_rows_rings<NU>::SA <= SA && few_rows_rings<NU>::SW <= SW, "the rings of either pass");
+    constexpr size_t rings = (size_t)(SA * pass_shape<MT>::TILES + SW * NU) * TILE_BYTES;
+    size_t lds = rings;
+    if constexpr (MT == 0) {
+        constexpr size_t fallback = (size_t)(few_rows_fallback<NU>::SA * pass_shape<2>::TILES + few_rows_fallback<NU>::SW * NU) * TILE_BYTES;
+        static_assert(rings <= fallback && fallback <= 160 * 1024, "LDS of one compute unit");
+        lds = fallback;
+    }
+    static_assert(rings <= 160 * 1024, "LDS of one compute unit");
     if (!configured) {      // more than 64 KB of dynamic LDS has to be asked for once per kernel
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         configured = true;

@@ -2,7 +2,8 @@
 #include "hs_gemm_stream.h"
 
 // NU weight units per workgroup, MT row tiles per wavefront pair (128*MT rows per pass; 64 for MT = 0), SA / SW ring stages
-// (three and more activation stages: the two operands are fetched by a wavefront group each).
+// (three and more activation stages: the two operands are fetched by a wavefront group each; MT = 0: of passes of 64 rows,
+// with more rows few_rows_fallback says).
 // (External linkage: the host takes the kernel's address to raise its dynamic LDS limit.)
 template <int EPI, bool PARTIAL, int NU, int MT, int SA, int SW>
 __global__ __launch_bounds__(512) void hs_gemm_stream(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
@@ -27,9 +28,6 @@ void launch_stream(const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, 
 #ifndef HS_FEW_ROWS
 #define HS_FEW_ROWS 32
 #endif
-// Split K in chunks of at least this many k-tiles fetches the two operands apart (7B down, 33 tiles: 1 to 4 %; QKV of the 1.5B
-// shape, in chunks of 4, would take 5.4 us instead of 5.1, its down projection, in chunks of 14, the same either way).
-constexpr int HS_APART_TILES = 16;
 constexpr int HS_TALL_ROWS = 160, HS_WIDE_KERNEL_ROWS = 512;
 // A round of 256 workgroups takes this long per k-tile (four wavefronts; eight, for each unit).
 constexpr int HS_WIDE_TILE_NS = 1600, HS_UNIT_TILE_NS = 305;
@@ -98,13 +96,12 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
     } else if (nu == 3) {
         if constexpr (EPI != HS_EPI_ROWMAX) {
             if (tall) launch_stream<EPI, PARTIAL, 3, 3, 2, 5>(HS_ARGS);
-            else if (few) { if constexpr (!PARTIAL) launch_stream<EPI, PARTIAL, 3, 0, 6, 9>(HS_ARGS); }
+            else if (few) { if constexpr (!PARTIAL) launch_stream<EPI, PARTIAL, 3, 0, 4, 5>(HS_ARGS); }
             else launch_stream<EPI, PARTIAL, 3, 2, 3, 5>(HS_ARGS);
         }
     } else {
         if (tall) launch_stream<EPI, PARTIAL, 4, 3, 2, 4>(HS_ARGS);
-        else if (few) { if constexpr (!PARTIAL) launch_stream<EPI, PARTIAL, 4, 0, 6, 7>(HS_ARGS); }
-        else if (PARTIAL && tpc < HS_APART_TILES) { if constexpr (PARTIAL) launch_stream<EPI, PARTIAL, 4, 2, 2, 5>(HS_ARGS); }
+        else if (few) { if constexpr (!PARTIAL) launch_stream<EPI, PARTIAL, 4, 0, 3, 4>(HS_ARGS); }
         else launch_stream<EPI, PARTIAL, 4, 2, 3, 4>(HS_ARGS);
     }
 #undef HS_ARGS

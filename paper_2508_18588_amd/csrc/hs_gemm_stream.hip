@@ -56,6 +56,28 @@ int rowmax_units(int n) {
     return (units + 1279) / 1280 * 5 <= (units + 1023) / 1024 * 4 ? 5 : 4;
 }
 
+// How a projection of so many weight units (and K chunks) runs when rows_hint rows are expected.
+struct launch_plan {
+    int nu;                             // weight units per workgroup of eight wavefronts
+    long long rounds, wide_rounds;      // of 256 workgroups; and of four wavefronts
+    bool wide;
+};
+launch_plan plan_launch(int units, int chunks, int rows_hint, int m_max) {
+    const int rows = std::min(rows_hint, m_max), pass_rows = rows_hint > HS_TALL_ROWS ? 384 : 256;
+    const int passes = std::max(1, (rows + pass_rows - 1) / pass_rows);
+    launch_plan p;
+    p.nu = choose_units(units, chunks, passes);
+    p.rounds = ((long long)((units + p.nu - 1) / p.nu) * chunks * passes + 255) / 256;
+    p.wide_rounds = ((long long)((units + 7) / 8) * chunks * ((rows + 255) / 256) + 255) / 256;
+    // Workgroups of 256 rows x 8 units in four wavefronts, where their rounds take less time.  A round is 1.6 us per k-tile
+    // there and 0.305 us per unit here (gate/up, down and QKV of the 7B and 14B shapes at 1000 to 4096 rows; of these 36
+    // the rule picks the faster one or one that is within 2 %.  us, here against there: 7B gate/up at 1280 rows, 4 rounds
+    // against 3: 318, 278; at 1500, 4 against 4: 344, 346; QKV at 1500, 2 of 4 units against 2: 73, 83; 14B gate/up at
+    // 2048, 5 against 4: 544, 480; 7B down at 4096, 9 against 8: 674, 615).
+    p.wide = rows_hint >= HS_WIDE_KERNEL_ROWS && p.wide_rounds * HS_WIDE_TILE_NS < p.rounds * HS_UNIT_TILE_NS * p.nu;
+    return p;
+}
+
 template <int EPI, bool PARTIAL>
 void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, void* c, float* part,
                          const int32_t* m_dev, int m_max, int n, int k, int chunks, int tpc, int rows_hint,
@@ -64,23 +86,13 @@ void launch_stream_shape(const bf16_t* a, const bf16_t* w, const bf16_t* w2, voi
     // row count of a speculative step swings by a third around its mean), so that a step above its average does
     // not pay a second pass over the weights.  Row tiles that do not exist cost nothing in either shape.
     const bool tall = rows_hint > HS_TALL_ROWS, few = rows_hint <= HS_FEW_ROWS && !PARTIAL && k >= 16 * BK;
-    const int unit_cols = (EPI == HS_EPI_SWIGLU_BF16) ? 16 : 32, pass_rows = tall ? 384 : 256;
-    const int passes = std::max(1, (std::min(rows_hint, m_max) + pass_rows - 1) / pass_rows);
-    const int nu = EPI == HS_EPI_ROWMAX ? rowmax_units(n) : choose_units((n + unit_cols - 1) / unit_cols, chunks, passes);
+    const int unit_cols = (EPI == HS_EPI_SWIGLU_BF16) ? 16 : 32;
+    const launch_plan plan = plan_launch((n + unit_cols - 1) / unit_cols, chunks, rows_hint, m_max);
+    const int nu = EPI == HS_EPI_ROWMAX ? rowmax_units(n) : plan.nu;
 #define HS_ARGS a, w, w2, c, part, m_dev, m_max, n, k, chunks, tpc, rows_hint, st
-    if (EPI != HS_EPI_ROWMAX && rows_hint >= HS_WIDE_KERNEL_ROWS) {
-        // Workgroups of 256 rows x 8 units in four wavefronts, where their rounds take less time.  A round is 1.6 us per k-tile
-        // there and 0.305 us per unit here (gate/up, down and QKV of the 7B and 14B shapes at 1000 to 4096 rows; of these 36
-        // the rule picks the faster one or one that is within 2 %.  us, here against there: 7B gate/up at 1280 rows, 4 rounds
-        // against 3: 318, 278; at 1500, 4 against 4: 344, 346; QKV at 1500, 2 of 4 units against 2: 73, 83; 14B gate/up at
-        // 2048, 5 against 4: 544, 480; 7B down at 4096, 9 against 8: 674, 615).
-        const int units = (n + unit_cols - 1) / unit_cols;
-        const long long wgs = (long long)((units + nu - 1) / nu) * chunks * passes;
-        const long long wide_wgs = (long long)((units + 7) / 8) * chunks * ((std::min(rows_hint, m_max) + 255) / 256);
-        if ((wide_wgs + 255) / 256 * HS_WIDE_TILE_NS < (wgs + 255) / 256 * HS_UNIT_TILE_NS * nu) {
-            hs_launch_gemm_wide(EPI, PARTIAL, HS_ARGS);
-            return;
-        }
+    if (EPI != HS_EPI_ROWMAX && plan.wide) {
+        hs_launch_gemm_wide(EPI, PARTIAL, HS_ARGS);
+        return;
     }
     // The 64-row groups of the smaller split-K shapes (QKV, O, the 1.5B down projection) pay at a few hundred rows, where they halve the
     // partial sums; with many row passes every group re-reads the whole activation slab of its pass, and wider groups
@@ -114,15 +126,12 @@ int hs_gemm_rowmax_groups(int n) {
     return (n + 32 * nu - 1) / (32 * nu);
 }
 
-// By the rounds of the kernel that launch_stream_shape takes at this many rows (512 and more): what its k-tiles take and about 8 us for
+// By the rounds of the kernel that is taken at this many rows (512 and more): what its k-tiles take and about 8 us for
 // a round's first tiles and its stores, and the partial sums read back at 5.5 TB/s (7B shape, 4096 rows, us: QKV 148 and 27 for
 // 152 and 34, O 117 and 53 for 120 and 53, down 486 and 107 for 491 and 107; 14B at 1088: 89, 65, 156 for 92, 68, 158).
 double hs_gemm_split_us(bool add, int n, int chunks, int tpc, int rows) {
-    const int units = (n + 31) / 32, passes = (rows + 383) / 384, nu = choose_units(units, chunks, passes);
-    const int rounds = ((units + nu - 1) / nu * chunks * passes + 255) / 256;
-    const int wide_rounds = ((units + 7) / 8 * chunks * ((rows + 255) / 256) + 255) / 256;
-    const bool wide = wide_rounds * HS_WIDE_TILE_NS < rounds * HS_UNIT_TILE_NS * nu;
-    const double gemm = wide ? wide_rounds * (tpc * 1e-3 * HS_WIDE_TILE_NS + 8.) : rounds * (tpc * 1e-3 * HS_UNIT_TILE_NS * nu + 8.);
+    const launch_plan p = plan_launch((n + 31) / 32, chunks, rows, rows);
+    const double gemm = p.wide ? p.wide_rounds * (tpc * 1e-3 * HS_WIDE_TILE_NS + 8.) : p.rounds * (tpc * 1e-3 * HS_UNIT_TILE_NS * p.nu + 8.);
     return gemm + (add ? chunks + 1 : chunks - 1) * 4e-6 * rows * n / 5.5;
 }
 

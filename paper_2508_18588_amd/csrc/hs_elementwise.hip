@@ -226,7 +226,8 @@ __global__ __launch_bounds__(1024, EARLY ? 4 : 8) void rope_kv_kernel(const floa
     const int n_rot = (hq + hkv) * per_head, n_items = n_rot + hkv * (h >> 2);
     const int nqkv = (hq + 2 * hkv) * h;
     const bool cs_vec = ((unsigned long long)rope_cs & 15ull) == 0;
-    // by_page: of 128 neighbouring rows 16 at a time go to one XCD (workgroups are dealt to the eight of them in turn).
+    // by_page: of 128 neighbouring rows 16 at a time go to one XCD (workgroups are dealt to the eight of them in turn; the grid
+    // is a multiple of 128).
     int row = blockIdx.x;
     if (by_page) row = (row & ~127) | (row & 7) << 4 | (row >> 3 & 15);
     int m = EARLY && row < early ? INT32_MAX : *m_dev;
@@ -537,8 +538,9 @@ void hs_launch_rope_kv(const hs_ctx* ctx, int layer, const hs_kv_cache* cache, c
     // an item per thread if a workgroup has that many, else as many rounds of equal size as it takes
     const int items = (d.n_q_heads + d.n_kv_heads) * (d.head_dim / 8) + d.n_kv_heads * (d.head_dim / 4);
     const int rounds = (items + 1023) / 1024, threads = ((items + rounds - 1) / rounds + 63) / 64 * 64;
-    const dim3 grid(hs_row_grid(ctx, threads)), block(threads);
-    const int by_page = expected >= HS_PAGE_ROWS && grid.x % 128 == 0, early = hs_early_rows(expected);
+    const int by_page = expected >= HS_PAGE_ROWS, early = hs_early_rows(expected), resident = hs_row_grid(ctx, threads);
+    static_assert(HS_PAGE_ROWS > HS_EARLY_ROWS, "a grid beyond max_rows: the count comes before anything is read");
+    const dim3 grid(by_page ? (resident + 127) / 128 * 128 : resident), block(threads);      // (whole sets of 128)
 #define HS_ROPE_ARGS(T)                                                                                          \
     qkv, ctx->rope_cs, infos, step->row_off + seq->batch, (T*)q, (T*)cache->k, (T*)cache->v, layer_off,          \
         d.n_q_heads, d.n_kv_heads, d.head_dim, part, pending.chunks, pending.rows, (size_t)ctx->lim.max_rows * nqkv, early, by_page

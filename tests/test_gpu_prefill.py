@@ -215,15 +215,22 @@ def test_rows_of_one_call(toy, batch, longest, chunk, max_rows):
     eng.close()
 
 
+@pytest.mark.parametrize("max_rows", [1279, 1280, 700])
 @pytest.mark.parametrize("longest", [130, 1000])
-def test_cache_does_not_depend_on_how_rows_are_dealt_to_workgroups(toy, longest):
-    """The rotary kernel deals rows to its workgroups in turn, or 16 neighbours at a time where its grid is a multiple of 128
-    (max_rows here) and 512 rows and more are expected: the same cache."""
+def test_cache_does_not_depend_on_how_rows_are_dealt_to_workgroups(toy, longest, max_rows):
+    """The rotary kernel deals rows to its workgroups in turn without an estimate of them, and 16 neighbours at a time, in sets of 128,
+    from 512 expected on, where its grid is the next multiple of 128 of the rows that there can be: the same cache."""
+    from paper_2508_18588_amd import hs_prefill, hs_prefill_args
     shape, w, rope = toy
     toks = texts(np.random.default_rng(longest), [longest, 700, 3, 611, 17], shape.vocab)
-    caches = []
-    for max_rows in (1279, 1280):
-        eng, _ = run_prefill(shape, w, rope, toks, 1024, max_rows, pages_seed=5)
-        caches.append((np_of(eng.kc).copy(), np_of(eng.vc).copy()))
-        eng.close()
-    assert (caches[0][0] == caches[1][0]).all() and (caches[0][1] == caches[1][1]).all()
+    eng, calls = run_prefill(shape, w, rope, toks, 1024, max_rows, pages_seed=5)
+    kc, vc = np_of(eng.kc).copy(), np_of(eng.vc).copy()
+    eng.kc.zero_()
+    eng.vc.zero_()
+    eng.kv_done.zero_()
+    for _ in range(calls):
+        hs_prefill(eng.ctx, eng.c_cache, eng.c_seq, eng.c_step, hs_prefill_args(1024, 0, eng.kv_done.data_ptr()), eng.stream())
+    torch.cuda.synchronize()
+    assert np_of(eng.kv_done)[:5].tolist() == [len(t) - 1 for t in toks]
+    assert (np_of(eng.kc) == kc).all() and (np_of(eng.vc) == vc).all()
+    eng.close()

@@ -807,7 +807,7 @@ __global__ __launch_bounds__(256) void attn_merge(const _Float16* part_o, const 
     int row = blockIdx.x, lim = max_parts;
     if (row >= expected || expected > HS_MERGE_EARLY_ROWS) {
         if (row >= *m_dev) return;
-        lim = infos[row].parts;
+        lim = max(infos[row].parts, 1);     // (a sequence without tokens has no partition: its first is read, and not used)
     }
     for (;;) {
         const unsigned zero = hs_opaque_zero();     // (all of a row's loads inside the loop: one in front of it would be waited for there)
@@ -868,7 +868,7 @@ __global__ __launch_bounds__(256) void attn_merge(const _Float16* part_o, const 
             *dst = f32_to_bf16(acc[0] / den);
         row += gridDim.x;
         if (row >= m) return;
-        lim = hs_uniform(next_lane);
+        lim = max(hs_uniform(next_lane), 1);
     }
 }
 

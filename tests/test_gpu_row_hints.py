@@ -86,3 +86,28 @@ def test_more_rows_expected_than_there_are_cost_the_row_kernels_little(shape):
     eng.close()
     print("row kernels of a pass, us, without an estimate and with one of 1078 rows:", none, many)
     assert many <= 1.2 * none, (none, many)
+
+
+@pytest.mark.parametrize("hint", [0, 7, 40])
+def test_a_sequence_without_tokens_leaves_the_others_alone(hint):
+    """It has no partition of keys: the merge reads none of its partial results (with few rows expected and more, counted first)."""
+    from paper_2508_18588_amd.runtime import Engine
+    shape = ModelShape(n_layers=2, d_model=256, n_q_heads=4, n_kv_heads=4, head_dim=64, d_ffn=512, vocab=512)
+    rng = np.random.default_rng(3)
+    toks = [rng.integers(0, 512, n).astype(np.int32) for n in (9, 40, 300)]
+    eng = Engine(shape, make_weights(shape, 4), rope_table(400, 64), max_batch=3, k_max=4, c_max=1, max_len=310)
+    eng.load_sequences(toks, [9] * 3)
+    eng.prefill_chunked(512)
+    rows = [dict(tok=t[-1:], parent=[-1], pos=[len(t) - 1]) for t in toks]
+    outs = []
+    for empty in (False, True):
+        eng.set_rows(rows)
+        if empty:
+            eng.seq_len[0] = 0
+            eng.st["pos"][0] = -1
+        eng.c_step.rows_hint = hint
+        eng.verify()
+        torch.cuda.synchronize()
+        outs.append(eng.logits[1:3].clone())
+    eng.close()
+    assert torch.equal(*outs) and bool(torch.isfinite(outs[0]).all())

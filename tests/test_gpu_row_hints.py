@@ -10,11 +10,13 @@ from gpu_common import np_of
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,hq,hkv,h,f", [(256, 4, 4, 64, 1024), (1536, 12, 2, 128, 1024), (5120, 8, 8, 128, 8192)])
+@pytest.mark.parametrize("d,hq,hkv,h,f", [(256, 4, 4, 64, 1024), (1536, 12, 2, 128, 1024), (5120, 8, 8, 128, 8192),
+                                          (1024, 4, 2, 128, 4096), (2048, 8, 4, 128, 1024)])
 def test_a_step_does_not_depend_on_the_expected_rows(d, hq, hkv, h, f):
-    """One and two rounds per row of the norm, with and without pending partial sums (up to more chunks than are in flight at
-    once), heads of 64 and 128; estimates of no row, some, exactly all, more (and more than the merge asks ahead for).  A
-    sequence whose page is missing writes no K/V, whatever the estimate."""
+    """One and two rounds per row of the norm, with and without pending partial sums (two rounds with six chunks, three of them in
+    flight at once; one with sixteen, ten in flight; the rotary kernel with eight, six in flight), heads of 64 and 128; estimates
+    of no row, some, exactly all, more (and more than the merge and the other kernels ask ahead for).  A sequence whose page is
+    missing writes no K/V, whatever the estimate."""
     from paper_2508_18588_amd.runtime import Engine
     shape = ModelShape(n_layers=2, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=h, d_ffn=f, vocab=512)
     rng, B = np.random.default_rng(d), 5

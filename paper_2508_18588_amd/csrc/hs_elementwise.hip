@@ -208,8 +208,8 @@ constexpr auto counted_rmsnorm = &rmsnorm_kernel<OutT, ITEMS, false>;
 // then keep every bit).
 // One workgroup per row, an item per thread: four neighbouring pairs of a q or k head, or four elements of a v head.  A
 // thread adds up its own elements' pending partials (chunk order) and rotates them; nothing passes through LDS, no
-// barrier, and the loads depend on nothing but the row, so they are on their way while the chain row -> sequence ->
-// slot -> page is followed.  Bound by the partial sums it reads.  With the row gathered in LDS by 1024 threads first:
+// barrier, and the loads depend on nothing but the row, as does that of the row's place (hs_row_info).  Bound by the partial
+// sums it reads.  With the row gathered in LDS by 1024 threads first:
 // 74 us for 4096 rows of 4608 in three chunks, 28 us for 1067 rows of 7168 in two, 28 us
 // for 2048 rows of 2048 in six; now 70, 25 and 21 (2.7 to 5 TB/s of partial sums).
 // EARLY as in the norm: with few rows six chunks in flight and 70 registers (74 where T is float), else three and 64, for eight

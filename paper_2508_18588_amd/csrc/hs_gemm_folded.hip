@@ -8,9 +8,10 @@
 // them, and adds each chunk's sum to a second set of accumulators.  Same bits: the same products in each chunk, from zero, and
 // the chunks' sums added left to right.
 // Eight wavefronts of up to 2 x 2 tiles, twice 64 registers; twice 96 (six units, or 384 rows of four) and the twice 128 of four
-// wavefronts do not fit beside the fragments.  A k-tile and round takes 0.70, 0.77, 0.88 us with 2, 3, 4 units.
+// wavefronts do not fit beside the fragments.
 // Five prompts of 129 to 1500 tokens, 1.5B shape, two layers: 749 -> 679 us (QKV at 2048 rows 32 and 18 of the rotary kernel -> 23 and 8,
-// O 28 and 13 of the norm -> 24 and 6); 8 x 4096 tokens of the 7B shape 18990 -> 17610; 256 sequences with 1078 rows, 7B, 1337 -> 1320.
+// O 28 and 13 of the norm -> 24 and 6); 8 x 4096 tokens of the 7B shape 18990 -> 17610; 1078 rows of a 7B step, QKV and the rotary
+// kernel 52 and 17 -> 47 and 11.
 // (External linkage: the host takes the kernel's address to raise its dynamic LDS limit.)
 template <int EPI, int NU, int SW>
 __global__ __launch_bounds__(512) void hs_gemm_folded(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,

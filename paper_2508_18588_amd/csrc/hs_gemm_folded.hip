@@ -63,9 +63,11 @@ double chunks_apart_us(bool add, int n, int nu, int chunks, int tpc, int passes)
 // 101, at 2176 161 against 161) and what it leaves loses, gains less than 8 us, or is the long K of the 14B shape in three rounds
 // (4096 rows, 28 us of 2687 a pass).
 // Drafting makes the row count swing around what is expected, and a walk along all of K takes its time however few rows there are.
-// With up to split_rows rows, by the same estimates, the kernel leaves partial sums after all, and HS_FOLD_GUESSED asks for more.
+// With up to split_rows rows, by the same estimates, the kernel leaves partial sums after all (a tenth in their favour: a partly filled
+// round is faster than a whole one; 7B QKV at 300, 400, 540 and 700 rows, the rotary kernel included, folded 47, 46, 49, 50 us, apart
+// 41, 43, 46, 51), and HS_FOLD_GUESSED asks for more.
 // us with 1078 expected and 64, 220, 300, 540, 1078, 1300 there, the next kernel included, split / always folded / now: 7B QKV 20, 29,
-// 33, 51, 69, 90 / 34, 51, 47, 50, 57, 85 / 20, 29, 46, 49, 57, 86; O, which is split (1.09 expected), 18, 24, 28, 42, 60, 85 / 33, 51, 47,
+// 33, 51, 69, 90 / 34, 51, 47, 50, 57, 85 / 20, 29, 41, 46, 57, 86; O, which is split (1.09 expected), 18, 24, 28, 42, 60, 85 / 33, 51, 47,
 // 49, 57, 83; O of 4096 columns 19, 26, 32, 52, 73, 92 / 36, 55, 50, 53, 65, 92 / 19, 27, 37, 52, 64, 90.
 bool hs_launch_gemm_folded(int epi, const bf16_t* a, const bf16_t* w, void* c, float* part, const int32_t* m_dev, int m_max, int n,
                            int k, int chunks, int tpc, int rows_hint, double gain, hipStream_t st, int* split_rows) {
@@ -80,7 +82,7 @@ bool hs_launch_gemm_folded(int epi, const bf16_t* a, const bf16_t* w, void* c, f
     }
     if (nu == 0) return false;
     int live = 0;       // passes up to which the chunks are taken apart
-    while (split_rows && live + 1 < passes && chunks_apart_us(add, n, nu, chunks, tpc, live + 1) < folded_us(add, n, k, nu, live + 1, 256 * (live + 1))) live++;
+    while (split_rows && live + 1 < passes && chunks_apart_us(add, n, nu, chunks, tpc, live + 1) < 1.1 * folded_us(add, n, k, nu, live + 1, 256 * (live + 1))) live++;
     if (split_rows) *split_rows = 256 * live;
 #define HS_ARGS nu, a, w, c, part, m_dev, m_max, n, k, tpc, rows_hint, 256 * live, st
     if (add) launch_folded_units<HS_EPI_ADD_F32>(HS_ARGS);
